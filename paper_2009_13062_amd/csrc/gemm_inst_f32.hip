@@ -1,0 +1,82 @@
+// Instantiation, tile choice and launch of the float32 matrix-pipe kernels (gemm_f32.h).
+#include <atomic>
+
+#include "gemm_f32.h"
+
+namespace nf {
+
+// 128-row tiles were tried as well and are never ahead (12 models, 512 x 3072 x 768: 377 us at 128 x 128, 308 at
+// 128 x 64, 252 at 64 x 64): a compute unit with several tiles hides one workgroup's waits behind another's.
+using F64x64 = F32Cfg<64, 64, 2, 2, 32, 2>;
+using F64x64s = F32Cfg<64, 64, 2, 2, 32, 2, 2>;
+using F64x48s = F32Cfg<64, 48, 4, 1, 32, 2, 2>;
+using F32x64s = F32Cfg<32, 64, 2, 2, 32, 2, 2>;
+using F32x64q = F32Cfg<32, 64, 2, 2, 32, 2, 4>;
+using F16x64s = F32Cfg<16, 64, 1, 4, 32, 2, 2>;
+using F16x64q = F32Cfg<16, 64, 1, 4, 32, 2, 4>;
+
+enum { kF64x64, kF64x64s, kF64x48s, kF32x64s, kF32x64q, kF16x64s, kF16x64q, kNumF32Tiles };
+constexpr int kBMs[kNumF32Tiles] = {64, 64, 64, 32, 32, 16, 16};
+constexpr int kBNs[kNumF32Tiles] = {64, 64, 48, 64, 64, 64, 64};
+// Measured time per unit of tile area and k of the busiest compute unit, dense / gathered B, where a compute unit
+// has one tile / several (then its workgroups fill each other's waits).  With one tile per unit the forms with k
+// split over 2 or 4 groups of wavefronts are ahead of the plain ones (128 x 3072 x 768 at 8 models: 51 us against 64;
+// 512 -> 512 at 7 x 7: 54 against 138); small tiles pay for gathering B once per row tile.
+constexpr int kUnitCost[2][2][kNumF32Tiles] = {
+    {{159, 142, 166, 170, 165, 176, 165}, {130, 142, 150, 143, 170, 176, 210}},
+    {{220, 185, 0, 255, 230, 360, 320}, {173, 190, 0, 210, 250, 330, 340}}};
+
+template <class Cfg, int KIND, bool AVEC>
+static nf_status launch_kernel(GemmF32Args& a, long long total, hipStream_t s) {
+  auto kern = gemm_f32_kernel<Cfg, KIND, AVEC>;
+  if (Cfg::kLdsBytes > 64 * 1024) {
+    static std::atomic<bool> opted_in{false};        // per kernel: idempotent, a benign race
+    if (!opted_in.load(std::memory_order_acquire)) {
+      if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              Cfg::kLdsBytes) != hipSuccess)
+        return NF_ELAUNCH;
+      opted_in.store(true, std::memory_order_release);
+    }
+  }
+  nf_launch(kern, dim3((unsigned)total), dim3(Cfg::kThreads), Cfg::kLdsBytes, s, a);
+  return hipGetLastError() == hipSuccess ? NF_OK : NF_ELAUNCH;
+}
+
+template <class Cfg, int KIND>
+static nf_status launch_cfg(GemmF32Args& a, long long problems, hipStream_t s) {
+  a.tiles_m = (a.rows + Cfg::kBM - 1) / Cfg::kBM;
+  a.tiles_n = (a.cols + Cfg::kBN - 1) / Cfg::kBN;
+  const long long total = problems * a.tiles_m * a.tiles_n;
+  if (total <= 0 || total > 0x7fffffffLL) return NF_EUNSUPPORTED;
+  return a.K % 4 == 0 ? launch_kernel<Cfg, KIND, true>(a, total, s) : launch_kernel<Cfg, KIND, false>(a, total, s);
+}
+
+nf_status launch_gemm_f32(GemmF32Args& a, int nz1, bool gather, hipStream_t s) {
+  const long long problems = (long long)a.nz0 * nz1;
+  // a wide kernel over few channels (the image networks' stem)
+  if (gather && a.khw > 31) return launch_cfg<F64x64, kF32GatherWide>(a, problems, s);
+  auto tiles = [&](int t) { return problems * ((a.rows + kBMs[t] - 1) / kBMs[t]) * ((a.cols + kBNs[t] - 1) / kBNs[t]); };
+  int best = -1;
+  long long best_cost = 0;
+  for (int t = 0; t < kNumF32Tiles; ++t) {
+    if (gather && t == kF64x48s) continue;
+    if ((t == kF32x64q || t == kF16x64q) && a.K < 512) continue;      // too few k-steps to deal out four ways
+    const long long rounds = (tiles(t) + 255) / 256;
+    const long long cost = rounds * kBMs[t] * kBNs[t] * kUnitCost[gather][rounds > 1][t];
+    if (best < 0 || cost < best_cost) { best = t; best_cost = cost; }
+  }
+#define NF_F32(C) return gather ? launch_cfg<C, kF32Gather>(a, problems, s) : launch_cfg<C, kF32Dense>(a, problems, s)
+  switch (best) {
+    case kF64x64: NF_F32(F64x64);
+    case kF64x64s: NF_F32(F64x64s);
+    case kF64x48s: return launch_cfg<F64x48s, kF32Dense>(a, problems, s);
+    case kF32x64s: NF_F32(F32x64s);
+    case kF32x64q: NF_F32(F32x64q);
+    case kF16x64s: NF_F32(F16x64s);
+    case kF16x64q: NF_F32(F16x64q);
+  }
+#undef NF_F32
+  return NF_EUNSUPPORTED;
+}
+
+}  // namespace nf

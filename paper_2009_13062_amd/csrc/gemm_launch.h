@@ -70,6 +70,22 @@ nf_status launch_pack_fragments(const bf16_t* W, bf16_t* Wp, long long problems,
 template <int BKIND>
 nf_status launch_gemm_bkind(int align_a, int tile, GemmLaunch& L, hipStream_t s);
 
+// float32 storage (gemm_f32.h)
+struct GemmF32Args {
+  const float* A; const float* B; const float* R; float* C;
+  long lda, ldb, ldc;
+  long sA0, sB0, sB1, sC0, sC1;            // z = z1 * nz0 + z0 (elements)
+  unsigned a_bytes, b_bytes;               // bytes of one problem's A and B operand (below 2^31)
+  int rows, cols, K, nz0, tiles_m, tiles_n;
+  Epilogue ep;
+  // gathered B: k = (ci, ky, kx), column = output position; division by multiplication with the host's reciprocals
+  int H, W, KW, khw, Wo, stride, pad, dil;
+  unsigned rcp_khw, rcp_kw;                // ceil(2^32 / d), or 0 for d = 1, where
+  unsigned one_khw, one_kw;                // all bits are set here instead
+};
+// gather: B through the convolution geometry (any shape); else dense rows, cols % 4 == 0
+nf_status launch_gemm_f32(GemmF32Args& a, int nz1, bool gather, hipStream_t s);
+
 struct ConvPatchArgs;
 // 3x3 convolution through the LDS patch-gather kernel (conv_patch.h); see netfuse_conv2d for the conditions.
 nf_status launch_conv_patch_3x3(ConvPatchArgs& a, int B, hipStream_t s);

@@ -191,6 +191,19 @@ int pick_tile(int rows, int cols, long long problems) {
   return rows > 64 && tiles(T128x128w8) >= 200 ? T128x128w8 : T64x64;
 }
 
+// The float32 matrix-pipe kernels address one problem's operands with 32-bit byte offsets.
+bool f32_fits(long long a_elems, long long b_elems, int K) {
+  return a_elems < (1LL << 29) && b_elems < (1LL << 29) && K < (1 << 24);
+}
+void f32_divisors(GemmF32Args& a) {
+  auto rcp = [](int d, unsigned* r, unsigned* one) {
+    *r = d == 1 ? 0u : (unsigned)(((1ULL << 32) + d - 1) / d);
+    *one = d == 1 ? ~0u : 0u;
+  };
+  rcp(a.khw, &a.rcp_khw, &a.one_khw);
+  rcp(a.KW, &a.rcp_kw, &a.one_kw);
+}
+
 // largest alignment (16, 8, 4 or 2 bytes) shared by a pointer and a row pitch / stride set
 int common_align(std::initializer_list<const void*> ptrs, std::initializer_list<long long> elem_strides) {
   int al = 16;
@@ -295,6 +308,22 @@ nf_status netfuse_linear(const void* X, const void* W, const float* bias, const 
       }
     }
     return launch_gemm_any(bkind, al, pick_tile(N, Nout, M), L, s);
+  }
+  if (f32_fits(prod({N, K}), prod({K, Nout}), K)) {
+    GemmF32Args a;
+    memset(&a, 0, sizeof(a));
+    a.A = (const float*)X; a.B = (const float*)W; a.R = (const float*)residual; a.C = (float*)Y;
+    a.lda = K; a.ldb = Nout; a.ldc = Nout;
+    a.sA0 = (long)N * K; a.sB0 = (long)K * Nout; a.sC0 = (long)N * Nout;
+    a.a_bytes = (unsigned)(a.sA0 * 4); a.b_bytes = (unsigned)(a.sB0 * 4);
+    a.rows = N; a.cols = Nout; a.K = K; a.nz0 = M;
+    a.ep.col_bias = bias; a.ep.col_vec_stride0 = Nout;
+    a.ep.act = act; a.ep.act_before_residual = 1;
+    a.ep.vec_store = Nout % 4 == 0 && aligned(Y, 16) && aligned(residual, 16) ? 2 : 0;
+    const bool gather = Nout % 4 != 0;                      // then a weight row is a one-row image of Nout positions
+    a.H = 1; a.W = Nout; a.KW = 1; a.khw = 1; a.Wo = Nout; a.stride = 1; a.dil = 1;
+    f32_divisors(a);
+    return launch_gemm_f32(a, 1, gather, s);
   }
   const int tiles_m = (N + 63) / 64, tiles_n = (Nout + 63) / 64;
   const long long total = prod({tiles_m, tiles_n, M});
@@ -609,6 +638,25 @@ nf_status netfuse_conv2d(const void* x, const void* w, const float* bias, const 
       }
     }
     return launch_gemm_any(bkind, al, tile, L, s);
+  }
+
+  if (dt == NF_F32 && KH * KW < 64 && f32_fits((long long)cog * Kdim, prod({cig, H, W}), Kdim)) {
+    GemmF32Args a;
+    memset(&a, 0, sizeof(a));
+    a.A = (const float*)w; a.B = (const float*)x; a.R = (const float*)residual; a.C = (float*)y;
+    a.lda = Kdim; a.ldb = (long)H * W; a.ldc = HoWo;
+    a.sA0 = (long)cog * Kdim;
+    a.sB0 = (long)cig * H * W; a.sB1 = (long)Ctot_in * H * W;
+    a.sC0 = (long)cog * HoWo; a.sC1 = (long)Ctot_out * HoWo;
+    a.a_bytes = (unsigned)(a.sA0 * 4); a.b_bytes = (unsigned)(a.sB0 * 4);
+    a.rows = cog; a.cols = HoWo; a.K = Kdim; a.nz0 = M * g;
+    a.ep.row_bias = bias; a.ep.row_scale = scale; a.ep.row_shift = shift; a.ep.row_vec_stride0 = cog;
+    a.ep.act = act;
+    a.ep.vec_store = HoWo % 4 == 0 && aligned(y, 16) && aligned(residual, 16) ? 2 : 0;
+    const bool dense = KH == 1 && KW == 1 && stride == 1 && pad == 0 && HoWo % 4 == 0;
+    a.H = H; a.W = W; a.KW = KW; a.khw = KH * KW; a.Wo = (int)Wo; a.stride = stride; a.pad = pad; a.dil = dilation;
+    f32_divisors(a);
+    return launch_gemm_f32(a, B, !dense, s);
   }
 
   ConvGeom geo;

@@ -1,0 +1,85 @@
+"""float32 storage on the matrix pipe: sizes at the edges of every tile (64, 48, 32 and 16 wide or high), k remainders
+of the 32-element steps and of the split of k over two or four groups, both B paths, kernels of one and of two tap
+words.  The bound is derived, not fitted: a sum of K products in any order is off by at most
+(K + 4) 2^-24 sum |x||w| before the epilogue, whose operations add at most four more roundings of the result's
+operands."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+rng = np.random.default_rng(31)
+
+
+@pytest.fixture(scope="module")
+def nf():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2009_13062_amd as nf_
+    return nf_
+
+
+def rnd(*shape):
+    return rng.standard_normal(shape).astype(np.float32)
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a, np.float32)).cuda()
+
+
+def check(got, ref, absref, K):
+    got = got.detach().cpu().numpy().astype(np.float64)
+    bound = (K + 8) * 2.0 ** -24 * absref + 1e-30
+    assert got.shape == ref.shape and np.isfinite(got).all()
+    bad = np.abs(got - ref) > bound
+    assert not bad.any(), "%d of %d outside the rounding bound, worst %.2f of it" % (
+        bad.sum(), bad.size, (np.abs(got - ref) / bound).max())
+
+
+@pytest.mark.parametrize("M,N,K,Nout", [
+    (1, 1, 1, 1), (1, 1, 36, 4),                 # one element; 16 x 64 tile
+    (2, 16, 31, 64), (2, 17, 33, 65),            # tile edges, k = 32 -+ 1
+    (2, 1, 516, 4), (2, 15, 1025, 63),           # 16 x 64 tile, k in four groups, dense and gathered
+    (16, 277, 17, 4), (24, 222, 17, 3),          # 32 x 64 tile
+    (24, 169, 520, 4), (32, 142, 520, 1),        # 32 x 64 tile, k in four groups
+    (32, 294, 17, 4),                            # 64 x 48 tile, one column block of four
+    (16, 146, 17, 260), (32, 270, 17, 1),        # 64 x 64 tile, k in two groups
+    (32, 65, 65, 860), (32, 33, 129, 788 + 1),   # 64 x 64 tile, several per compute unit
+], ids=lambda v: str(v))
+def test_linear(nf, M, N, K, Nout):
+    X, W, b, R = rnd(M, N, K), rnd(M, K, Nout), rnd(M, Nout), rnd(M, N, Nout)
+    x, w = X.astype(np.float64), W.astype(np.float64)
+    prod = np.matmul(x, w) + b[:, None]
+    size = np.matmul(np.abs(x), np.abs(w)) + np.abs(b)[:, None] + np.abs(R)
+    check(nf.linear(dev(X), dev(W), bias=dev(b), residual=dev(R), act=nf.ACT_RELU), np.maximum(prod, 0) + R, size, K)
+    check(nf.linear(dev(X), dev(W)), np.matmul(x, w), size, K)
+    if M > 1:                                    # nothing of another problem is read, not even times zero
+        X[1:], W[1:] = np.nan, np.nan
+        check(nf.linear(dev(X), dev(W))[:1], np.matmul(x, w)[:1], size[:1], K)
+
+
+@pytest.mark.parametrize("M,B,Cin,Cout,g,H,W,KH,KW,stride,pad,dil", [
+    (1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 0, 1),        # one pixel
+    (2, 1, 17, 15, 1, 8, 8, 3, 3, 1, 1, 1),      # 64 positions, k = 153
+    (2, 2, 24, 33, 1, 5, 13, 3, 3, 1, 1, 1),     # 65 positions
+    (1, 1, 64, 16, 1, 9, 9, 3, 3, 2, 1, 1),      # stride 2, k in four groups
+    (3, 1, 8, 20, 2, 11, 7, 5, 5, 1, 2, 1),      # 25 taps
+    (2, 1, 6, 20, 1, 12, 12, 6, 5, 1, 3, 1),     # 30 taps, padding wider than half the kernel
+    (2, 1, 3, 70, 1, 17, 19, 7, 7, 2, 3, 1),     # 49 taps: two words; k = 147
+    (1, 1, 2, 65, 1, 12, 9, 8, 4, 1, 2, 1),      # 32 taps: the first count of the second word
+    (2, 1, 5, 9, 1, 10, 10, 3, 3, 1, 2, 2),      # dilation
+    (2, 1, 33, 48, 1, 7, 7, 1, 1, 1, 0, 1),      # pointwise, 49 positions: gathered rows
+    (2, 1, 33, 48, 1, 6, 6, 1, 1, 1, 0, 1),      # pointwise, 36 positions: dense rows
+    (16, 1, 64, 65, 1, 29, 29, 1, 1, 2, 0, 1),   # strided projection, many tiles
+], ids=lambda v: str(v))
+def test_conv2d(nf, oracle, M, B, Cin, Cout, g, H, W, KH, KW, stride, pad, dil):
+    x, w = rnd(B, M * Cin, H, W), rnd(M * Cout, Cin // g, KH, KW)
+    Ho, Wo = oracle.conv_out_size(H, KH, stride, pad, dil), oracle.conv_out_size(W, KW, stride, pad, dil)
+    R, scale, shift = rnd(B, M * Cout, Ho, Wo), rnd(M * Cout), rnd(M * Cout)
+    conv = lambda a, c: torch.nn.functional.conv2d(torch.from_numpy(a).double(), torch.from_numpy(c).double(), stride=stride,
+                                                   padding=pad, dilation=dil, groups=M * g).numpy()
+    s, t = scale[None, :, None, None].astype(np.float64), shift[None, :, None, None].astype(np.float64)
+    size = conv(np.abs(x), np.abs(w)) * np.abs(s) + np.abs(t) + np.abs(R)
+    got = nf.conv2d(dev(x), dev(w), M, g=g, scale=dev(scale), shift=dev(shift), residual=dev(R), stride=stride, pad=pad,
+                    dil=dil, act=nf.ACT_RELU)
+    check(got, np.maximum(conv(x, w) * s + t + R, 0), size, Cin // g * KH * KW)
