@@ -11,6 +11,7 @@
 #include <atomic>
 
 #include "../../include/netfuse.h"
+#include "attention_f32.h"
 #include "attention_kernels.h"
 #include "conv_patch.h"
 #include "conv_stem.h"
@@ -798,6 +799,17 @@ nf_status netfuse_attention(const void* Q, const void* K, const void* V, const f
     const long long total = prod({M, B, heads, qblocks});
     if (total > kMaxGrid) return NF_EUNSUPPORTED;
     nf_launch(attention_mfma_d64_kernel, dim3((unsigned)total), dim3(256), 0, s, a, qblocks);
+    return launched();
+  }
+  const long long head_elems = (long long)(S - 1) * stride_row + d;         // one head's rows, first to last element
+  if (dt == NF_F32 && d % 4 == 0 && d <= 128 && head_elems < (1LL << 29)) {
+    const int qblocks = (S + kAttnF32Queries - 1) / kAttnF32Queries;
+    const long long total = prod({M, B, heads, qblocks});
+    if (total > kMaxGrid) return NF_EUNSUPPORTED;
+    const unsigned bytes = (unsigned)(head_elems * 4);
+    if (d <= 32) nf_launch((attention_f32_kernel<2, 64>), dim3((unsigned)total), dim3(256), 0, s, a, qblocks, bytes);
+    else if (d <= 64) nf_launch((attention_f32_kernel<4, 64>), dim3((unsigned)total), dim3(256), 0, s, a, qblocks, bytes);
+    else nf_launch((attention_f32_kernel<8, 32>), dim3((unsigned)total), dim3(256), 0, s, a, qblocks, bytes);
     return launched();
   }
   if (d > 256) return NF_EUNSUPPORTED;

@@ -83,3 +83,27 @@ def test_conv2d(nf, oracle, M, B, Cin, Cout, g, H, W, KH, KW, stride, pad, dil):
     got = nf.conv2d(dev(x), dev(w), M, g=g, scale=dev(scale), shift=dev(shift), residual=dev(R), stride=stride, pad=pad,
                     dil=dil, act=nf.ACT_RELU)
     check(got, np.maximum(conv(x, w) * s + t + R, 0), size, Cin // g * KH * KW)
+
+
+@pytest.mark.parametrize("M,B,S,heads,d,use_mask", [
+    (1, 1, 1, 1, 4, False),                      # one query, one key, a quarter of a feature block
+    (2, 1, 63, 2, 16, True), (1, 2, 64, 1, 32, False), (2, 1, 65, 1, 28, True),      # edges of the 64-key stage, d <= 32
+    (2, 1, 128, 3, 64, False), (1, 3, 129, 2, 64, True), (2, 1, 17, 1, 60, True),    # d <= 64
+    (1, 1, 96, 2, 128, True), (2, 1, 33, 1, 68, False), (1, 1, 100, 1, 80, True),    # d <= 128: 32-key stages
+], ids=lambda v: str(v))
+def test_attention(nf, oracle, M, B, S, heads, d, use_mask):
+    """Against the oracle (double accumulation).  A score carries d products, the weights S of them, and the
+    exponential doubles neither: (d + S + 16) 2^-24 times the largest |score| + 4 (the exponent's own rounding is
+    absolute in the score), relative to the largest |V| that is averaged."""
+    qkv = rnd(M, B * S, 3 * heads * d)
+    mask = rnd(M, B, S) if use_mask else None
+    ref = oracle.attention_packed(qkv, B, S, heads, mask=mask).astype(np.float64)
+    got = nf.attention_packed(dev(qkv), B, S, heads, mask=None if mask is None else dev(mask)).cpu().numpy()
+    smax = np.abs(qkv).max() ** 2 * d * d ** -0.5
+    assert np.isfinite(got).all()
+    assert np.abs(got - ref).max() <= (d + S + 16) * 2.0 ** -24 * (smax + 4) * np.abs(qkv).max()
+    if M > 1:                                    # NaN in another model stays there
+        dirty = qkv.copy()
+        dirty[1:] = np.nan
+        alone = nf.attention_packed(dev(dirty), B, S, heads, mask=None if mask is None else dev(mask)).cpu().numpy()
+        assert np.array_equal(alone[0], got[0])
