@@ -7,57 +7,77 @@
 namespace nf {
 
 // Ragged merged matmul: per-model output widths (the per-task classification heads, Section 5.1).
-// One workgroup = (model, 8 rows, 64 columns); its 4 wavefronts split K, each lane owns one column and 8
-// rows, so a wavefront reads 64 consecutive weights of a k row (coalesced, any alignment) and the
-// activations as wave-uniform broadcasts; the four partial sums meet in LDS.  The model of a workgroup is
-// found from the prefix sums of the per-model tile counts, which travel in the kernel arguments.
+// One workgroup = (model, R rows, 64 columns), 16 wavefronts that share k.  A model's weights are one dense run
+// [K][nout], so a wavefront reads KQ = 64 / CW consecutive k rows at a time (CW = the columns of the tile rounded up
+// to a power of two): lane = (k of the KQ, column), and narrow heads keep all lanes busy on contiguous memory.
+// Partial sums meet first across the KQ lanes of a column, then in LDS, in a fixed order.
+// Bound by latency -- a head is a few hundred dependent loads long, whatever its width -- hence the 16 wavefronts
+// and the unrolled, unconditional loads: 12 models x 3 rows x 768 -> 2 ... 20 classes took 88 us on four wavefronts
+// with one k row in flight each, and takes 8.2 us.
 constexpr int kRaggedMaxModels = 256;
+constexpr int kRaggedWaves = 16;
 struct RaggedTable {
   int tile_start[kRaggedMaxModels + 1];   // first workgroup of model m (prefix sum of rows tiles x column tiles)
   int col_start[kRaggedMaxModels + 1];    // first output column of model m in the concatenation (prefix sum of nout)
 };
 
-template <typename T>
-__global__ __launch_bounds__(256) void linear_ragged_kernel(const T* __restrict__ X, const T* __restrict__ W,
-                                                           const float* __restrict__ bias, T* __restrict__ Y, int M,
-                                                           int N, int K, int act, RaggedTable tab) {
-  __shared__ float part[4][8][64];
+template <typename T, int R>
+__global__ __launch_bounds__(kRaggedWaves * kWave) void linear_ragged_kernel(const T* __restrict__ X, const T* __restrict__ W,
+                                                                            const float* __restrict__ bias, T* __restrict__ Y,
+                                                                            int M, int N, int K, int act, RaggedTable tab) {
+  __shared__ float part[kRaggedWaves][R][kWave];
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-  // binary search: the last model whose first tile is <= blockIdx.x
-  int lo = 0, hi = M - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) / 2;
-    if (tab.tile_start[mid] <= (int)blockIdx.x) lo = mid; else hi = mid - 1;
-  }
-  const int m = lo;
+  // the model: how many of the first tiles lie at or before this workgroup
+  int m = -1;
+#pragma unroll
+  for (int i = 0; i < kRaggedMaxModels; i += kWave)
+    m += __popcll(__ballot(i + lane < M && tab.tile_start[i + lane] <= (int)blockIdx.x));
+  m = __builtin_amdgcn_readfirstlane(m);
   const int nout = tab.col_start[m + 1] - tab.col_start[m];
   const int tiles_n = (nout + 63) / 64;
   const int t = blockIdx.x - tab.tile_start[m];
-  const int row0 = (t / tiles_n) * 8, col = (t % tiles_n) * 64 + lane;
-  const T* Xm = X + ((size_t)m * N + row0) * K;
-  const T* Wm = W + (size_t)tab.col_start[m] * K;          // model m's [K][nout] block of the concatenation
-  const int rows = min(8, N - row0);
-  float acc[8] = {};
-  const int kper = (K + 3) / 4, k0 = wave * kper, k1 = min(K, k0 + kper);
-  if (col < nout) {
-    for (int k = k0; k < k1; ++k) {
-      const float w = load_f32(Wm + (size_t)k * nout + col);
+  const int row0 = (t / tiles_n) * R, col0 = (t % tiles_n) * 64;
+  const int rows = min(R, N - row0), cols = min(64, nout - col0);
+  const int cw_log = cols > 1 ? 32 - __builtin_clz(cols - 1) : 0, cw = 1 << cw_log, kq_n = kWave >> cw_log;
+  const int c = lane & (cw - 1), kq = lane >> cw_log;
+  const T* Wm = W + (size_t)tab.col_start[m] * K + col0 + min(c, cols - 1);      // model m's [K][nout] block of the concatenation
+  const T* Xm[R];
 #pragma unroll
-      for (int r = 0; r < 8; ++r)
-        if (r < rows) acc[r] = fmaf(load_f32(Xm + (size_t)r * K + k), w, acc[r]);
+  for (int r = 0; r < R; ++r) Xm[r] = X + ((size_t)m * N + row0 + min(r, rows - 1)) * K;
+  float acc[R] = {};
+  constexpr int U = R >= 8 ? 4 : 8;
+  const int step = kRaggedWaves * kq_n;
+  for (int k0 = wave * kq_n + kq; k0 - kq < K; k0 += U * step) {
+    float w[U], x[U][R];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = min(k0 + u * step, K - 1);
+      w[u] = load_f32(Wm + (size_t)k * nout);
+#pragma unroll
+      for (int r = 0; r < R; ++r) x[u][r] = load_f32(Xm[r] + k);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool in = k0 + u * step < K;
+#pragma unroll
+      for (int r = 0; r < R; ++r) acc[r] = in ? fmaf(x[u][r], w[u], acc[r]) : acc[r];
     }
   }
 #pragma unroll
-  for (int r = 0; r < 8; ++r) part[wave][r][lane] = acc[r];
+  for (int r = 0; r < R; ++r) {
+    for (int off = kWave / 2; off >= cw; off >>= 1) acc[r] += __shfl_xor(acc[r], off, kWave);
+    part[wave][r][lane] = acc[r];
+  }
   __syncthreads();
-  // 512 outputs, 256 threads: two each; the k slices are added in order
-  for (int o = threadIdx.x; o < 8 * 64; o += 256) {
-    const int r = o / 64, c = (t % tiles_n) * 64 + o % 64;
-    if (r >= rows || c >= nout) continue;
-    float v = ((part[0][r][o % 64] + part[1][r][o % 64]) + part[2][r][o % 64]) + part[3][r][o % 64];
-    if (bias) v += bias[tab.col_start[m] + c];
+  for (int o = threadIdx.x; o < R * cw; o += kRaggedWaves * kWave) {
+    const int r = o >> cw_log, cc = o & (cw - 1);
+    if (r >= rows || cc >= cols) continue;
+    float v = 0.f;
+#pragma unroll
+    for (int q = 0; q < kRaggedWaves; ++q) v += part[q][r][cc];
+    if (bias) v += bias[tab.col_start[m] + col0 + cc];
     v = apply_act(v, act);
-    store_f32(Y + (size_t)tab.col_start[m] * N + (size_t)(row0 + r) * nout + c, v);
+    store_f32(Y + (size_t)tab.col_start[m] * N + (size_t)(row0 + r) * nout + col0 + cc, v);
   }
 }
 

@@ -465,11 +465,13 @@ nf_status netfuse_linear_ragged(const void* X, const void* W, const float* bias,
   const size_t esz = dt == NF_F32 ? 4 : 2;
   if (!aligned(X, esz) || !aligned(W, esz) || !aligned(Y, esz) || !aligned(bias, 4)) return NF_EINVAL;
   if (prod({M, N, K}) >= kMaxElems) return NF_EINVAL;
+  // rows per workgroup: as many as there are, up to 8
+  const int R = N >= 5 ? 8 : N >= 3 ? 4 : N;
   long long cols = 0, tiles = 0;
   for (int m = 0; m < M; ++m) {
     if (nout[m] <= 0) return NF_EINVAL;
     cols += nout[m];
-    tiles += (long long)((N + 7) / 8) * ((nout[m] + 63) / 64);
+    tiles += (long long)((N + R - 1) / R) * ((nout[m] + 63) / 64);
     if (cols > INT_MAX || tiles > kMaxGrid) return NF_EINVAL;
   }
   if (prod({cols, K}) >= kMaxElems || prod({cols, N}) >= kMaxElems) return NF_EINVAL;
@@ -477,17 +479,19 @@ nf_status netfuse_linear_ragged(const void* X, const void* W, const float* bias,
   RaggedTable tab;
   tab.tile_start[0] = 0; tab.col_start[0] = 0;
   for (int m = 0; m < M; ++m) {
-    tab.tile_start[m + 1] = tab.tile_start[m] + ((N + 7) / 8) * ((nout[m] + 63) / 64);
+    tab.tile_start[m + 1] = tab.tile_start[m] + ((N + R - 1) / R) * ((nout[m] + 63) / 64);
     tab.col_start[m + 1] = tab.col_start[m] + nout[m];
   }
   for (int m = M + 1; m <= kRaggedMaxModels; ++m) { tab.tile_start[m] = tab.tile_start[M]; tab.col_start[m] = tab.col_start[M]; }
   hipStream_t s = (hipStream_t)stream;
-  if (dt == NF_F32)
-    nf_launch(linear_ragged_kernel<float>, dim3((unsigned)tiles), dim3(256), 0, s, (const float*)X, (const float*)W,
-              bias, (float*)Y, M, N, K, (int)act, tab);
-  else
-    nf_launch(linear_ragged_kernel<bf16_t>, dim3((unsigned)tiles), dim3(256), 0, s, (const bf16_t*)X, (const bf16_t*)W,
-              bias, (bf16_t*)Y, M, N, K, (int)act, tab);
+#define NF_RAGGED(T, R_)                                                                                             \
+  nf_launch((linear_ragged_kernel<T, R_>), dim3((unsigned)tiles), dim3(kRaggedWaves * kWave), 0, s, (const T*)X,       \
+            (const T*)W, bias, (T*)Y, M, N, K, (int)act, tab)
+#define NF_RAGGED_R(T) \
+  if (R == 1) NF_RAGGED(T, 1); else if (R == 2) NF_RAGGED(T, 2); else if (R == 4) NF_RAGGED(T, 4); else NF_RAGGED(T, 8)
+  if (dt == NF_F32) { NF_RAGGED_R(float); } else { NF_RAGGED_R(bf16_t); }
+#undef NF_RAGGED_R
+#undef NF_RAGGED
   return launched();
 }
 
