@@ -187,9 +187,9 @@ __device__ __forceinline__ void gemm_frag_tile(const bf16_t* __restrict__ A, lon
 
   if constexpr (KG == 1) {
     f32x16_t (&acc2)[RB][1] = reinterpret_cast<f32x16_t (&)[RB][1]>(acc);
-    if (act == NF_ACT_GELU) reg_epilogue<RB, 1, NF_ACT_GELU>(acc2, C, R, ldc, col_bias, 0, 32 * j);
-    else if (act == NF_ACT_RELU) reg_epilogue<RB, 1, NF_ACT_RELU>(acc2, C, R, ldc, col_bias, 0, 32 * j);
-    else reg_epilogue<RB, 1, NF_ACT_NONE>(acc2, C, R, ldc, col_bias, 0, 32 * j);
+    if (act == NF_ACT_GELU) reg_epilogue<RB, 1, NF_ACT_GELU>(acc2, C, R, ldc, col_bias, 0, 32 * j, Cfg::kBM, Cfg::kBN);
+    else if (act == NF_ACT_RELU) reg_epilogue<RB, 1, NF_ACT_RELU>(acc2, C, R, ldc, col_bias, 0, 32 * j, Cfg::kBM, Cfg::kBN);
+    else reg_epilogue<RB, 1, NF_ACT_NONE>(acc2, C, R, ldc, col_bias, 0, 32 * j, Cfg::kBM, Cfg::kBN);
   } else {
     // Partial sums of row block i go to wavefront (i, j): region of wave d = i NB + j, then [slot][r4][lane] x 16 B,
     // slot = the sender's k-group with the receiver's own left out.
@@ -227,9 +227,9 @@ __device__ __forceinline__ void gemm_frag_tile(const bf16_t* __restrict__ A, lon
         }
       }
     }
-    if (act == NF_ACT_GELU) reg_epilogue<1, 1, NF_ACT_GELU>(sum, C, R, ldc, col_bias, 32 * q, 32 * j);
-    else if (act == NF_ACT_RELU) reg_epilogue<1, 1, NF_ACT_RELU>(sum, C, R, ldc, col_bias, 32 * q, 32 * j);
-    else reg_epilogue<1, 1, NF_ACT_NONE>(sum, C, R, ldc, col_bias, 32 * q, 32 * j);
+    if (act == NF_ACT_GELU) reg_epilogue<1, 1, NF_ACT_GELU>(sum, C, R, ldc, col_bias, 32 * q, 32 * j, Cfg::kBM, Cfg::kBN);
+    else if (act == NF_ACT_RELU) reg_epilogue<1, 1, NF_ACT_RELU>(sum, C, R, ldc, col_bias, 32 * q, 32 * j, Cfg::kBM, Cfg::kBN);
+    else reg_epilogue<1, 1, NF_ACT_NONE>(sum, C, R, ldc, col_bias, 32 * q, 32 * j, Cfg::kBM, Cfg::kBN);
   }
 }
 

@@ -22,75 +22,71 @@
 
 namespace nf {
 
-// Epilogue of one whole BM x BN tile straight from the accumulators (layout: see gemm_mfma.h): a lane holds,
-// per 32 x 32 block, four groups of 4 consecutive columns of its row (columns 8 q + 4 half + 0..3).  The two
-// lanes of a row (lane and lane + 32) swap one group per pair of groups, after the activation, so that each
-// ends up with 8 consecutive columns: residual and output then move 16 bytes per lane (8-byte stores
-// measured 1.4x the algorithmic write traffic: partially written sectors reaching HBM).
-// Needs 16-byte aligned rows of C and R (ldc % 8 == 0) and a 16-byte aligned column-constant vector.
-// acc[i][j] is the 32 x 32 block at rows row_base + 32 i, columns col_base + 32 j of the tile that C, R and col_bias
-// point at.
+// Eight consecutive output columns of one row out of two groups of 4 accumulators.  A lane holds, per 32 x 32 block, four
+// groups of 4 consecutive columns of its row (columns 8 q + 4 half + 0..3); a0 / a1 are groups 2 qq and 2 qq + 1.  After the
+// activation the two lanes of a row (lane and lane + 32) exchange one group: permlane32_swap swaps the upper half of
+// its first operand with the lower half of its second, which leaves each lane with 8 consecutive columns in one
+// instruction per element pair.  Residual and output then move 16 bytes per lane (8-byte stores measured 1.4x the
+// algorithmic write traffic: partially written sectors reaching HBM).
+// (An accumulator is never -0 -- it starts at +0 and (+0) + (-0) = +0 -- so neither is the sum, and the "+ 0, x 1 + 0"
+// steps with which the other epilogues normalise a -0 would change no bit here.)
+template <int ACT>
+__device__ __forceinline__ uint4 epi_piece(const float (&a0)[4], const float (&a1)[4], float4 b0, float4 b1, uint4 res) {
+  const float c0[4] = {b0.x, b0.y, b0.z, b0.w}, c1[4] = {b1.x, b1.y, b1.z, b1.w};
+  float v[8];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float v0 = act_const<ACT>(a0[e] + c0[e]), v1 = act_const<ACT>(a1[e] + c1[e]);
+    const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(v0), __float_as_uint(v1), false, false);
+    v[e] = __uint_as_float(s[0]);
+    v[4 + e] = __uint_as_float(s[1]);
+  }
+  const uint32_t w[4] = {res.x, res.y, res.z, res.w};
+  uint32_t o[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    o[e] = pack_bf16x2(v[2 * e] + __uint_as_float(w[e] << 16), v[2 * e + 1] + __uint_as_float(w[e] & 0xffff0000u));
+  return make_uint4(o[0], o[1], o[2], o[3]);
+}
+
+// Epilogue of FM x FN 32 x 32 blocks straight from the accumulators (layout: see gemm_mfma.h): acc[i][j] is the block at
+// rows row0 + 32 i, columns col0 + 32 j of the matrix that C, R and col_bias point at, of which rows x cols exist (cols
+// a multiple of 8).  Needs 16-byte aligned rows of C and R and a 16-byte aligned column-constant vector.
+// Row blocks outermost: the column blocks of a row block are stored one right after the other, so the 64-byte
+// halves of a 128-byte output line (two neighbouring column blocks of one wavefront) reach L2 close together.
+// With the column blocks outermost they were four row blocks of epilogue arithmetic apart, and L2 wrote a
+// third of the lines back half filled: 135.7 MB written for a 100.7 MB output (768 -> 3072 + GELU at 512 rows
+// and 32 models), 120 us against 108 us this way.
 template <int FM, int FN, int ACT>
-__device__ __forceinline__ void reg_epilogue(f32x16_t (&acc)[FM][FN], bf16_t* C, const bf16_t* R, long ldc,
-                                             const float* col_bias, int row_base, int col_base) {
+__device__ __forceinline__ void reg_epilogue(const f32x16_t (&acc)[FM][FN], bf16_t* C, const bf16_t* R, long ldc,
+                                             const float* col_bias, int row0, int col0, int rows, int cols) {
   const int lane = threadIdx.x % kWave;
   const int half = lane / 32, l32 = lane % 32;
-  // Row blocks outermost: the column blocks of a row block are stored one right after the other, so the 64-byte
-  // halves of a 128-byte output line (two neighbouring column blocks of one wavefront) reach L2 close together.
-  // With the column blocks outermost they were four row blocks of epilogue arithmetic apart, and L2 wrote a
-  // third of the lines back half filled: 135.7 MB written for a 100.7 MB output (768 -> 3072 + GELU at 512 rows
-  // and 32 models), 120 us against 108 us this way.
-  float4 cball[FN][4];
+  float4 cb[FN][4];
 #pragma unroll
   for (int j = 0; j < FN; ++j)
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-      cball[j][q] = col_bias ? *reinterpret_cast<const float4*>(col_bias + col_base + j * 32 + q * 8 + half * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int q = 0; q < 4; ++q) {
+      const int c = col0 + j * 32 + q * 8 + half * 4;
+      cb[j][q] = col_bias && c < cols ? *reinterpret_cast<const float4*>(col_bias + c) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
 #pragma unroll
   for (int i = 0; i < FM; ++i) {
+    const int row = row0 + 32 * i + l32;
+    const long off = (long)row * ldc + col0 + half * 8;       // this lane's pieces: columns col0 + 16 p + 8 half + 0..7
+    const int left = row < rows ? cols - col0 - half * 8 : 0;
+    uint4 rr[2 * FN];
 #pragma unroll
-    for (int j = 0; j < FN; ++j) {
-      const int colb = col_base + j * 32;
-      float4 (&cb)[4] = cball[j];
-      // this lane's two 8-column pieces: columns colb + 16 qq + 8 half + 0..7
-      const long off = (long)(row_base + i * 32 + l32) * ldc + colb + half * 8;
-      uint4 rr[2];
+    for (int p = 0; p < 2 * FN; ++p)
+      rr[p] = R && 16 * p < left ? *reinterpret_cast<const uint4*>(R + off + 16 * p) : make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
-      for (int qq = 0; qq < 2; ++qq)
-        rr[qq] = R ? *reinterpret_cast<const uint4*>(R + off + qq * 16) : make_uint4(0u, 0u, 0u, 0u);
+    for (int p = 0; p < 2 * FN; ++p) {
+      const int j = p / 2, qq = p % 2;
+      float a0[4], a1[4];
 #pragma unroll
-      for (int qq = 0; qq < 2; ++qq) {
-        float own[4], send[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          // group 2 qq + half stays (its other half comes from the partner), group 2 qq + 1 - half is sent
-          const float b0[4] = {cb[2 * qq].x, cb[2 * qq].y, cb[2 * qq].z, cb[2 * qq].w};
-          const float b1[4] = {cb[2 * qq + 1].x, cb[2 * qq + 1].y, cb[2 * qq + 1].z, cb[2 * qq + 1].w};
-          // (an accumulator is never -0 -- it starts at +0 and (+0) + (-0) = +0 -- so neither is the sum, and the
-          // "+ 0, x 1 + 0" steps with which the other epilogues normalise a -0 would change no bit here)
-          const float v0 = act_const<ACT>(acc[i][j][(2 * qq) * 4 + e] + b0[e]);
-          const float v1 = act_const<ACT>(acc[i][j][(2 * qq + 1) * 4 + e] + b1[e]);
-          own[e] = half ? v1 : v0;
-          send[e] = half ? v0 : v1;
-        }
-        float recv[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) recv[e] = __shfl_xor(send[e], 32, kWave);
-        // columns within the piece: the lower lane's group sits at 4 half' ... : half 0 holds columns 0..3 of its
-        // group and receives 4..7; half 1 holds 4..7 and receives 0..3
-        float v[8];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          v[e] = half ? recv[e] : own[e];
-          v[4 + e] = half ? own[e] : recv[e];
-        }
-        const uint32_t w[4] = {rr[qq].x, rr[qq].y, rr[qq].z, rr[qq].w};
-        uint32_t o[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          o[e] = pack_bf16x2(v[2 * e] + __uint_as_float(w[e] << 16), v[2 * e + 1] + __uint_as_float(w[e] & 0xffff0000u));
-        *reinterpret_cast<uint4*>(C + off + qq * 16) = make_uint4(o[0], o[1], o[2], o[3]);
-      }
+      for (int e = 0; e < 4; ++e) { a0[e] = acc[i][j][8 * qq + e]; a1[e] = acc[i][j][8 * qq + 4 + e]; }
+      const uint4 o = epi_piece<ACT>(a0, a1, cb[j][2 * qq], cb[j][2 * qq + 1], rr[p]);
+      if (16 * p < left) *reinterpret_cast<uint4*>(C + off + 16 * p) = o;
     }
   }
 }
@@ -99,7 +95,8 @@ template <class Cfg, int ACT>
 __device__ __forceinline__ void stream_epilogue_act(f32x16_t (&acc)[Cfg::FM][Cfg::FN], bf16_t* C, const bf16_t* R,
                                                     long ldc, const float* col_bias) {
   const int wave = threadIdx.x / kWave;
-  reg_epilogue<Cfg::FM, Cfg::FN, ACT>(acc, C, R, ldc, col_bias, (wave / Cfg::kWGN) * Cfg::WM, (wave % Cfg::kWGN) * Cfg::WN);
+  reg_epilogue<Cfg::FM, Cfg::FN, ACT>(acc, C, R, ldc, col_bias, (wave / Cfg::kWGN) * Cfg::WM, (wave % Cfg::kWGN) * Cfg::WN,
+                                    Cfg::kBM, Cfg::kBN);
 }
 
 // A, B, C, R, col_bias point at the workgroup's first tile; consecutive tiles are b_tile_stride elements
