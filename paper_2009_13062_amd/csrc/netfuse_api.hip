@@ -192,6 +192,35 @@ int pick_tile(int rows, int cols, long long problems) {
   return rows > 64 && tiles(T128x128w8) >= 200 ? T128x128w8 : T64x64;
 }
 
+// Time model of the matmul kernels for choosing between them: 4 us of launch and ramp, plus per round of tiles over the
+// 256 compute units b us per 768 of k and e us of prologue and epilogue.  Fitted to every kernel measured alone at
+// hidden sizes 256, 768 and 1024 (the four matmuls of an encoder layer), 1 ... 32 models of 17 ... 1000 rows, weights
+// cold: 252 row-major problems, mean error of a prediction 4 to 7 %.
+struct TileCost { int bm, bn; float b, e; };
+float tile_us(const TileCost& t, int N, int Nout, int K, long long M) {
+  const long long tiles = M * ((N + t.bm - 1) / t.bm) * ((Nout + t.bn - 1) / t.bn);
+  return 4.0f + (float)((tiles + 255) / 256) * (t.b * (float)K / 768.0f + t.e);
+}
+constexpr TileCost kRegCost[kNumTiles] = {{64, 64, 3.77f, 0.48f}, {32, 128, 5.08f, 0.15f}, {128, 128, 6.69f, 3.04f}};
+constexpr TileCost kDmaCost[kNumDmaTiles] = {{256, 256, 20.1f, 10.7f}, {128, 128, 9.4f, 4.3f}, {128, 128, 8.8f, 0.f},
+                                             {128, 384, 13.8f, 18.1f}, {128, 288, 21.6f, 0.f}, {128, 96, 8.0f, 2.0f}};
+constexpr TileCost kRingCost[kNumRingTiles] = {{32, 32, 2.38f, 0.74f}, {64, 64, 3.61f, 0.43f}, {64, 128, 5.18f, 1.51f},
+                                               {96, 128, 6.10f, 1.51f}, {96, 256, 9.95f, 2.07f}, {128, 128, 6.89f, 1.53f},
+                                               {128, 256, 11.6f, 2.83f}, {128, 384, 16.2f, 4.24f}, {256, 256, 19.0f, 4.30f}};
+constexpr TileCost kRingPackedCost[kNumRingPackedTiles] = {{32, 32, 1.42f, 1.42f}, {64, 64, 3.35f, 1.60f}, {128, 64, 4.60f, 2.07f},
+                                                           {128, 128, 7.14f, 2.69f}, {128, 256, 11.0f, 2.96f}, {256, 256, 18.6f, 4.12f}};
+
+// The gemm_ring.h tile that is predicted to take less than `limit` us, or -1.
+template <int N_TILES>
+int pick_ring(const TileCost (&cost)[N_TILES], int N, int Nout, int K, long long M, float limit) {
+  int best = -1;
+  for (int t = 0; t < N_TILES; ++t) {
+    const float us = tile_us(cost[t], N, Nout, K, M);
+    if (us < limit) { best = t; limit = us; }
+  }
+  return best;
+}
+
 // The float32 matrix-pipe kernels address one problem's operands with 32-bit byte offsets.
 bool f32_fits(long long a_elems, long long b_elems, int K) {
   return a_elems < (1LL << 29) && b_elems < (1LL << 29) && K < (1 << 24);
@@ -298,6 +327,18 @@ nf_status netfuse_linear(const void* X, const void* W, const float* bias, const 
         if (st != NF_EUNSUPPORTED) return st;
       }
       const int d = pick_dma_or_small(N, Nout, K, M);
+      if (forced_dma() == -2 && forced_tile() < 0 && ring_fits(Nout, K)) {
+        // gemm_ring.h where its tiles are predicted to be faster, by more than the prediction is worth where a whole-tile
+        // kernel is the alternative.  Over the 252 problems this takes 11 % off on average, most for ragged rows: 12
+        // models of 279 rows 31.9 -> 25.1 (768 -> 2304), 42.5 -> 33.7 (3072), 14.1 -> 12.2 (768), 36.0 -> 30.7 us (3072 -> 768);
+        // 1 model of 93 rows 3072 -> 768 20 -> 16.1 us.
+        const float now = tile_us(d >= 0 ? kDmaCost[d] : kRegCost[d == kPreferSmallTile ? T64x64 : pick_tile(N, Nout, M)], N, Nout, K, M);
+        const int r = pick_ring(kRingCost, N, Nout, K, M, d >= 0 ? 0.93f * now : now);
+        if (r >= 0) {
+          const nf_status st = launch_gemm_ring(r, false, L, s);
+          if (st != NF_EUNSUPPORTED) return st;
+        }
+      }
       if (d == kPreferSmallTile) return launch_gemm_any(bkind, al, T64x64, L, s);
       if (d >= 0) {
         const int sc = pick_stream(d, N, Nout, K, M, act, &snsub);
@@ -453,6 +494,19 @@ nf_status netfuse_linear_packed(const void* X, const void* Wp, const float* bias
     a.ep.vec_store = 2;
     const nf_status st = launch_gemm_stream_packed(ps, L, (hipStream_t)stream);
     if (st != NF_EUNSUPPORTED || f < 0) return st;
+  }
+  // gemm_ring.h where its tiles are faster: few models (no tile of the fragment kernel fills the chip: 2 models of 128
+  // rows 11.9 -> 5.6 us at 768 -> 768, 28.7 -> 10 us at 3072 -> 768), and widths that only the 128- and 256-column
+  // tiles divide (hidden size 1024: 16 models of 128 rows 52.6 -> 30.2 us at 4096 -> 1024, 32 of 512 155.8 -> 121.7 us).
+  // The 64-row tiles of the fragment kernel are ahead wherever they are chosen.
+  if (f < kNumFragFullTiles && ring_fits(Nout, K)) {
+    constexpr TileCost kFragCost[kNumFragFullTiles] = {{128, 96, 5.40f, 2.65f}, {128, 288, 16.2f, 0.f}, {128, 384, 16.7f, 2.44f},
+                                                       {128, 128, 7.85f, 1.69f}, {128, 256, 11.8f, 2.52f}};
+    const int r = pick_ring(kRingPackedCost, N, Nout, K, M, 0.93f * tile_us(kFragCost[f], N, Nout, K, M));
+    if (r >= 0) {
+      const nf_status st = launch_gemm_ring(r, true, L, (hipStream_t)stream);
+      if (st != NF_EUNSUPPORTED) return st;
+    }
   }
   return launch_gemm_frag(f, L, (hipStream_t)stream);
 }
