@@ -30,6 +30,8 @@ namespace nf {
 constexpr int kTapCB = 32;          // input channels per block
 constexpr int kTapPixPitch = 40;    // elements per patch pixel (32 channels + 8)
 
+template <class V> struct __attribute__((packed, aligned(2))) Unaligned { V v; };
+
 template <int BM, int WGM, int WGN, int MINW = 1>
 struct ConvTapCfg {
   static_assert(WGM * WGN == 4, "4 wavefronts");
@@ -52,7 +54,7 @@ struct ConvTapCfg {
   }
 };
 
-// VW: pixels per patch chunk (= a.VW; VW | W).  NT: patch tasks per thread (the host checks the bound).
+// VW: pixels per patch chunk (= a.VW <= W).  NT: patch tasks per thread (the host checks the bound).
 // FUSED: S > 1 narrow groups (4, 8 or 16 channels each) share the single 32-channel block: the weight tile
 // is block diagonal (row r carries its own group's channels at channel offset (r / cog_real) * cig_real,
 // zeros elsewhere), filled once; see conv_patch.h for why no product crosses a group.
@@ -140,12 +142,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Cfg::kMinWa
 #pragma unroll
     for (int u = 0; u < NT; ++u) {
       const int task = tid + u * 256;
-      const int rest = task / a.cpr, ch = task - rest * a.cpr;
+      const int rest = task / a.cpr;
+      // the last chunk of a row is pulled back to end with it: it writes some pixels a second time, with the same values
+      const int ix = min((task - rest * a.cpr) * VW, a.W - VW);
       const int o = rest / PH, py = rest - o * PH;
       const int iy = iy0 + py;
       const bool live = task < ntasks && iy >= 0 && iy < a.H;
-      g_off[u] = live ? (8 * o * a.H + iy) * a.W + ch * VW : -1;
-      l_off[u] = (py * a.PW + kLPad + ch * VW) * PP + 8 * o;
+      g_off[u] = live ? (8 * o * a.H + iy) * a.W + ix : -1;
+      l_off[u] = (py * a.PW + kLPad + ix) * PP + 8 * o;
     }
   }
   // zero the whole patch once: padding and out-of-image rows are never written again
@@ -159,14 +163,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Cfg::kMinWa
 #pragma unroll
       for (int c = 0; c < 8; ++c) {
         const bf16_t* p = xc + g_off[u] + c * plane;
+        // rows and chunks start at any 2-byte address
         if constexpr (VW == 8) {
-          const uint4 v = *reinterpret_cast<const uint4*>(p);
+          const uint4 v = reinterpret_cast<const Unaligned<uint4>*>(p)->v;
           pv[u][c][0] = v.x; pv[u][c][1] = v.y; pv[u][c][2] = v.z; pv[u][c][3] = v.w;
         } else if constexpr (VW == 4) {
-          const uint2 v = *reinterpret_cast<const uint2*>(p);
+          const uint2 v = reinterpret_cast<const Unaligned<uint2>*>(p)->v;
           pv[u][c][0] = v.x; pv[u][c][1] = v.y;
         } else if constexpr (VW == 2) {
-          pv[u][c][0] = *reinterpret_cast<const uint32_t*>(p);
+          pv[u][c][0] = reinterpret_cast<const Unaligned<uint32_t>*>(p)->v;
         } else {
           pv[u][c][0] = *p;
         }

@@ -30,12 +30,22 @@ static nf_status launch_tap(ConvPatchArgs& a, int B, hipStream_t s) {
   const long long total = (long long)a.tiles_m * a.tiles_n * a.nG * B;
   if (total <= 0 || total > 0x7fffffffLL) return NF_EUNSUPPORTED;
   a.PS = (a.PS + 7) / 8 * 8;
-  const long long tasks = (long long)(kTapCB / 8) * (a.PS / a.PW) * a.cpr;     // patch tasks of the tallest tile
-  const int nt = (int)((tasks + 255) / 256);
+  // Pixels per chunk: the width with the fewest chunks per thread (a chunk is 8 loads and up to 32 staging registers),
+  // the narrowest of those, which spreads the chunks over most threads.  Chunks start at any 2-byte address, so widths
+  // need not be multiples of anything: 25 x 25 planes (12 groups of 128 channels) 47 -> 11.8 us and 13 x 13 -> 7 x 7
+  // (512 channels) 189 -> 28.9 us against the implicit-GEMM kernel that took them when a chunk had to divide the width.
+  int nt = 0;
+  for (int vw = 8; vw >= 1; vw /= 2) {
+    if (vw > a.W) continue;
+    const int cpr = (a.W + vw - 1) / vw;
+    const long long tasks = (long long)(kTapCB / 8) * (a.PS / a.PW) * cpr;     // patch tasks of the tallest tile
+    const int n = (int)((tasks + 255) / 256);
+    if (n <= (vw == 8 ? 2 : 3) && (nt == 0 || n <= nt)) { nt = n; a.VW = vw; a.cpr = cpr; }
+  }
   const int lds = Cfg::lds_bytes(a.PS);
   if (lds > 160 * 1024) return NF_EUNSUPPORTED;
 #define NF_TAP(VW_, NT_) return launch_tap_kernel<Cfg, VW_, NT_, FUSED>(total, lds, a, s)
-  switch (a.VW) {
+  if (nt > 0) switch (a.VW) {
     case 8: if (nt == 1) NF_TAP(8, 1); if (nt == 2) NF_TAP(8, 2); break;     // 32 staging registers per task
     case 4: if (nt == 1) NF_TAP(4, 1); if (nt == 2) NF_TAP(4, 2); if (nt == 3) NF_TAP(4, 3); break;
     case 2: if (nt == 1) NF_TAP(2, 1); if (nt == 2) NF_TAP(2, 2); if (nt == 3) NF_TAP(2, 3); break;
