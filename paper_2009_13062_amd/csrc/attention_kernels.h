@@ -378,25 +378,31 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void a
 // the position term.  For a wave's 32 queries i0.. and a 32-key sub-block j0.. the positions S - i + j span
 // 63 consecutive rows of Kr starting at S - i0 + j0 - 31, so the term is computed as a dense 32 x 64 "band"
 // product RAW[o][i] = q_i . kr[base + o] on the matrix pipe (two more accumulators per sub-block) and the
-// diagonal bd[i][j] = RAW[(j - j0) - (i - i0) + 31][i] is picked out through a wave-private LDS tile (row =
-// query, pitch 66 floats: both the writes by position and the skewed reads by key are spread over the banks).
+// diagonal bd[i][j] = RAW[(j - j0) - (i - i0) + 31][i] is picked out through a wave-private LDS tile.  Of the two
+// accumulators a lane holds for position offsets o and o + 32 exactly one is wanted, and it belongs to key
+// (o + i - i0 + 1) mod 32: one select and one write per register pair, a 32 x 32 tile (pitch 36 floats: the reads by key
+// move 16 bytes without bank conflicts).
 // The query biases enter exactly, as two fp32 vectors per key block: c_j = bias_w . k_j per key and
-// e_p = bias_r . kr[p] per position, ((q + b) . k = q . k + b . k), one dot product per thread.
+// e_p = bias_r . kr[p] per position, ((q + b) . k = q . k + b . k), one dot product per thread; they are what the
+// accumulators start from.
 // Workgroup = 128 queries of one (model, sequence, head); per key block of 64 keys it stages the 64 K and V
 // rows and the 192 Kr rows its four waves' bands cover (rows outside [0, 2S) are zero: they only meet
-// query/key pairs past the end).  One workgroup per CU (130 KB of LDS).
+// query/key pairs past the end).  One LDS stage, the next block waiting in registers: 68 KB, so two workgroups share a
+// compute unit and 384 of them (32 models x 12 heads x 128 tokens) run in one round; with two stages and a 32 x 64
+// tile (130 KB) they took two: 31.6 -> 15 us.
 // ------------------------------------------------------------------------------------------
 constexpr int kRelBand = 192;                              // Kr rows per (query block, key block)
-constexpr int kRelXPitch = 66;
+constexpr int kRelXPitch = 36;
 constexpr int kRelOffK = 0;
-constexpr int kRelOffV = kRelOffK + 2 * kAttnKB * kAttnKPitch * 2;
-constexpr int kRelOffR = kRelOffV + 2 * kAttnKB * kAttnVPitch * 2;
-constexpr int kRelOffX = kRelOffR + 2 * kRelBand * kAttnKPitch * 2;
+constexpr int kRelOffV = kRelOffK + kAttnKB * kAttnKPitch * 2;
+constexpr int kRelOffR = kRelOffV + kAttnKB * kAttnVPitch * 2;
+constexpr int kRelOffX = kRelOffR + kRelBand * kAttnKPitch * 2;
 constexpr int kRelOffC = kRelOffX + 4 * 32 * kRelXPitch * 4;
 constexpr int kRelOffE = kRelOffC + kAttnKB * 4;
 constexpr int kRelLdsBytes = kRelOffE + kRelBand * 4;
+static_assert(kRelLdsBytes <= 80 * 1024 && kRelOffC % 16 == 0 && kRelOffX % 16 == 0, "two workgroups per compute unit");
 
-__global__ __launch_bounds__(256) void attention_relpos_mfma_d64_kernel(AttnRelArgs ra, int qblocks) {
+__global__ __launch_bounds__(256, 2) void attention_relpos_mfma_d64_kernel(AttnRelArgs ra, int qblocks) {
   const AttnArgs& a = ra.a;
   extern __shared__ __align__(16) unsigned char rel_smem[];
   lds_bf16_t* const Ks = (lds_bf16_t*)(rel_smem + kRelOffK);
@@ -405,7 +411,8 @@ __global__ __launch_bounds__(256) void attention_relpos_mfma_d64_kernel(AttnRelA
   lds_f32_t* const Xs = (lds_f32_t*)(rel_smem + kRelOffX);
   lds_f32_t* const Cs = (lds_f32_t*)(rel_smem + kRelOffC);
   lds_f32_t* const Es = (lds_f32_t*)(rel_smem + kRelOffE);
-  const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+  const int tid = threadIdx.x, lane = tid % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int half = lane / 32, lq = lane % 32, l16 = lane % 16;
   unsigned id = xcd_remap(blockIdx.x, gridDim.x);
   const int qb = id % qblocks;  id /= qblocks;
@@ -460,35 +467,34 @@ __global__ __launch_bounds__(256) void attention_relpos_mfma_d64_kernel(AttnRelA
       if (p >= 0 && p < 2 * a.S) rreg[t] = *reinterpret_cast<const uint4*>(Rp + (long)p * hd + kc);
     }
   };
-  auto commit = [&](int stage) {
+  auto commit = [&]() {
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       const int c = tid + t * 256, key = c / 8, kc = (c % 8) * 8;
-      lds_store16(Ks + stage * kAttnKB * kAttnKPitch + key * kAttnKPitch + kc, kreg[t]);
-      lds_store16(Vs + stage * kAttnKB * kAttnVPitch + key * kAttnVPitch + kc, vreg[t]);
+      lds_store16(Ks + key * kAttnKPitch + kc, kreg[t]);
+      lds_store16(Vs + key * kAttnVPitch + kc, vreg[t]);
     }
 #pragma unroll
     for (int t = 0; t < 6; ++t) {
       const int c = tid + t * 256, row = c / 8, kc = (c % 8) * 8;
-      lds_store16(Rs + stage * kRelBand * kAttnKPitch + row * kAttnKPitch + kc, rreg[t]);
+      lds_store16(Rs + row * kAttnKPitch + kc, rreg[t]);
     }
   };
   fetch(0);
-  commit(0);
-  __syncthreads();
 
   lds_f32_t* const Xw = Xs + wave * 32 * kRelXPitch;       // this wave's exchange tile [query][position offset]
   const int nblk = (a.S + kAttnKB - 1) / kAttnKB;
   for (int blk = 0; blk < nblk; ++blk) {
-    const int j0 = blk * kAttnKB, cur = blk & 1;
+    const int j0 = blk * kAttnKB;
+    const lds_bf16_t *Kc = Ks, *Vc = Vs, *Rc = Rs;
+    commit();
+    __syncthreads();
     if (blk + 1 < nblk) fetch(j0 + kAttnKB);
-    const lds_bf16_t* Kc = Ks + cur * kAttnKB * kAttnKPitch;
-    const lds_bf16_t* Vc = Vs + cur * kAttnKB * kAttnVPitch;
-    const lds_bf16_t* Rc = Rs + cur * kRelBand * kAttnKPitch;
 
     // ---- the bias terms of this block: thread t < 64: c_t = bias_w . k_t; thread 64 + r: e_r = bias_r . kr[band row r]
+    // (wavefront 0 and the others: the bias values are uniform and come through scalar loads)
     {
-      const bool is_key = tid < kAttnKB;
+      const bool is_key = wave == 0;
       const lds_bf16_t* row = is_key ? Kc + tid * kAttnKPitch : Rc + (tid - kAttnKB) * kAttnKPitch;
       const float* bias = is_key ? bw : br;
       float dot = 0.f;
@@ -513,7 +519,7 @@ __global__ __launch_bounds__(256) void attention_relpos_mfma_d64_kernel(AttnRelA
 #pragma unroll
     for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) s_acc[sb][r] = 0.f;
+      for (int r = 0; r < 16; ++r) s_acc[sb][r] = Cs[sb * 32 + 8 * (r / 4) + 4 * half + r % 4];
     {
       bf16x8_t kf[kAttnD / 16][2];
 #pragma unroll
@@ -535,7 +541,7 @@ __global__ __launch_bounds__(256) void attention_relpos_mfma_d64_kernel(AttnRelA
 #pragma unroll
       for (int ob = 0; ob < 2; ++ob)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) rb[ob][r] = 0.f;
+        for (int r = 0; r < 16; ++r) rb[ob][r] = Es[start + 32 * ob + 8 * (r / 4) + 4 * half + r % 4];
 #pragma unroll
       for (int kk = 0; kk < kAttnD / 16; ++kk)
 #pragma unroll
@@ -543,26 +549,26 @@ __global__ __launch_bounds__(256) void attention_relpos_mfma_d64_kernel(AttnRelA
           const bf16x8_t rf = *(const lds_bf16x8_t*)(Rc + (start + ob * 32 + lq) * kAttnKPitch + kk * 16 + half * 8);
           rb[ob] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rf, qf[kk], rb[ob], 0, 0, 0);
         }
-      // register r of block ob: position offset o = 32 ob + 8 (r/4) + 4 half + r%4, query lq
+      // register r of block ob: position offset 32 ob + o, o = 8 (r/4) + 4 half + r%4, query lq; of the two blocks
+      // the one whose offset is key + 31 - lq of a key in 0 ... 31
 #pragma unroll
-      for (int ob = 0; ob < 2; ++ob)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int o = 32 * ob + 8 * (r / 4) + 4 * half + (r % 4);
-          Xw[lq * kRelXPitch + o] = rb[ob][r] + Es[start + o];
-        }
+      for (int r = 0; r < 16; ++r) {
+        const int o = 8 * (r / 4) + 4 * half + r % 4;
+        Xw[lq * kRelXPitch + ((o + lq + 1) & 31)] = o + lq >= 31 ? rb[0][r] : rb[1][r];
+      }
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int jj = 8 * (r / 4) + 4 * half + (r % 4);    // key within the sub-block
-        s_acc[sb][r] += Xw[lq * kRelXPitch + jj - lq + 31] + Cs[sb * 32 + jj];
+      for (int r4 = 0; r4 < 4; ++r4) {                       // keys 8 r4 + 4 half + 0..3 of the sub-block
+        const f32x4v_t x = *(const lds_f32x4_t*)(Xw + lq * kRelXPitch + 8 * r4 + 4 * half);
+        s_acc[sb][4 * r4] += x.x; s_acc[sb][4 * r4 + 1] += x.y; s_acc[sb][4 * r4 + 2] += x.z; s_acc[sb][4 * r4 + 3] += x.w;
       }
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();                      // the tile is rewritten for the next sub-block
     }
 
+    const bool raw = mk == nullptr && sc > 0.f;              // as attention_mfma_d64_kernel
     if (mk != nullptr) {
 #pragma unroll
       for (int sb = 0; sb < 2; ++sb)
@@ -571,7 +577,7 @@ __global__ __launch_bounds__(256) void attention_relpos_mfma_d64_kernel(AttnRelA
           const int key = j0 + sb * 32 + 8 * (r / 4) + 4 * half + (r % 4);
           s_acc[sb][r] = fmaf(s_acc[sb][r], sc, (key < a.S ? mk[key] : 0.f) * kLog2e);
         }
-    } else {
+    } else if (!raw) {
 #pragma unroll
       for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
@@ -592,11 +598,13 @@ __global__ __launch_bounds__(256) void attention_relpos_mfma_d64_kernel(AttnRelA
 #pragma unroll
       for (int r = 0; r < 16; ++r) mloc = fmaxf(mloc, s_acc[sb][r]);
     mloc = fmaxf(mloc, __shfl_xor(mloc, 32, kWave));
+    if (raw) mloc = fmaxf(mloc * sc, -3.0e38f);
     const float mnew = fmaxf(mrun, mloc);
     const float corr = __builtin_amdgcn_exp2f(mrun - mnew);
     mrun = mnew;
     float psum = 0.f;
     bf16x8_t pf[2][2];
+    const float esc = raw ? sc : 1.0f;
 #pragma unroll
     for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
@@ -604,8 +612,8 @@ __global__ __launch_bounds__(256) void attention_relpos_mfma_d64_kernel(AttnRelA
         uint32_t w[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const float p0 = __builtin_amdgcn_exp2f(s_acc[sb][8 * st + 2 * e] - mnew);
-          const float p1 = __builtin_amdgcn_exp2f(s_acc[sb][8 * st + 2 * e + 1] - mnew);
+          const float p0 = __builtin_amdgcn_exp2f(fmaf(s_acc[sb][8 * st + 2 * e], esc, -mnew));
+          const float p1 = __builtin_amdgcn_exp2f(fmaf(s_acc[sb][8 * st + 2 * e + 1], esc, -mnew));
           w[e] = pack_bf16x2(p0, p1);
           psum += p0 + p1;
         }
@@ -631,8 +639,7 @@ __global__ __launch_bounds__(256) void attention_relpos_mfma_d64_kernel(AttnRelA
           o_acc[tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, both), pf[sb][st],
                                                               o_acc[tb], 0, 0, 0);
         }
-    if (blk + 1 < nblk) commit(cur ^ 1);
-    __syncthreads();
+    __syncthreads();                                        // the stage is free for the next block's commit
   }
 
   const float ltot = lrun + __shfl_xor(lrun, 32, kWave);
