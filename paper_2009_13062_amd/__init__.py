@@ -96,8 +96,10 @@ def _ptr(t: Optional[torch.Tensor], like: Optional[torch.Tensor] = None, f32: bo
 
 
 def _stream(stream) -> Optional[int]:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream or None
+    if stream is None:
+        # the raw handle of torch.cuda.current_stream(), without building a Stream object on every call (3.5 of 8 us)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
+    return stream.cuda_stream or None
 
 
 def _check(fn: str, st: int):
