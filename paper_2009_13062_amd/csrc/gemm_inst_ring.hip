@@ -6,28 +6,29 @@
 
 namespace nf {
 
-template <class Cfg, bool PB>
+template <class Cfg, bool PB, bool CONV>
 __global__ __launch_bounds__(Cfg::kThreads, Cfg::kWPE) void gemm_ring_kernel(GemmArgs a) {
   extern __shared__ __align__(1024) unsigned char smem_raw[];
   unsigned id = xcd_remap(blockIdx.x, gridDim.x);
   // consecutive ids: row tiles of one column panel, then the next panel, then the next problem
   const int tm = id % a.tiles_m;  id /= a.tiles_m;
-  const int tn = id % a.tiles_n;
-  const int z = id / a.tiles_n;
-  const bf16_t* R = a.R ? a.R + z * a.sC0 : nullptr;
+  const int tn = id % a.tiles_n;  id /= a.tiles_n;
+  const int z = id % a.nz0, z1 = id / a.nz0;
+  const long coff = z * a.sC0 + z1 * a.sC1;
   const float* bias = a.ep.col_bias ? a.ep.col_bias + z * a.ep.col_vec_stride0 : nullptr;
-  gemm_ring_tile<Cfg, PB>(a.A + z * a.sA0, a.lda, a.B + z * a.sB0, a.ldb, a.K, (lds_u8_t*)smem_raw, a.C + z * a.sC0, R,
-                          a.ldc, bias, a.ep.act, tm * Cfg::kBM, tn * Cfg::kBN, a.rows, a.cols);
+  gemm_ring_tile<Cfg, PB, CONV>(a.A + z * a.sA0, a.lda, a.B + z * a.sB0 + z1 * a.sB1, a.ldb, a.K, (lds_u8_t*)smem_raw,
+                                a.C + coff, a.R ? a.R + coff : nullptr, a.ldc, bias, a.ep, z * a.ep.row_vec_stride0,
+                                tm * Cfg::kBM, tn * Cfg::kBN, a.rows, a.cols);
 }
 
-template <class Cfg, bool PB>
+template <class Cfg, bool PB, bool CONV = false>
 static nf_status launch_ring(GemmLaunch& L, hipStream_t s) {
   GemmArgs& a = L.a;
   a.tiles_m = (a.rows + Cfg::kBM - 1) / Cfg::kBM;
   a.tiles_n = (a.cols + Cfg::kBN - 1) / Cfg::kBN;
-  const long long total = (long long)a.tiles_m * a.tiles_n * a.nz0;
+  const long long total = (long long)a.tiles_m * a.tiles_n * a.nz0 * L.nz1;
   if (total <= 0 || total > 0x7fffffffLL) return NF_EUNSUPPORTED;
-  auto kern = gemm_ring_kernel<Cfg, PB>;
+  auto kern = gemm_ring_kernel<Cfg, PB, CONV>;
   constexpr int kLds = Cfg::kLdsBytes;
   if (kLds > 64 * 1024) {
     static std::atomic<bool> opted_in{false};
@@ -72,15 +73,36 @@ static nf_status launch_ring_packed_tile(int tile, GemmLaunch& L, hipStream_t s)
   return NF_EUNSUPPORTED;
 }
 
+// Pointwise convolutions: short k (64 ... 2048 channels), so a tile is mostly prologue and epilogue; two or more workgroups
+// per compute unit run them under each other's loads.
+static nf_status launch_ring_conv_tile(int tile, GemmLaunch& L, hipStream_t s) {
+  switch (tile) {
+    case RC64x64: return launch_ring<RingCfg<1, 1, 2, 2, 1, 64, 3, 2>, false, true>(L, s);
+    case RC64x128: return launch_ring<RingCfg<1, 1, 2, 4, 1, 64, 3, 2>, false, true>(L, s);
+    case RC64x256: return launch_ring<RingCfg<1, 2, 2, 4, 1, 32, 3, 4>, false, true>(L, s);
+    case RC128x128: return launch_ring<RingCfg<2, 1, 2, 4, 1, 64, 2, 4>, false, true>(L, s);
+    case RC128x256: return launch_ring<RingCfg<2, 2, 2, 4, 1, 32, 3, 2>, false, true>(L, s);
+  }
+  return NF_EUNSUPPORTED;
+}
+
+static bool ring_aligned(const GemmArgs& a) {
+  return a.rows > 0 && a.lda % 8 == 0 && a.ldb % 8 == 0 && a.ldc % 8 == 0 && ((uintptr_t)a.A & 15) == 0 &&
+         ((uintptr_t)a.B & 15) == 0 && ((uintptr_t)a.C & 15) == 0 && ((uintptr_t)a.R & 15) == 0 &&
+         (long long)a.rows * a.K < (1LL << 30) && (long long)a.K * a.cols < (1LL << 30);   // 32-bit byte offsets
+}
+
 nf_status launch_gemm_ring(int tile, bool packed, GemmLaunch& L, hipStream_t s) {
   const GemmArgs& a = L.a;
-  if (a.rows <= 0 || !ring_fits(a.cols, a.K) || (packed && a.cols % 32) || L.nz1 != 1) return NF_EUNSUPPORTED;
-  if (a.lda % 8 || a.ldb % 8 || a.ldc % 8 || ((uintptr_t)a.A & 15) || ((uintptr_t)a.B & 15) || ((uintptr_t)a.C & 15) ||
-      ((uintptr_t)a.R & 15) || ((uintptr_t)a.ep.col_bias & 15) || a.ep.col_vec_stride0 % 4)
-    return NF_EUNSUPPORTED;
-  // byte offsets inside one problem's operands are 32 bits wide
-  if ((long long)a.rows * a.K >= (1LL << 30) || (long long)a.K * a.cols >= (1LL << 30)) return NF_EUNSUPPORTED;
+  if (!ring_fits(a.cols, a.K) || (packed && a.cols % 32) || L.nz1 != 1 || !ring_aligned(a)) return NF_EUNSUPPORTED;
+  if (((uintptr_t)a.ep.col_bias & 15) || a.ep.col_vec_stride0 % 4) return NF_EUNSUPPORTED;
   return packed ? launch_ring_packed_tile(tile, L, s) : launch_ring_tile(tile, L, s);
+}
+
+nf_status launch_conv_ring(int tile, GemmLaunch& L, hipStream_t s) {
+  const GemmArgs& a = L.a;
+  if (a.cols % 8 || a.K % 64 || !ring_aligned(a)) return NF_EUNSUPPORTED;
+  return launch_ring_conv_tile(tile, L, s);
 }
 
 }  // namespace nf

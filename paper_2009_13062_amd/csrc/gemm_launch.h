@@ -71,6 +71,9 @@ enum RingTileId { R32x32 = 0, R64x64, R64x128, R96x128, R96x256, R128x128, R128x
 enum RingPackedTileId { RP32x32 = 0, RP64x64, RP128x64, RP128x128, RP128x256, RP256x256, kNumRingPackedTiles };
 inline bool ring_fits(int cols, int K) { return cols % 8 == 0 && K % 64 == 0 && K >= 256; }     // shorter k: not measured
 nf_status launch_gemm_ring(int tile, bool packed, GemmLaunch& L, hipStream_t s);
+// The same for a pointwise convolution (A = weights, B = planes of cols % 8 == 0 positions, K % 64 == 0 channels).
+enum RingConvTileId { RC64x64 = 0, RC64x128, RC64x256, RC128x128, RC128x256 };
+nf_status launch_conv_ring(int tile, GemmLaunch& L, hipStream_t s);
 
 // BKIND: 8 / 4 / 1 = dense B read with that vector width; 0 = implicit (im2col) B.
 // align_a: 16, 8, 4 or 2 = byte alignment of every A row start (and K a multiple of align_a/2).

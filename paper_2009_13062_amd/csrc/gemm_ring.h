@@ -48,6 +48,45 @@ struct RingCfg {
   }
 };
 
+// Epilogue of a convolution: act((acc + bias[row]) * scale[row] + shift[row] + residual), constants per output row.
+template <int FM, int FN, int ACT>
+__device__ __forceinline__ void conv_epilogue(const f32x16_t (&acc)[FM][FN], bf16_t* C, const bf16_t* R, long ldc, const Epilogue& ep,
+                                              long rvo, int row0, int col0, int rows, int cols) {
+  const int lane = threadIdx.x % kWave, half = lane / 32, l32 = lane % 32;
+#pragma unroll
+  for (int i = 0; i < FM; ++i) {
+    const int row = row0 + 32 * i + l32;
+    const long off = (long)row * ldc + col0 + half * 8;
+    const int left = row < rows ? cols - col0 - half * 8 : 0;
+    const long rv = rvo + min(row, rows - 1);
+    const float bias = ep.row_bias ? ep.row_bias[rv] : 0.f;
+    const float scale = ep.row_scale ? ep.row_scale[rv] : 1.f, shift = ep.row_scale ? ep.row_shift[rv] : 0.f;
+    uint4 rr[2 * FN];
+#pragma unroll
+    for (int p = 0; p < 2 * FN; ++p)
+      rr[p] = R && 16 * p < left ? *reinterpret_cast<const uint4*>(R + off + 16 * p) : make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+    for (int p = 0; p < 2 * FN; ++p) {
+      float v[8];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float v0 = fmaf(acc[i][p / 2][8 * (p % 2) + e] + bias, scale, shift);
+        const float v1 = fmaf(acc[i][p / 2][8 * (p % 2) + 4 + e] + bias, scale, shift);
+        const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(v0), __float_as_uint(v1), false, false);
+        v[e] = __uint_as_float(s[0]);
+        v[4 + e] = __uint_as_float(s[1]);
+      }
+      const uint32_t w[4] = {rr[p].x, rr[p].y, rr[p].z, rr[p].w};
+      uint32_t o[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        o[e] = pack_bf16x2(act_const<ACT>(v[2 * e] + __uint_as_float(w[e] << 16)),
+                           act_const<ACT>(v[2 * e + 1] + __uint_as_float(w[e] & 0xffff0000u)));
+      if (16 * p < left) *reinterpret_cast<uint4*>(C + off + 16 * p) = make_uint4(o[0], o[1], o[2], o[3]);
+    }
+  }
+}
+
 // Partial sums of KG groups: every group leaves its accumulators in LDS ([group][wave][block][4-column group][lane],
 // 16 bytes per lane), then group q finishes pieces q, q + KG, ... of its wave position's FM x FN x 2.
 template <class Cfg, int ACT>
@@ -80,11 +119,13 @@ __device__ __forceinline__ void ring_reduce_epilogue(lds_f32_t* red, int w, int 
   }
 }
 
-// A, B: this problem's operands (B: row-major or packed); C, R, bias: this problem's output.
-template <class Cfg, bool PB>
+// A, B: this problem's operands (B: row-major or packed); C, R, bias: this problem's output.  CONV: a pointwise
+// convolution, A its weights, B its input planes, rvo the offset of its per-row constants.
+template <class Cfg, bool PB, bool CONV>
 __device__ __forceinline__ void gemm_ring_tile(const bf16_t* __restrict__ A, long lda, const bf16_t* __restrict__ B, long ldb, int K, lds_u8_t* smem,
-                                               bf16_t* C, const bf16_t* R, long ldc, const float* bias, int act, int row0,
-                                               int col0, int rows, int cols) {
+                                               bf16_t* C, const bf16_t* R, long ldc, const float* bias, const Epilogue& ep, long rvo,
+                                               int row0, int col0, int rows, int cols) {
+  const int act = ep.act;
   constexpr int FM = Cfg::FM, FN = Cfg::FN, NS = Cfg::kNS, BK = Cfg::kBK, KG = Cfg::kKG, NW = Cfg::kNW;
   const int lane = threadIdx.x % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -123,7 +164,7 @@ __device__ __forceinline__ void gemm_ring_tile(const bf16_t* __restrict__ A, lon
         if (t * NW + w < Cfg::kABlocks)
           __builtin_amdgcn_global_load_lds((glb_u8_t*)(pa + voff[t]), stage + (t * NW + w) * 1024, 16, 0, 0);
         else
-          __builtin_amdgcn_global_load_lds((glb_u8_t*)(pb + voff[t]), stage + (t * NW + w) * 1024, 16, 0, kWeightCpol);
+          __builtin_amdgcn_global_load_lds((glb_u8_t*)(pb + voff[t]), stage + (t * NW + w) * 1024, 16, 0, CONV ? 0 : kWeightCpol);
       }
     }
     pa += inc_a;
@@ -225,7 +266,12 @@ __device__ __forceinline__ void gemm_ring_tile(const bf16_t* __restrict__ A, lon
   }
 
   const int rw = row0 + wm * Cfg::WM, cw = col0 + wn * Cfg::WN;
-  if constexpr (KG == 1) {
+  if constexpr (CONV) {
+    static_assert(KG == 1, "no split k");
+    if (act == NF_ACT_RELU) conv_epilogue<FM, FN, NF_ACT_RELU>(acc, C, R, ldc, ep, rvo, rw, cw, rows, cols);
+    else if (act == NF_ACT_GELU) conv_epilogue<FM, FN, NF_ACT_GELU>(acc, C, R, ldc, ep, rvo, rw, cw, rows, cols);
+    else conv_epilogue<FM, FN, NF_ACT_NONE>(acc, C, R, ldc, ep, rvo, rw, cw, rows, cols);
+  } else if constexpr (KG == 1) {
     if (act == NF_ACT_GELU) reg_epilogue<FM, FN, NF_ACT_GELU>(acc, C, R, ldc, bias, rw, cw, rows, cols);
     else if (act == NF_ACT_RELU) reg_epilogue<FM, FN, NF_ACT_RELU>(acc, C, R, ldc, bias, rw, cw, rows, cols);
     else reg_epilogue<FM, FN, NF_ACT_NONE>(acc, C, R, ldc, bias, rw, cw, rows, cols);

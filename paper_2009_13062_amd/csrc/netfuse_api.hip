@@ -615,6 +615,20 @@ nf_status netfuse_conv2d(const void* x, const void* w, const float* bias, const 
       const int al_b = common_align({x}, {(long long)H * W});
       int bkind = 1;
       if (al_b == 16 && HoWo % 8 == 0) bkind = 8;
+      if (bkind == 8 && al == 16 && cog > 32 && Kdim % 64 == 0 && forced_tile() < 0) {
+        // gemm_ring.h with the widest tile that still gives 400 workgroups (two or three run on a compute unit).  Measured
+        // against the register-staged tiles (us): 32 models 64 -> 64 at 56 x 56 11.8 -> 8.4, 64 -> 256 23.9 -> 19.2,
+        // 128 -> 512 at 28 x 28 16.2 -> 13.7, 512 -> 128 11.3 -> 10.0; 2 models 512 -> 128 6.5 -> 5.8; 4 models of 4 images
+        // 512 -> 2048 at 8 x 8 11.1 -> 9.5.
+        auto tiles = [&](int bm, int bn) { return problems * ((cog + bm - 1) / bm) * ((HoWo + bn - 1) / bn); };
+        int t = RC64x64;
+        if (cog >= 128 && tiles(128, 256) >= 400) t = RC128x256;
+        else if (cog >= 128 && tiles(128, 128) >= 400) t = RC128x128;
+        else if (cog < 128 && tiles(64, 256) >= 400) t = RC64x256;
+        else if (HoWo > 64 && tiles(64, 128) >= 200) t = RC64x128;
+        const nf_status st = launch_conv_ring(t, L, s);
+        if (st != NF_EUNSUPPORTED) return st;
+      }
       return launch_gemm_any(bkind, al, tile, L, s);
     }
     static const bool no_patch = dev_getenv("NETFUSE_NO_PATCH") != nullptr;
