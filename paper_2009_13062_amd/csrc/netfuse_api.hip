@@ -771,13 +771,17 @@ nf_status netfuse_layernorm(const void* x, const void* residual, const float* ga
   // 3.9 -> 4.7 us)
   static const int ln_forced = [] { const char* e = dev_getenv("NETFUSE_LN_ROWS"); return e ? atoi(e) : 0; }();
   const int ln_rows = ln_forced ? ln_forced : (nrows >= 16384 ? 2 : 1);
-  if (vec && H <= kWave * 4 * 4 && (ln_rows == 2 || ln_rows == 4) && rows % ln_rows == 0) {
-    const long long blocks_r = (nrows / ln_rows + 3) / 4;
-#define NF_LNR(T, R)                                                                                      \
-  nf_launch((layernorm_rows_kernel<T, 4, 4, R>), dim3((unsigned)blocks_r), dim3(256), 0, s,       \
+  if (vec && H <= kWave * 4 * 4) {
+    const int R = ln_rows == 2 && rows % 2 == 0 ? 2 : 1, nit = (H + 255) / 256;
+    const long long blocks_r = (nrows / R + 3) / 4;
+#define NF_LNR(T, N, R_)                                                                                  \
+  nf_launch((layernorm_rows_kernel<T, N, R_>), dim3((unsigned)blocks_r), dim3(256), 0, s,                  \
                      (const T*)x, (const T*)residual, gamma, beta, (T*)y, M, rows, H, eps, ch)
-    if (dt == NF_F32) { if (ln_rows == 2) NF_LNR(float, 2); else NF_LNR(float, 4); }
-    else { if (ln_rows == 2) NF_LNR(bf16_t, 2); else NF_LNR(bf16_t, 4); }
+#define NF_LNR_N(T, N) if (R == 2) NF_LNR(T, N, 2); else NF_LNR(T, N, 1)
+#define NF_LNR_T(T) switch (nit) { case 1: NF_LNR_N(T, 1); break; case 2: NF_LNR_N(T, 2); break; case 3: NF_LNR_N(T, 3); break; default: NF_LNR_N(T, 4); }
+    if (dt == NF_F32) { NF_LNR_T(float) } else { NF_LNR_T(bf16_t) }
+#undef NF_LNR_T
+#undef NF_LNR_N
 #undef NF_LNR
     return launched();
   }

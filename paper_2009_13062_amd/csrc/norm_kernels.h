@@ -138,10 +138,14 @@ __global__ __launch_bounds__(256) void layernorm_kernel(
   }
 }
 
-// The same for rows that fit in registers, ROWS consecutive rows of one model per wavefront (rows % ROWS
-// == 0): gamma and beta, 8 bytes per feature against 2 or 4 of the row itself, are fetched once per ROWS
-// rows instead of once per row, and the loads of all ROWS rows are in flight together.
-template <typename T, int VEC, int MAXIT, int ROWS>
+// The same for rows of up to 256 NIT features in whole 4-feature pieces, ROWS consecutive rows of one model per wavefront
+// (rows % ROWS == 0; gamma and beta, 8 bytes per feature against 2 or 4 of the row itself, are then fetched once per
+// ROWS rows).  At a few thousand rows a launch is one trip to memory long, so there is only one: every load of the
+// wavefront, gamma and beta included, is issued up front and without a condition (pieces past the end re-read the last
+// one and count as zeros).  With the loads under `if` and the affine vectors fetched after the statistics it was one
+// trip per 256 features and one more: the 12-layer encoder at 2 models 660 -> 626 us (24 of these launches).
+struct __attribute__((packed, aligned(4))) Float4Unaligned { float v[4]; };
+template <typename T, int NIT, int ROWS>
 __global__ __launch_bounds__(256) void layernorm_rows_kernel(
     const T* x, const T* residual, const float* __restrict__ gamma, const float* __restrict__ beta,
     T* y, int M, int rows, int H, float eps, int channel_layout) {
@@ -149,65 +153,73 @@ __global__ __launch_bounds__(256) void layernorm_rows_kernel(
   const long wrow = ((long)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave) * ROWS;   // m*rows + r of the first row
   if (wrow >= (long)M * rows) return;
   const int m = (int)(wrow / rows), r0 = (int)(wrow % rows);
-  const float* gm = gamma + (size_t)m * H;
-  const float* bt = beta + (size_t)m * H;
   size_t base[ROWS];
 #pragma unroll
   for (int q = 0; q < ROWS; ++q)
     base[q] = channel_layout ? ((size_t)(r0 + q) * M + m) * H : ((size_t)m * rows + r0 + q) * H;
-  float v[ROWS][MAXIT][VEC];
-  float sum[ROWS];
+  int idx[NIT];
 #pragma unroll
-  for (int q = 0; q < ROWS; ++q) {
-    sum[q] = 0.f;
+  for (int it = 0; it < NIT; ++it) idx[it] = min((it * kWave + lane) * 4, H - 4);
+  float v[ROWS][NIT][4], t[ROWS][NIT][4];
 #pragma unroll
-    for (int it = 0; it < MAXIT; ++it) {
-      const int i = (it * kWave + lane) * VEC;
-      if (i < H) {
-        VecIO<T, VEC>::load(x + base[q] + i, v[q][it]);
-        if (residual) {
-          float t[VEC];
-          VecIO<T, VEC>::load(residual + base[q] + i, t);
+  for (int q = 0; q < ROWS; ++q)
 #pragma unroll
-          for (int e = 0; e < VEC; ++e) v[q][it][e] += t[e];
-        }
+    for (int it = 0; it < NIT; ++it) VecIO<T, 4>::load(x + base[q] + idx[it], v[q][it]);
+  if (residual) {
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) sum[q] += v[q][it][e];
-      }
-    }
+    for (int q = 0; q < ROWS; ++q)
+#pragma unroll
+      for (int it = 0; it < NIT; ++it) VecIO<T, 4>::load(residual + base[q] + idx[it], t[q][it]);
+  }
+  Float4Unaligned g[NIT], b[NIT];
+#pragma unroll
+  for (int it = 0; it < NIT; ++it) {
+    g[it] = *reinterpret_cast<const Float4Unaligned*>(gamma + (size_t)m * H + idx[it]);
+    b[it] = *reinterpret_cast<const Float4Unaligned*>(beta + (size_t)m * H + idx[it]);
+  }
+  __builtin_amdgcn_sched_barrier(0);                         // the loads stay in front
+  if (residual) {
+#pragma unroll
+    for (int q = 0; q < ROWS; ++q)
+#pragma unroll
+      for (int it = 0; it < NIT; ++it)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[q][it][e] += t[q][it][e];
   }
   float mean[ROWS], rstd[ROWS];
 #pragma unroll
-  for (int q = 0; q < ROWS; ++q) mean[q] = wave_sum(sum[q]) / (float)H;
+  for (int q = 0; q < ROWS; ++q) {
+    float sum = 0.f;
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) {
+      const bool in = (it * kWave + lane) * 4 < H;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sum += in ? v[q][it][e] : 0.f;
+    }
+    mean[q] = sum;
+  }
+#pragma unroll
+  for (int q = 0; q < ROWS; ++q) mean[q] = wave_sum(mean[q]) / (float)H;
 #pragma unroll
   for (int q = 0; q < ROWS; ++q) {
     float sq = 0.f;
 #pragma unroll
-    for (int it = 0; it < MAXIT; ++it) {
-      const int i = (it * kWave + lane) * VEC;
-      if (i < H) {
+    for (int it = 0; it < NIT; ++it) {
+      const bool in = (it * kWave + lane) * 4 < H;
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) { const float dlt = v[q][it][e] - mean[q]; sq = fmaf(dlt, dlt, sq); }
-      }
+      for (int e = 0; e < 4; ++e) { const float dlt = in ? v[q][it][e] - mean[q] : 0.f; sq = fmaf(dlt, dlt, sq); }
     }
     rstd[q] = 1.0f / sqrtf(wave_sum(sq) / (float)H + eps);
   }
 #pragma unroll
-  for (int it = 0; it < MAXIT; ++it) {
-    const int i = (it * kWave + lane) * VEC;
-    if (i < H) {
-      float g[VEC], b[VEC];
+  for (int q = 0; q < ROWS; ++q)
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) { g[e] = gm[i + e]; b[e] = bt[i + e]; }
+    for (int it = 0; it < NIT; ++it) {
+      float o[4];
 #pragma unroll
-      for (int q = 0; q < ROWS; ++q) {
-        float o[VEC];
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) o[e] = fmaf((v[q][it][e] - mean[q]) * rstd[q], g[e], b[e]);
-        VecIO<T, VEC>::store(y + base[q] + i, o);
-      }
+      for (int e = 0; e < 4; ++e) o[e] = fmaf((v[q][it][e] - mean[q]) * rstd[q], g[it].v[e], b[it].v[e]);
+      if ((it * kWave + lane) * 4 < H) VecIO<T, 4>::store(y + base[q] + idx[it], o);
     }
-  }
 }
 
 // Merged inference batch norm (Section 3.1): per merged channel c of x[B][Ctot][HW].
