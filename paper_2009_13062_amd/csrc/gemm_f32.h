@@ -20,6 +20,10 @@
 //
 // D k-steps of loads are in flight in a ring of register slots while a double-buffered LDS stage is multiplied.
 //
+// One order of the sum for every tile: k-step n belongs to chain n mod CH, and the chains are added at the end, first
+// those 2 apart, then the two sums.  Which tile runs depends on how many models (and images) are merged, and a model's
+// bits must not, so CH follows from K alone; the tiles differ in how many groups of wavefronts the chains are dealt to.
+//
 // Measured (8 models, us; the plain FMA kernels before -> this): 128 x 768 x 3072 matmul 187 -> 45 (31.6 at the fp32
 // matrix peak), 128 x 3072 x 768 750 -> 52, 3x3 convolution 256 -> 256 at 14 x 14 570 -> 40, 512 -> 512 at 7 x 7 1060
 // -> 54, pointwise 64 -> 256 at 56 x 56 460 -> 17; a 12-layer encoder 16.3 -> 3.2 ms, ResNet-50 29.9 -> 1.4 ms.
@@ -28,19 +32,22 @@
 
 namespace nf {
 
-// KG groups of 4 wavefronts share a tile: group q takes k-steps q, q + KG, ... through LDS stages of its own, and the
-// partial sums are added in ascending group order at the end.  For tiles of which a compute unit gets only one
-// (few models, small images): one wavefront per SIMD would wait out every load and LDS read.
-template <int BM, int BN, int WGM, int WGN, int BK, int D, int KG = 1>
+// KG groups of 4 wavefronts share a tile: group q takes k-steps q, q + KG, ... (chains q and, if there are more than
+// KG, q + KG ...) through LDS stages of its own, and the partial sums meet in LDS at the end.  For tiles of which a
+// compute unit gets only one (few models, small images): one wavefront per SIMD would wait out every load and LDS read.
+template <int BM, int BN, int WGM, int WGN, int BK, int D, int CH, int KG = 1>
 struct F32Cfg {
-  static_assert(WGM * WGN == 4, "4 wavefronts");
+  static_assert(WGM * WGN == 4 && (CH == 2 || CH == 4) && CH % KG == 0, "4 wavefronts per group, whole chains");
   static constexpr int kBM = BM, kBN = BN, kWGM = WGM, kWGN = WGN, kBK = BK, kD = D, kKG = KG, kThreads = 256 * KG;
+  static constexpr int kChains = CH / KG;                                           // accumulated by one wavefront
+  static constexpr int kUnroll = D > kChains ? D : kChains;
   static constexpr int WM = BM / WGM, WN = BN / WGN, FM = WM / 16, FN = WN / 16;
-  static_assert(WM % 16 == 0 && WN % 16 == 0 && BK % 16 == 0 && D % 2 == 0, "16 x 16 x 16 blocks, even ring");
+  static_assert(WM % 16 == 0 && WN % 16 == 0 && BK % 16 == 0 && D % 2 == 0 && kUnroll % D == 0 && kUnroll % kChains == 0, "16 x 16 x 16 blocks, even ring");
   static constexpr int kPitchA = BK + 4, kPitchB = BN + 4;
   static constexpr int kStageA = BM * kPitchA, kStage = kStageA + BK * kPitchB;     // floats
   static constexpr int kLdsBytes = KG * 2 * kStage * 4;
   static_assert(kLdsBytes <= 160 * 1024 && (KG - 1) * BM * BN <= KG * 2 * kStage, "LDS");
+  static_assert(BK == 32, "the chains are made of 32-k steps in every tile");
   static constexpr int kAChunks = BM * BK / 4, kAPer = (kAChunks + 255) / 256;
   static constexpr int kBChunks = BK * BN / 4, kBPer = (kBChunks + 255) / 256;
   static constexpr int kGPer = BK * BN / 256;                                       // gathered elements per thread
@@ -64,7 +71,8 @@ __device__ __forceinline__ unsigned div_by(unsigned n, unsigned rcp, unsigned on
 // KIND kF32Dense: B rows of whole 4-column chunks; kF32Gather / kF32GatherWide: B through the convolution geometry,
 // 4 bytes at a time, any shape, with at most 31 / 63 taps.  AVEC: K % 4 == 0, so A moves in whole 4-k chunks.
 template <class Cfg, int KIND, bool AVEC>
-__global__ __launch_bounds__(Cfg::kThreads) void gemm_f32_kernel(GemmF32Args a) {
+__global__ __launch_bounds__(Cfg::kThreads, 2) void gemm_f32_kernel(GemmF32Args a) {   // 2: keeps the chains out of the
+  // accumulation registers, where the compiler moves them about in the loop (4 % of a 64 x 64 tile's time)
   constexpr bool GATHER = KIND != kF32Dense;
   constexpr int BK = Cfg::kBK, D = Cfg::kD, FM = Cfg::FM, FN = Cfg::FN, BN = Cfg::kBN;
   constexpr int KG = Cfg::kKG;
@@ -191,18 +199,22 @@ __global__ __launch_bounds__(Cfg::kThreads) void gemm_f32_kernel(GemmF32Args a) 
     }
   };
 
-  f32x4_t acc[FM][FN];
+  constexpr int NC = Cfg::kChains;
+  f32x4_t chain[NC][FM][FN];
 #pragma unroll
-  for (int i = 0; i < FM; ++i)
+  for (int c = 0; c < NC; ++c)
 #pragma unroll
-    for (int j = 0; j < FN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j) chain[c][i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  f32x4_t (&acc)[FM][FN] = chain[0];
   const int a_off = (wm * Cfg::WM + l16) * Cfg::kPitchA + 4 * g;
   const int b_off = 4 * g * Cfg::kPitchB + wn * Cfg::WN + l16;
   // One k-step: stage i (LDS buffer `buf`) is multiplied, the loads of stage i + D go out into the slot that stage i
   // left, and stage i + 1 moves from its slot into the other buffer.  A step is BK / 4 groups of FM x FN matrix
   // instructions, and the other work is dealt out over the groups: issuing it takes the wavefront no longer than the
   // matrix pipe is busy with a group anyway.  The fragments of group n + 1 are read before group n is multiplied.
-  auto step = [&](int buf, int slot, int k_fetch, int next_slot) {
+  auto step = [&](f32x4_t (&sum)[FM][FN], int buf, int slot, int k_fetch, int next_slot) {
     constexpr int G = BK / 4;
     const lds_f32_t* As = lds + buf * Cfg::kStage + a_off;
     const lds_f32_t* Bs = lds + buf * Cfg::kStage + Cfg::kStageA + b_off;
@@ -236,13 +248,14 @@ __global__ __launch_bounds__(Cfg::kThreads) void gemm_f32_kernel(GemmF32Args a) 
       for (int i = 0; i < FM; ++i)
 #pragma unroll
         for (int j = 0; j < FN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(bf[n & 1][j], af[(n / 4) & 1][i][n % 4], acc[i][j], 0, 0, 0);
+          sum[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(bf[n & 1][j], af[(n / 4) & 1][i][n % 4], sum[i][j], 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
 
   // k-steps past the end load zeros and add nothing
-  const int nst = ((a.K + BK * KG - 1) / (BK * KG) + D - 1) / D * D;
+  constexpr int U = Cfg::kUnroll;
+  const int nst = ((a.K + BK * KG - 1) / (BK * KG) + U - 1) / U * U;
 #pragma unroll
   for (int u = 0; u < D; ++u) {
     const int k0 = (u * KG + q) * BK;
@@ -255,14 +268,24 @@ __global__ __launch_bounds__(Cfg::kThreads) void gemm_f32_kernel(GemmF32Args a) 
   commit_a(0, 0, 0, Cfg::kAPer);
   commit_b(0, 0, 0, kBPieces);
   __syncthreads();
-  for (int i = 0; i < nst; i += D) {
+  for (int i = 0; i < nst; i += U) {
 #pragma unroll
-    for (int u = 0; u < D; ++u) {
-      step(u & 1, u, ((i + u + D) * KG + q) * BK, (u + 1) % D);
+    for (int u = 0; u < U; ++u) {
+      step(chain[u % NC], u & 1, u % D, ((i + u + D) * KG + q) * BK, (u + 1) % D);
       __syncthreads();                                       // stage i + u + 1 is published, the buffer of stage i + u free
     }
   }
-  if constexpr (KG > 1) {                                    // the stages are free: partial sums of groups 1 .. KG - 1 go there
+  auto add_to = [&](f32x4_t (&sum)[FM][FN], const f32x4_t (&other)[FM][FN]) {
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sum[i][j][e] += other[i][j][e];
+  };
+  if constexpr (NC == 4) { add_to(chain[0], chain[2]); add_to(chain[1], chain[3]); }
+  if constexpr (NC >= 2) add_to(chain[0], chain[1]);
+  if constexpr (KG > 1) {                                    // the stages are free: sums of groups 1 .. KG - 1 go there
     lds_f32_t* const part = (lds_f32_t*)smem + (wave * FM * FN * kWave + lane) * 4;
     constexpr int kGroup = 4 * FM * FN * kWave * 4;          // floats per group
     if (q > 0) {
@@ -273,13 +296,16 @@ __global__ __launch_bounds__(Cfg::kThreads) void gemm_f32_kernel(GemmF32Args a) 
     __syncthreads();
     if (q > 0) return;
 #pragma unroll
-    for (int p = 0; p < KG - 1; ++p)
+    for (int i = 0; i < FM * FN; ++i) {
+      f32x4v_t v[KG];
 #pragma unroll
-      for (int i = 0; i < FM * FN; ++i) {
-        const f32x4v_t v = *(const lds_f32x4_t*)(part + p * kGroup + i * kWave * 4);
+      for (int p = 1; p < KG; ++p) v[p] = *(const lds_f32x4_t*)(part + (p - 1) * kGroup + i * kWave * 4);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc[i / FN][i % FN][e] += v[e];
+      for (int e = 0; e < 4; ++e) {
+        if constexpr (KG == 4) acc[i / FN][i % FN][e] = (acc[i / FN][i % FN][e] + v[2][e]) + (v[1][e] + v[3][e]);
+        else acc[i / FN][i % FN][e] += v[1][e];
       }
+    }
   }
 
   // ---- epilogue: lane = row l16 of a 16-row block, columns 4 g .. 4 g + 3 of a 16-column block

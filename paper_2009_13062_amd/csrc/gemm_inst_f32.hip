@@ -7,13 +7,17 @@ namespace nf {
 
 // 128-row tiles were tried as well and are never ahead (12 models, 512 x 3072 x 768: 377 us at 128 x 128, 308 at
 // 128 x 64, 252 at 64 x 64): a compute unit with several tiles hides one workgroup's waits behind another's.
-using F64x64 = F32Cfg<64, 64, 2, 2, 32, 2>;
-using F64x64s = F32Cfg<64, 64, 2, 2, 32, 2, 2>;
-using F64x48s = F32Cfg<64, 48, 4, 1, 32, 2, 2>;
-using F32x64s = F32Cfg<32, 64, 2, 2, 32, 2, 2>;
-using F32x64q = F32Cfg<32, 64, 2, 2, 32, 2, 4>;
-using F16x64s = F32Cfg<16, 64, 1, 4, 32, 2, 2>;
-using F16x64q = F32Cfg<16, 64, 1, 4, 32, 2, 4>;
+// CH chains (gemm_f32.h): 4 where dealing k out to four groups of wavefronts pays, else 2.  One model (us), 16-row tiles on
+// two / four groups: 17 x 3072 x 768 23.6 / 22.0, 512 -> 512 at 7 x 7 62.2 / 52.0, 2048 -> 512 30.7 / 26.3, but 17 x 768 x 768
+// 8.8 / 8.9 and 128 -> 128 at 28 x 28 (k = 1152) 20.1 / 19.8; four chains on one group cost it up to a tenth of its rate.
+constexpr int kLongK = 1536;
+template <int CH> using F64x64 = F32Cfg<64, 64, 2, 2, 32, 2, CH>;
+template <int CH> using F64x64s = F32Cfg<64, 64, 2, 2, 32, 2, CH, 2>;
+template <int CH> using F64x48s = F32Cfg<64, 48, 4, 1, 32, 2, CH, 2>;
+template <int CH> using F32x64s = F32Cfg<32, 64, 2, 2, 32, 2, CH, 2>;
+template <int CH> using F16x64s = F32Cfg<16, 64, 1, 4, 32, 2, CH, 2>;
+using F32x64q = F32Cfg<32, 64, 2, 2, 32, 2, 4, 4>;
+using F16x64q = F32Cfg<16, 64, 1, 4, 32, 2, 4, 4>;
 
 enum { kF64x64, kF64x64s, kF64x48s, kF32x64s, kF32x64q, kF16x64s, kF16x64q, kNumF32Tiles };
 constexpr int kBMs[kNumF32Tiles] = {64, 64, 64, 32, 32, 16, 16};
@@ -51,32 +55,40 @@ static nf_status launch_cfg(GemmF32Args& a, long long problems, hipStream_t s) {
   return a.K % 4 == 0 ? launch_kernel<Cfg, KIND, true>(a, total, s) : launch_kernel<Cfg, KIND, false>(a, total, s);
 }
 
+template <int CH>
+static nf_status launch_tile(int tile, GemmF32Args& a, long long problems, bool gather, hipStream_t s) {
+#define NF_F32(C) return gather ? launch_cfg<C, kF32Gather>(a, problems, s) : launch_cfg<C, kF32Dense>(a, problems, s)
+  switch (tile) {
+    case kF64x64: NF_F32(F64x64<CH>);
+    case kF64x64s: NF_F32(F64x64s<CH>);
+    case kF64x48s: return launch_cfg<F64x48s<CH>, kF32Dense>(a, problems, s);
+    case kF32x64s: NF_F32(F32x64s<CH>);
+    case kF16x64s: NF_F32(F16x64s<CH>);
+  }
+  if constexpr (CH == 4) {
+    if (tile == kF32x64q) NF_F32(F32x64q);
+    if (tile == kF16x64q) NF_F32(F16x64q);
+  }
+#undef NF_F32
+  return NF_EUNSUPPORTED;
+}
+
 nf_status launch_gemm_f32(GemmF32Args& a, int nz1, bool gather, hipStream_t s) {
   const long long problems = (long long)a.nz0 * nz1;
   // a wide kernel over few channels (the image networks' stem)
-  if (gather && a.khw > 31) return launch_cfg<F64x64, kF32GatherWide>(a, problems, s);
+  if (gather && a.khw > 31) return launch_cfg<F64x64<2>, kF32GatherWide>(a, problems, s);
   auto tiles = [&](int t) { return problems * ((a.rows + kBMs[t] - 1) / kBMs[t]) * ((a.cols + kBNs[t] - 1) / kBNs[t]); };
+  const bool chains4 = a.K >= kLongK;
   int best = -1;
   long long best_cost = 0;
   for (int t = 0; t < kNumF32Tiles; ++t) {
     if (gather && t == kF64x48s) continue;
-    if ((t == kF32x64q || t == kF16x64q) && a.K < 512) continue;      // too few k-steps to deal out four ways
+    if ((t == kF32x64q || t == kF16x64q) && !chains4) continue;
     const long long rounds = (tiles(t) + 255) / 256;
     const long long cost = rounds * kBMs[t] * kBNs[t] * kUnitCost[gather][rounds > 1][t];
     if (best < 0 || cost < best_cost) { best = t; best_cost = cost; }
   }
-#define NF_F32(C) return gather ? launch_cfg<C, kF32Gather>(a, problems, s) : launch_cfg<C, kF32Dense>(a, problems, s)
-  switch (best) {
-    case kF64x64: NF_F32(F64x64);
-    case kF64x64s: NF_F32(F64x64s);
-    case kF64x48s: return launch_cfg<F64x48s, kF32Dense>(a, problems, s);
-    case kF32x64s: NF_F32(F32x64s);
-    case kF32x64q: NF_F32(F32x64q);
-    case kF16x64s: NF_F32(F16x64s);
-    case kF16x64q: NF_F32(F16x64q);
-  }
-#undef NF_F32
-  return NF_EUNSUPPORTED;
+  return chains4 ? launch_tile<4>(best, a, problems, gather, s) : launch_tile<2>(best, a, problems, gather, s);
 }
 
 }  // namespace nf

@@ -1,6 +1,6 @@
 """float32 storage on the matrix pipe: sizes at the edges of every tile (64, 48, 32 and 16 wide or high), k remainders
 of the 32-element steps and of the split of k over two or four groups, both B paths, kernels of one and of two tap
-words.  The bound is derived, not fitted: a sum of K products in any order is off by at most
+words; and the same bits for a model whatever tile the number of models or images leads to.  The bound is derived, not fitted: a sum of K products in any order is off by at most
 (K + 4) 2^-24 sum |x||w| before the epilogue, whose operations add at most four more roundings of the result's
 operands."""
 import numpy as np
@@ -39,12 +39,15 @@ def check(got, ref, absref, K):
 @pytest.mark.parametrize("M,N,K,Nout", [
     (1, 1, 1, 1), (1, 1, 36, 4),                 # one element; 16 x 64 tile
     (2, 16, 31, 64), (2, 17, 33, 65),            # tile edges, k = 32 -+ 1
-    (2, 1, 516, 4), (2, 15, 1025, 63),           # 16 x 64 tile, k in four groups, dense and gathered
+    (2, 1, 516, 4), (2, 15, 1025, 63),           # 16 x 64 tile, dense and gathered
+    (2, 1, 1540, 4), (2, 15, 1541, 63),          # the same with k in four groups
     (16, 277, 17, 4), (24, 222, 17, 3),          # 32 x 64 tile
-    (24, 169, 520, 4), (32, 142, 520, 1),        # 32 x 64 tile, k in four groups
+    (24, 169, 520, 4), (32, 142, 520, 1),        # 32 x 64 tile
+    (24, 169, 1544, 4), (32, 142, 1543, 1),      # the same with k in four groups
     (32, 294, 17, 4),                            # 64 x 48 tile, one column block of four
     (16, 146, 17, 260), (32, 270, 17, 1),        # 64 x 64 tile, k in two groups
     (32, 65, 65, 860), (32, 33, 129, 788 + 1),   # 64 x 64 tile, several per compute unit
+    (24, 130, 1545, 516), (24, 130, 1569, 513),  # the same with four chains
 ], ids=lambda v: str(v))
 def test_linear(nf, M, N, K, Nout):
     X, W, b, R = rnd(M, N, K), rnd(M, K, Nout), rnd(M, Nout), rnd(M, N, Nout)
@@ -107,3 +110,30 @@ def test_attention(nf, oracle, M, B, S, heads, d, use_mask):
         dirty[1:] = np.nan
         alone = nf.attention_packed(dev(dirty), B, S, heads, mask=None if mask is None else dev(mask)).cpu().numpy()
         assert np.array_equal(alone[0], got[0])
+
+
+@pytest.mark.parametrize("N,K,Nout", [(8, 64, 64), (128, 768, 768), (17, 520, 3), (93, 768, 2304), (128, 1536, 768),
+                                      (128, 3072, 768), (256, 1568, 257)], ids=lambda v: str(v))
+def test_linear_merged_equals_single(nf, N, K, Nout):
+    """One order of the sum for every tile: k below and from 1536 up, dense and gathered columns."""
+    X, W = torch.randn(32, N, K, device="cuda"), torch.randn(32, K, Nout, device="cuda")
+    one = nf.linear(X[31:], W[31:])
+    for M in (2, 5, 8, 12, 32):
+        assert torch.equal(nf.linear(X[32 - M:], W[32 - M:])[M - 1], one[0]), M
+
+
+@pytest.mark.parametrize("Cin,Cout,g,H,KH,stride,pad", [
+    (64, 64, 1, 56, 3, 1, 1), (64, 256, 1, 56, 1, 1, 0), (512, 512, 1, 7, 3, 1, 1), (2048, 512, 1, 7, 1, 1, 0),
+    (512, 512, 1, 13, 3, 2, 1), (3, 64, 1, 64, 7, 2, 3), (256, 256, 32, 28, 3, 1, 1), (32, 32, 32, 28, 3, 1, 1),
+    (128, 128, 32, 21, 3, 1, 1)], ids=lambda v: str(v))
+def test_conv2d_merged_equals_single(nf, Cin, Cout, g, H, KH, stride, pad):
+    """The same for models and for images of one model, wide and narrow groups."""
+    kw = dict(g=g, stride=stride, pad=pad)
+    x, w = torch.randn(1, 24 * Cin, H, H, device="cuda"), torch.randn(24 * Cout, Cin // g, KH, KH, device="cuda")
+    one = nf.conv2d(x[:, 23 * Cin:].contiguous(), w[23 * Cout:], 1, **kw)[0]
+    for M in (2, 5, 8, 24):
+        got = nf.conv2d(x[:, (24 - M) * Cin:].contiguous(), w[(24 - M) * Cout:], M, **kw)
+        assert torch.equal(got[0, (M - 1) * Cout:], one), M
+    xb = torch.cat([torch.randn(7, Cin, H, H, device="cuda"), x[:, 23 * Cin:]])
+    for B in (2, 4, 8):
+        assert torch.equal(nf.conv2d(xb[8 - B:], w[23 * Cout:], 1, **kw)[B - 1], one), B
