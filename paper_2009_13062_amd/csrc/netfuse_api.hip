@@ -713,7 +713,16 @@ nf_status netfuse_conv2d(const void* x, const void* w, const float* bias, const 
     return launch_gemm_any(bkind, al, tile, L, s);
   }
 
-  if (dt == NF_F32 && KH * KW < 64 && f32_fits((long long)cog * Kdim, prod({cig, H, W}), Kdim)) {
+  // float32: the matrix-pipe kernel, except for narrow groups.  Its lowest tile is 16 rows x 64 positions with k padded to
+  // 64 or 128, so a group of a few products per position costs it as much as one of 16 x 64; the direct kernel (one
+  // thread per output) pays for what there is, but walks k alone: 0.15 to 0.3 us per k where the chip is not full.
+  // Hence a limit on the products per position, by the taps that the other kernel has to look up per tile, and one on k
+  // where a model has few groups.  Direct / matrix (us): depthwise 3x3 of 1024 channels at 14 x 14 5 / 50, 16 -> 1
+  // channels per group 29 / 64, 4 -> 8 38 / 47, 8 -> 8 81 / 47; 7x7 depthwise 10 / 63, 2 -> 8 79 / 83; pointwise 8 -> 8
+  // 23 / 25, 16 -> 8 38 / 25; one model with one group at 56 x 56: 8 -> 1 13 / 7, 16 -> 1 24 / 8.
+  const bool f32_dense = KH == 1 && KW == 1 && stride == 1 && pad == 0 && HoWo % 4 == 0;
+  const bool f32_narrow = (long long)cog * Kdim <= (f32_dense ? 64 : 220 + 10 * KH * KW) && (g >= 64 || Kdim <= (f32_dense ? 16 : 72));
+  if (dt == NF_F32 && KH * KW < 64 && !f32_narrow && f32_fits((long long)cog * Kdim, prod({cig, H, W}), Kdim)) {
     GemmF32Args a;
     memset(&a, 0, sizeof(a));
     a.A = (const float*)w; a.B = (const float*)x; a.R = (const float*)residual; a.C = (float*)y;
@@ -726,10 +735,10 @@ nf_status netfuse_conv2d(const void* x, const void* w, const float* bias, const 
     a.ep.row_bias = bias; a.ep.row_scale = scale; a.ep.row_shift = shift; a.ep.row_vec_stride0 = cog;
     a.ep.act = act;
     a.ep.vec_store = HoWo % 4 == 0 && aligned(y, 16) && aligned(residual, 16) ? 2 : 0;
-    const bool dense = KH == 1 && KW == 1 && stride == 1 && pad == 0 && HoWo % 4 == 0;
     a.H = H; a.W = W; a.KW = KW; a.khw = KH * KW; a.Wo = (int)Wo; a.stride = stride; a.pad = pad; a.dil = dilation;
     f32_divisors(a);
-    return launch_gemm_f32(a, B, !dense, s);
+    const nf_status st = launch_gemm_f32(a, B, !f32_dense, s);
+    if (st != NF_EUNSUPPORTED) return st;               // more tiles than a grid holds: the direct kernel strides over any number
   }
 
   ConvGeom geo;

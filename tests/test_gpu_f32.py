@@ -137,3 +137,46 @@ def test_conv2d_merged_equals_single(nf, Cin, Cout, g, H, KH, stride, pad):
     xb = torch.cat([torch.randn(7, Cin, H, H, device="cuda"), x[:, 23 * Cin:]])
     for B in (2, 4, 8):
         assert torch.equal(nf.conv2d(xb[8 - B:], w[23 * Cout:], 1, **kw)[B - 1], one), B
+
+
+@pytest.mark.parametrize("M,B,Cin,Cout,g,H,W,KH,KW,stride,pad,dil", [
+    (2, 1, 64, 64, 64, 9, 7, 3, 3, 1, 1, 1), (3, 2, 40, 40, 40, 12, 12, 5, 5, 2, 2, 1),       # depthwise
+    (2, 1, 64, 64, 64, 8, 8, 7, 7, 1, 3, 1), (1, 2, 70, 140, 70, 1, 1, 1, 1, 1, 0, 1),
+    (2, 1, 128, 128, 32, 11, 13, 3, 3, 1, 1, 2), (2, 2, 64, 256, 16, 10, 8, 3, 3, 1, 1, 1),   # 4 -> 4; 4 -> 16 channels
+    (1, 1, 512, 64, 64, 6, 5, 3, 3, 1, 1, 1), (1, 1, 1088, 64, 64, 6, 5, 3, 3, 1, 1, 1),      # 8 -> 1, 17 -> 1, 64 groups
+    (2, 1, 64, 8, 8, 6, 4, 3, 3, 1, 1, 1), (2, 1, 72, 8, 8, 6, 4, 3, 3, 1, 1, 1),             # k = 72, 81 with 8 groups
+    (2, 1, 64, 32, 8, 8, 4, 1, 1, 1, 0, 1), (2, 1, 64, 72, 8, 8, 4, 1, 1, 1, 0, 1),           # pointwise 8 -> 4, 8 -> 9
+], ids=lambda v: str(v))
+def test_conv2d_narrow_groups(nf, M, B, Cin, Cout, g, H, W, KH, KW, stride, pad, dil):
+    """Either side of the line between the direct and the matrix-pipe kernel."""
+    x, w = rnd(B, M * Cin, H, W), rnd(M * Cout, Cin // g, KH, KW)
+    scale, shift = rnd(M * Cout), rnd(M * Cout)
+    conv = lambda a, b: torch.nn.functional.conv2d(torch.from_numpy(a).double(), torch.from_numpy(b).double(), stride=stride,
+                                                   padding=pad, dilation=dil, groups=M * g).numpy()
+    s, t = scale[None, :, None, None].astype(np.float64), shift[None, :, None, None].astype(np.float64)
+    got = nf.conv2d(dev(x), dev(w), M, g=g, scale=dev(scale), shift=dev(shift), stride=stride, pad=pad, dil=dil)
+    check(got, conv(x, w) * s + t, conv(np.abs(x), np.abs(w)) * np.abs(s) + np.abs(t), Cin // g * KH * KW)
+
+
+def test_depthwise_is_bound_by_memory(nf):
+    """Nine products per output: a depthwise 3x3 takes a few times as long as moving its planes (3 times), not as long as
+    the 16 x 128 products per output that its smallest matrix tile would spend (57 times)."""
+    M, C, H = 8, 256, 28
+    x, w = torch.randn(1, M * C, H, H, device="cuda"), torch.randn(M * C, 1, 3, 3, device="cuda")
+    y = torch.empty_like(x)
+
+    def us(f):
+        f()
+        best = 1e9
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(20):
+                f()
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b) * 50)
+        return best
+    copy = us(lambda: nf.merge_transpose(x.view(M, C, H * H), M, True, out=y.view(C, M * H * H)))
+    conv = us(lambda: nf.conv2d(x, w, M, g=C, pad=1, out=y))
+    assert conv < 15 * max(copy, 5.0), (conv, copy)
