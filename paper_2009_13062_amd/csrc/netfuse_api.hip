@@ -887,7 +887,10 @@ nf_status netfuse_attention(const void* Q, const void* K, const void* V, const f
     return launched();
   }
   const long long head_elems = (long long)(S - 1) * stride_row + d;         // one head's rows, first to last element
-  if (dt == NF_F32 && d % 4 == 0 && d <= 128 && head_elems < (1LL << 29)) {
+  // Up to 8 tokens a 64-query workgroup is nearly empty and the wavefront-per-query kernel below is ahead.  float32, 32 models x 8
+  // sequences x 12 heads of 64 (us, that kernel / this one): 1 token 4.8 / 38.8, 4 11.6 / 39.5, 8 27.6 / 39.1, 10 38.8 / 39.1, 16
+  // 72 / 40; one model, 1 sequence: 3.8 / 6.4, 4.9 / 6.5 at 8, 6.4 / 6.6 at 20.
+  if (dt == NF_F32 && S > 8 && d % 4 == 0 && d <= 128 && head_elems < (1LL << 29)) {
     const int qblocks = (S + kAttnF32Queries - 1) / kAttnF32Queries;
     const long long total = prod({M, B, heads, qblocks});
     if (total > kMaxGrid) return NF_EUNSUPPORTED;

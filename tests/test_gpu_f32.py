@@ -36,6 +36,21 @@ def check(got, ref, absref, K):
         bad.sum(), bad.size, (np.abs(got - ref) / bound).max())
 
 
+def us(f):
+    """Shortest of five averages over 20 calls."""
+    f()
+    best = 1e9
+    for _ in range(5):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(20):
+            f()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) * 50)
+    return best
+
+
 @pytest.mark.parametrize("M,N,K,Nout", [
     (1, 1, 1, 1), (1, 1, 36, 4),                 # one element; 16 x 64 tile
     (2, 16, 31, 64), (2, 17, 33, 65),            # tile edges, k = 32 -+ 1
@@ -90,6 +105,7 @@ def test_conv2d(nf, oracle, M, B, Cin, Cout, g, H, W, KH, KW, stride, pad, dil):
 
 @pytest.mark.parametrize("M,B,S,heads,d,use_mask", [
     (1, 1, 1, 1, 4, False),                      # one query, one key, a quarter of a feature block
+    (3, 1, 7, 2, 20, True), (2, 2, 8, 2, 64, True), (2, 2, 9, 2, 64, True), (1, 2, 9, 1, 4, False),   # 8 tokens and past them
     (2, 1, 63, 2, 16, True), (1, 2, 64, 1, 32, False), (2, 1, 65, 1, 28, True),      # edges of the 64-key stage, d <= 32
     (2, 1, 128, 3, 64, False), (1, 3, 129, 2, 64, True), (2, 1, 17, 1, 60, True),    # d <= 64
     (1, 1, 96, 2, 128, True), (2, 1, 33, 1, 68, False), (1, 1, 100, 1, 80, True),    # d <= 128: 32-key stages
@@ -164,19 +180,17 @@ def test_depthwise_is_bound_by_memory(nf):
     M, C, H = 8, 256, 28
     x, w = torch.randn(1, M * C, H, H, device="cuda"), torch.randn(M * C, 1, 3, 3, device="cuda")
     y = torch.empty_like(x)
-
-    def us(f):
-        f()
-        best = 1e9
-        for _ in range(5):
-            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-            a.record()
-            for _ in range(20):
-                f()
-            b.record()
-            b.synchronize()
-            best = min(best, a.elapsed_time(b) * 50)
-        return best
     copy = us(lambda: nf.merge_transpose(x.view(M, C, H * H), M, True, out=y.view(C, M * H * H)))
     conv = us(lambda: nf.conv2d(x, w, M, g=C, pad=1, out=y))
     assert conv < 15 * max(copy, 5.0), (conv, copy)
+
+
+def test_attention_of_single_tokens_is_bound_by_memory(nf):
+    """One token per sequence: about twice as long as moving the operands, not as long as the 64-query tiles of longer
+    sequences (15 times)."""
+    M, B, heads = 32, 8, 16
+    qkv = torch.randn(M, B, 3 * heads * 64, device="cuda")
+    out, dst = torch.empty(M, B, heads * 64, device="cuda"), torch.empty(B, M * 3 * heads * 64, device="cuda")
+    copy = us(lambda: nf.merge_transpose(qkv, M, True, out=dst))
+    att = us(lambda: nf.attention_packed(qkv, B, 1, heads, out=out))
+    assert att < 4 * max(copy, 5.0), (att, copy)
