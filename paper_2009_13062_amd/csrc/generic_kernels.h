@@ -7,7 +7,7 @@
 namespace nf {
 
 // Ragged merged matmul: per-model output widths (the per-task classification heads, Section 5.1).
-// One workgroup = (model, R rows, 64 columns), 16 wavefronts that share k.  A model's weights are one dense run
+// One workgroup = (model, R rows, 64 columns), NW wavefronts that share k: 16, or 4 for short k.  A model's weights are one dense run
 // [K][nout], so a wavefront reads KQ = 64 / CW consecutive k rows at a time (CW = the columns of the tile rounded up
 // to a power of two): lane = (k of the KQ, column), and narrow heads keep all lanes busy on contiguous memory.
 // Partial sums meet first across the KQ lanes of a column, then in LDS, in a fixed order.
@@ -15,17 +15,16 @@ namespace nf {
 // and the unrolled, unconditional loads: 12 models x 3 rows x 768 -> 2 ... 20 classes took 88 us on four wavefronts
 // with one k row in flight each, and takes 8.2 us.
 constexpr int kRaggedMaxModels = 256;
-constexpr int kRaggedWaves = 16;
 struct RaggedTable {
   int tile_start[kRaggedMaxModels + 1];   // first workgroup of model m (prefix sum of rows tiles x column tiles)
   int col_start[kRaggedMaxModels + 1];    // first output column of model m in the concatenation (prefix sum of nout)
 };
 
-template <typename T, int R>
-__global__ __launch_bounds__(kRaggedWaves * kWave) void linear_ragged_kernel(const T* __restrict__ X, const T* __restrict__ W,
+template <typename T, int R, int NW>
+__global__ __launch_bounds__(NW * kWave) void linear_ragged_kernel(const T* __restrict__ X, const T* __restrict__ W,
                                                                             const float* __restrict__ bias, T* __restrict__ Y,
                                                                             int M, int N, int K, int act, RaggedTable tab) {
-  __shared__ float part[kRaggedWaves][R][kWave];
+  __shared__ float part[NW][R][kWave];
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   // the model: how many of the first tiles lie at or before this workgroup
   int m = -1;
@@ -46,7 +45,7 @@ __global__ __launch_bounds__(kRaggedWaves * kWave) void linear_ragged_kernel(con
   for (int r = 0; r < R; ++r) Xm[r] = X + ((size_t)m * N + row0 + min(r, rows - 1)) * K;
   float acc[R] = {};
   constexpr int U = R >= 8 ? 4 : 8;
-  const int step = kRaggedWaves * kq_n;
+  const int step = NW * kq_n;
   for (int k0 = wave * kq_n + kq; k0 - kq < K; k0 += U * step) {
     float w[U], x[U][R];
 #pragma unroll
@@ -69,12 +68,12 @@ __global__ __launch_bounds__(kRaggedWaves * kWave) void linear_ragged_kernel(con
     part[wave][r][lane] = acc[r];
   }
   __syncthreads();
-  for (int o = threadIdx.x; o < R * cw; o += kRaggedWaves * kWave) {
+  for (int o = threadIdx.x; o < R * cw; o += NW * kWave) {
     const int r = o >> cw_log, cc = o & (cw - 1);
     if (r >= rows || cc >= cols) continue;
     float v = 0.f;
 #pragma unroll
-    for (int q = 0; q < kRaggedWaves; ++q) v += part[q][r][cc];
+    for (int q = 0; q < NW; ++q) v += part[q][r][cc];
     if (bias) v += bias[tab.col_start[m] + col0 + cc];
     v = apply_act(v, act);
     store_f32(Y + (size_t)tab.col_start[m] * N + (size_t)(row0 + r) * nout + col0 + cc, v);

@@ -538,12 +538,18 @@ nf_status netfuse_linear_ragged(const void* X, const void* W, const float* bias,
   }
   for (int m = M + 1; m <= kRaggedMaxModels; ++m) { tab.tile_start[m] = tab.tile_start[M]; tab.col_start[m] = tab.col_start[M]; }
   hipStream_t s = (hipStream_t)stream;
-#define NF_RAGGED(T, R_)                                                                                             \
-  nf_launch((linear_ragged_kernel<T, R_>), dim3((unsigned)tiles), dim3(kRaggedWaves * kWave), 0, s, (const T*)X,       \
-            (const T*)W, bias, (T*)Y, M, N, K, (int)act, tab)
+  // 16 wavefronts share k where a model's rows leave compute units idle, 4 where there are plenty of workgroups or too little
+  // k to share.  bf16, 4 models x 4096 rows (us, 4 / 16 wavefronts): 8 -> 1000 72 / 250, 128 -> 256 80 / 130, 768 -> 2 14 / 46; 8
+  // models x 64 rows: 64 -> 64 and 256 -> 64 a quarter and two thirds slower with 4.
+  const bool wide = K > 32 && N < 1024;
+#define NF_RAGGED(T, R_, NW)                                                                                         \
+  nf_launch((linear_ragged_kernel<T, R_, NW>), dim3((unsigned)tiles), dim3(NW * kWave), 0, s, (const T*)X, (const T*)W, \
+            bias, (T*)Y, M, N, K, (int)act, tab)
+#define NF_RAGGED_W(T, R_) if (wide) NF_RAGGED(T, R_, 16); else NF_RAGGED(T, R_, 4)
 #define NF_RAGGED_R(T) \
-  if (R == 1) NF_RAGGED(T, 1); else if (R == 2) NF_RAGGED(T, 2); else if (R == 4) NF_RAGGED(T, 4); else NF_RAGGED(T, 8)
-  if (dt == NF_F32) { NF_RAGGED_R(float); } else { NF_RAGGED_R(bf16_t); }
+  if (R == 1) { NF_RAGGED_W(T, 1); } else if (R == 2) { NF_RAGGED_W(T, 2); } else if (R == 4) { NF_RAGGED_W(T, 4); } else { NF_RAGGED_W(T, 8); }
+  if (dt == NF_F32) { NF_RAGGED_R(float) } else { NF_RAGGED_R(bf16_t) }
+#undef NF_RAGGED_W
 #undef NF_RAGGED_R
 #undef NF_RAGGED
   return launched();
