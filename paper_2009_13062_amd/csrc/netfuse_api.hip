@@ -351,7 +351,9 @@ nf_status netfuse_linear(const void* X, const void* W, const float* bias, const 
     }
     return launch_gemm_any(bkind, al, pick_tile(N, Nout, M), L, s);
   }
-  if (f32_fits(prod({N, K}), prod({K, Nout}), K)) {
+  // A few k over thousands of rows is mostly the matrix kernel's fixed cost per tile (8 models of 8192 rows, FMA / matrix kernel, us:
+  // 2 -> 1 5.7 / 12.6, 16 -> 64 12.7 / 13.4, 32 -> 257 51 / 65); at 128 rows the matrix kernel is ahead (16 -> 16 7.8 / 4.3).
+  if (!(K <= 32 && N >= 2048) && f32_fits(prod({N, K}), prod({K, Nout}), K)) {
     GemmF32Args a;
     memset(&a, 0, sizeof(a));
     a.A = (const float*)X; a.B = (const float*)W; a.R = (const float*)residual; a.C = (float*)Y;
@@ -365,7 +367,8 @@ nf_status netfuse_linear(const void* X, const void* W, const float* bias, const 
     const bool gather = Nout % 4 != 0;                      // then a weight row is a one-row image of Nout positions
     a.H = 1; a.W = Nout; a.KW = 1; a.khw = 1; a.Wo = Nout; a.stride = 1; a.dil = 1;
     f32_divisors(a);
-    return launch_gemm_f32(a, 1, gather, s);
+    const nf_status st = launch_gemm_f32(a, 1, gather, s);
+    if (st != NF_EUNSUPPORTED) return st;
   }
   const int tiles_m = (N + 63) / 64, tiles_n = (Nout + 63) / 64;
   const long long total = prod({tiles_m, tiles_n, M});

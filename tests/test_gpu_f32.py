@@ -63,6 +63,7 @@ def us(f):
     (16, 146, 17, 260), (32, 270, 17, 1),        # 64 x 64 tile, k in two groups
     (32, 65, 65, 860), (32, 33, 129, 788 + 1),   # 64 x 64 tile, several per compute unit
     (24, 130, 1545, 516), (24, 130, 1569, 513),  # the same with four chains
+    (2, 2047, 32, 3), (2, 2048, 32, 3), (1, 2049, 31, 65), (2, 2050, 33, 7),         # few k, around 2048 rows
 ], ids=lambda v: str(v))
 def test_linear(nf, M, N, K, Nout):
     X, W, b, R = rnd(M, N, K), rnd(M, K, Nout), rnd(M, Nout), rnd(M, N, Nout)
@@ -194,3 +195,12 @@ def test_attention_of_single_tokens_is_bound_by_memory(nf):
     copy = us(lambda: nf.merge_transpose(qkv, M, True, out=dst))
     att = us(lambda: nf.attention_packed(qkv, B, 1, heads, out=out))
     assert att < 4 * max(copy, 5.0), (att, copy)
+
+
+def test_few_k_over_many_rows_is_bound_by_memory(nf):
+    """8192 rows of 2 k and one output: about as long as a launch takes, not as the fixed cost of its matrix tiles."""
+    M, N, K = 8, 8192, 2
+    X, W, Y = torch.randn(M, N, K, device="cuda"), torch.randn(M, K, 1, device="cuda"), torch.empty(M, N, 1, device="cuda")
+    few = us(lambda: nf.linear(X, W, out=Y))
+    copy = us(lambda: nf.merge_transpose(X, M, True, out=torch.empty(N, M * K, device="cuda")))
+    assert few < 1.6 * max(copy, 6.0), (few, copy)
