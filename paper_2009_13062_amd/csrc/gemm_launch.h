@@ -72,7 +72,7 @@ enum RingPackedTileId { RP32x32 = 0, RP64x64, RP128x64, RP128x128, RP128x256, RP
 inline bool ring_fits(int cols, int K) { return cols % 8 == 0 && K % 64 == 0 && K >= 256; }     // shorter k: not measured
 nf_status launch_gemm_ring(int tile, bool packed, GemmLaunch& L, hipStream_t s);
 // The same for a pointwise convolution (A = weights, B = planes of cols % 8 == 0 positions, K % 64 == 0 channels).
-enum RingConvTileId { RC64x64 = 0, RC64x128, RC64x256, RC128x128, RC128x256 };
+enum RingConvTileId { RC64x64 = 0, RC64x128, RC64x256, RC128x128, RC128x256, kNumRingConvTiles };
 nf_status launch_conv_ring(int tile, GemmLaunch& L, hipStream_t s);
 
 // BKIND: 8 / 4 / 1 = dense B read with that vector width; 0 = implicit (im2col) B.

@@ -221,6 +221,22 @@ int pick_ring(const TileCost (&cost)[N_TILES], int N, int Nout, int K, long long
   return best;
 }
 
+// The same for pointwise convolutions, whose k is short and whose planes may fill little of a tile: a + l us of latency per
+// 64 of k, and per 256 tiles (padding included) b us per 64 of k and e us.  Fitted to every tile at planes of 2 x 4 to 72 x 72
+// positions, 64 to 2048 channels, 1 to 256 images: 298 problems, mean error 7 to 11 %.
+struct PointwiseCost { int bm, bn; float a, l, b, e; };
+float pointwise_us(const PointwiseCost& t, int cog, int HoWo, int K, long long problems) {
+  const long long tiles = problems * ((cog + t.bm - 1) / t.bm) * ((HoWo + t.bn - 1) / t.bn);
+  const float k = (float)K / 64.0f;
+  return t.a + t.l * k + (float)tiles / 256.0f * (t.b * k + t.e);
+}
+constexpr PointwiseCost kPointwiseCost[kNumRingConvTiles] = {{64, 64, 2.90f, 0.218f, 0.186f, 0.70f},
+                                                             {64, 128, 3.12f, 0.273f, 0.255f, 1.40f},
+                                                             {64, 256, 3.67f, 0.591f, 0.427f, 1.98f},
+                                                             {128, 128, 3.41f, 0.486f, 0.458f, 1.94f},
+                                                             {128, 256, 4.69f, 0.756f, 0.651f, 3.06f}};
+constexpr PointwiseCost kPointwiseRegCost[2] = {{64, 64, 3.50f, 0.227f, 0.141f, 0.94f}, {128, 128, 3.25f, 0.315f, 0.518f, 2.46f}};
+
 // The float32 matrix-pipe kernels address one problem's operands with 32-bit byte offsets.
 bool f32_fits(long long a_elems, long long b_elems, int K) {
   return a_elems < (1LL << 29) && b_elems < (1LL << 29) && K < (1 << 24);
@@ -630,12 +646,22 @@ nf_status netfuse_conv2d(const void* x, const void* w, const float* bias, const 
         // 128 -> 512 at 28 x 28 16.2 -> 13.7, 512 -> 128 11.3 -> 10.0; 2 models 512 -> 128 6.5 -> 5.8; 4 models of 4 images
         // 512 -> 2048 at 8 x 8 11.1 -> 9.5.
         auto tiles = [&](int bm, int bn) { return problems * ((cog + bm - 1) / bm) * ((HoWo + bn - 1) / bn); };
+        auto us = [&](const PointwiseCost& c) { return pointwise_us(c, cog, HoWo, Kdim, problems); };
         int t = RC64x64;
         if (cog >= 128 && tiles(128, 256) >= 400) t = RC128x256;
         else if (cog >= 128 && tiles(128, 128) >= 400) t = RC128x128;
         else if (cog < 128 && tiles(64, 256) >= 400) t = RC64x256;
         else if (HoWo > 64 && tiles(64, 128) >= 200) t = RC64x128;
-        const nf_status st = launch_conv_ring(t, L, s);
+        // Such a tile may be mostly padding: 512 -> 2048 at 8 x 8, 32 models of 8 images 154 us in 128 x 256 tiles, 83 in 64 x 64.
+        // Another one where the time model says so by 5 %; on planes of up to 64 positions, where the deep load pipeline of
+        // the register-staged 64 x 64 tile counts, that one too (32 models 2048 -> 512 at 4 x 4: 16.3 against 14.1).
+        float best = 0.95f * us(kPointwiseCost[t]);
+        int pick = t;
+        for (int i = 0; i < kNumRingConvTiles; ++i)
+          if (us(kPointwiseCost[i]) < best) { pick = i; best = us(kPointwiseCost[i]); }
+        if (HoWo <= 64 && us(kPointwiseRegCost[tile == T128x128w8]) < us(kPointwiseCost[pick]))
+          return launch_gemm_any(bkind, al, tile, L, s);
+        const nf_status st = launch_conv_ring(pick, L, s);
         if (st != NF_EUNSUPPORTED) return st;
       }
       return launch_gemm_any(bkind, al, tile, L, s);
