@@ -100,7 +100,9 @@ int forced_dma() {
   return v;
 }
 
-// Direct-to-LDS kernel for a dense, fully aligned problem made of whole tiles, or -1.  *cost_out receives the
+// Direct-to-LDS kernel for a dense, fully aligned problem made of whole tiles, or -1.  With k a multiple of 64 from 256 up
+// the ring tiles are compared with it and mostly taken (see netfuse_linear): there the 128 x 384 tile stays for full rounds of
+// 128-row problems, the 128 x 288 tile for full rounds of 2304 columns; the others run for shorter and odd k.  *cost_out receives the
 // cost of the choice in the model's unit (operand elements loaded by the busiest CU).
 int pick_dma(int rows, int cols, int K, long long problems, long long* cost_out = nullptr) {
   const int f = forced_dma();
@@ -146,7 +148,7 @@ int pick_dma_or_small(int N, int Nout, int K, long long M) {
 
 // Streaming kernel (gemm_stream.h) for a problem that pick_dma() routed to direct-to-LDS tile d, or -1.
 // Measured on MI355X, 32 models (us, register epilogue / LDS-staged epilogue of the same tile):
-//   GELU epilogues, 128 rows: 768 -> 3072  37.8 / 39.4;   512 rows, three 256x256 tiles per workgroup through
+//   GELU epilogues, 128 rows: 768 -> 3072  37.8 / 39.4 (the only one of these that the ring tiles leave to it);   512 rows, three 256x256 tiles per workgroup through
 //   one pipeline: 105.6 / 119.1.  The barrier-free epilogue pays where the epilogue is VALU heavy; plain
 //   bias / residual epilogues are as fast or faster through LDS (full-line stores), so they keep it --
 //   except that 512-row problems whose 256x256 tiling leaves a quarter of the last round of workgroups
@@ -195,7 +197,8 @@ int pick_tile(int rows, int cols, long long problems) {
 // Time model of the matmul kernels for choosing between them: 4 us of launch and ramp, plus per round of tiles over the
 // 256 compute units b us per 768 of k and e us of prologue and epilogue.  Fitted to every kernel measured alone at
 // hidden sizes 256, 768 and 1024 (the four matmuls of an encoder layer), 1 ... 32 models of 17 ... 1000 rows, weights
-// cold: 252 row-major problems, mean error of a prediction 4 to 7 %.
+// cold: 252 row-major problems, mean error of a prediction 4 to 7 %.  (The whole-tile 128 x 288 kernel from full rounds at
+// 768 and 1536 of k, 27 and 45 us: on 768 alone b came out too high and 1536 -> 2304 went to ring tiles that are a sixth slower.)
 struct TileCost { int bm, bn; float b, e; };
 float tile_us(const TileCost& t, int N, int Nout, int K, long long M) {
   const long long tiles = M * ((N + t.bm - 1) / t.bm) * ((Nout + t.bn - 1) / t.bn);
@@ -203,7 +206,7 @@ float tile_us(const TileCost& t, int N, int Nout, int K, long long M) {
 }
 constexpr TileCost kRegCost[kNumTiles] = {{64, 64, 3.77f, 0.48f}, {32, 128, 5.08f, 0.15f}, {128, 128, 6.69f, 3.04f}};
 constexpr TileCost kDmaCost[kNumDmaTiles] = {{256, 256, 20.1f, 10.7f}, {128, 128, 9.4f, 4.3f}, {128, 128, 8.8f, 0.f},
-                                             {128, 384, 13.8f, 18.1f}, {128, 288, 21.6f, 0.f}, {128, 96, 8.0f, 2.0f}};
+                                             {128, 384, 13.8f, 18.1f}, {128, 288, 17.0f, 5.0f}, {128, 96, 8.0f, 2.0f}};
 constexpr TileCost kRingCost[kNumRingTiles] = {{32, 32, 2.38f, 0.74f}, {64, 64, 3.61f, 0.43f}, {64, 128, 5.18f, 1.51f},
                                                {96, 128, 6.10f, 1.51f}, {96, 256, 9.95f, 2.07f}, {128, 128, 6.89f, 1.53f},
                                                {128, 256, 11.6f, 2.83f}, {128, 384, 16.2f, 4.24f}, {256, 256, 19.0f, 4.30f}};
@@ -349,7 +352,10 @@ nf_status netfuse_linear(const void* X, const void* W, const float* bias, const 
         // models of 279 rows 31.9 -> 25.1 (768 -> 2304), 42.5 -> 33.7 (3072), 14.1 -> 12.2 (768), 36.0 -> 30.7 us (3072 -> 768);
         // 1 model of 93 rows 3072 -> 768 20 -> 16.1 us.
         const float now = tile_us(d >= 0 ? kDmaCost[d] : kRegCost[d == kPreferSmallTile ? T64x64 : pick_tile(N, Nout, M)], N, Nout, K, M);
-        const int r = pick_ring(kRingCost, N, Nout, K, M, d >= 0 ? 0.93f * now : now);
+        // With one row tile nothing shares the weights of a 128 x 384 tile, whole-tile or ring, and the model, fitted to both,
+        // is too low for the ring one: 24, 32 and 48 models of 128 rows 768 -> 3072 32.2, 35.0, 59.4 us as before, 34.0, 36.5, 61.3 there.
+        const float margin = d < 0 ? 1.0f : N == 128 && kDmaBN[d] == 384 ? 0.65f : 0.93f;
+        const int r = pick_ring(kRingCost, N, Nout, K, M, margin * now);
         if (r >= 0) {
           const nf_status st = launch_gemm_ring(r, false, L, s);
           if (st != NF_EUNSUPPORTED) return st;

@@ -1,5 +1,5 @@
-"""Every tile of the ragged matmul kernel at shapes that route to it: rows and columns past the last whole tile, several
-rounds of workgroups, with packed weights k-groups with unequal numbers of steps and with none.  Integer-coded: every sum is exact in
+"""Every tile of the ragged matmul kernel at shapes that route to it, and those of the whole-tile kernels, which are left
+with k below 256 or not a multiple of 64: rows and columns past the last whole tile, several rounds of workgroups, with packed weights k-groups with unequal numbers of steps and with none.  Integer-coded: every sum is exact in
 float32 in any order, so bias, residual and ReLU included the result must match the oracle bit for bit; GELU within the
 rounding of a bf16 result (2^-8) and the 6.3e-7 of its polynomial."""
 import numpy as np
@@ -16,6 +16,10 @@ CASES = [
 ]
 PACKED = [(1, 128, 256, 96), (24, 128, 256, 96), (48, 256, 256, 128), (48, 128, 384, 384), (48, 384, 256, 192),
           (48, 256, 256, 672)]                                                    # the six packed tiles, 32 x 32 first
+
+WHOLE = [(2, 128, 160, 128), (2, 128, 192, 384), (2, 128, 160, 288), (2, 128, 192, 96), (32, 512, 160, 1024),
+         (100, 256, 160, 384),                     # 128 x 128 (32- and 64-k steps), 128 x 288, 128 x 96, 256 x 256, 128 x 384
+         (32, 512, 160, 3072), (32, 512, 160, 2304)]    # three tiles per workgroup: 256 x 256 with GELU; 128 x 384 without
 
 
 def run(oracle, shape, packed, act):
@@ -38,13 +42,14 @@ def run(oracle, shape, packed, act):
 
 
 @pytest.mark.parametrize("act", [0, 1])
-@pytest.mark.parametrize("shape,packed", [(s, False) for s in CASES] + [(s, True) for s in PACKED])
+@pytest.mark.parametrize("shape,packed", [(s, False) for s in CASES] + [(s, True) for s in PACKED] + [(s, False) for s in WHOLE])
 def test_exact(oracle, shape, packed, act):
     got, ref = run(oracle, shape, packed, act)
     assert np.array_equal(got, ref)
 
 
-@pytest.mark.parametrize("shape,packed", [(CASES[0], False), (CASES[4], False), (PACKED[0], True), (PACKED[5], True)])
+@pytest.mark.parametrize("shape,packed", [(CASES[0], False), (CASES[4], False), (PACKED[0], True), (PACKED[5], True)] +
+                         [(s, False) for s in WHOLE])
 def test_gelu(oracle, shape, packed):
     got, ref = run(oracle, shape, packed, 2)
     assert np.all(np.abs(got - ref) <= 2.0 ** -7 * np.abs(ref) + 2e-6)
