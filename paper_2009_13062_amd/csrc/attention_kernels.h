@@ -181,10 +181,11 @@ constexpr int kAttnKPitch = kAttnD + 8;     // K tile [key][t]: 144 B rows, 16-b
 constexpr int kAttnVPitch = kAttnD + 32;    // V tile [key][t]: 192 B rows, so the 4 keys x 64 B that 32 lanes of a
                                             // transposing read touch tile the 256 bytes of the 64 LDS banks
 
+template <bool MASK>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void attention_mfma_d64_kernel(AttnArgs a, int qblocks) {
   __shared__ __align__(16) bf16_t Ks_raw[2 * kAttnKB * kAttnKPitch];
   __shared__ __align__(16) bf16_t Vs_raw[2 * kAttnKB * kAttnVPitch];
-  __shared__ __align__(16) float Ms_raw[2 * kAttnKB];
+  __shared__ __align__(16) float Ms_raw[MASK ? 2 * kAttnKB : 4];
   // the key mask of a block, in log2 units, staged with its keys: read from memory by every lane at its use it cost as
   // much as the scores (32 models x 12 heads x 512 tokens 82 -> 49 us, 47.6 without a mask)
   lds_f32_t* const Ms = (lds_f32_t*)Ms_raw;
@@ -201,7 +202,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void a
   const bf16_t* Qp = (const bf16_t*)a.Q + head_off;
   const bf16_t* Kp = (const bf16_t*)a.K + head_off;
   const bf16_t* Vp = (const bf16_t*)a.V + head_off;
-  const float* mk = a.mask ? a.mask + ((long)m * a.B + b) * a.S : nullptr;
+  const float* mk = MASK ? a.mask + ((long)m * a.B + b) * a.S : nullptr;
   const float kLog2e = 1.4426950408889634f;
   const float sc = a.scale * kLog2e;          // scores are kept in log2 units: exp(x) = exp2(x log2 e)
 
@@ -226,7 +227,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void a
   uint4 kreg[2], vreg[2];
   float mreg = 0.f;
   auto fetch = [&](int j0) {
-    if (mk != nullptr) mreg = tid < kAttnKB && j0 + tid < a.S ? mk[j0 + tid] : 0.f;
+    if (MASK) mreg = tid < kAttnKB && j0 + tid < a.S ? mk[j0 + tid] : 0.f;
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       const int c = tid + t * 256, key = c / 8, kc = (c % 8) * 8;
@@ -238,7 +239,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void a
     }
   };
   auto commit = [&](int stage) {
-    if (mk != nullptr && tid < kAttnKB) Ms[stage * kAttnKB + tid] = mreg * kLog2e;
+    if (MASK && tid < kAttnKB) Ms[stage * kAttnKB + tid] = mreg * kLog2e;
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       const int c = tid + t * 256, key = c / 8, kc = (c % 8) * 8;
@@ -280,8 +281,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void a
     // register r of block sb is key j0 + 32 sb + 8 (r/4) + 4 half + r%4, query lane%32
     // Without a mask and with a positive scale (uniform over the launch) the scores stay unscaled: the running
     // maximum is taken on them and scaled once, and scale and maximum enter the exponent in one fma.
-    const bool raw = mk == nullptr && sc > 0.f;
-    if (mk != nullptr) {                       // uniform branch: additive key mask (in log2 units)
+    const bool raw = !MASK && sc > 0.f;
+    if constexpr (MASK) {                      // additive key mask (in log2 units)
 #pragma unroll
       for (int sb = 0; sb < 2; ++sb)
 #pragma unroll

@@ -924,7 +924,8 @@ nf_status netfuse_attention(const void* Q, const void* K, const void* V, const f
     const int qblocks = (S + 127) / 128;
     const long long total = prod({M, B, heads, qblocks});
     if (total > kMaxGrid) return NF_EUNSUPPORTED;
-    nf_launch(attention_mfma_d64_kernel, dim3((unsigned)total), dim3(256), 0, s, a, qblocks);
+    if (mask) nf_launch(attention_mfma_d64_kernel<true>, dim3((unsigned)total), dim3(256), 0, s, a, qblocks);
+    else nf_launch(attention_mfma_d64_kernel<false>, dim3((unsigned)total), dim3(256), 0, s, a, qblocks);
     return launched();
   }
   const long long head_elems = (long long)(S - 1) * stride_row + d;         // one head's rows, first to last element
