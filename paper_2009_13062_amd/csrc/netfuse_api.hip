@@ -816,22 +816,24 @@ nf_status netfuse_layernorm(const void* x, const void* residual, const float* ga
   const size_t va = 4 * esz;
   const bool vec = H % 4 == 0 && aligned(x, va) && aligned(y, va) && aligned(residual, va);
   const int ch = layout == NF_MERGE_CHANNEL;
-  // rows that fit in registers: two per wavefront (they share the model's gamma and beta) once there are
-  // enough rows to keep every CU busy that way (measured: 16384 rows of 768 11.8 -> 10.4 us, 4096 rows
-  // 3.9 -> 4.7 us)
-  static const int ln_forced = [] { const char* e = dev_getenv("NETFUSE_LN_ROWS"); return e ? atoi(e) : 0; }();
-  const int ln_rows = ln_forced ? ln_forced : (nrows >= 16384 ? 2 : 1);
+  // rows that fit in registers: two per wavefront (they share the model's gamma and beta) of up to 512 features once there
+  // are enough rows to keep every CU busy that way.  16384 rows of bf16 (us, one / two): 256 features 6.8 / 5.9, 512 8.2 /
+  // 8.1, 768 10.4 / 10.7, with a residual 14.8 / 15.3; 4096 rows of 768 3.9 / 4.7.
   if (vec && H <= kWave * 4 * 4) {
-    const int R = ln_rows == 2 && rows % 2 == 0 ? 2 : 1, nit = (H + 255) / 256;
+    const int R = nrows >= 16384 && H <= 512 && rows % 2 == 0 ? 2 : 1, nit = (H + 255) / 256;
     const long long blocks_r = (nrows / R + 3) / 4;
 #define NF_LNR(T, N, R_)                                                                                  \
   nf_launch((layernorm_rows_kernel<T, N, R_>), dim3((unsigned)blocks_r), dim3(256), 0, s,                  \
                      (const T*)x, (const T*)residual, gamma, beta, (T*)y, M, rows, H, eps, ch)
-#define NF_LNR_N(T, N) if (R == 2) NF_LNR(T, N, 2); else NF_LNR(T, N, 1)
-#define NF_LNR_T(T) switch (nit) { case 1: NF_LNR_N(T, 1); break; case 2: NF_LNR_N(T, 2); break; case 3: NF_LNR_N(T, 3); break; default: NF_LNR_N(T, 4); }
+#define NF_LNR_T(T)                                                   \
+  switch (nit) {                                                      \
+    case 1: if (R == 2) NF_LNR(T, 1, 2); else NF_LNR(T, 1, 1); break; \
+    case 2: if (R == 2) NF_LNR(T, 2, 2); else NF_LNR(T, 2, 1); break; \
+    case 3: NF_LNR(T, 3, 1); break;                                   \
+    default: NF_LNR(T, 4, 1); break;                                  \
+  }
     if (dt == NF_F32) { NF_LNR_T(float) } else { NF_LNR_T(bf16_t) }
 #undef NF_LNR_T
-#undef NF_LNR_N
 #undef NF_LNR
     return launched();
   }
