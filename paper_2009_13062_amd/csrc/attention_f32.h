@@ -68,7 +68,7 @@ __global__ __launch_bounds__(256) void attention_f32_kernel(AttnArgs a, int qblo
   f32x4_t o_acc[NB];
 #pragma unroll
   for (int i = 0; i < NB; ++i) o_acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  float mrun = -3.0e38f, lrun = 0.f;            // lrun: this lane's partial sum
+  float mrun = kLowest, lrun = 0.f;            // lrun: this lane's partial sum
   fetch(0);
   for (int j0 = 0; j0 < a.S; j0 += KB) {
     commit();
@@ -88,13 +88,13 @@ __global__ __launch_bounds__(256) void attention_f32_kernel(AttnArgs a, int qblo
         for (int kb = 0; kb < KB / 16; ++kb) sc[kb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[kb][t], qf[s][t], sc[kb], 0, 0, 0);
     }
     // element r of block kb: key j0 + 16 kb + 4 g + r of query l16
-    float mloc = -3.0e38f;
+    float mloc = kLowest;
 #pragma unroll
     for (int kb = 0; kb < KB / 16; ++kb)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int key = j0 + kb * 16 + 4 * g + r;
-        sc[kb][r] = key < a.S ? sc[kb][r] * a.scale + (mk ? mk[key] : 0.f) : -3.0e38f;
+        sc[kb][r] = key < a.S ? sc[kb][r] * a.scale + (mk ? mk[key] : 0.f) : kLowest;
         mloc = fmaxf(mloc, sc[kb][r]);
       }
     mloc = fmaxf(mloc, __shfl_xor(mloc, 16, kWave));

@@ -14,6 +14,15 @@ struct AttnArgs {
   float scale;
 };
 
+// Running maxima start here: a row whose keys are all masked with the lowest finite value gets even weights (every score
+// is absorbed by the mask), one masked with -infinity throughout has none (0 / 0).
+constexpr float kLowest = -3.402823466e38f;
+// A key's mask in log2 units.  A finite value stays finite: the lowest one would become -infinity.
+__device__ __forceinline__ float mask_log2(float m) {
+  const float v = m * 1.4426950408889634f;
+  return fabsf(m) <= -kLowest ? fminf(fmaxf(v, kLowest), -kLowest) : v;
+}
+
 // ------------------------------------------------------------------------------------------
 // General kernel (float or bf16 storage, any d <= 64*DPL): one wavefront per query row.
 // Keys are visited 64 at a time (one per lane) with a running maximum and sum (online softmax);
@@ -41,12 +50,12 @@ __global__ __launch_bounds__(256) void attention_generic_kernel(AttnArgs a) {
     qs[wave][tt] = tt < a.d ? load_f32(Qp + tt) : 0.f;
   }
   __builtin_amdgcn_wave_barrier();
-  float mrun = -3.0e38f, lrun = 0.f, acc[DPL];
+  float mrun = kLowest, lrun = 0.f, acc[DPL];
 #pragma unroll
   for (int e = 0; e < DPL; ++e) acc[e] = 0.f;
   for (int j0 = 0; j0 < a.S; j0 += 64) {
     const int j = j0 + lane;
-    float s = -3.0e38f;
+    float s = kLowest;
     if (j < a.S) {
       const T* kr = Kp + (long)j * a.stride_row;
       float dot = 0.f;
@@ -120,12 +129,12 @@ __global__ __launch_bounds__(256) void attention_relpos_kernel(AttnRelArgs ra) {
     qr[wave][tt] = tt < a.d ? q + (ra.bias_r ? ra.bias_r[m * hd + h * a.d + tt] : 0.f) : 0.f;
   }
   __builtin_amdgcn_wave_barrier();
-  float mrun = -3.0e38f, lrun = 0.f, acc[DPL];
+  float mrun = kLowest, lrun = 0.f, acc[DPL];
 #pragma unroll
   for (int e = 0; e < DPL; ++e) acc[e] = 0.f;
   for (int j0 = 0; j0 < a.S; j0 += 64) {
     const int j = j0 + lane;
-    float s = -3.0e38f;
+    float s = kLowest;
     if (j < a.S) {
       const T* kr = Kp + (long)j * a.stride_row;
       const T* pr = Rp + (long)j * hd;
@@ -221,7 +230,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void a
   for (int tb = 0; tb < kAttnD / 32; ++tb)
 #pragma unroll
     for (int r = 0; r < 16; ++r) o_acc[tb][r] = 0.f;
-  float mrun = -3.0e38f, lrun = 0.f;          // lrun: this half's partial sum
+  float mrun = kLowest, lrun = 0.f;           // lrun: this half's partial sum
 
   // K and V blocks: 64 keys x 8 chunks of 16 bytes each = 2 chunks per thread per tensor
   uint4 kreg[2], vreg[2];
@@ -239,7 +248,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void a
     }
   };
   auto commit = [&](int stage) {
-    if (MASK && tid < kAttnKB) Ms[stage * kAttnKB + tid] = mreg * kLog2e;
+    if (MASK && tid < kAttnKB) Ms[stage * kAttnKB + tid] = mask_log2(mreg);
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       const int c = tid + t * 256, key = c / 8, kc = (c % 8) * 8;
@@ -303,16 +312,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void a
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int key = j0 + sb * 32 + 8 * (r / 4) + 4 * half + (r % 4);
-          s_acc[sb][r] = key < a.S ? s_acc[sb][r] : -3.0e38f;      // stays the minimum under a positive scale
+          s_acc[sb][r] = key < a.S ? s_acc[sb][r] : -INFINITY;      // weight 0 under any scale and mask
         }
     }
-    float mloc = -3.0e38f;
+    float mloc = kLowest;
 #pragma unroll
     for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
       for (int r = 0; r < 16; ++r) mloc = fmaxf(mloc, s_acc[sb][r]);
     mloc = fmaxf(mloc, __shfl_xor(mloc, 32, kWave));
-    if (raw) mloc = fmaxf(mloc * sc, -3.0e38f);
+    if (raw) mloc = fmaxf(mloc * sc, kLowest);
     const float mnew = fmaxf(mrun, mloc);
     const float corr = __builtin_amdgcn_exp2f(mrun - mnew);
     mrun = mnew;
@@ -452,7 +461,7 @@ __global__ __launch_bounds__(256, 2) void attention_relpos_mfma_d64_kernel(AttnR
   for (int tb = 0; tb < kAttnD / 32; ++tb)
 #pragma unroll
     for (int r = 0; r < 16; ++r) o_acc[tb][r] = 0.f;
-  float mrun = -3.0e38f, lrun = 0.f;
+  float mrun = kLowest, lrun = 0.f;
 
   // staging: 64 K rows, 64 V rows (2 chunks of 16 bytes per thread each) and 192 Kr rows (6 chunks per thread)
   uint4 kreg[2], vreg[2], rreg[6];
@@ -478,7 +487,7 @@ __global__ __launch_bounds__(256, 2) void attention_relpos_mfma_d64_kernel(AttnR
     }
   };
   auto commit = [&]() {
-    if (mk != nullptr && tid < kAttnKB) Ms[tid] = mreg * kLog2e;
+    if (mk != nullptr && tid < kAttnKB) Ms[tid] = mask_log2(mreg);
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       const int c = tid + t * 256, key = c / 8, kc = (c % 8) * 8;
@@ -601,16 +610,16 @@ __global__ __launch_bounds__(256, 2) void attention_relpos_mfma_d64_kernel(AttnR
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int key = j0 + sb * 32 + 8 * (r / 4) + 4 * half + (r % 4);
-          s_acc[sb][r] = key < a.S ? s_acc[sb][r] : -3.0e38f;
+          s_acc[sb][r] = key < a.S ? s_acc[sb][r] : -INFINITY;
         }
     }
-    float mloc = -3.0e38f;
+    float mloc = kLowest;
 #pragma unroll
     for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
       for (int r = 0; r < 16; ++r) mloc = fmaxf(mloc, s_acc[sb][r]);
     mloc = fmaxf(mloc, __shfl_xor(mloc, 32, kWave));
-    if (raw) mloc = fmaxf(mloc * sc, -3.0e38f);
+    if (raw) mloc = fmaxf(mloc * sc, kLowest);
     const float mnew = fmaxf(mrun, mloc);
     const float corr = __builtin_amdgcn_exp2f(mrun - mnew);
     mrun = mnew;
