@@ -93,9 +93,13 @@ nf_status launch_conv_tap_3x3(ConvPatchArgs& a, int B, hipStream_t s) {
     c.PW = a.PW + ((a.Wo - a.PW) % 16 + 16) % 16;
     c.PS = rows * c.PW;
   }
-  if (bm == 128) return launch_tap<ConvTapCfg<128, 2, 2, 1>>(c, B, s);
-  if (bm == 64) return launch_tap<ConvTapCfg<64, 1, 4, 2>>(c, B, s);
-  return launch_tap<ConvTapCfg<32, 1, 4, 2>>(c, B, s);
+  // A patch that leaves no room for the weights of a tall tile runs in the next lower one, not in another kernel: the sum
+  // has the same order in all three, and the number of models must not decide about it.
+  nf_status st = NF_EUNSUPPORTED;
+  if (bm == 128) st = launch_tap<ConvTapCfg<128, 2, 2, 1>>(c, B, s);
+  if (st == NF_EUNSUPPORTED && bm >= 64) st = launch_tap<ConvTapCfg<64, 1, 4, 2>>(c, B, s);
+  if (st == NF_EUNSUPPORTED) st = launch_tap<ConvTapCfg<32, 1, 4, 2>>(c, B, s);
+  return st;
 }
 
 }  // namespace nf

@@ -22,3 +22,16 @@ def test_conv_any_width(oracle, H, W, stride, cig, cog, g):
     dev = lambda a, dt=torch.bfloat16: torch.from_numpy(a).to("cuda", dt)
     got = nf.conv2d(dev(x), dev(w), M, g=g, bias=dev(bias, torch.float32), stride=stride, pad=1, act=nf.ACT_RELU)
     assert np.array_equal(got.float().cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("C,W,stride,pad", [(128, 112, 2, 2), (128, 107, 2, 2), (128, 112, 2, 1), (128, 25, 1, 1), (64, 50, 1, 1), (512, 13, 2, 1)])
+def test_merged_equals_single(C, W, stride, pad):
+    """The row tile follows from the number of models, also where a patch is too large for the tallest one: the same bits."""
+    import paper_2009_13062_amd as nf
+    M = 10
+    x = torch.randn(1, M * C, W, W, device="cuda").bfloat16()
+    w = (torch.randn(M * C, C, 3, 3, device="cuda") * 0.05).bfloat16()
+    merged = nf.conv2d(x, w, M, stride=stride, pad=pad)
+    for m in (0, M - 1):
+        one = nf.conv2d(x[:, m * C:(m + 1) * C].contiguous(), w[m * C:(m + 1) * C], 1, stride=stride, pad=pad)
+        assert torch.equal(merged[:, m * C:(m + 1) * C], one), m
