@@ -95,10 +95,17 @@ def _ptr(t: Optional[torch.Tensor], like: Optional[torch.Tensor] = None, f32: bo
     return t.data_ptr()
 
 
+# the raw handle of the current stream, without building a Stream object on every call (3.5 of 8 us); both are private to
+# torch, so a torch without them gets the object
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        # the raw handle of torch.cuda.current_stream(), without building a Stream object on every call (3.5 of 8 us)
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
+        if _raw_stream is not None and _device is not None:
+            return _raw_stream(_device()) or None
+        stream = torch.cuda.current_stream()
     return stream.cuda_stream or None
 
 

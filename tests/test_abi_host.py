@@ -161,3 +161,18 @@ def test_binding_has_no_cpu_fallback():
     for mod in (nf, wl):
         src = open(mod.__file__).read()
         assert "import oracle" not in src and "from oracle" not in src
+
+
+@pytest.mark.parametrize("missing", ["_raw_stream", "_device"])
+def test_stream_without_torch_internals(monkeypatch, missing):
+    """A torch without its private stream functions still gives a launch its stream."""
+    import types
+
+    import torch
+
+    import paper_2009_13062_amd as nf
+    monkeypatch.setattr(nf, missing, None)
+    for handle in (4096, 0):
+        monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=handle))
+        assert nf._stream(None) == (handle or None)
+    assert nf._stream(types.SimpleNamespace(cuda_stream=64)) == 64
