@@ -39,7 +39,8 @@ struct ConvPatchArgs {
   const bf16_t* x; const bf16_t* w; const bf16_t* R; bf16_t* y;
   int cig, cog, nG, H, W, Ho, Wo, HoWo, stride, pad;
   int PW, PS;                 // patch row pitch and plane pitch (elements); PS covers the tallest patch
-  int VW, cpr;                // patch rows are copied in chunks of VW pixels (VW | W, power of two <= 8); cpr = W / VW
+  int VW, cpr;                // patch rows are copied in cpr chunks of VW pixels (a power of two <= 8): VW | W and cpr = W / VW, but
+                              // conv_tap.h takes any VW <= W, cpr rounded up
   int S;                      // groups fused per workgroup (see below); 1 = one group per workgroup
   int cig_real, cog_real;     // S > 1: channels of ONE group; cig = S*cig_real, cog = S*cog_real then describe the fused group
   int tiles_m, tiles_n;

@@ -43,8 +43,8 @@ static nf_status launch_ring(GemmLaunch& L, hipStream_t s) {
   return hipGetLastError() == hipSuccess ? NF_OK : NF_ELAUNCH;
 }
 
-// Row-major weights: k is summed in one ascending chain, as by every other kernel behind netfuse_linear, so that a
-// model's result does not depend on how many models are merged with it.  Small wave tiles (a 32 x 32 block per
+// Row-major weights: k is summed in one ascending chain, as by every other bf16 kernel behind netfuse_linear (float32 has an
+// order of its own, gemm_f32.h), so that a model's result does not depend on how many models are merged with it.  Small wave tiles (a 32 x 32 block per
 // wavefront) with deep rings: 2 to 16 wavefronts share the loads and leave their latency to each other.
 //                             FM FN WGM WGN KG BK NS waves per SIMD
 static nf_status launch_ring_tile(int tile, GemmLaunch& L, hipStream_t s) {

@@ -1,6 +1,7 @@
 // General-shape kernels for the merged matmul and the merged convolution: plain fp32 FMA, any
-// size, any alignment, float or bf16 storage.  They serve the fp32 storage type and every bf16
-// shape the MFMA kernels do not take.
+// size, any alignment, float or bf16 storage.  They serve what the MFMA kernels do not take or are
+// slower at: float32 convolutions over narrow groups and with 64 taps or more, float32 matmuls of a
+// few k over thousands of rows, operands of 2 GB and more, the per-task heads.
 #pragma once
 #include "nf_common.h"
 

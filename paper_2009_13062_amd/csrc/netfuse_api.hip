@@ -992,7 +992,7 @@ nf_status netfuse_attention_relpos(const void* Q, const void* K, const void* V, 
     const int qblocks = (S + 127) / 128;
     const long long total = prod({M, B, heads, qblocks});
     if (total > kMaxGrid) return NF_EUNSUPPORTED;
-    static std::atomic<bool> opted_in{false};          // 130 KB of LDS: one opt-in per process (idempotent)
+    static std::atomic<bool> opted_in{false};          // 68 KB of LDS: one opt-in per process (idempotent)
     if (!opted_in.load(std::memory_order_acquire)) {
       if (hipFuncSetAttribute(reinterpret_cast<const void*>(attention_relpos_mfma_d64_kernel),
                               hipFuncAttributeMaxDynamicSharedMemorySize, kRelLdsBytes) != hipSuccess)
