@@ -37,8 +37,8 @@ def edges(oracle, nout, N, K, dtype):
 
 
 def test_many_rows_of_short_k_are_bound_by_the_output():
-    """4096 rows of 8 k and 1000 outputs: a few times as long as writing the outputs (5 times), not what sixteen wavefronts per
-    eight rows take for a k that four can share (16 times)."""
+    """4096 rows of 8 k and 1000 outputs: six to seven times as long as moving the outputs, not what sixteen wavefronts
+    per eight rows take for a k that four can share (22 times)."""
     import paper_2009_13062_amd as nf
     from test_gpu_f32 import us
     M, N, K, n = 4, 4096, 8, 1000
@@ -46,4 +46,4 @@ def test_many_rows_of_short_k_are_bound_by_the_output():
     X, W, Y, dst = bf(M, N, K), bf(M * K * n), bf(M * N * n), bf(N, M * n)
     copy = us(lambda: nf.merge_transpose(Y.view(M, N, n), M, True, out=dst))
     head = us(lambda: nf.linear_ragged(X, W, [n] * M, out=Y))
-    assert head < 10 * copy, (head, copy)
+    assert head < 12 * copy, (head, copy)
