@@ -148,8 +148,8 @@ int pick_dma_or_small(int N, int Nout, int K, long long M) {
 
 // Streaming kernel (gemm_stream.h) for a problem that pick_dma() routed to direct-to-LDS tile d, or -1.
 // Measured on MI355X, 32 models (us, register epilogue / LDS-staged epilogue of the same tile):
-//   GELU epilogues, 128 rows: 768 -> 3072  37.8 / 39.4 (the only one of these that the ring tiles leave to it);   512 rows, three 256x256 tiles per workgroup through
-//   one pipeline: 105.6 / 119.1.  The barrier-free epilogue pays where the epilogue is VALU heavy; plain
+//   GELU epilogues, 128 rows: 768 -> 3072  37.8 / 39.4 (the only one of these that the ring tiles leave to it);
+//   512 rows, three 256x256 tiles per workgroup through one pipeline: 105.6 / 119.1.  The barrier-free epilogue pays where the epilogue is VALU heavy; plain
 //   bias / residual epilogues are as fast or faster through LDS (full-line stores), so they keep it --
 //   except that 512-row problems whose 256x256 tiling leaves a quarter of the last round of workgroups
 //   empty (768 -> 2304: 576 tiles) run as three 128x384 tiles per workgroup (82.7 / 88.4).
@@ -348,9 +348,10 @@ nf_status netfuse_linear(const void* X, const void* W, const float* bias, const 
       const int d = pick_dma_or_small(N, Nout, K, M);
       if (forced_dma() == -2 && forced_tile() < 0 && ring_fits(Nout, K)) {
         // gemm_ring.h where its tiles are predicted to be faster, by more than the prediction is worth where a whole-tile
-        // kernel is the alternative.  Over the 252 problems this takes 11 % off on average, most for ragged rows: 12
-        // models of 279 rows 31.9 -> 25.1 (768 -> 2304), 42.5 -> 33.7 (3072), 14.1 -> 12.2 (768), 36.0 -> 30.7 us (3072 -> 768);
-        // 1 model of 93 rows 3072 -> 768 20 -> 16.1 us.
+        // kernel is the alternative (a streaming kernel, 4 to 12 % faster, is priced as the whole-tile kernel of its tile).
+        // Over the 252 problems this takes 11 % off on average, most for ragged rows: 12 models of 279 rows 31.9 -> 25.1
+        // (768 -> 2304), 42.5 -> 33.7 (3072), 14.1 -> 12.2 (768), 36.0 -> 30.7 us (3072 -> 768); 1 model of 93 rows 3072 -> 768
+        // 20 -> 16.1 us.
         const float now = tile_us(d >= 0 ? kDmaCost[d] : kRegCost[d == kPreferSmallTile ? T64x64 : pick_tile(N, Nout, M)], N, Nout, K, M);
         // With one row tile nothing shares the weights of a 128 x 384 tile, whole-tile or ring, and the model, fitted to both,
         // is too low for the ring one: 24, 32 and 48 models of 128 rows 768 -> 3072 32.2, 35.0, 59.4 us as before, 34.0, 36.5, 61.3 there.
@@ -762,7 +763,7 @@ nf_status netfuse_conv2d(const void* x, const void* w, const float* bias, const 
   // channels per group 29 / 64, 4 -> 8 38 / 47, 8 -> 8 81 / 47; 7x7 depthwise 10 / 63, 2 -> 8 79 / 83; pointwise 8 -> 8
   // 23 / 25, 16 -> 8 38 / 25; one model with one group at 56 x 56: 8 -> 1 13 / 7, 16 -> 1 24 / 8.
   const bool f32_dense = KH == 1 && KW == 1 && stride == 1 && pad == 0 && HoWo % 4 == 0;
-  const bool f32_narrow = (long long)cog * Kdim <= (f32_dense ? 64 : 220 + 10 * KH * KW) && (g >= 64 || Kdim <= (f32_dense ? 16 : 72));
+  const bool f32_narrow = (long long)cog * Kdim <= (f32_dense ? 64 : 220 + 10LL * KH * KW) && (g >= 64 || Kdim <= (f32_dense ? 16 : 72));
   if (dt == NF_F32 && KH * KW < 64 && !f32_narrow && f32_fits((long long)cog * Kdim, prod({cig, H, W}), Kdim)) {
     GemmF32Args a;
     memset(&a, 0, sizeof(a));
