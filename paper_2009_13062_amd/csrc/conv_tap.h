@@ -19,6 +19,9 @@
 // (conv_patch.h keeps the planes apart in LDS and gathers each tap of each channel with a 2-byte read:
 // eight LDS reads per fragment, which bounds its 3x3 layers on small images.)
 //
+// It runs where many positions share a block's weights (planes beyond 14 x 14, narrow groups in pairs); small planes and many
+// channels are conv_wave.h's (the rule and both sides' times: conv_wave_inst.hip).
+//
 // The patch carries its zero padding: it is zeroed once, and every channel block overwrites only the
 // in-image pixels.  Image column ix lives at patch column ix + kLPad.  One workgroup = one (image, group,
 // 128-position tile, BM output channels); accumulators and the fused epilogue are those of gemm_mfma.h.

@@ -1,0 +1,151 @@
+// Instantiation, tile choice and launch of the 3x3 kernels with wavefront-private pipelines (conv_wave.h).
+#include <algorithm>
+#include <atomic>
+#include <cmath>
+#include <cstdio>
+
+#include "conv_wave.h"
+#include "gemm_launch.h"
+
+namespace nf {
+
+template <typename T, int NB, int KG, int NT>
+static nf_status launch_kernel(long long total, int lds, const ConvWaveArgs<T>& a, hipStream_t s) {
+  auto kern = conv_wave_kernel<T, NB, KG, NT>;
+  if (lds > 64 * 1024) {
+    static std::atomic<bool> opted_in{false};        // per kernel: idempotent, a benign race
+    if (!opted_in.load(std::memory_order_acquire)) {
+      if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) !=
+          hipSuccess)
+        return NF_ELAUNCH;
+      opted_in.store(true, std::memory_order_release);
+    }
+  }
+  nf_launch(kern, dim3((unsigned)total), dim3(KG * kWave), lds, s, a);
+  return hipGetLastError() == hipSuccess ? NF_OK : NF_ELAUNCH;
+}
+
+// The tile with NB blocks of positions: patch, tasks per lane, LDS; nt == 0: it does not fit.
+struct WaveTile { int tiles_n, PS, nt, lds; };
+template <typename T>
+static WaveTile wave_tile(const ConvWaveArgs<T>& a, int Ho, int NB, int KG) {
+  constexpr int PX = ConvWaveType<T>::kPix, kMostTasks = sizeof(T) == 4 ? 24 : 15;      // a task is 4 or 8 registers
+  WaveTile t{(a.HoWo + 32 * NB - 1) / (32 * NB), 0, 0, 0};
+  // output rows that 32 NB consecutive positions can touch, the patch rows and image rows they need
+  const int span = (int)std::min<long long>(Ho, 32 * NB % a.Wo == 0 ? 32 * NB / a.Wo : (32 * NB - 2 + a.Wo) / a.Wo + 1);
+  const int PH = (span - 1) * a.stride + 3;
+  const long long PS = (long long)PH * a.PW;
+  if (PS >= 32768) return t;                                 // two 16-bit pixel slots share a register
+  t.PS = (int)PS;
+  t.lds = conv_wave_lds_bytes(NB, KG, t.PS);
+  const long long npx = (long long)std::min(PH, a.H) * a.W;
+  const long long nt = (2 * ((npx + PX - 1) / PX) + kWave - 1) / kWave;
+  if (t.lds <= 160 * 1024 && nt <= kMostTasks) t.nt = (int)nt;
+  return t;
+}
+
+template <typename T, int NB, int KG>
+static nf_status launch_tile(const WaveTile& t, ConvWaveArgs<T>& a, int B, hipStream_t s) {
+  a.tiles_m = (a.cog + 31) / 32;
+  a.tiles_n = t.tiles_n;
+  a.PS = t.PS;
+  const long long total = (long long)a.tiles_m * a.tiles_n * a.nG * B;
+  if (total <= 0 || total > 0x7fffffffLL) return NF_EUNSUPPORTED;
+#define NF_CW(NT_) if (t.nt <= NT_) return launch_kernel<T, NB, KG, NT_>(total, t.lds, a, s)
+  NF_CW(1); NF_CW(2); NF_CW(4); NF_CW(7); NF_CW(10); NF_CW(15);
+  if constexpr (sizeof(T) == 4) { NF_CW(24); }
+#undef NF_CW
+  return NF_EUNSUPPORTED;
+}
+
+// Time of a tile (us) for choosing the number of blocks: launch, per round of workgroups the latency of one, and the rate at which a
+// compute unit gets through the others of its round.  n: steps of a wavefront.  Fitted to every tile over 1265 bf16 and 1250
+// float32 problems (8 ... 512 channels, planes of 7 x 7 to 100 x 100, either stride, 1 ... 128 images): predictions are off by 5 to
+// 10 %, the tile chosen is 0.5 to 1 % behind the best one on average.
+struct WaveCost { float launch, lat, lat_nb, lat_n, lat_n_nb, lat_n_nt, thr, thr_nb, thr_n, thr_n_nb; };
+constexpr WaveCost kWaveCost[2][2] = {   // [float32][four wavefronts per tile]
+    {{2.45f, 1.63f, 0.96f, 0.24f, 0.15f, 0.11f, 0.54f, 0.38f, 0.37f, 0.22f},
+     {3.01f, 1.04f, 0.42f, 0.47f, 0.16f, 0.16f, 0.45f, 0.10f, 0.28f, 0.18f}},
+    {{1.44f, 2.38f, 1.23f, 0.20f, 1.01f, 0.05f, 0.32f, 0.55f, 0.00f, 1.18f},
+     {2.68f, 1.42f, 0.42f, 0.24f, 1.03f, 0.09f, 0.13f, 0.03f, 0.32f, 1.16f}}};
+
+template <typename T>
+static float wave_us(const ConvWaveArgs<T>& a, const WaveTile& t, int NB, int KG, int B) {
+  constexpr bool kF32 = sizeof(T) == 4;
+  const WaveCost& c = kWaveCost[kF32][KG == 4];
+  const int n = (a.cig / (2 * ConvWaveType<T>::kEV) + KG - 1) / KG;
+  const int nt = t.nt <= 1 ? 1 : t.nt <= 2 ? 2 : t.nt <= 4 ? 4 : t.nt <= 7 ? 7 : t.nt <= 10 ? 10 : t.nt <= 15 ? 15 : 24;
+  const float W = (float)((double)((a.cog + 31) / 32) * t.tiles_n * a.nG * B * KG / 1024);      // workgroups of four wavefronts per compute unit
+  const int occ = std::min(160 * 1024 / t.lds, conv_wave_occupancy(kF32, NB, nt) * 4 / KG);
+  const float rounds = ceilf(W * 4 / (KG * occ));
+  return c.launch + rounds * (c.lat + c.lat_nb * NB + n * (c.lat_n + c.lat_n_nb * NB + c.lat_n_nt * nt)) +
+         std::max(ceilf(W) - rounds, 0.f) * (c.thr + c.thr_nb * NB + n * (c.thr_n + c.thr_n_nb * NB));
+}
+
+// How many wavefronts share a tile, by the shape of ONE group (never by how many models or images there are: the order of the sum
+// follows from it); 0 = another kernel.
+//   bf16 (conv_tap.h, which multiplies four wavefronts' worth of positions out of one block of 32 channels, is the alternative for
+//   groups of 32 k channels): small planes, where that kernel waits, and many channels.  Times against it, averaged over 1 ...
+//   128 images (and the worst of them, always one of the largest counts):
+//     stride 1: up to 14 x 14 positions 0.61 ... 0.89 (1.16), 512 channels any plane 0.61 ... 0.82 (1.03), 256 channels up to 50 x 50
+//     0.84 ... 0.92 (1.09); left out: 128 channels at 28 x 28 0.96 (1.14), 56 x 56 1.08 (1.39), 64 channels at 56 x 56 1.20
+//     stride 2: up to 28 x 28 positions 0.54 ... 0.90 (1.36); left out: 128 channels at 100 -> 50 1.14 (1.54)
+//   and against the kernels that take groups of 16 (2 k + 1) channels (conv_patch.h, implicit GEMM): 16 channels on one wavefront
+//   0.64 ... 0.81 (0.92), 48 and 80 channels on four up to 36 x 36 positions 0.47 ... 0.72, on one beyond 0.66 ... 0.97 (1.10).
+//   Groups of 16 in pairs that conv_tap.h fuses: 512 channels at 14 x 14 7.6 against 7.7 us (16 models), 6.4 against 5.0 (2), stride 2
+//   14.6 against 11.6; left out: 256 at 28 x 28 12.8 against 14.8.  Fewer than 32 outputs leave rows idle: 32 -> 16 6.7 against 8.2.
+//   float32 (the gathered kernel of gemm_f32.h): 8 channels on one wavefront 0.60 ... 0.83, others on four 0.45 ... 0.87 (1.02) at
+//   stride 1; stride 2 up to 32 x 32 positions 0.45 ... 0.88 (1.2); left out: 64 channels at 72 -> 36 0.97 (1.48).
+static int wave_shares(bool f32, int cig, int cog, int g, long long HoWo, int stride) {
+  if (f32) {
+    if (stride > 1 && HoWo > 1024) return cig <= 16 ? 1 : 0;
+    return cig == 8 || (cig == 16 && HoWo > 1200) ? 1 : 4;
+  }
+  if (cig == 16) return g % 2 == 0 && cog <= 16 && HoWo > 256 ? 0 : 1;
+  if (cog < 32 && cig % 32 == 0) return 0;
+  if (cig % 32) return HoWo * stride * stride <= 1300 ? 4 : 1;
+  if (cig >= 512) return 4;
+  if (stride > 1) return HoWo <= 784 ? 4 : 0;
+  return HoWo <= (cig >= 256 ? 2500 : 196) ? 4 : 0;
+}
+
+template <typename T>
+nf_status launch_conv_wave(ConvWaveArgs<T>& a, int Ho, int B, hipStream_t s) {
+  constexpr int EV = ConvWaveType<T>::kEV;
+  const long long plane = (long long)a.H * a.W;
+  if (a.cig % (2 * EV) != 0 || a.pad > 2 || a.W < 2 || ((uintptr_t)a.w & 15) != 0 || Ho <= 0) return NF_EUNSUPPORTED;
+  // 32-bit byte offsets inside one group's weights and inside one step's planes; exact divisions by Wo and W
+  if ((long long)a.cog * a.cig * 9 * sizeof(T) >= (1LL << 31) || 2 * EV * plane * sizeof(T) >= (1LL << 31) ||
+      (long long)a.HoWo * a.Wo >= (1LL << 32) || plane * a.W >= (1LL << 32)) return NF_EUNSUPPORTED;
+  a.PW = std::max(a.W + a.pad, (a.Wo - 1) * a.stride + 3);
+  auto rcp = [](int d, unsigned* r, unsigned* one) {
+    *r = d == 1 ? 0u : (unsigned)(((1ULL << 32) + d - 1) / d);
+    *one = d == 1 ? ~0u : 0u;
+  };
+  rcp(a.W, &a.rcp_w, &a.one_w);
+  rcp(a.Wo, &a.rcp_wo, &a.one_wo);
+  int kg = wave_shares(sizeof(T) == 4, a.cig, a.cog, a.g, a.HoWo, a.stride), forced = 0;
+  if (const char* e = dev_getenv("NETFUSE_CW")) sscanf(e, "%d,%d", &kg, &forced);
+  if (kg == 0) return NF_EUNSUPPORTED;
+  constexpr int kBlocks[] = {1, 2, 3, 4, 5, 7};
+  WaveTile best{};
+  int nb = 0;
+  float best_us = 0.f;
+  for (int b : kBlocks) {
+    if (forced > 0 ? b != forced : kg == 1 && (b == 3 || b == 5)) continue;
+    const WaveTile t = wave_tile(a, Ho, b, kg);
+    if (t.nt == 0) continue;
+    const float us = wave_us(a, t, b, kg, B);
+    if (nb == 0 || us < best_us) { nb = b; best = t; best_us = us; }
+  }
+#define NF_CWT(NB_, KG_) if (kg == KG_ && nb == NB_) return launch_tile<T, NB_, KG_>(best, a, B, s)
+  NF_CWT(1, 4); NF_CWT(2, 4); NF_CWT(3, 4); NF_CWT(4, 4); NF_CWT(5, 4); NF_CWT(7, 4);
+  NF_CWT(1, 1); NF_CWT(2, 1); NF_CWT(4, 1); NF_CWT(7, 1);
+#undef NF_CWT
+  return NF_EUNSUPPORTED;
+}
+
+template nf_status launch_conv_wave<bf16_t>(ConvWaveArgs<bf16_t>&, int, int, hipStream_t);
+template nf_status launch_conv_wave<float>(ConvWaveArgs<float>&, int, int, hipStream_t);
+
+}  // namespace nf

@@ -25,9 +25,10 @@
 // bits must not, so CH follows from K alone; the tiles differ in how many groups of wavefronts the chains are dealt to.
 //
 // Measured (8 models, us; the plain FMA kernels before -> this): 128 x 768 x 3072 matmul 187 -> 45 (31.6 at the fp32
-// matrix peak), 128 x 3072 x 768 750 -> 52, 3x3 convolution 256 -> 256 at 14 x 14 570 -> 40, 512 -> 512 at 7 x 7 1060
-// -> 54, pointwise 64 -> 256 at 56 x 56 460 -> 17; a 12-layer encoder 16.3 -> 3.2 ms, ResNet-50 29.9 -> 1.4 ms.  Narrow groups
-// and few k over many rows stay with the FMA kernels (netfuse_api.hip).
+// matrix peak), 128 x 3072 x 768 750 -> 52, pointwise 64 -> 256 at 56 x 56 460 -> 17; a 12-layer encoder 16.3 -> 3.2 ms.
+// Of the convolutions it runs the pointwise ones, k x k but 3 x 3, and 3 x 3 over wide planes at stride 2 or groups that are no
+// multiple of 8 channels; the other 3 x 3 ones are conv_wave.h's.  Narrow groups and few k over many rows stay with the FMA
+// kernels (netfuse_api.hip).
 #pragma once
 #include "gemm_launch.h"
 

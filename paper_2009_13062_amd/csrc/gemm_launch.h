@@ -101,6 +101,9 @@ struct ConvPatchArgs;
 nf_status launch_conv_patch_3x3(ConvPatchArgs& a, int B, hipStream_t s);
 // the same layers through the tap-major kernel (conv_tap.h) where it applies; NF_EUNSUPPORTED = it does not
 nf_status launch_conv_tap_3x3(ConvPatchArgs& a, int B, hipStream_t s);
+// 3x3 convolution with wavefront-private pipelines (conv_wave.h), bf16 and float32; NF_EUNSUPPORTED = take another kernel
+template <typename T> struct ConvWaveArgs;
+template <typename T> nf_status launch_conv_wave(ConvWaveArgs<T>& a, int Ho, int B, hipStream_t s);
 struct ConvStemArgs;
 // 7x7 / stride 2 / pad 3 over 3 input channels per group (conv_stem.h)
 nf_status launch_conv_stem(ConvStemArgs& a, int B, hipStream_t s);

@@ -15,6 +15,7 @@
 #include "attention_kernels.h"
 #include "conv_patch.h"
 #include "conv_stem.h"
+#include "conv_wave.h"
 #include "gemm_launch.h"
 #include "gemm_mfma.h"
 #include "generic_kernels.h"
@@ -251,6 +252,21 @@ void f32_divisors(GemmF32Args& a) {
   };
   rcp(a.khw, &a.rcp_khw, &a.one_khw);
   rcp(a.KW, &a.rcp_kw, &a.one_kw);
+}
+
+// 3x3 through the wavefront-private pipelines of conv_wave.h, or NF_EUNSUPPORTED.
+template <typename T>
+nf_status conv_wave(const void* x, const void* w, const void* residual, void* y, const Epilogue& ep, int M, int B, int Cin, int Cout,
+                    int g, int H, int W, int Ho, int Wo, int stride, int pad, hipStream_t s) {
+  ConvWaveArgs<T> c;
+  memset(&c, 0, sizeof(c));
+  c.x = (const T*)x; c.w = (const T*)w; c.R = (const T*)residual; c.y = (T*)y;
+  c.cig = Cin / g; c.cog = Cout / g; c.g = g; c.nG = M * g;
+  c.H = H; c.W = W; c.Wo = Wo; c.HoWo = Ho * Wo; c.stride = stride; c.pad = pad;
+  c.x_group = (long)c.cig * H * W; c.x_image = (long)M * Cin * H * W;
+  c.y_group = (long)c.cog * c.HoWo; c.y_image = (long)M * Cout * c.HoWo;
+  c.ep = ep;
+  return launch_conv_wave(c, Ho, B, s);
 }
 
 // largest alignment (16, 8, 4 or 2 bytes) shared by a pointer and a row pitch / stride set
@@ -692,6 +708,10 @@ nf_status netfuse_conv2d(const void* x, const void* w, const float* bias, const 
       const nf_status st = launch_conv_stem(c, B, s);
       if (st != NF_EUNSUPPORTED) return st;
     }
+    if (KH == 3 && KW == 3 && dilation == 1) {
+      const nf_status st = conv_wave<bf16_t>(x, w, residual, y, a.ep, M, B, Cin, Cout, g, H, W, (int)Ho, (int)Wo, stride, pad, s);
+      if (st != NF_EUNSUPPORTED) return st;
+    }
     // patch geometry (conv_patch.h): image column ix sits at patch column ix + 8; rows are copied in
     // chunks of VW pixels; a 128-position tile touches at most `span` output rows
     const int VW = W % 8 == 0 ? 8 : (W % 4 == 0 ? 4 : (W % 2 == 0 ? 2 : 1));
@@ -779,6 +799,10 @@ nf_status netfuse_conv2d(const void* x, const void* w, const float* bias, const 
     a.ep.vec_store = HoWo % 4 == 0 && aligned(y, 16) && aligned(residual, 16) ? 2 : 0;
     a.H = H; a.W = W; a.KW = KW; a.khw = KH * KW; a.Wo = (int)Wo; a.stride = stride; a.pad = pad; a.dil = dilation;
     f32_divisors(a);
+    if (KH == 3 && KW == 3 && dilation == 1) {
+      const nf_status st = conv_wave<float>(x, w, residual, y, a.ep, M, B, Cin, Cout, g, H, W, (int)Ho, (int)Wo, stride, pad, s);
+      if (st != NF_EUNSUPPORTED) return st;
+    }
     const nf_status st = launch_gemm_f32(a, B, !f32_dense, s);
     if (st != NF_EUNSUPPORTED) return st;               // more tiles than a grid holds: the direct kernel strides over any number
   }
