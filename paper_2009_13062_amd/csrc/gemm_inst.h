@@ -58,6 +58,16 @@ void gemm_mfma_kernel(GemmArgs a) {
         return;
       }
     }
+    if constexpr (BKIND == 2 && Cfg::kDepth > 1 && ALIGN_A == 16) {
+      if (a.K % (kBK * Cfg::kDepth) == 0 && (long)a.geom.H * a.geom.W < 1L << 26) {   // a k-step's offsets in 32 bits
+        ADeepLoader<Cfg::kBM, Cfg::kThreads> la;
+        la.init(Abase, a.lda, rows_left, threadIdx.x);
+        BStridedDeepLoader<Cfg::kBN, Cfg::kThreads> lb;
+        lb.init(Bbase, a.geom, col0, cols_left, threadIdx.x);
+        gemm_tile<Cfg, true>(la, lb, a.K, smem, C, R, a.ldc, rows_left, cols_left, a.ep, rvo, cvo);
+        return;
+      }
+    }
     ATileLoader<Cfg::kBM, ALIGN_A, false, Cfg::kThreads> la;
     la.base = Abase; la.lda = a.lda; la.rows_left = rows_left; la.K = a.K;
     using Pairs = BStride2PairLoader<Cfg::kBN, BKIND == 24 ? 4 : 2, Cfg::kThreads>;
@@ -135,7 +145,7 @@ nf_status launch_gemm(GemmLaunch& L, hipStream_t s) {
 template <int ALIGN_A, int BKIND>
 nf_status launch_gemm_tile(int tile, GemmLaunch& L, hipStream_t s) {
   // depth of the load pipeline for the B kinds with branch-free loaders (the others keep one step in flight)
-  constexpr bool kDense = BKIND == 8 || BKIND == 1 || BKIND == 21 || BKIND == 22 || BKIND == 24 || BKIND == 27;
+  constexpr bool kDense = BKIND == 8 || BKIND == 1 || BKIND == 2 || BKIND == 21 || BKIND == 22 || BKIND == 24 || BKIND == 27;
   constexpr int D2 = kDense ? 2 : 1, D4 = kDense ? 4 : 1;
   switch (tile) {
     case T64x64: return launch_gemm<TileCfg<64, 64, 2, 2, D4>, ALIGN_A, BKIND>(L, s);

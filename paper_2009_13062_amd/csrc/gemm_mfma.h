@@ -528,6 +528,58 @@ struct BPairDeepLoader {
   __device__ __forceinline__ void finish(lds_bf16_t*, int) const {}
 };
 
+// Branch-free B loader of a strided pointwise convolution over an image of any size, for the deep pipeline: one 2-byte load per
+// output position, at an offset fixed at init; positions past the end of the image are redirected to the last one.
+// Against the loader above, whose predicated loads leave one k-step in flight and wait for all of it (us, 3 models of 4 images):
+// 1024 -> 2048 at 13 x 13 -> 7 x 7 45.1 -> 35.2, 512 -> 1024 at 25 x 25 -> 13 x 13 32.7 -> 29.0.  Planes
+// of fewer than 2^26 positions.
+template <int BN, int NT>
+struct BStridedDeepLoader {
+  static constexpr int kPitch = BN + kPadB;
+  static constexpr int kPerRow = BN / 8;
+  static constexpr int kTasks = kBK * kPerRow;
+  static constexpr int kPer = kTasks / NT;
+  static_assert(kTasks % NT == 0, "tile too small for the workgroup");
+  const char* planes;                    // first input plane of this group and image
+  unsigned off[kPer][8];                 // byte offsets at k = 0
+  long step;                             // bytes per k-step
+  struct Regs { uint16_t v[kPer][8]; };
+  __device__ __forceinline__ void init(const bf16_t* xg, const Im2colGeom& g, int col0, int cols_left, int tid) {
+    planes = reinterpret_cast<const char*>(xg);
+    const int plane = g.H * g.W;
+    step = (long)kBK * plane * 2;
+#pragma unroll
+    for (int t = 0; t < kPer; ++t) {
+      const int task = tid + t * NT;
+      const int krow = task / kPerRow, p = min(col0 + (task % kPerRow) * 8, col0 + cols_left - 1);
+      int oy = p / g.Wo, ox = p - oy * g.Wo;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        off[t][e] = (unsigned)(krow * plane + (oy * g.W + ox) * g.stride) * 2u;
+        if (p + e + 1 < col0 + cols_left && ++ox == g.Wo) { ox = 0; ++oy; }
+      }
+    }
+  }
+  __device__ __forceinline__ void fetch(Regs& regs, int k0, int) const {
+    const char* base = planes + (long)(k0 / kBK) * step;
+#pragma unroll
+    for (int t = 0; t < kPer; ++t)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) regs.v[t][e] = *reinterpret_cast<const uint16_t*>(base + off[t][e]);
+  }
+  __device__ __forceinline__ void commit(const Regs& regs, lds_bf16_t* lds, int tid) const {
+#pragma unroll
+    for (int t = 0; t < kPer; ++t) {
+      const int task = tid + t * NT;
+      uint32_t o[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) o[q] = (uint32_t)regs.v[t][2 * q] | (uint32_t)regs.v[t][2 * q + 1] << 16;
+      lds_store16(lds + (task / kPerRow) * kPitch + (task % kPerRow) * 8, make_uint4(o[0], o[1], o[2], o[3]));
+    }
+  }
+  __device__ __forceinline__ void finish(lds_bf16_t*, int) const {}
+};
+
 // The same for 7 output columns (a 14-wide input: the last projection shortcut of a 224 x 224 ResNet), where
 // groups of 8 consecutive output positions would straddle rows and every position would cost its own load:
 // task = one (k row, output row): the 7 pixel pairs of input row 2 oy are contiguous (28 bytes at an 8-byte

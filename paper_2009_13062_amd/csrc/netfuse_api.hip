@@ -771,6 +771,14 @@ nf_status netfuse_conv2d(const void* x, const void* w, const float* bias, const 
         else if (Wo == 7 && Ho <= 8 && plane % 4 == 0 && aligned(x, 8)) bkind = 27;
         else if (aligned(x, 4)) bkind = 21;
       }
+      if (bkind == 2 && forced_tile() < 0) {
+        // Eight 2-byte loads per 16 bytes of activations weigh more than a compute unit or two left idle: from 160 tiles of 128 x 128
+        // up (3 models of 4 images 512 -> 1024 at 25 x 25: 37.8 us in 64 x 64 tiles, 29.0), but not where they fill a few
+        // compute units only (2 models of one image 1024 -> 2048 at 13 x 13: 33.4 us in 32 of them, 26.5 in 64 x 64).
+        const long long t128 = problems * ((cog + 127) / 128) * ((HoWo + 127) / 128);
+        if (cog > 64 && HoWo > 64 && t128 >= 160) tile = T128x128w8;
+        else if (HoWo <= 64 && tile == T128x128w8 && t128 < 64) tile = T64x64;
+      }
     }
     return launch_gemm_any(bkind, al, tile, L, s);
   }
