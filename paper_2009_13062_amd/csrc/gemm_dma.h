@@ -75,6 +75,14 @@ struct DmaCfg {
   static constexpr int kBSwz = kBNatural ? 0 : 4;
 };
 
+// Direct-to-LDS loads of gemm_ring.h go through a buffer resource over the operand: the global form counts as an access to
+// memory AND LDS for the compiler, which then waits for every LDS read in flight wherever it waits for one (12 models of 279
+// rows, 128 x 384 tile 28.9 -> 26.4 us at 768 -> 2304, 288 x 128 tile 24.1 -> 22.8; the kernels that read all of a stage's fragments
+// in front of its multiplications did not change).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t lds_rsrc(const void* base, unsigned bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)bytes, 0x00020000);
+}
+
 // s_waitcnt with only the vector-memory counter constrained (gfx9 encoding: vmcnt in bits 3:0 and
 // 15:14, expcnt 6:4 and lgkmcnt 11:8 left at their "don't wait" maxima).
 template <int N>

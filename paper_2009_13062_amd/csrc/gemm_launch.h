@@ -67,7 +67,8 @@ nf_status launch_pack_fragments(const bf16_t* W, bf16_t* Wp, long long problems,
 
 // Ragged rows and columns, row-major or packed weights (gemm_ring.h); `tile` is a RingTileId or a RingPackedTileId.
 // NF_EUNSUPPORTED if an operand is not 16-byte aligned, or 2 GB or more per problem.
-enum RingTileId { R32x32 = 0, R64x64, R64x128, R96x128, R96x256, R128x128, R128x256, R128x384, R256x256, kNumRingTiles };
+enum RingTileId { R32x32 = 0, R64x64, R64x128, R96x128, R96x256, R128x128, R128x256, R128x384, R256x256, R64x256, R160x256,
+                  R192x192, R288x128, kNumRingTiles };
 enum RingPackedTileId { RP32x32 = 0, RP64x64, RP128x64, RP128x128, RP128x256, RP256x256, kNumRingPackedTiles };
 inline bool ring_fits(int cols, int K) { return cols % 8 == 0 && K % 64 == 0 && K >= 256; }     // shorter k: not measured
 nf_status launch_gemm_ring(int tile, bool packed, GemmLaunch& L, hipStream_t s);

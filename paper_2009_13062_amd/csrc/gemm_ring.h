@@ -151,9 +151,22 @@ __device__ __forceinline__ void gemm_ring_tile(const bf16_t* __restrict__ A, lon
       voff[t] = (unsigned)((long)kr * ldb + min(col0 + c * 8, cols - 8)) * 2u;
     }
   }
-  const long inc_a = (long)KG * BK * 2, inc_b = PB ? (long)KG * (BK / 16) * 1024 : (long)KG * BK * ldb * 2;
-  const char* pa = (const char*)A + (long)q * BK * 2;
-  const char* pb = (const char*)B + (PB ? (long)q * (BK / 16) * 1024 : (long)q * BK * ldb * 2);
+  // k position of the next stage in A and B (bytes, uniform; an operand is smaller than 2 GB)
+  const unsigned inc_a = KG * BK * 2, inc_b = PB ? KG * (BK / 16) * 1024 : KG * BK * (unsigned)ldb * 2;
+  unsigned pa = (unsigned)q * BK * 2, pb = PB ? (unsigned)q * (BK / 16) * 1024 : (unsigned)q * BK * (unsigned)ldb * 2;
+  // Loads through a buffer resource where a slice is more than one multiplication (see lds_rsrc): they let the multiplications of a
+  // slice start while the next slice's reads are under way.
+  constexpr bool kBuf = FM * FN > 1;
+  const auto ra = lds_rsrc(A, (unsigned)((long)rows * lda * 2)), rb = lds_rsrc(B, (unsigned)((long)K * (PB ? cols : ldb) * 2));
+  auto load = [&](bool weights, unsigned off, lds_u8_t* dst) {
+    if constexpr (kBuf) {
+      if (weights) __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, dst, 16, off, pb, 0, CONV ? 0 : kWeightCpol);
+      else __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, dst, 16, off, pa, 0, 0);
+    } else {
+      if (weights) __builtin_amdgcn_global_load_lds((glb_u8_t*)((const char*)B + pb + off), dst, 16, 0, CONV ? 0 : kWeightCpol);
+      else __builtin_amdgcn_global_load_lds((glb_u8_t*)((const char*)A + pa + off), dst, 16, 0, 0);
+    }
+  };
   const bool extra = Cfg::kRem == 0 || w < Cfg::kRem;
   auto issue_stage = [&](int slot) {
     lds_u8_t* stage = ring + slot * Cfg::kStage;
@@ -161,10 +174,7 @@ __device__ __forceinline__ void gemm_ring_tile(const bf16_t* __restrict__ A, lon
     for (int t = 0; t < Cfg::kMaxPer; ++t) {
       if (t + 1 < Cfg::kMaxPer || extra) {
         // activations keep the default cache policy, weights (read once per forward pass) are non-temporal
-        if (t * NW + w < Cfg::kABlocks)
-          __builtin_amdgcn_global_load_lds((glb_u8_t*)(pa + voff[t]), stage + (t * NW + w) * 1024, 16, 0, 0);
-        else
-          __builtin_amdgcn_global_load_lds((glb_u8_t*)(pb + voff[t]), stage + (t * NW + w) * 1024, 16, 0, CONV ? 0 : kWeightCpol);
+        load(t * NW + w >= Cfg::kABlocks, voff[t], stage + (t * NW + w) * 1024);
       }
     }
     pa += inc_a;

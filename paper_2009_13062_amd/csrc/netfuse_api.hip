@@ -208,15 +208,34 @@ float tile_us(const TileCost& t, int N, int Nout, int K, long long M) {
 constexpr TileCost kRegCost[kNumTiles] = {{64, 64, 3.77f, 0.48f}, {32, 128, 5.08f, 0.15f}, {128, 128, 6.69f, 3.04f}};
 constexpr TileCost kDmaCost[kNumDmaTiles] = {{256, 256, 20.1f, 10.7f}, {128, 128, 9.4f, 4.3f}, {128, 128, 8.8f, 0.f},
                                              {128, 384, 13.8f, 18.1f}, {128, 288, 17.0f, 5.0f}, {128, 96, 8.0f, 2.0f}};
-constexpr TileCost kRingCost[kNumRingTiles] = {{32, 32, 2.38f, 0.74f}, {64, 64, 3.61f, 0.43f}, {64, 128, 5.18f, 1.51f},
+constexpr TileCost kRingCost[R256x256 + 1] = {{32, 32, 2.38f, 0.74f}, {64, 64, 3.61f, 0.43f}, {64, 128, 5.18f, 1.51f},
                                                {96, 128, 6.10f, 1.51f}, {96, 256, 9.95f, 2.07f}, {128, 128, 6.89f, 1.53f},
                                                {128, 256, 11.6f, 2.83f}, {128, 384, 16.2f, 4.24f}, {256, 256, 19.0f, 4.30f}};
+// More than 128 rows, where row tiles share the weights: every ring tile, those between the powers of two too.  Workgroups partly
+// share a compute unit, so a us of launch, per 768 of k b us for every round begun and c us for every round's worth of tiles,
+// e us of prologue and epilogue per round.  Fitted to every tile over 792 problems (an encoder layer's four matmuls at hidden
+// sizes 256, 768 and 1024, 1 ... 32 models of 17 ... 1024 rows): mean error 5 to 10 %.  Over another 1104 problems (other
+// counts and rows) it and the four tiles take 4 % off where there are more than 128 rows (8 % at 279: 24 models 4096 -> 1024
+// 117 -> 74, 12 models 768 -> 2304 30.4 -> 22.6 us; 16 of 760 rows 3072 -> 768 90 -> 61 us; at 256 of k 1 %, from 0.8 to
+// 1.1 of the time), but with fewer they give nothing on average and 16 models of 128 rows 1024 -> 3072 took 32 in place of 26 us.
+struct RingCost { int bm, bn; float a, b, e, c; };
+float tile_us(const RingCost& t, int N, int Nout, int K, long long M) {
+  const long long tiles = M * ((N + t.bm - 1) / t.bm) * ((Nout + t.bn - 1) / t.bn);
+  const float n = (float)((tiles + 255) / 256), f = std::max(1.f, (float)tiles / 256), k = (float)K / 768.0f;
+  return t.a + k * (t.b * n + t.c * f) + t.e * n;
+}
+constexpr RingCost kRingTallCost[kNumRingTiles] = {
+    {32, 32, 4.05f, 1.45f, 0.61f, 1.26f},  {64, 64, 3.59f, 2.79f, 0.75f, 0.99f},  {64, 128, 1.27f, 3.79f, 3.81f, 1.48f},
+    {96, 128, 1.47f, 4.92f, 3.95f, 0.98f}, {96, 256, 0.41f, 8.02f, 6.29f, 1.10f}, {128, 128, 1.03f, 5.24f, 4.74f, 1.22f},
+    {128, 256, 0.f, 9.10f, 7.74f, 0.83f},  {128, 384, 0.f, 12.9f, 8.44f, 2.97f},  {256, 256, 0.f, 13.9f, 9.96f, 3.05f},
+    {64, 256, 1.34f, 7.19f, 4.32f, 1.30f}, {160, 256, 0.f, 10.9f, 8.38f, 2.21f},  {192, 192, 0.f, 9.38f, 7.73f, 0.53f},
+    {288, 128, 0.f, 8.98f, 7.48f, 1.08f}};
 constexpr TileCost kRingPackedCost[kNumRingPackedTiles] = {{32, 32, 1.42f, 1.42f}, {64, 64, 3.35f, 1.60f}, {128, 64, 4.60f, 2.07f},
                                                            {128, 128, 7.14f, 2.69f}, {128, 256, 11.0f, 2.96f}, {256, 256, 18.6f, 4.12f}};
 
 // The gemm_ring.h tile that is predicted to take less than `limit` us, or -1.
-template <int N_TILES>
-int pick_ring(const TileCost (&cost)[N_TILES], int N, int Nout, int K, long long M, float limit) {
+template <class Cost, int N_TILES>
+int pick_ring(const Cost (&cost)[N_TILES], int N, int Nout, int K, long long M, float limit) {
   int best = -1;
   for (int t = 0; t < N_TILES; ++t) {
     const float us = tile_us(cost[t], N, Nout, K, M);
@@ -372,7 +391,7 @@ nf_status netfuse_linear(const void* X, const void* W, const float* bias, const 
         // With one row tile nothing shares the weights of a 128 x 384 tile, whole-tile or ring, and the model, fitted to both,
         // is too low for the ring one: 24, 32 and 48 models of 128 rows 768 -> 3072 32.2, 35.0, 59.4 us as before, 34.0, 36.5, 61.3 there.
         const float margin = d < 0 ? 1.0f : N == 128 && kDmaBN[d] == 384 ? 0.65f : 0.93f;
-        const int r = pick_ring(kRingCost, N, Nout, K, M, margin * now);
+        const int r = N > 128 ? pick_ring(kRingTallCost, N, Nout, K, M, margin * now) : pick_ring(kRingCost, N, Nout, K, M, margin * now);
         if (r >= 0) {
           const nf_status st = launch_gemm_ring(r, false, L, s);
           if (st != NF_EUNSUPPORTED) return st;

@@ -65,3 +65,29 @@ def test_merged_equals_single(oracle):
         one = nf.linear(X[31:], W[31:])
         for M in (2, 5, 12, 32):
             assert torch.equal(nf.linear(X[32 - M:], W[32 - M:])[M - 1], one[0]), (M, N, K, Nout)
+
+
+# more than 128 rows: 64 x 256, 160 x 256, 192 x 192, 288 x 128 (five and seven steps of 64 as well as four), then the others
+TALL = [(24, 129, 256, 656), (24, 129, 448, 656), (48, 300, 256, 392), (48, 300, 320, 392), (48, 300, 256, 264), (48, 300, 448, 264),
+        (48, 199, 256, 328), (48, 577, 320, 120), (32, 129, 320, 136), (16, 129, 256, 656), (48, 129, 256, 328), (48, 199, 256, 136),
+        (48, 415, 256, 264), (48, 344, 256, 392)]
+
+
+@pytest.mark.parametrize("act", [0, 1])
+@pytest.mark.parametrize("shape", TALL)
+def test_tall_exact(oracle, shape, act):
+    got, ref = run(oracle, shape, False, act)
+    assert np.array_equal(got, ref)
+
+
+@pytest.mark.parametrize("shape", [(48, 300, 256, 392), (48, 300, 320, 264), (48, 199, 256, 328), (24, 129, 256, 656)])
+def test_tall_one_model(shape):
+    """Random values: a model's bits are those it has alone, in whatever tile."""
+    import paper_2009_13062_amd as nf
+    M, N, K, Nout = shape
+    torch.manual_seed(N + K)
+    X, W = torch.randn(M, N, K, device="cuda").bfloat16(), torch.randn(M, K, Nout, device="cuda").bfloat16()
+    b = torch.randn(M, Nout, device="cuda")
+    Y = nf.linear(X, W, bias=b, act=2)
+    for m in (0, M - 1):
+        assert torch.equal(Y[m:m + 1], nf.linear(X[m:m + 1].clone(), W[m:m + 1].clone(), bias=b[m:m + 1].clone(), act=2))
