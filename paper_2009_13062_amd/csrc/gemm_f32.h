@@ -327,10 +327,13 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void gemm_f32_kernel(GemmF32Args 
       if (col >= a.cols) continue;
       const long o = cz + (long)row * a.ldc + col;
       f32x4_t v = acc[i][j];
-      const bool whole = ep.vec_store == 2;                  // rows of whole, 16-byte aligned 4-column pieces
+      // 4 columns in one access, 4-byte aligned, but for the columns behind a row's last four (one by one, us:
+      // pointwise 64 -> 256 with residual, 64 images at 49 x 49 182 -> 127; 32 models of 384 rows 64 -> 1001 52 -> 36).
+      struct __attribute__((packed, aligned(4))) any16 { f32x4_t v; };
+      const bool whole = col + 4 <= a.cols;
       f32x4_t res = f32x4_t{0.f, 0.f, 0.f, 0.f}, bias = res;
       if (whole) {
-        if (a.R) res = *reinterpret_cast<const f32x4_t*>(a.R + o);
+        if (a.R) res = reinterpret_cast<const any16*>(a.R + o)->v;
       } else if (a.R) {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
@@ -348,7 +351,7 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void gemm_f32_kernel(GemmF32Args 
         v[e] = ep.act_before_residual ? apply_act(x, ep.act) + res[e] : apply_act(x + res[e], ep.act);
       }
       if (whole) {
-        *reinterpret_cast<f32x4_t*>(a.C + o) = v;
+        reinterpret_cast<any16*>(a.C + o)->v = v;
       } else {
 #pragma unroll
         for (int e = 0; e < 4; ++e)

@@ -66,7 +66,7 @@ struct Epilogue {
   int act_before_residual;  // matmul: act(.) + residual;  convolution: act(. + residual)
   int vec_store;            // 2: C (and residual) rows are 16-byte aligned and cols % 8 == 0; 1: 8-byte aligned
                             // and cols % 4 == 0 (e.g. 14 x 14 planes); 3: ldc == cols <= 64, so every tile spans
-                            // whole rows, and 32 rows start 16-byte aligned (e.g. 7 x 7 planes); 0: element by element
+                            // whole rows, and 32 rows start 16-byte aligned (e.g. 7 x 7 planes); 0: any
 };
 
 // ------------------------------------------------------------------------------------------
@@ -667,7 +667,11 @@ __device__ __forceinline__ float act_const(float v) {
 
 // ACT1: activation applied to the accumulator side (before the residual), ACT2: after the residual.
 // HALVES: the body for ep.vec_store == 1 (8-byte accesses, each half of an 8-column chunk whole or absent) and
-// == 3 (flat mode, see below); otherwise 16-byte accesses or, for ep.vec_store == 0, single elements.
+// == 3 (flat mode, see below); otherwise 16-byte accesses, for ep.vec_store == 0 at any 2-byte address and with the columns
+// behind a row's last whole chunk one by one.  (Element by element the lanes of a store are 16 bytes apart: eight passes over
+// the same lines, and as many for the residual.  Before -> now, us: pointwise 64 -> 256 with residual, 64 images, at
+// 25 x 25 33.0 -> 17.4, 49 x 49 89.9 -> 42.7 = 3.9 TB/s; 32 models 256 -> 1024 at 9 x 9 15.3 -> 11.1; matmul 32 models of 384 rows
+// 64 -> 770 32.2 -> 14.6.)
 template <class Cfg, int ACT1, int ACT2, bool HALVES>
 __device__ __forceinline__ void gemm_epilogue_act(f32x16_t (&acc)[Cfg::FM][Cfg::FN], lds_f32_t* const Es, bf16_t* C,
                                                   const bf16_t* R, long ldc, int rows_left, int cols_left,
@@ -680,6 +684,9 @@ __device__ __forceinline__ void gemm_epilogue_act(f32x16_t (&acc)[Cfg::FM][Cfg::
   constexpr int kChunksPerRow = Cfg::kBN / 8;
   constexpr int kPassChunks = Cfg::kWGM * 32 * kChunksPerRow;
   constexpr int kPer = (kPassChunks + Cfg::kThreads - 1) / Cfg::kThreads;
+  struct __attribute__((packed, aligned(2))) unaligned16 { uint4 v; };
+  // what is added where there is no residual: -0 in the unaligned form, which leaves every value (and its sign) as it is
+  const uint32_t none = !HALVES && ep.vec_store == 0 && R == nullptr ? 0x80008000u : 0u;
 
   // per-column constants of this lane (4 consecutive columns per 8-column group), fetched once, all
   // loads in flight together
@@ -801,7 +808,7 @@ __device__ __forceinline__ void gemm_epilogue_act(f32x16_t (&acc)[Cfg::FM][Cfg::
       const int row = (prow / 32) * Cfg::WM + i * 32 + (prow % 32);
       live[t] = (kPassChunks % Cfg::kThreads == 0 || c < kPassChunks) && row < rows_left && col < cols_left;
       off[t] = (long)row * ldc + col;
-      rr[t] = make_uint4(0, 0, 0, 0);
+      rr[t] = make_uint4(none, none, none, none);
       if constexpr (HALVES) {
         if (live[t] && R != nullptr) {
           const uint2 lo = *reinterpret_cast<const uint2*>(R + off[t]);
@@ -810,7 +817,8 @@ __device__ __forceinline__ void gemm_epilogue_act(f32x16_t (&acc)[Cfg::FM][Cfg::
           rr[t] = make_uint4(lo.x, lo.y, hi.x, hi.y);
         }
       } else {
-        if (live[t] && R != nullptr && ep.vec_store) rr[t] = *reinterpret_cast<const uint4*>(R + off[t]);
+        if (live[t] && R != nullptr && (ep.vec_store || col + 8 <= cols_left))
+          rr[t] = reinterpret_cast<const unaligned16*>(R + off[t])->v;
       }
     }
 #pragma unroll
@@ -821,7 +829,7 @@ __device__ __forceinline__ void gemm_epilogue_act(f32x16_t (&acc)[Cfg::FM][Cfg::
       const lds_f32_t* src = Es + prow * kEP + col;
       const f32x4v_t v0 = *(const lds_f32x4_t*)src, v1 = *(const lds_f32x4_t*)(src + 4);
       float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
-      if (HALVES || ep.vec_store) {
+      if (HALVES || ep.vec_store || col + 8 <= cols_left) {
         const uint32_t w[4] = {rr[t].x, rr[t].y, rr[t].z, rr[t].w};
         uint32_t o[4];
 #pragma unroll
@@ -834,7 +842,7 @@ __device__ __forceinline__ void gemm_epilogue_act(f32x16_t (&acc)[Cfg::FM][Cfg::
           *reinterpret_cast<uint2*>(C + off[t]) = make_uint2(o[0], o[1]);
           if (col + 4 < cols_left) *reinterpret_cast<uint2*>(C + off[t] + 4) = make_uint2(o[2], o[3]);
         } else {
-          *reinterpret_cast<uint4*>(C + off[t]) = make_uint4(o[0], o[1], o[2], o[3]);
+          reinterpret_cast<unaligned16*>(C + off[t])->v = make_uint4(o[0], o[1], o[2], o[3]);
         }
       } else {
 #pragma unroll

@@ -421,7 +421,6 @@ nf_status netfuse_linear(const void* X, const void* W, const float* bias, const 
     a.rows = N; a.cols = Nout; a.K = K; a.nz0 = M;
     a.ep.col_bias = bias; a.ep.col_vec_stride0 = Nout;
     a.ep.act = act; a.ep.act_before_residual = 1;
-    a.ep.vec_store = Nout % 4 == 0 && aligned(Y, 16) && aligned(residual, 16) ? 2 : 0;
     const bool gather = Nout % 4 != 0;                      // then a weight row is a one-row image of Nout positions
     a.H = 1; a.W = Nout; a.KW = 1; a.khw = 1; a.Wo = Nout; a.stride = 1; a.dil = 1;
     f32_divisors(a);
@@ -823,7 +822,6 @@ nf_status netfuse_conv2d(const void* x, const void* w, const float* bias, const 
     a.rows = cog; a.cols = HoWo; a.K = Kdim; a.nz0 = M * g;
     a.ep.row_bias = bias; a.ep.row_scale = scale; a.ep.row_shift = shift; a.ep.row_vec_stride0 = cog;
     a.ep.act = act;
-    a.ep.vec_store = HoWo % 4 == 0 && aligned(y, 16) && aligned(residual, 16) ? 2 : 0;
     a.H = H; a.W = W; a.KW = KW; a.khw = KH * KW; a.Wo = (int)Wo; a.stride = stride; a.pad = pad; a.dil = dilation;
     f32_divisors(a);
     if (KH == 3 && KW == 3 && dilation == 1) {
