@@ -150,7 +150,11 @@ nf_status launch_gemm_tile(int tile, GemmLaunch& L, hipStream_t s) {
   switch (tile) {
     case T64x64: return launch_gemm<TileCfg<64, 64, 2, 2, D4>, ALIGN_A, BKIND>(L, s);
     case T32x128: return launch_gemm<TileCfg<32, 128, 1, 4, D2>, ALIGN_A, BKIND>(L, s);
-    case T128x128w8: return launch_gemm<TileCfg<128, 128, 2, 4, D2>, ALIGN_A, BKIND>(L, s);
+    case T128x128w8:
+      if constexpr (BKIND == 2) {
+        if (L.one_step) return launch_gemm<TileCfg<128, 128, 2, 4, 1>, ALIGN_A, BKIND>(L, s);
+      }
+      return launch_gemm<TileCfg<128, 128, 2, 4, D2>, ALIGN_A, BKIND>(L, s);
   }
   return NF_EUNSUPPORTED;
 }

@@ -25,6 +25,7 @@ struct GemmLaunch {
   GemmArgs a;
   int nz1;
   int weights_are_a;                       // convolution: A is the weight tensor; matmul (0): B is
+  int one_step;                            // strided pointwise convolution, 128 x 128 tile: one k-step of loads in flight
 };
 
 enum TileId { T64x64 = 0, T32x128, T128x128w8, kNumTiles };
