@@ -11,7 +11,8 @@ pytestmark = pytest.mark.gpu
 CASES = [   # M, B, cin, cout, H, W, stride
     (2, 2, 256, 72, 13, 13, 2), (2, 1, 1024, 264, 13, 13, 2),     # 64 x 64 tiles, fewer than 64 positions
     (32, 2, 256, 520, 13, 13, 2),                                 # 128 x 128 over 49 positions
-    (3, 2, 256, 136, 25, 25, 2), (40, 2, 128, 264, 25, 25, 2),    # 64 x 64 and 128 x 128, more than 64 positions
+    (3, 2, 256, 136, 25, 25, 2), (14, 2, 256, 264, 25, 25, 2),    # 64 x 64 and 128 x 128, more than 64 positions
+    (40, 2, 128, 264, 25, 25, 2), (64, 2, 128, 520, 5, 5, 2), (20, 2, 64, 264, 25, 25, 2),   # 128 x 128, one k-step in flight
     (2, 1, 384, 24, 25, 25, 2), (3, 1, 160, 72, 13, 13, 2),       # up to 32 channels; k of no whole number of pipeline rounds
     (2, 2, 256, 72, 10, 19, 3), (2, 1, 256, 72, 5, 26, 5), (2, 2, 256, 72, 2, 1, 2), (2, 1, 512, 136, 41, 41, 2),
 ]
