@@ -59,10 +59,11 @@ void gemm_mfma_kernel(GemmArgs a) {
       }
     }
     if constexpr (BKIND == 2 && Cfg::kDepth > 1 && ALIGN_A == 16) {
-      if (a.K % (kBK * Cfg::kDepth) == 0 && (long)a.geom.H * a.geom.W < 1L << 26) {   // a k-step's offsets in 32 bits
+      using Deep = BStridedDeepLoader<Cfg::kBN, Cfg::kThreads>;
+      if (a.K % (kBK * Cfg::kDepth) == 0 && Deep::fits(a.geom)) {
         ADeepLoader<Cfg::kBM, Cfg::kThreads> la;
         la.init(Abase, a.lda, rows_left, threadIdx.x);
-        BStridedDeepLoader<Cfg::kBN, Cfg::kThreads> lb;
+        Deep lb;
         lb.init(Bbase, a.geom, col0, cols_left, threadIdx.x);
         gemm_tile<Cfg, true>(la, lb, a.K, smem, C, R, a.ldc, rows_left, cols_left, a.ep, rvo, cvo);
         return;

@@ -532,10 +532,13 @@ struct BPairDeepLoader {
 // Branch-free B loader of a strided pointwise convolution over an image of any size, for the deep pipeline: one 2-byte load per
 // output position, at an offset fixed at init; positions past the end of the image are redirected to the last one.
 // Against the loader above, whose predicated loads leave one k-step in flight and wait for all of it (us, 3 models of 4 images):
-// 1024 -> 2048 at 13 x 13 -> 7 x 7 45.1 -> 35.2, 512 -> 1024 at 25 x 25 -> 13 x 13 32.7 -> 29.0.  Planes
-// of fewer than 2^26 positions.
+// 1024 -> 2048 at 13 x 13 -> 7 x 7 45.1 -> 35.2, 512 -> 1024 at 25 x 25 -> 13 x 13 32.7 -> 29.0.  Planes of up to kMaxPlane
+// positions (fits()): the byte offsets inside a k-step's kBK planes take 32 bits.
 template <int BN, int NT>
 struct BStridedDeepLoader {
+  static constexpr long kMaxPlane = (1L << 32) / (2 * kBK);
+  static_assert(kBK * kMaxPlane * 2 - 1 <= 0xffffffffL, "the last byte offset of a k-step fits 32 bits");
+  static __device__ __forceinline__ bool fits(const Im2colGeom& g) { return (long)g.H * g.W <= kMaxPlane; }
   static constexpr int kPitch = BN + kPadB;
   static constexpr int kPerRow = BN / 8;
   static constexpr int kTasks = kBK * kPerRow;
@@ -547,7 +550,7 @@ struct BStridedDeepLoader {
   struct Regs { uint16_t v[kPer][8]; };
   __device__ __forceinline__ void init(const bf16_t* xg, const Im2colGeom& g, int col0, int cols_left, int tid) {
     planes = reinterpret_cast<const char*>(xg);
-    const int plane = g.H * g.W;
+    const unsigned plane = (unsigned)(g.H * g.W);
     step = (long)kBK * plane * 2;
 #pragma unroll
     for (int t = 0; t < kPer; ++t) {
@@ -556,7 +559,7 @@ struct BStridedDeepLoader {
       int oy = p / g.Wo, ox = p - oy * g.Wo;
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        off[t][e] = (unsigned)(krow * plane + (oy * g.W + ox) * g.stride) * 2u;
+        off[t][e] = ((unsigned)krow * plane + (unsigned)((oy * g.W + ox) * g.stride)) * 2u;
         if (p + e + 1 < col0 + cols_left && ++ox == g.Wo) { ox = 0; ++oy; }
       }
     }

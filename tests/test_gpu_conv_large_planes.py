@@ -1,0 +1,39 @@
+"""Convolutions over planes whose offsets reach the ends of 32 bits: the largest plane a kernel's offsets hold and the next, which
+another one takes.  Integer-coded (every sum exact in float32); positions all over the plane are compared with a
+float32 product of the pixels they read."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def integers(shape, lo, hi, seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    return torch.empty(shape, device="cuda", dtype=torch.bfloat16).random_(lo, hi, generator=g)
+
+
+@pytest.fixture(autouse=True)
+def release():
+    yield
+    torch.cuda.empty_cache()
+
+
+def check_pointwise(cin, cout, H, W, stride, seed):
+    import paper_2009_13062_amd as nf
+    x, w = integers((1, cin, H, W), -2, 3, seed), integers((cout, cin, 1, 1), -1, 2, seed + 1)
+    y = nf.conv2d(x, w, 1, stride=stride)
+    Ho, Wo = y.shape[2:]
+    for oy in sorted({0, Ho // 2, Ho - 1}):
+        ref = w.view(cout, cin).float() @ x[0, :, oy * stride, ::stride].float()
+        assert torch.equal(y[0, :, oy], ref.bfloat16()), oy
+
+
+# 2^25 positions are the most that 64 planes' byte offsets hold: just below, and beyond.  9 x 9 outputs in 128 x 128
+# tiles (160 of them), 7 x 7 in 64 x 64 tiles.
+@pytest.mark.parametrize("cin,cout,H,W,out", [(128, 20480, 5791, 5793, 9), (128, 20480, 6001, 6001, 9), (256, 72, 6001, 6001, 7),
+                                              (256, 72, 5793, 5791, 7), (128, 128, 6001, 6001, 3001)])
+def test_strided_pointwise(cin, cout, H, W, out):
+    assert H % 2 and W % 2 and (H * W <= 2 ** 25) == (H < 6000)
+    stride = -(-max(H, W) // out)
+    check_pointwise(cin, cout, H, W, stride, cin + H)
