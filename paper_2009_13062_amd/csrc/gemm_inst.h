@@ -49,10 +49,11 @@ void gemm_mfma_kernel(GemmArgs a) {
     }
     if constexpr ((BKIND == 21 || BKIND == 22 || BKIND == 24) && Cfg::kDepth > 1 && ALIGN_A == 16) {
       // whole k-step multiples stream through the deep pipeline
-      if (a.K % (kBK * Cfg::kDepth) == 0) {
+      using Deep = BPairDeepLoader<Cfg::kBN, BKIND == 24 ? 4 : (BKIND == 22 ? 2 : 1), Cfg::kThreads>;
+      if (a.K % (kBK * Cfg::kDepth) == 0 && Deep::fits(a.geom)) {
         ADeepLoader<Cfg::kBM, Cfg::kThreads> la;
         la.init(Abase, a.lda, rows_left, threadIdx.x);
-        BPairDeepLoader<Cfg::kBN, BKIND == 24 ? 4 : (BKIND == 22 ? 2 : 1), Cfg::kThreads> lb;
+        Deep lb;
         lb.init(Bbase, a.geom, col0, cols_left, threadIdx.x);
         gemm_tile<Cfg, true>(la, lb, a.K, smem, C, R, a.ldc, rows_left, cols_left, a.ep, rvo, cvo);
         return;

@@ -465,9 +465,10 @@ struct BDeepLoader {
 // deep pipeline: the image is read as (even, odd) pixel pairs (see BStride2PairLoader), VW pairs per load
 // (VW = 4, 2 or 1; VW divides Wo, and plane pitch and base are multiples of 2*VW elements).  The pair
 // offsets of this thread's 8 / VW loads per task are fixed at init; output positions past the end of the
-// image are redirected to the last group of VW.
+// image are redirected to the last group of VW.  Planes for which fits() holds: the pairs of a k-step are counted in an int.
 template <int BN, int VW, int NT>
 struct BPairDeepLoader {
+  static __device__ __forceinline__ bool fits(const Im2colGeom& g) { return (long)kBK * ((long)g.H * g.W / 2) <= 0x7fffffffL; }
   static_assert(VW == 4 || VW == 2 || VW == 1, "pairs per load");
   static constexpr int kPitch = BN + kPadB;
   static constexpr int kPerRow = BN / 8;

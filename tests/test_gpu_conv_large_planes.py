@@ -37,3 +37,12 @@ def test_strided_pointwise(cin, cout, H, W, out):
     assert H % 2 and W % 2 and (H * W <= 2 ** 25) == (H < 6000)
     stride = -(-max(H, W) // out)
     check_pointwise(cin, cout, H, W, stride, cin + H)
+
+
+# Stride 2 over even widths reads pixel pairs, 4, 2 or 1 per load by the output width; 64 planes of fewer than 2^26 positions count
+# their pairs in an int (8190 x 8194 is the last such plane, at four positions less).
+@pytest.mark.parametrize("W", [8192, 8194, 8196, 8198, 8200])
+def test_stride_2_pairs(W):
+    H = 8190
+    assert (H * W < 2 ** 26) == (W <= 8194)
+    check_pointwise(128, 16, H, W, 2, W)
