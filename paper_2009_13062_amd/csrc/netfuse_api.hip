@@ -747,12 +747,14 @@ nf_status netfuse_conv2d(const void* x, const void* w, const float* bias, const 
       S = 32 / cig;
     const int cig_e = S * cig, cog_e = S * cog;               // channels of the (fused) group a workgroup handles
     const long long patch_tasks = (long long)std::min(cig_e, 16) * PHmax * (W / VW);   // chunk copies per channel block
-    const bool patch_ok = KH == 3 && KW == 3 && dilation == 1 && pad <= kLPad && aligned(x, 16) &&
+    // Both kernels below hold offsets inside a block of up to 32 planes, conv_tap.h also inside its up to 128 weight rows, in an int.
+    const bool offsets_fit = 32LL * H * W <= INT_MAX && 128LL * 9 * cig_e <= INT_MAX;
+    const bool patch_ok = offsets_fit && KH == 3 && KW == 3 && dilation == 1 && pad <= kLPad && aligned(x, 16) &&
                           ((S == 1 && cig % 16 == 0 && aligned(w, 16) && patch_tasks <= 12 * 256) ||
                            (S > 1 && 2 * patch_tasks <= 12 * 256));
     // the tap-major kernel (conv_tap.h) checks its own task and LDS bounds
     static const bool no_tap = dev_getenv("NETFUSE_NO_TAP") != nullptr;
-    const bool tap_ok = !no_tap && KH == 3 && KW == 3 && dilation == 1 && pad <= kLPad && cig_e % 32 == 0;
+    const bool tap_ok = !no_tap && offsets_fit && KH == 3 && KW == 3 && dilation == 1 && pad <= kLPad && cig_e % 32 == 0;
     if (!no_patch && (patch_ok || tap_ok)) {
       // k x k: MFMA operands from an LDS copy of the zero-padded input patch (conv_tap.h, conv_patch.h)
       ConvPatchArgs c;

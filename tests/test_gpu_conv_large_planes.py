@@ -46,3 +46,26 @@ def test_stride_2_pairs(W):
     H = 8190
     assert (H * W < 2 ** 26) == (W <= 8194)
     check_pointwise(128, 16, H, W, 2, W)
+
+
+# 3 x 3: 32 planes of up to 2^26 - 1 positions count in an int; groups of 32 k channels, of 16 (2 k + 1) under a wide padding, and
+# narrow ones that share a block.
+@pytest.mark.parametrize("H", [524287, 700000])
+@pytest.mark.parametrize("cin,cout,g,pad", [(32, 40, 1, 1), (48, 8, 1, 3), (32, 32, 4, 1)])
+def test_3x3(H, cin, cout, g, pad):
+    import paper_2009_13062_amd as nf
+    W = 128
+    x, w = integers((1, cin, H, W), -2, 3, H), integers((cout, cin // g, 3, 3), -1, 2, cin)
+    y = nf.conv2d(x, w, 1, g=g, pad=pad)
+    Ho, Wo = y.shape[2:]
+    for oy in (0, Ho // 2 + 1, Ho - 1):
+        # the image rows that output row oy reads, zeros outside
+        rows = torch.zeros(cin, 3, W + 2 * pad, device="cuda")
+        for ky in range(3):
+            iy = oy - pad + ky
+            if 0 <= iy < H:
+                rows[:, ky, pad:pad + W] = x[0, :, iy].float()
+        taps = torch.stack([rows[:, :, kx:kx + Wo] for kx in range(3)], 2)                     # channel, ky, kx, position
+        ref = torch.cat([w[i * cout // g:(i + 1) * cout // g].float().flatten(1) @ taps[i * cin // g:(i + 1) * cin // g].flatten(0, 2)
+                         for i in range(g)])
+        assert torch.equal(y[0, :, oy], ref.bfloat16()), oy
