@@ -18,7 +18,9 @@
 //     pixels.
 //   * multiplication: bf16 one 32x32x16 instruction per tap and block, float32 four 32x32x2 (one per channel of the
 //     vector).  Transposed as everywhere here: a lane ends up with 4 consecutive positions of one output channel.
-// The partial sums meet in LDS and are added pairwise in one order, so a result does not depend on NB.
+// The partial sums meet in LDS and are added pairwise in one order, so a result does not depend on NB.  A float32 wavefront that
+// has a tile to itself keeps two chains (even and odd channels of a vector): with one its sums were rounded 1.35 (8 and 16
+// channels, random signs) to 1.7 times (one sign) as far off as the two chains of gemm_f32.h, which it stands in for.
 //
 // Why: at 14 x 14 and 7 x 7 a workgroup that shares one channel block between its wavefronts (conv_tap.h) has nothing
 // to multiply while the next block arrives and is shuffled into LDS between two barriers (matrix pipe 15 to 20 % busy);
@@ -72,15 +74,17 @@ __device__ __forceinline__ unsigned cw_div(unsigned n, unsigned rcp, unsigned on
 
 // The fragments of tap + ahead are read in front of the instructions of a tap: enough of them to cover an LDS read.
 constexpr int conv_wave_ahead(bool f32, int NB) { return f32 || NB >= 6 ? 1 : NB >= 3 ? 2 : NB == 2 ? 3 : 5; }
+// Chains of a wavefront's sum: two for float32 where no other wavefront shares the tile.
+constexpr int conv_wave_chains(bool f32, int KG) { return f32 && KG == 1 ? 2 : 1; }
 // Wavefronts per SIMD that the registers leave room for: two where that takes no more than a few of them away.
-constexpr int conv_wave_occupancy(bool f32, int NB, int NT) {
-  return 122 + 16 * NB + NT * (f32 ? 6 : 10) + 4 * NB * (conv_wave_ahead(f32, NB) + 1) <= 280 ? 2 : 1;
+constexpr int conv_wave_occupancy(bool f32, int NB, int KG, int NT) {
+  return 122 + 16 * NB * conv_wave_chains(f32, KG) + NT * (f32 ? 6 : 10) + 4 * NB * (conv_wave_ahead(f32, NB) + 1) <= 280 ? 2 : 1;
 }
 
 // NB: blocks of 32 positions.  KG: wavefronts that share a tile's channels.  NT: input tasks per lane and step (the host
 // checks the bound).
 template <typename T, int NB, int KG, int NT>
-__global__ __launch_bounds__(KG * kWave, conv_wave_occupancy(sizeof(T) == 4, NB, NT)) void conv_wave_kernel(ConvWaveArgs<T> a) {
+__global__ __launch_bounds__(KG * kWave, conv_wave_occupancy(sizeof(T) == 4, NB, KG, NT)) void conv_wave_kernel(ConvWaveArgs<T> a) {
   constexpr int EV = ConvWaveType<T>::kEV, PX = ConvWaveType<T>::kPix, CB = 2 * EV;
   constexpr bool F32 = sizeof(T) == 4;
   extern __shared__ __align__(1024) unsigned char smem_raw[];
@@ -166,11 +170,14 @@ __global__ __launch_bounds__(KG * kWave, conv_wave_occupancy(sizeof(T) == 4, NB,
     b_off[j] = ((oy - oy_first) * a.stride * a.PW + ox * a.stride + half * a.PS) * 16;
   }
 
-  f32x16_t acc[NB];
+  constexpr int CH = conv_wave_chains(F32, KG);
+  f32x16_t acc[CH][NB];
 #pragma unroll
-  for (int j = 0; j < NB; ++j)
+  for (int h = 0; h < CH; ++h)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[h][j][r] = 0.f;
 
   // selectors of perm(hi, lo, sel): 16 bits of `lo` (its low or high half) below 16 bits of `hi`
   auto pick = [](int lo_half, int hi_half) -> uint32_t {
@@ -244,9 +251,9 @@ __global__ __launch_bounds__(KG * kWave, conv_wave_occupancy(sizeof(T) == 4, NB,
         for (int j = 0; j < NB; ++j) {
           const cw_u32x4_t& x = bv[tap % (kAhead + 1)][j];
           if constexpr (F32)
-            acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(x[c]), __uint_as_float(wv[9 * c + tap]), acc[j], 0, 0, 0);
+            acc[c % CH][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(x[c]), __uint_as_float(wv[9 * c + tap]), acc[c % CH][j], 0, 0, 0);
           else
-            acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, x), af[tap & 1], acc[j], 0, 0, 0);
+            acc[0][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, x), af[tap & 1], acc[0][j], 0, 0, 0);
         }
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -293,11 +300,13 @@ __global__ __launch_bounds__(KG * kWave, conv_wave_occupancy(sizeof(T) == 4, NB,
   lds_f32_t* const red = (lds_f32_t*)smem_raw;
   if constexpr (KG > 1) __syncthreads();
 #pragma unroll
-  for (int j = 0; j < NB; ++j)
+  for (int j = 0; j < NB; ++j) {
+    if constexpr (CH == 2) acc[0][j] += acc[1][j];
 #pragma unroll
     for (int r4 = 0; r4 < 4; ++r4)
       *(lds_f32x4_t*)(red + q * kPart + l32 * kPitch + j * 32 + r4 * 8 + half * 4) =
-          f32x4v_t{acc[j][4 * r4], acc[j][4 * r4 + 1], acc[j][4 * r4 + 2], acc[j][4 * r4 + 3]};
+          f32x4v_t{acc[0][j][4 * r4], acc[0][j][4 * r4 + 1], acc[0][j][4 * r4 + 2], acc[0][j][4 * r4 + 3]};
+  }
   if constexpr (KG > 1) __syncthreads();
   static_assert(KG == 1 || KG == 4, "one chain, or four added pairwise");
   auto finish = [&](auto act) {

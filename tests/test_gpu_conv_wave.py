@@ -70,3 +70,21 @@ def test_merged_equals_single(dt, C, H, stride):
     for m in (0, M - 1):
         one = nf.conv2d(x[:, m * C:(m + 1) * C].contiguous(), w[m * C:(m + 1) * C], 1, stride=stride, pad=1)
         assert torch.equal(merged[:, m * C:(m + 1) * C], one), m
+
+
+@pytest.mark.parametrize("C,g,H,stride", [(8, 32, 28, 1), (8, 8, 56, 1), (8, 16, 56, 2), (16, 8, 40, 1), (16, 4, 72, 2), (16, 32, 14, 1), (16, 32, 28, 2)])
+def test_f32_narrow_groups_round_as_two_chains(C, g, H, stride):
+    """Groups of 8 and 16 channels, products of one sign: two chains of K / 2 products each (the matrix instruction rounds after
+    either of its two).  Adding n terms of one size one after the other leaves a relative error of c sqrt(n / 3 + 1 / 2), c =
+    0.425 * 2^-24 the root mean square of one rounding over evenly spread logarithms; two independent chains average theirs and
+    add one rounding.  A quarter above that; a single chain is at 1.5 times the bound."""
+    import paper_2009_13062_amd as nf
+    x = np.abs(rng.standard_normal((2, g * C, H, H))).astype(np.float32)
+    w = np.abs(rng.standard_normal((g * C, C, 3, 3))).astype(np.float32)
+    ref = torch.nn.functional.conv2d(torch.from_numpy(x).double(), torch.from_numpy(w).double(), stride=stride, padding=1, groups=g)
+    got = nf.conv2d(dev(x), dev(w), 1, g=g, stride=stride, pad=1).cpu().double()
+    n = 9 * C / 2
+    bound = 1.25 * 0.425 * 2.0 ** -24 * (((n / 3 + 0.5) / 2) + 1) ** 0.5
+    inner = slice(1, -1)                                       # positions that read the whole 3 x 3 window
+    err = ((got - ref) / ref)[:, :, inner, inner].pow(2).mean().sqrt().item()
+    assert err <= bound, (err, bound)
