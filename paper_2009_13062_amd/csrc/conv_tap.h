@@ -33,7 +33,6 @@ namespace nf {
 constexpr int kTapCB = 32;          // input channels per block
 constexpr int kTapPixPitch = 40;    // elements per patch pixel (32 channels + 8)
 
-template <class V> struct __attribute__((packed, aligned(2))) Unaligned { V v; };
 
 template <int BM, int WGM, int WGN, int MINW = 1>
 struct ConvTapCfg {
@@ -168,13 +167,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Cfg::kMinWa
         const bf16_t* p = xc + g_off[u] + c * plane;
         // rows and chunks start at any 2-byte address
         if constexpr (VW == 8) {
-          const uint4 v = reinterpret_cast<const Unaligned<uint4>*>(p)->v;
+          const u32x4_t v = load_unaligned<u32x4_t, 2>(p);
           pv[u][c][0] = v.x; pv[u][c][1] = v.y; pv[u][c][2] = v.z; pv[u][c][3] = v.w;
         } else if constexpr (VW == 4) {
-          const uint2 v = reinterpret_cast<const Unaligned<uint2>*>(p)->v;
+          const u32x2_t v = load_unaligned<u32x2_t, 2>(p);
           pv[u][c][0] = v.x; pv[u][c][1] = v.y;
         } else if constexpr (VW == 2) {
-          pv[u][c][0] = reinterpret_cast<const Unaligned<uint32_t>*>(p)->v;
+          pv[u][c][0] = load_unaligned<uint32_t, 2>(p);
         } else {
           pv[u][c][0] = *p;
         }

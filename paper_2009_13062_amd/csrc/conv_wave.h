@@ -66,8 +66,8 @@ inline int conv_wave_lds_bytes(int NB, int KG, int PS) {
 typedef uint32_t cw_u32x4_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) cw_u32x4_t lds_cw_u32x4_t;
 typedef __attribute__((address_space(1))) const cw_u32x4_t glb_cw_u32x4_t;
-template <class V> struct __attribute__((packed, aligned(2))) AnyAlign { V v; };
-typedef __attribute__((address_space(1))) const AnyAlign<uint32_t> glb_any_u32_t;
+typedef __attribute__((address_space(1))) const Unaligned<uint32_t, 2> glb_any_u32_t;
+static_assert(alignof(Unaligned<uint32_t, 2>) == 2);
 
 // n / d, branch free; exact while n < 2^32 / d
 __device__ __forceinline__ unsigned cw_div(unsigned n, unsigned rcp, unsigned one) { return __umulhi(n, rcp) + (n & one); }
@@ -283,7 +283,7 @@ __global__ __launch_bounds__(KG * kWave, conv_wave_occupancy(sizeof(T) == 4, NB,
     live[i] = row < min(rows_left, 32) && c < whole;
     k_it[i] = consts(min(row, rows_left - 1));
     r_it[i] = make_uint4(0u, 0u, 0u, 0u);
-    if (a.R && live[i]) r_it[i] = reinterpret_cast<const AnyAlign<uint4>*>(a.R + out0 + (long)row * a.HoWo + c)->v;
+    if (a.R && live[i]) r_it[i] = ld16_any(a.R + out0 + (long)row * a.HoWo + c);
   }
   constexpr int kTail = (32 * EV + KG * kWave - 1) / (KG * kWave);            // fewer than kEV positions of 32 rows
   Consts t_k[kTail];
@@ -329,9 +329,9 @@ __global__ __launch_bounds__(KG * kWave, conv_wave_occupancy(sizeof(T) == 4, NB,
           store_f32<T>(&out[4 * h + e], act_const<ACT>(fmaf(v + k_it[i].bias, k_it[i].scale, k_it[i].shift) + load_f32<T>(&res[4 * h + e])));
         }
       }
-      AnyAlign<uint4> packed;
+      uint4 packed;
       __builtin_memcpy(&packed, out, 16);
-      *reinterpret_cast<AnyAlign<uint4>*>(a.y + out0 + (long)row * a.HoWo + c) = packed;
+      st16_any(a.y + out0 + (long)row * a.HoWo + c, packed);
     }
 #pragma unroll
     for (int i = 0; i < kTail; ++i) {

@@ -329,11 +329,10 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void gemm_f32_kernel(GemmF32Args 
       f32x4_t v = acc[i][j];
       // 4 columns in one access, 4-byte aligned, but for the columns behind a row's last four (one by one, us:
       // pointwise 64 -> 256 with residual, 64 images at 49 x 49 182 -> 127; 32 models of 384 rows 64 -> 1001 52 -> 36).
-      struct __attribute__((packed, aligned(4))) any16 { f32x4_t v; };
       const bool whole = col + 4 <= a.cols;
       f32x4_t res = f32x4_t{0.f, 0.f, 0.f, 0.f}, bias = res;
       if (whole) {
-        if (a.R) res = reinterpret_cast<const any16*>(a.R + o)->v;
+        if (a.R) res = load_unaligned<f32x4_t, 4>(a.R + o);
       } else if (a.R) {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
@@ -351,7 +350,7 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void gemm_f32_kernel(GemmF32Args 
         v[e] = ep.act_before_residual ? apply_act(x, ep.act) + res[e] : apply_act(x + res[e], ep.act);
       }
       if (whole) {
-        reinterpret_cast<any16*>(a.C + o)->v = v;
+        store_unaligned<f32x4_t, 4>(a.C + o, v);
       } else {
 #pragma unroll
         for (int e = 0; e < 4; ++e)

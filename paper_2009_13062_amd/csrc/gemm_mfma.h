@@ -156,7 +156,6 @@ struct BDenseLoader {
   long ldb;
   int cols_left, K;
   struct Regs { uint32_t v[kPer][kDw]; };
-  struct __attribute__((packed, aligned(2))) unaligned16 { uint4 v; };
 
   __device__ __forceinline__ void fetch(Regs& regs, int k0, int tid) const {
 #pragma unroll
@@ -172,7 +171,7 @@ struct BDenseLoader {
         uint4 v = make_uint4(0, 0, 0, 0);
         if (live) {
           if (p + 8 <= end) {
-            v = reinterpret_cast<const unaligned16*>(p)->v;
+            v = ld16_any(p);
           } else {
             uint32_t h[8];
 #pragma unroll
@@ -408,7 +407,6 @@ struct BDeepLoader {
   const bf16_t* tail_src;               // valid elements of that chunk, or null when the tile does not reach the end
   int tail_n, tail_col;
   struct Regs { uint4 v[kPer]; };
-  struct __attribute__((packed, aligned(2))) unaligned16 { uint4 v; };
   // first column of the last chunk that holds a valid column
   static __device__ __forceinline__ int last_chunk(int cols_left) { return (min(cols_left, BN) - 1) & ~7; }
   // ldb >= 8, K a multiple of kBK; `end` = one past the last element of the whole operand
@@ -437,7 +435,7 @@ struct BDeepLoader {
         regs.v[t] = ld16<WNT>(src[t] + off);
       } else {
         const bf16_t* p = src[t] + off;
-        regs.v[t] = reinterpret_cast<const unaligned16*>(p < limit ? p : limit)->v;
+        regs.v[t] = ld16_any(p < limit ? p : limit);
       }
     }
   }
@@ -692,8 +690,6 @@ __device__ __forceinline__ void gemm_epilogue_act(f32x16_t (&acc)[Cfg::FM][Cfg::
   // The whole-tile matmul kernels (Cfg::kRowConsts == false) meet such rows only where the caller's output is misaligned; the
   // form costs them 1 % (12 layers, 32 models of 512 rows 4471 -> 4516 us), so they keep single elements there.
   constexpr bool kAny = !HALVES && Cfg::kRowConsts;
-  struct __attribute__((packed, aligned(2))) unaligned16 { uint4 v; };
-  using piece = std::conditional_t<kAny, unaligned16, uint4>;
   // what is added where there is no residual: -0 in the unaligned form, which leaves every value (and its sign) as it is
   const uint32_t none = kAny && ep.vec_store == 0 && R == nullptr ? 0x80008000u : 0u;
 
@@ -827,7 +823,7 @@ __device__ __forceinline__ void gemm_epilogue_act(f32x16_t (&acc)[Cfg::FM][Cfg::
         }
       } else {
         if (live[t] && R != nullptr && (ep.vec_store || (kAny && col + 8 <= cols_left)))
-          rr[t] = __builtin_bit_cast(uint4, *reinterpret_cast<const piece*>(R + off[t]));
+          rr[t] = kAny ? ld16_any(R + off[t]) : *reinterpret_cast<const uint4*>(R + off[t]);
       }
     }
 #pragma unroll
@@ -851,7 +847,8 @@ __device__ __forceinline__ void gemm_epilogue_act(f32x16_t (&acc)[Cfg::FM][Cfg::
           *reinterpret_cast<uint2*>(C + off[t]) = make_uint2(o[0], o[1]);
           if (col + 4 < cols_left) *reinterpret_cast<uint2*>(C + off[t] + 4) = make_uint2(o[2], o[3]);
         } else {
-          *reinterpret_cast<piece*>(C + off[t]) = __builtin_bit_cast(piece, make_uint4(o[0], o[1], o[2], o[3]));
+          const uint4 v = make_uint4(o[0], o[1], o[2], o[3]);
+          if constexpr (kAny) st16_any(C + off[t], v); else *reinterpret_cast<uint4*>(C + off[t]) = v;
         }
       } else {
 #pragma unroll
