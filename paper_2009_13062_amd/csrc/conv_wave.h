@@ -69,6 +69,13 @@ typedef __attribute__((address_space(1))) const cw_u32x4_t glb_cw_u32x4_t;
 typedef __attribute__((address_space(1))) const Unaligned<uint32_t, 2> glb_any_u32_t;
 static_assert(alignof(Unaligned<uint32_t, 2>) == 2);
 
+// Lanes of one wavefront exchange values through LDS: the hardware keeps a wavefront's LDS accesses in order, this keeps the compiler
+// from moving one side's accesses past the other's.  No instruction.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // n / d, branch free; exact while n < 2^32 / d
 __device__ __forceinline__ unsigned cw_div(unsigned n, unsigned rcp, unsigned one) { return __umulhi(n, rcp) + (n & one); }
 
@@ -204,7 +211,9 @@ __global__ __launch_bounds__(KG * kWave, conv_wave_occupancy(sizeof(T) == 4, NB,
   // One step: its operands move from registers to LDS, the registers are loaded with the next step's (MORE), and the step is
   // multiplied.  A wavefront's LDS accesses take effect in order, so nothing waits between the writes and the reads.
   auto step = [&](auto more) {
+    wave_lds_order();                                        // the reads of the step before (or the zero fill)
     to_lds();
+    wave_lds_order();
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (decltype(more)::value) {
       load_w();
@@ -298,7 +307,7 @@ __global__ __launch_bounds__(KG * kWave, conv_wave_occupancy(sizeof(T) == 4, NB,
   if (n > 0) step(std::false_type{});
 
   lds_f32_t* const red = (lds_f32_t*)smem_raw;
-  if constexpr (KG > 1) __syncthreads();
+  if constexpr (KG > 1) __syncthreads(); else wave_lds_order();
 #pragma unroll
   for (int j = 0; j < NB; ++j) {
     if constexpr (CH == 2) acc[0][j] += acc[1][j];
@@ -307,7 +316,7 @@ __global__ __launch_bounds__(KG * kWave, conv_wave_occupancy(sizeof(T) == 4, NB,
       *(lds_f32x4_t*)(red + q * kPart + l32 * kPitch + j * 32 + r4 * 8 + half * 4) =
           f32x4v_t{acc[0][j][4 * r4], acc[0][j][4 * r4 + 1], acc[0][j][4 * r4 + 2], acc[0][j][4 * r4 + 3]};
   }
-  if constexpr (KG > 1) __syncthreads();
+  if constexpr (KG > 1) __syncthreads(); else wave_lds_order();
   static_assert(KG == 1 || KG == 4, "one chain, or four added pairwise");
   auto finish = [&](auto act) {
     constexpr int ACT = decltype(act)::value;
