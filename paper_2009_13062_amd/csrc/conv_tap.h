@@ -167,13 +167,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Cfg::kMinWa
         const bf16_t* p = xc + g_off[u] + c * plane;
         // rows and chunks start at any 2-byte address
         if constexpr (VW == 8) {
-          const u32x4_t v = load_unaligned<u32x4_t, 2>(p);
+          const uint4 v = load_at<uint4>(p);
           pv[u][c][0] = v.x; pv[u][c][1] = v.y; pv[u][c][2] = v.z; pv[u][c][3] = v.w;
         } else if constexpr (VW == 4) {
-          const u32x2_t v = load_unaligned<u32x2_t, 2>(p);
+          const uint2 v = load_at<uint2>(p);
           pv[u][c][0] = v.x; pv[u][c][1] = v.y;
         } else if constexpr (VW == 2) {
-          pv[u][c][0] = load_unaligned<uint32_t, 2>(p);
+          pv[u][c][0] = load_at<uint32_t>(p);
         } else {
           pv[u][c][0] = *p;
         }

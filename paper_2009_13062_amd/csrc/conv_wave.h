@@ -66,8 +66,9 @@ inline int conv_wave_lds_bytes(int NB, int KG, int PS) {
 typedef uint32_t cw_u32x4_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) cw_u32x4_t lds_cw_u32x4_t;
 typedef __attribute__((address_space(1))) const cw_u32x4_t glb_cw_u32x4_t;
-typedef __attribute__((address_space(1))) const Unaligned<uint32_t, 2> glb_any_u32_t;
-static_assert(alignof(Unaligned<uint32_t, 2>) == 2);
+struct __attribute__((packed, aligned(2))) AnyU32 { uint32_t v; };
+static_assert(alignof(AnyU32) == 2);
+typedef __attribute__((address_space(1))) const AnyU32 glb_any_u32_t;
 
 // Lanes of one wavefront exchange values through LDS: the hardware keeps a wavefront's LDS accesses in order, this keeps the compiler
 // from moving one side's accesses past the other's.  No instruction.
@@ -292,7 +293,7 @@ __global__ __launch_bounds__(KG * kWave, conv_wave_occupancy(sizeof(T) == 4, NB,
     live[i] = row < min(rows_left, 32) && c < whole;
     k_it[i] = consts(min(row, rows_left - 1));
     r_it[i] = make_uint4(0u, 0u, 0u, 0u);
-    if (a.R && live[i]) r_it[i] = ld16_any(a.R + out0 + (long)row * a.HoWo + c);
+    if (a.R && live[i]) r_it[i] = load_at<uint4>(a.R + out0 + (long)row * a.HoWo + c);
   }
   constexpr int kTail = (32 * EV + KG * kWave - 1) / (KG * kWave);            // fewer than kEV positions of 32 rows
   Consts t_k[kTail];
@@ -340,7 +341,7 @@ __global__ __launch_bounds__(KG * kWave, conv_wave_occupancy(sizeof(T) == 4, NB,
       }
       uint4 packed;
       __builtin_memcpy(&packed, out, 16);
-      st16_any(a.y + out0 + (long)row * a.HoWo + c, packed);
+      store_at(a.y + out0 + (long)row * a.HoWo + c, packed);
     }
 #pragma unroll
     for (int i = 0; i < kTail; ++i) {

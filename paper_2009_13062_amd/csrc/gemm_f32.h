@@ -332,7 +332,7 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void gemm_f32_kernel(GemmF32Args 
       const bool whole = col + 4 <= a.cols;
       f32x4_t res = f32x4_t{0.f, 0.f, 0.f, 0.f}, bias = res;
       if (whole) {
-        if (a.R) res = load_unaligned<f32x4_t, 4>(a.R + o);
+        if (a.R) res = load_at<f32x4_t>(a.R + o);
       } else if (a.R) {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
@@ -350,7 +350,7 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void gemm_f32_kernel(GemmF32Args 
         v[e] = ep.act_before_residual ? apply_act(x, ep.act) + res[e] : apply_act(x + res[e], ep.act);
       }
       if (whole) {
-        store_unaligned<f32x4_t, 4>(a.C + o, v);
+        store_at(a.C + o, v);
       } else {
 #pragma unroll
         for (int e = 0; e < 4; ++e)

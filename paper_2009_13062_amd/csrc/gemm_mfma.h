@@ -171,7 +171,7 @@ struct BDenseLoader {
         uint4 v = make_uint4(0, 0, 0, 0);
         if (live) {
           if (p + 8 <= end) {
-            v = ld16_any(p);
+            v = load_at<uint4>(p);
           } else {
             uint32_t h[8];
 #pragma unroll
@@ -435,7 +435,7 @@ struct BDeepLoader {
         regs.v[t] = ld16<WNT>(src[t] + off);
       } else {
         const bf16_t* p = src[t] + off;
-        regs.v[t] = ld16_any(p < limit ? p : limit);
+        regs.v[t] = load_at<uint4>(p < limit ? p : limit);
       }
     }
   }
@@ -823,7 +823,7 @@ __device__ __forceinline__ void gemm_epilogue_act(f32x16_t (&acc)[Cfg::FM][Cfg::
         }
       } else {
         if (live[t] && R != nullptr && (ep.vec_store || (kAny && col + 8 <= cols_left)))
-          rr[t] = kAny ? ld16_any(R + off[t]) : *reinterpret_cast<const uint4*>(R + off[t]);
+          rr[t] = kAny ? load_at<uint4>(R + off[t]) : *reinterpret_cast<const uint4*>(R + off[t]);
       }
     }
 #pragma unroll
@@ -848,7 +848,7 @@ __device__ __forceinline__ void gemm_epilogue_act(f32x16_t (&acc)[Cfg::FM][Cfg::
           if (col + 4 < cols_left) *reinterpret_cast<uint2*>(C + off[t] + 4) = make_uint2(o[2], o[3]);
         } else {
           const uint4 v = make_uint4(o[0], o[1], o[2], o[3]);
-          if constexpr (kAny) st16_any(C + off[t], v); else *reinterpret_cast<uint4*>(C + off[t]) = v;
+          if constexpr (kAny) store_at(C + off[t], v); else *reinterpret_cast<uint4*>(C + off[t]) = v;
         }
       } else {
 #pragma unroll

@@ -36,20 +36,14 @@ __device__ __forceinline__ uint4 ldnt16(const void* p) {
   return make_uint4(v.x, v.y, v.z, v.w);
 }
 
-// A value at an address that is only A bytes aligned, in one access.  V: a scalar or an ext_vector type.  (On HIP's own vector
-// classes the compiler ignores `packed`: a struct of a uint4 keeps an alignment of 16, which the address would not have.)
-template <class V, int A> struct __attribute__((packed, aligned(A))) Unaligned { V v; };
-template <class V, int A> __device__ __forceinline__ V load_unaligned(const void* p) {
-  static_assert(alignof(Unaligned<V, A>) == A && sizeof(Unaligned<V, A>) == sizeof(V));
-  return static_cast<const Unaligned<V, A>*>(p)->v;
+// A wide value at an address that has the alignment of its element type E only (a row may start at any element), in one access.
+// (Not through a packed struct of a uint4: the compiler ignores `packed` on HIP's vector classes, which keep their 16 bytes.)
+template <class V, class E> __device__ __forceinline__ V load_at(const E* p) {
+  V v;
+  __builtin_memcpy(&v, p, sizeof(V));
+  return v;
 }
-template <class V, int A> __device__ __forceinline__ void store_unaligned(void* p, V v) {
-  static_assert(alignof(Unaligned<V, A>) == A && sizeof(Unaligned<V, A>) == sizeof(V));
-  static_cast<Unaligned<V, A>*>(p)->v = v;
-}
-// 16 bytes at any bf16
-__device__ __forceinline__ uint4 ld16_any(const void* p) { return __builtin_bit_cast(uint4, load_unaligned<nf_u32x4_t, 2>(p)); }
-__device__ __forceinline__ void st16_any(void* p, uint4 v) { store_unaligned<nf_u32x4_t, 2>(p, __builtin_bit_cast(nf_u32x4_t, v)); }
+template <class V, class E> __device__ __forceinline__ void store_at(E* p, const V& v) { __builtin_memcpy(p, &v, sizeof(V)); }
 
 template <typename T> __device__ __forceinline__ float load_f32(const T* p);
 template <> __device__ __forceinline__ float load_f32<float>(const float* p) { return *p; }
