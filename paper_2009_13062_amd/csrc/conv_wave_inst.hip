@@ -1,4 +1,6 @@
 // Instantiation, tile choice and launch of the 3x3 kernels with wavefront-private pipelines (conv_wave.h).
+#include <limits.h>
+
 #include <algorithm>
 #include <atomic>
 #include <cmath>
@@ -83,30 +85,37 @@ static float wave_us(const ConvWaveArgs<T>& a, const WaveTile& t, int NB, int KG
 }
 
 // How many wavefronts share a tile, by the shape of ONE group (never by how many models or images there are: the order of the sum
-// follows from it); 0 = another kernel.
-//   bf16 (conv_tap.h, which multiplies four wavefronts' worth of positions out of one block of 32 channels, is the alternative for
-//   groups of 32 k channels): small planes, where that kernel waits, and many channels.  Times against it, averaged over 1 ...
-//   128 images (and the worst of them, always one of the largest counts):
-//     stride 1: up to 14 x 14 positions 0.61 ... 0.89 (1.16), 512 channels any plane 0.61 ... 0.82 (1.03), 256 channels up to 50 x 50
-//     0.84 ... 0.92 (1.09); left out: 128 channels at 28 x 28 0.96 (1.14), 56 x 56 1.08 (1.39), 64 channels at 56 x 56 1.20
-//     stride 2: up to 28 x 28 positions 0.54 ... 0.90 (1.36); left out: 128 channels at 100 -> 50 1.14 (1.54)
+// follows from it); 0 = another kernel.  A shape is taken where no number of images from 1 to 256 (float32: 1 to 48) is slower for it by more
+// than two runs differ; the one exception, 256 channels at 14 x 14, takes 8 % more from 64 images up and 6 to 44 % less up to 32.
+//   bf16, groups of 32 k channels (conv_tap.h, which multiplies four wavefronts' worth of positions out of one block of 32 channels, is
+//   the alternative): few positions and many channels, where that kernel waits; with many images it is ahead on larger planes, because
+//   a 32-row tile reads a fragment from LDS for every multiplication.  Times against it at 1 / 32 / 256 images:
+//     stride 1: 512 channels 7 x 7 0.43 / 0.77 / 0.78, 28 x 28 0.55 / 0.90 / 0.94; 256 channels 14 x 14 0.56 / 0.94 / 1.08, left out
+//     17 x 17 0.53 / 1.06 / 1.16; 128 channels 11 x 11 0.80 / 0.70 / 0.96, left out 14 x 14 0.76 / 0.87 / 1.23; 64 channels 9 x 9 0.93 /
+//     0.95 / 0.97, left out 14 x 14 1.0 / 1.0 / 1.38; 32 channels 5 x 5 1.0 / 0.84 / 0.86, left out 8 x 8 1.0 / 1.10 / 1.28
+//     stride 2: 512 channels 14 x 14 0.32 / 0.91 / 0.90, left out 18 x 18 0.31 / 1.10 / 1.43; 256 channels 8 x 8 0.50 / 0.62 / 0.66, 13 x 13
+//     0.36 / 0.74 / 0.88, left out 10 x 10 0.47 / 0.81 / 1.14 and 14 x 14 0.40 / 0.94 / 1.19; 128 channels 8 x 8 0.74 / 0.64 / 0.81, left
+//     out 9 x 9 0.65 / 0.81 / 1.33
 //   and against the kernels that take groups of 16 (2 k + 1) channels (conv_patch.h, implicit GEMM): 16 channels on one wavefront
-//   0.64 ... 0.81 (0.92), 48 and 80 channels on four up to 36 x 36 positions 0.47 ... 0.72, on one beyond 0.66 ... 0.97 (1.10).
-//   Groups of 16 in pairs that conv_tap.h fuses: 512 channels at 14 x 14 7.6 against 7.7 us (16 models), 6.4 against 5.0 (2), stride 2
-//   14.6 against 11.6; left out: 256 at 28 x 28 12.8 against 14.8.  Fewer than 32 outputs leave rows idle: 32 -> 16 6.7 against 8.2.
-//   float32 (the gathered kernel of gemm_f32.h): 8 channels on one wavefront 0.60 ... 0.83, others on four 0.45 ... 0.87 (1.02) at
-//   stride 1; stride 2 up to 32 x 32 positions 0.45 ... 0.88 (1.2); left out: 64 channels at 72 -> 36 0.97 (1.48).
+//   14 x 14 0.94 / 0.95 / 0.77, 28 x 28 0.98 / 0.78 / 0.55; 48 channels on four 13 x 13 0.66 / 0.63 / 0.86, stride 2 16 -> 8 0.73 / 0.70 / 0.69, left
+//   out 14 x 14 0.73 / 0.69 / 1.15 and 36 -> 18 0.68 / 1.03 / 1.87.
+//   Groups of 16 in pairs that conv_tap.h fuses: 32 groups at 8 x 8 1.0 / 0.99 / 0.79, stride 2 28 -> 14 0.90 / 0.60 / 0.53; left out 6 groups at
+//   10 x 10 1.0 / 1.0 / 1.23.  Fewer than 32 outputs leave rows idle: 32 -> 16 6.7 against 8.2.
+//   float32 (the gathered kernel of gemm_f32.h) at 1 / 12 / 48 images: stride 1 up to 64 x 64 positions 256 channels 14 x 14 0.55 / 0.60 /
+//   0.99, 64 channels 64 x 64 0.59 / 0.91 / 0.91 (left out 72 x 72 0.65 / 1.00 / 1.08), 32 groups of 8 channels on one wavefront 28 x 28 0.70 /
+//   0.43 / 0.40; left out 40 channels, five steps over four wavefronts, at 28 x 28 0.66 / 0.82 / 1.02 and 64 x 64 0.72 / 1.12 / 1.03.  Stride 2:
+//   16 channels on one wavefront 28 x 28 0.92 / 0.71 / 0.62 (on four 0.88 / 1.25 / 1.21), left out 56 x 56 1.08 / 1.24 / 1.11; others on four
+//   20 x 20 0.58 / 0.71 / 0.85, left out 128 channels 28 x 28 0.65 / 0.92 / 1.27.
 static int wave_shares(bool f32, int cig, int cog, int g, long long HoWo, int stride) {
   if (f32) {
-    if (stride > 1 && HoWo > 1024) return cig <= 16 ? 1 : 0;
-    return cig == 8 || (cig == 16 && HoWo > 1200) ? 1 : 4;
+    if (stride > 1) return cig == 8 || (cig == 16 && HoWo > 64) ? HoWo <= 1600 : HoWo <= 400 ? 4 : 0;
+    return cig == 8 || (cig == 16 && HoWo > 1200) ? 1 : HoWo <= (cig == 40 ? 400 : 4096) ? 4 : 0;
   }
-  if (cig == 16) return g % 2 == 0 && cog <= 16 && HoWo > 256 ? 0 : 1;
+  if (cig == 16) return g % 2 == 0 && cog <= 16 && HoWo > (stride > 1 ? 256 : 81) ? 0 : 1;
   if (cog < 32 && cig % 32 == 0) return 0;
-  if (cig % 32) return HoWo * stride * stride <= 1300 ? 4 : 1;
-  if (cig >= 512) return 4;
-  if (stride > 1) return HoWo <= 784 ? 4 : 0;
-  return HoWo <= (cig >= 256 ? 2500 : 196) ? 4 : 0;
+  if (cig % 32) return HoWo <= (stride > 1 ? 64 : 169) ? 4 : 0;
+  const int most = cig < 64 ? 25 : stride > 1 ? (cig < 384 ? 64 : 196) : cig < 128 ? 81 : cig < 256 ? 121 : cig < 384 ? 196 : cig < 512 ? 1300 : INT_MAX;
+  return HoWo <= most || (stride > 1 && cig >= 256 && HoWo > 100 && HoWo <= 169) ? 4 : 0;
 }
 
 template <typename T>
