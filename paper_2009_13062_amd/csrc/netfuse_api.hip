@@ -798,13 +798,12 @@ nf_status netfuse_conv2d(const void* x, const void* w, const float* bias, const 
         const long long t128 = problems * ((cog + 127) / 128) * ((HoWo + 127) / 128);
         if (cog > 64 && HoWo > 64 && t128 >= 160) tile = T128x128w8;
         else if (HoWo <= 64 && tile == T128x128w8 && t128 < 64) tile = T64x64;
-        // The deep pipeline holds twice the registers: one 128 x 128 tile per compute unit.  One k-step in flight and two tiles where the
-        // second covers the wait (half-empty tiles from 512 up; more than one, but no more than two per compute unit) or
-        // k is over before the loader's offsets have paid.  Deep / one step, us: 16 models of 4 images 512 -> 2048 at
-        // 13 x 13 72.3 / 63.1, 64 -> 256 at 49 x 49 25.4 / 21.2, 8 models 256 -> 1024 at 49 x 49 (320 tiles) 29.2 / 26.1;
-        // the other way 32 models 256 -> 1024 at 13 x 13 (256 tiles) 13.4 / 16.3.  3 models of 4 images 512 -> 2048 at 25 x 25
-        // (384 tiles) 41.7 / 44.4.
-        L.one_step = tile == T128x128w8 && (Kdim <= 64 || (HoWo <= 64 ? t128 >= 512 : t128 > 256 && t128 <= 512));
+        // The deep pipeline holds twice the registers: one 128 x 128 tile per compute unit.  One k-step in flight and two tiles where
+        // there is a second one to cover the wait, from 257 tiles on, or where k is over before the loader's offsets have paid.  One
+        // step against deep over 1933 problems (64 ... 1024 channels, planes of 3 x 3 to 71 x 71, 1 ... 256 images), by tiles: up to 256 1.12
+        // to 1.30; 257 ... 768 0.91 (up to 64 positions), 0.96 (more, k up to 256) and 1.0 (longer k; 0.90 for 8 models 1024 -> 2048 at
+        // 33 x 33, 1.06 for 3 models of 4 images 512 -> 2048 at 25 x 25); beyond 0.87, 0.90 and 0.95.
+        L.one_step = tile == T128x128w8 && (Kdim <= 64 || t128 > 256);
       }
     }
     return launch_gemm_any(bkind, al, tile, L, s);
