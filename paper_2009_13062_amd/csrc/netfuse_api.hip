@@ -211,13 +211,17 @@ constexpr TileCost kDmaCost[kNumDmaTiles] = {{256, 256, 20.1f, 10.7f}, {128, 128
 constexpr TileCost kRingCost[R256x256 + 1] = {{32, 32, 2.38f, 0.74f}, {64, 64, 3.61f, 0.43f}, {64, 128, 5.18f, 1.51f},
                                                {96, 128, 6.10f, 1.51f}, {96, 256, 9.95f, 2.07f}, {128, 128, 6.89f, 1.53f},
                                                {128, 256, 11.6f, 2.83f}, {128, 384, 16.2f, 4.24f}, {256, 256, 19.0f, 4.30f}};
-// More than 128 rows, where row tiles share the weights: every ring tile, those between the powers of two too.  Workgroups partly
+// More than 128 rows, where row tiles share the weights: every ring tile, those between the powers of two too, by a model of its own.  Workgroups partly
 // share a compute unit, so a us of launch, per 768 of k b us for every round begun and c us for every round's worth of tiles,
 // e us of prologue and epilogue per round.  Fitted to every tile over 792 problems (an encoder layer's four matmuls at hidden
-// sizes 256, 768 and 1024, 1 ... 32 models of 17 ... 1024 rows): mean error 5 to 10 %.  Over another 1104 problems (other
-// counts and rows) it and the four tiles take 4 % off where there are more than 128 rows (8 % at 279: 24 models 4096 -> 1024
-// 117 -> 74, 12 models 768 -> 2304 30.4 -> 22.6 us; 16 of 760 rows 3072 -> 768 90 -> 61 us; at 256 of k 1 %, from 0.8 to
-// 1.1 of the time), but with fewer they give nothing on average and 16 models of 128 rows 1024 -> 3072 took 32 in place of 26 us.
+// sizes 256, 768 and 1024, 1 ... 32 models of 17 ... 1024 rows): mean error 5 to 10 %.  That error is a tenth of a tile, so the choice
+// of the table above stands unless this model puts another tile kTallMargin below its own time for that choice: over 1632 problems
+// of 129 ... 2048 rows 2.2 % off on average (24 models of 279 rows 4096 -> 1024 117 -> 74, 12 models 768 -> 2304 30.4 -> 22.6 us; 16 of 760
+// rows 3072 -> 768 90 -> 61 us), one problem slower by 5 %; without the margin 1.9 %, and 55 slower by 4 to 20 % (32 models of 256
+// rows 3072 -> 768 71 in place of 59 us).  Not at 256 of k, where a tile is over before its ring is full: 32 models of 384 rows
+// 256 -> 768 took 12.8 to 17.3 us in 192 x 192 tiles, by where the operands lay, and 15.2 in 128 x 384.  With up to 128 rows the four
+// tiles give nothing on average, and 16 models of 128 rows 1024 -> 3072 took 32 in place of 26 us.
+constexpr float kTallMargin = 0.95f;
 struct RingCost { int bm, bn; float a, b, e, c; };
 float tile_us(const RingCost& t, int N, int Nout, int K, long long M) {
   const long long tiles = M * ((N + t.bm - 1) / t.bm) * ((Nout + t.bn - 1) / t.bn);
@@ -391,7 +395,11 @@ nf_status netfuse_linear(const void* X, const void* W, const float* bias, const 
         // With one row tile nothing shares the weights of a 128 x 384 tile, whole-tile or ring, and the model, fitted to both,
         // is too low for the ring one: 24, 32 and 48 models of 128 rows 768 -> 3072 32.2, 35.0, 59.4 us as before, 34.0, 36.5, 61.3 there.
         const float margin = d < 0 ? 1.0f : N == 128 && kDmaBN[d] == 384 ? 0.65f : 0.93f;
-        const int r = N > 128 ? pick_ring(kRingTallCost, N, Nout, K, M, margin * now) : pick_ring(kRingCost, N, Nout, K, M, margin * now);
+        int r = pick_ring(kRingCost, N, Nout, K, M, margin * now);
+        if (N > 128 && K >= 512) {
+          const int tall = pick_ring(kRingTallCost, N, Nout, K, M, r < 0 ? margin * now : kTallMargin * tile_us(kRingTallCost[r], N, Nout, K, M));
+          if (tall >= 0) r = tall;
+        }
         if (r >= 0) {
           const nf_status st = launch_gemm_ring(r, false, L, s);
           if (st != NF_EUNSUPPORTED) return st;
