@@ -5,6 +5,7 @@
 #include <atomic>
 #include <cmath>
 #include <cstdio>
+#include <cstring>
 
 #include "conv_wave.h"
 #include "gemm_launch.h"
@@ -118,39 +119,47 @@ static int wave_shares(bool f32, int cig, int cog, int g, long long HoWo, int st
   return HoWo <= most || (stride > 1 && cig >= 256 && HoWo > 100 && HoWo <= 169) ? 4 : 0;
 }
 
+// The tile of a problem: wavefronts that share it and its blocks of positions; kg == 0: another kernel.
+struct WaveChoice { int kg, nb; WaveTile tile; };
 template <typename T>
-nf_status launch_conv_wave(ConvWaveArgs<T>& a, int Ho, int B, hipStream_t s) {
+static WaveChoice choose_wave(ConvWaveArgs<T>& a, int Ho, int B) {
   constexpr int EV = ConvWaveType<T>::kEV;
+  const WaveChoice none{};
   const long long plane = (long long)a.H * a.W;
-  if (a.cig % (2 * EV) != 0 || a.pad > 2 || a.W < 2 || ((uintptr_t)a.w & 15) != 0 || Ho <= 0) return NF_EUNSUPPORTED;
+  if (a.cig % (2 * EV) != 0 || a.pad > 2 || a.W < 2 || Ho <= 0) return none;
   // 32-bit byte offsets inside one group's weights and inside one step's planes; exact divisions by Wo and W
   if ((long long)a.cog * a.cig * 9 * sizeof(T) >= (1LL << 31) || 2 * EV * plane * sizeof(T) >= (1LL << 31) ||
-      (long long)a.HoWo * a.Wo >= (1LL << 32) || plane * a.W >= (1LL << 32)) return NF_EUNSUPPORTED;
+      (long long)a.HoWo * a.Wo >= (1LL << 32) || plane * a.W >= (1LL << 32)) return none;
   a.PW = std::max(a.W + a.pad, (a.Wo - 1) * a.stride + 3);
+  WaveChoice c{wave_shares(sizeof(T) == 4, a.cig, a.cog, a.g, a.HoWo, a.stride), 0, {}};
+  int forced = 0;
+  if (const char* e = dev_getenv("NETFUSE_CW")) sscanf(e, "%d,%d", &c.kg, &forced);
+  if (c.kg == 0) return none;
+  float best_us = 0.f;
+  for (int b : {1, 2, 3, 4, 5, 7}) {
+    // one wavefront per tile: 3 and 5 blocks are not built, nor 7 in float32, where the registers of two chains leave room for one
+    // wavefront per SIMD (32 groups of 8 channels at 28 x 28, 8 models: 31.6 us against 18.5 in two blocks)
+    if (c.kg == 1 && (b == 3 || b == 5 || (b == 7 && sizeof(T) == 4))) continue;
+    if (forced > 0 && b != forced) continue;
+    const WaveTile t = wave_tile(a, Ho, b, c.kg);
+    if (t.nt == 0) continue;
+    const float us = wave_us(a, t, b, c.kg, B);
+    if (c.nb == 0 || us < best_us) { c.nb = b; c.tile = t; best_us = us; }
+  }
+  return c.nb ? c : none;
+}
+
+template <typename T>
+nf_status launch_conv_wave(ConvWaveArgs<T>& a, int Ho, int B, hipStream_t s) {
+  const WaveChoice c = choose_wave(a, Ho, B);
+  if (c.kg == 0 || ((uintptr_t)a.w & 15) != 0) return NF_EUNSUPPORTED;
   auto rcp = [](int d, unsigned* r, unsigned* one) {
     *r = d == 1 ? 0u : (unsigned)(((1ULL << 32) + d - 1) / d);
     *one = d == 1 ? ~0u : 0u;
   };
   rcp(a.W, &a.rcp_w, &a.one_w);
   rcp(a.Wo, &a.rcp_wo, &a.one_wo);
-  int kg = wave_shares(sizeof(T) == 4, a.cig, a.cog, a.g, a.HoWo, a.stride), forced = 0;
-  if (const char* e = dev_getenv("NETFUSE_CW")) sscanf(e, "%d,%d", &kg, &forced);
-  if (kg == 0) return NF_EUNSUPPORTED;
-  constexpr int kBlocks[] = {1, 2, 3, 4, 5, 7};
-  WaveTile best{};
-  int nb = 0;
-  float best_us = 0.f;
-  for (int b : kBlocks) {
-    // one wavefront per tile: 3 and 5 blocks are not built, nor 7 in float32, where the registers of two chains leave room for one
-    // wavefront per SIMD (32 groups of 8 channels at 28 x 28, 8 models: 31.6 us against 18.5 in two blocks)
-    if (kg == 1 && (b == 3 || b == 5 || (b == 7 && sizeof(T) == 4))) continue;
-    if (forced > 0 && b != forced) continue;
-    const WaveTile t = wave_tile(a, Ho, b, kg);
-    if (t.nt == 0) continue;
-    const float us = wave_us(a, t, b, kg, B);
-    if (nb == 0 || us < best_us) { nb = b; best = t; best_us = us; }
-  }
-#define NF_CWT(NB_, KG_) if (kg == KG_ && nb == NB_) return launch_tile<T, NB_, KG_>(best, a, B, s)
+#define NF_CWT(NB_, KG_) if (c.kg == KG_ && c.nb == NB_) return launch_tile<T, NB_, KG_>(c.tile, a, B, s)
   NF_CWT(1, 4); NF_CWT(2, 4); NF_CWT(3, 4); NF_CWT(4, 4); NF_CWT(5, 4); NF_CWT(7, 4);
   NF_CWT(1, 1); NF_CWT(2, 1); NF_CWT(4, 1);
   if constexpr (sizeof(T) == 2) { NF_CWT(7, 1); }
@@ -161,4 +170,21 @@ nf_status launch_conv_wave(ConvWaveArgs<T>& a, int Ho, int B, hipStream_t s) {
 template nf_status launch_conv_wave<bf16_t>(ConvWaveArgs<bf16_t>&, int, int, hipStream_t);
 template nf_status launch_conv_wave<float>(ConvWaveArgs<float>&, int, int, hipStream_t);
 
+template <typename T>
+static int tile_of(int M, int B, int cig, int cog, int g, int H, int W, int stride, int pad) {
+  ConvWaveArgs<T> a;
+  memset(&a, 0, sizeof(a));
+  const int Ho = (H + 2 * pad - 3) / stride + 1;
+  a.cig = cig; a.cog = cog; a.g = g; a.nG = M * g; a.H = H; a.W = W; a.Wo = (W + 2 * pad - 3) / stride + 1;
+  a.HoWo = Ho * a.Wo; a.stride = stride; a.pad = pad;
+  const WaveChoice c = choose_wave(a, Ho, B);
+  return 10 * c.kg + c.nb;
+}
+
 }  // namespace nf
+
+// For the tests, which name the tile that a case is meant to run; not part of the interface.  10 x wavefronts + blocks of
+// positions, 0 = another kernel.  Host only.
+extern "C" int netfuse_conv_wave_tile(int f32, int M, int B, int cig, int cog, int g, int H, int W, int stride, int pad) {
+  return f32 ? nf::tile_of<float>(M, B, cig, cog, g, H, W, stride, pad) : nf::tile_of<nf::bf16_t>(M, B, cig, cog, g, H, W, stride, pad);
+}

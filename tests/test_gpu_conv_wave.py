@@ -1,6 +1,6 @@
-"""3x3 convolutions with wavefront-private pipelines (conv_wave.h): steps that do not divide over four wavefronts, ragged rows, tiles
-of every number of position blocks, planes that end inside a 16-byte store, either stride, padding 0 to 2, every part of the
-epilogue; and the same bits for a model whatever tile the number of models leads to.  bf16 is integer-coded (every sum exact in
+"""3x3 convolutions with wavefront-private pipelines (conv_wave.h): steps that do not divide over four wavefronts, ragged rows, planes
+that end inside a 16-byte store, either stride, padding 0 to 2, in tiles of one block of positions (the others, and the rest of the
+epilogue: test_gpu_conv_wave_tiles.py); and the same bits for a model whatever tile the number of models leads to.  bf16 is integer-coded (every sum exact in
 float32), float32 is held to the rounding bound of a sum of K products in any order: (K + 8) 2^-24 sum |x||w|."""
 import numpy as np
 import pytest
