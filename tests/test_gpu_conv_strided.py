@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 
 CASES = [   # M, B, cin, cout, H, W, stride
     (2, 2, 256, 72, 13, 13, 2), (2, 1, 1024, 264, 13, 13, 2),     # 64 x 64 tiles, fewer than 64 positions
-    (32, 2, 256, 520, 13, 13, 2),                                 # 128 x 128 over 49 positions
+    (14, 2, 256, 520, 13, 13, 2), (32, 2, 256, 520, 13, 13, 2),   # 128 x 128 over 49 positions, deep and one k-step in flight
     (3, 2, 256, 136, 25, 25, 2), (14, 2, 256, 264, 25, 25, 2),    # 64 x 64 and 128 x 128, more than 64 positions
     (40, 2, 128, 264, 25, 25, 2), (64, 2, 128, 520, 5, 5, 2), (20, 2, 64, 264, 25, 25, 2),   # 128 x 128, one k-step in flight
     (2, 1, 384, 24, 25, 25, 2), (3, 1, 160, 72, 13, 13, 2),       # up to 32 channels; k of no whole number of pipeline rounds
@@ -43,7 +43,10 @@ def test_exact(oracle, M, B, cin, cout, H, W, stride):
     skipped = np.ones((H, W), bool)
     skipped[::stride, ::stride] = False
     x2[:, :, skipped] = np.inf
-    x2[:, :, stride * (Ho - 1), stride * (Wo - 1)] = np.inf
+    last = Ho * Wo > 1                                        # a plane of one position has no other output to compare
+    if last:
+        x2[:, :, stride * (Ho - 1), stride * (Wo - 1)] = np.inf
     got2 = nf.conv2d(dev(x2), dev(w), M, bias=dev(bias, f), scale=dev(scale, f), shift=dev(shift, f), residual=dev(res), stride=stride, act=1)
     same = (got2 == got).reshape(B, M * cout, Ho * Wo)
-    assert bool(same[:, :, :-1].all())
+    same = same[:, :, :-1] if last else same
+    assert same.numel() and bool(same.all())

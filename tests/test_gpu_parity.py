@@ -194,11 +194,11 @@ CONV_CASES = [
     (2, 2, 32, 64, 4, 9, 11, 3, 3, 1, 1, 1),       # batch 2 per model, non-square image
     (1, 1, 16, 24, 1, 10, 10, 3, 3, 1, 2, 2),      # dilation 2
     (3, 1, 8, 200, 2, 5, 5, 2, 3, 1, 1, 1),        # non-square kernel, 100 outputs per group
-    (2, 1, 128, 256, 1, 28, 28, 3, 3, 1, 1, 1),    # patch-gather 3x3: two 128-channel row tiles, 7 position tiles
-    (3, 2, 32, 32, 2, 7, 7, 3, 3, 1, 1, 1),        # patch-gather, 16 channels per group, image smaller than a tile
-    (1, 1, 64, 64, 1, 56, 56, 3, 3, 1, 1, 1),      # patch-gather, 58-wide patch, tiles that start mid-row
-    (2, 1, 64, 128, 1, 30, 30, 3, 3, 2, 1, 1),     # patch-gather, stride 2, odd output width 15
-    (2, 1, 48, 64, 1, 12, 12, 3, 3, 1, 0, 1),      # patch-gather, no padding, 3 channel blocks
+    (2, 1, 128, 256, 1, 28, 28, 3, 3, 1, 1, 1),    # tap-major 3x3: 256 rows, 7 position tiles
+    (3, 2, 32, 32, 2, 7, 7, 3, 3, 1, 1, 1),        # conv_wave: 16 channels per group, image smaller than a tile
+    (1, 1, 64, 64, 1, 56, 56, 3, 3, 1, 1, 1),      # tap-major: 58-wide patch, tiles that start mid-row
+    (2, 1, 64, 128, 1, 30, 30, 3, 3, 2, 1, 1),     # tap-major: stride 2, odd output width 15
+    (2, 1, 48, 64, 1, 12, 12, 3, 3, 1, 0, 1),      # conv_wave: no padding, 3 channel steps
     (2, 2, 64, 80, 1, 7, 7, 3, 3, 1, 1, 1),        # tap-major 3x3: 1-pixel chunks, ragged row tile, batch 2
     (2, 1, 96, 64, 1, 12, 20, 3, 3, 1, 0, 1),      # tap-major 3x3: 3 channel blocks, no padding, non-square, 4-pixel chunks
     (1, 1, 32, 32, 1, 28, 28, 3, 3, 2, 1, 1),      # tap-major 3x3: stride 2, three patch tasks per thread
