@@ -59,7 +59,8 @@ static nf_status launch_ring_tile(int tile, GemmLaunch& L, hipStream_t s) {
     case R128x384: return launch_ring<RingCfg<2, 3, 2, 4, 1, 32, 4, 2>, false>(L, s);
     case R256x256: return launch_ring<RingCfg<4, 2, 2, 4, 1, 64, 2, 2>, false>(L, s);
     case R64x256: return launch_ring<RingCfg<2, 1, 1, 8, 1, 64, 3, 2>, false>(L, s);
-    // heights between the powers of two, three row blocks per wavefront (three multiplications per slice for four LDS reads)
+    // heights between the powers of two, a column of row blocks per wavefront: five multiplications per slice of 16 k for seven LDS reads
+    // (five of rows, two transposing ones of the weights), in the other two three for five; a single block takes three for one
     case R160x256: return launch_ring<RingCfg<5, 1, 1, 8, 1, 32, 5, 2>, false>(L, s);
     case R192x192: return launch_ring<RingCfg<3, 1, 2, 6, 1, 64, 3, 3>, false>(L, s);
     case R288x128: return launch_ring<RingCfg<3, 1, 3, 4, 1, 64, 3, 3>, false>(L, s);
