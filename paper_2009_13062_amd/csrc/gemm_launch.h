@@ -76,6 +76,13 @@ nf_status launch_gemm_ring(int tile, bool packed, GemmLaunch& L, hipStream_t s);
 // The same for a pointwise convolution (A = weights, B = planes of cols % 8 == 0 positions, K % 64 == 0 channels).
 enum RingConvTileId { RC64x64 = 0, RC64x128, RC64x256, RC128x128, RC128x256, kNumRingConvTiles };
 nf_status launch_conv_ring(int tile, GemmLaunch& L, hipStream_t s);
+// Pointwise convolutions over planes of any size and any stride (conv_plane.h; 16-byte aligned operands, K % 64 == 0; geom holds W,
+// Wo and the stride, ldb the positions of an input plane).  PW: tiles that span planes of up to 56 positions, or of 4 k up to 200; PQ:
+// 128 positions of a plane of 4 k; PG: any, strided.  NF_EUNSUPPORTED if the shape does not fit the tile.
+enum ConvPlaneTileId { PW64x64 = 0, PW128x64, PW64x224, PW64x224d, PQ64x128, PQ128x128, PG32x64, PG128x64, PG128x64k32, PG128x128,
+                       kNumConvPlaneTiles };
+int pick_conv_plane(const GemmLaunch& L, int now, bool pairs);
+nf_status launch_conv_plane(int tile, const GemmLaunch& L, hipStream_t s);
 
 // BKIND: 8 / 4 / 1 = dense B read with that vector width; 0 = implicit (im2col) B.
 // align_a: 16, 8, 4 or 2 = byte alignment of every A row start (and K a multiple of align_a/2).

@@ -292,6 +292,15 @@ nf_status conv_wave(const void* x, const void* w, const void* residual, void* y,
   return launch_conv_wave(c, Ho, B, s);
 }
 
+// Pointwise through the kernels of conv_plane.h where they are ahead of the register-staged tile `now`, or NF_EUNSUPPORTED.
+nf_status conv_plane(const GemmLaunch& L, int H, int W, int Wo, int stride, int now, bool pairs, hipStream_t s) {
+  GemmLaunch P = L;
+  P.a.ldb = (long)H * W;
+  P.a.geom.W = W; P.a.geom.Wo = Wo; P.a.geom.stride = stride;
+  const int t = pick_conv_plane(P, now, pairs);
+  return t < 0 ? NF_EUNSUPPORTED : launch_conv_plane(t, P, s);
+}
+
 // largest alignment (16, 8, 4 or 2 bytes) shared by a pointer and a row pitch / stride set
 int common_align(std::initializer_list<const void*> ptrs, std::initializer_list<long long> elem_strides) {
   int al = 16;
@@ -713,6 +722,10 @@ nf_status netfuse_conv2d(const void* x, const void* w, const float* bias, const 
         const nf_status st = launch_conv_ring(pick, L, s);
         if (st != NF_EUNSUPPORTED) return st;
       }
+      if (bkind == 1 && forced_tile() < 0) {
+        const nf_status st = conv_plane(L, H, W, (int)Wo, stride, tile, false, s);
+        if (st != NF_EUNSUPPORTED) return st;
+      }
       return launch_gemm_any(bkind, al, tile, L, s);
     }
     static const bool no_patch = dev_getenv("NETFUSE_NO_PATCH") != nullptr;
@@ -798,6 +811,10 @@ nf_status netfuse_conv2d(const void* x, const void* w, const float* bias, const 
         else if (Wo % 2 == 0 && plane % 4 == 0 && aligned(x, 8)) bkind = 22;
         else if (Wo == 7 && Ho <= 8 && plane % 4 == 0 && aligned(x, 8)) bkind = 27;
         else if (aligned(x, 4)) bkind = 21;
+      }
+      if (forced_tile() < 0) {
+        const nf_status st = conv_plane(L, H, W, (int)Wo, stride, tile, bkind != 2, s);
+        if (st != NF_EUNSUPPORTED) return st;
       }
       if (bkind == 2 && forced_tile() < 0) {
         // Eight 2-byte loads per 16 bytes of activations weigh more than a compute unit or two left idle: from 160 tiles of 128 x 128
