@@ -2,7 +2,8 @@
 
 Argument marshalling only: every function here checks tensor types, takes ``data_ptr()`` and the
 current torch stream, and calls the C entry point of the same name in ``libnetfuse.so``
-(declared in ``include/netfuse.h``).  All arithmetic runs in the HIP kernels.  There is no
+(declared in ``include/netfuse.h``); those of a forward pass do so in native code for the calls that
+it takes as they are (``csrc/binding.cpp``).  All arithmetic runs in the HIP kernels.  There is no
 fallback: if the library has not been built, importing this package raises.
 
 Tensors are torch CUDA tensors, contiguous, dtype float32 or bfloat16 (activations/weights);
@@ -114,8 +115,26 @@ def _check(fn: str, st: int):
         raise NetFuseError(fn, st)
 
 
+# The calls of a forward pass marshalled in native code (csrc/binding.cpp); None where it was not built, or was built for another
+# torch: the functions below then do all of it themselves.
+_Tensor = torch.Tensor
+try:
+    from . import _binding as _native
+    _address = lambda f: ctypes.cast(f, ctypes.c_void_p).value
+    _native.bind(_check, _address(lib.netfuse_linear), _address(lib.netfuse_linear_packed), _address(lib.netfuse_layernorm),
+                 _address(lib.netfuse_attention), _address(lib.netfuse_attention_relpos), _address(lib.netfuse_conv2d))
+except ImportError:
+    _native = None
+if _raw_stream is None or _device is None:
+    _native = None
+
+
 def linear(X, W, bias=None, residual=None, act=ACT_NONE, out=None, stream=None):
     """Y[m] = act(X[m] @ W[m] + bias[m]) + residual[m];  X[M,N,K], W[M,K,Nout] -> Y[M,N,Nout]."""
+    if _native is not None and stream is None and type(X) is _Tensor and X.is_cuda:
+        Y = _native.linear(X, W, bias, residual, act, out, _raw_stream(_device()))
+        if Y is not None:
+            return Y
     M, N, K = X.shape
     Nout = W.shape[2]
     if W.shape[0] != M or W.shape[1] != K:
@@ -143,6 +162,10 @@ def linear_pack_weight(W, out=None, stream=None):
 
 def linear_packed(X, Wp, bias=None, residual=None, act=ACT_NONE, out=None, stream=None):
     """netfuse_linear on weights packed by linear_pack_weight(W); Wp keeps W's shape [M,K,Nout]."""
+    if _native is not None and stream is None and type(X) is _Tensor and X.is_cuda:
+        Y = _native.linear_packed(X, Wp, bias, residual, act, out, _raw_stream(_device()))
+        if Y is not None:
+            return Y
     M, N, K = X.shape
     Nout = Wp.shape[2]
     if Wp.shape[0] != M or Wp.shape[1] != K:
@@ -203,6 +226,10 @@ def conv_out_size(n, k, stride, pad, dil=1):
 def conv2d(x, w, M, g=1, bias=None, scale=None, shift=None, residual=None, stride=1, pad=0, dil=1,
            act=ACT_NONE, out=None, stream=None):
     """x[B, M*Cin, H, W], w[M*Cout, Cin/g, KH, KW] -> y[B, M*Cout, Ho, Wo]; merged groups = M*g."""
+    if _native is not None and stream is None and type(x) is _Tensor and x.is_cuda:
+        y = _native.conv2d(x, w, M, g, bias, scale, shift, residual, stride, pad, dil, act, out, _raw_stream(_device()))
+        if y is not None:
+            return y
     B, Ct, H, Wd = x.shape
     Cin, Cout = Ct // M, w.shape[0] // M
     KH, KW = w.shape[2], w.shape[3]
@@ -219,6 +246,10 @@ def conv2d(x, w, M, g=1, bias=None, scale=None, shift=None, residual=None, strid
 
 def layernorm(x, gamma, beta, M, residual=None, eps=1e-5, layout=MERGE_BATCH, out=None, stream=None):
     """layout MERGE_BATCH: x[M, rows, H]; MERGE_CHANNEL: x[rows, M*H]; gamma, beta float32[M*H]."""
+    if _native is not None and stream is None and type(x) is _Tensor and x.is_cuda:
+        y = _native.layernorm(x, gamma, beta, M, residual, eps, layout, out, _raw_stream(_device()))
+        if y is not None:
+            return y
     if layout == MERGE_BATCH:
         rows, H = x.shape[1], x.shape[2]
     else:
@@ -256,6 +287,10 @@ def bn_fold(gamma, beta, mean, var, eps=1e-5, stream=None):
 
 def attention_packed(QKV, B, S, heads, scale=None, mask=None, out=None, stream=None):
     """QKV[M, B*S, 3*heads*d] with column blocks [Q | K | V] -> O[M, B*S, heads*d]."""
+    if _native is not None and stream is None and type(QKV) is _Tensor and QKV.is_cuda:
+        O = _native.attention_packed(QKV, B, S, heads, scale, mask, out, _raw_stream(_device()))
+        if O is not None:
+            return O
     M, N, three_h = QKV.shape
     Hd = three_h // 3
     d = Hd // heads
@@ -288,6 +323,10 @@ def attention_relpos_packed(QKV, Kr, B, S, heads, bias_w=None, bias_r=None, scal
                             stream=None):
     """Relative-position attention on QKV[M, B*S, 3*heads*d] (column blocks [Q | K | V]) and the projected
     position encodings Kr[M, 2*S, heads*d]; bias_w, bias_r float32 [M, heads*d]."""
+    if _native is not None and stream is None and type(QKV) is _Tensor and QKV.is_cuda:
+        O = _native.attention_relpos_packed(QKV, Kr, B, S, heads, bias_w, bias_r, scale, mask, out, _raw_stream(_device()))
+        if O is not None:
+            return O
     M, N, three_h = QKV.shape
     Hd = three_h // 3
     d = Hd // heads

@@ -13,6 +13,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libnetfuse.so")
+BINDING = os.path.join(HERE, "_binding.so")
 SOURCES = ["netfuse_api.hip", "graph_merge.cpp", "gemm_inst_b8.hip", "gemm_inst_b2.hip", "gemm_inst_b24.hip", "gemm_inst_b22.hip", "gemm_inst_b21.hip", "gemm_inst_b27.hip", "gemm_inst_b1.hip",
            "gemm_inst_b0.hip", "gemm_inst_dma.hip", "gemm_inst_stream.hip", "gemm_inst_frag.hip", "gemm_inst_f32.hip", "gemm_inst_ring.hip", "conv_patch_inst.hip", "conv_tap_inst.hip", "conv_wave_inst.hip", "conv_plane_inst.hip"]
 
@@ -53,11 +54,34 @@ def _compile(src: str, extra, verbose: bool, force: bool) -> str:
     return obj
 
 
+def _build_binding(verbose: bool, force: bool) -> None:
+    """The call marshalling of the Python package (csrc/binding.cpp): a host-only extension against the installed torch."""
+    import sysconfig
+
+    import torch
+    src = os.path.join(CSRC, "binding.cpp")
+    if not force and os.path.exists(BINDING) and os.path.getmtime(BINDING) > max(os.path.getmtime(src), _newest_header()):
+        return
+    root = os.path.dirname(torch.__file__)                   # its libraries are found by name: the package imports torch first
+    # NDEBUG: without it a header keeps a thread-local counter.  A library with thread-local storage that is loaded late and whose storage is
+    # never touched leaves glibc 2.35 on the slow path of every other library's (17 % on torch's small operators).
+    cmd = ["g++", "-O2", "-DNDEBUG", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-isystem", os.path.join(root, "include"),
+           "-isystem", sysconfig.get_paths()["include"], src, "-o", BINDING + ".tmp",
+           "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    os.replace(BINDING + ".tmp", BINDING)
+
+
 def build(verbose: bool = False, extra=(), force: bool = True, jobs: int = 8) -> str:
     """Compile every translation unit (always, unless force=False and objects are newer) and link."""
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
+        binding = ex.submit(_build_binding, verbose, force)
         objs = list(ex.map(lambda s: _compile(s, extra, verbose, force), SOURCES))
+        binding.result()
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", LIB + ".tmp"]
     if verbose:
         print(" ".join(cmd), flush=True)
