@@ -526,13 +526,13 @@ int netfuse_linear_packed_supported(int M, int N, int K, int Nout, nf_dtype dt) 
   // With few models the fragment kernel's tiles leave most compute units idle.  netfuse_linear_packed then runs the tiles of gemm_ring.h that
   // split k over the wavefronts of a workgroup, which the row-major ones, one chain of k each, cannot: ahead where 32 x 32 tiles are
   // one round of workgroups (2 models of 128 rows 768 -> 768 7.0 -> 5.0 us, 3072 -> 768 15.8 -> 9.5, 4096 -> 1024 21.7 -> 12.0; 8 of 128 rows 256 -> 256
-  // 4.4 -> 3.9; never behind over 40 such problems of hidden size 256 to 1024) and for long k (8 models 3072 -> 768 19.7 -> 18.4, 4096 ->
-  // 1024 27.7 -> 23.8; over 34 problems 4 % behind once, 7 to 24 % ahead elsewhere).  Otherwise netfuse_linear's small tiles are as fast or faster (3
-  // models 768 -> 768 7.6 against 7.7; one layer at 8 models 0.088 ms packed throughout, 0.074): the answer is "no" below half a workgroup
-  // per compute unit, although netfuse_linear_packed itself still runs there.
+  // 4.4 -> 3.9; never behind over 40 such problems of hidden size 256 to 1024) and for long k over few rows (3 models of 128 rows 3072 -> 768 19.1
+  // -> 16.6, 4096 -> 1024 25.7 -> 21.2; 8 to 21 % ahead over 18 problems of up to 768 rows in all).  Otherwise netfuse_linear's small tiles are as fast
+  // or faster (3 models 768 -> 768 7.6 against 7.7; one layer at 8 models 0.088 ms packed throughout, 0.074): the answer is "no" below half a
+  // workgroup per compute unit, although netfuse_linear_packed itself still runs there.
   const long long tiles = (long long)M * (N / kFragBM[f]) * (Nout / kFragBN[f]);
   if (tiles >= 128) return 1;
-  return f < kNumFragFullTiles && ring_fits(Nout, K) && ((long long)M * (N / 32) * (Nout / 32) <= 256 || K >= 2048) ? 1 : 0;
+  return f < kNumFragFullTiles && ring_fits(Nout, K) && ((long long)M * (N / 32) * (Nout / 32) <= 256 || (K >= 2048 && (long long)M * N <= 768)) ? 1 : 0;
 }
 
 nf_status netfuse_linear_pack_weight(const void* W, void* Wp, int M, int K, int Nout, nf_dtype dt, void* stream) {
