@@ -1,4 +1,5 @@
 // Instantiation and launch of the patch-gather convolution kernels (3x3 and the 7x7 stem, bf16).
+#include <algorithm>
 #include <atomic>
 
 #include "conv_patch.h"
@@ -62,17 +63,43 @@ nf_status launch_conv_patch_3x3(ConvPatchArgs& a, int B, hipStream_t s) {
 
 // 7x7, stride 2, pad 3, 3 input channels per group.  The caller has filled everything but the tiling and
 // has checked W % 8 == 0, 16-byte aligned x, and the patch width.
+template <int NT>
+static nf_status launch_stem(const ConvStemArgs& a, long long total, int lds, hipStream_t s) {
+  typedef ConvStemCfg<3> Cfg;
+  auto kern = conv_stem_kernel<Cfg, 3, NT>;
+  if (lds > 64 * 1024) {
+    static std::atomic<bool> opted_in{false};
+    if (!opted_in.load(std::memory_order_acquire)) {
+      if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
+        return NF_ELAUNCH;
+      opted_in.store(true, std::memory_order_release);
+    }
+  }
+  nf_launch(kern, dim3((unsigned)total), dim3(Cfg::kThreads), lds, s, a);
+  return hipGetLastError() == hipSuccess ? NF_OK : NF_ELAUNCH;
+}
+
 nf_status launch_conv_stem(ConvStemArgs& a, int B, hipStream_t s) {
   typedef ConvStemCfg<3> Cfg;
   a.tiles_m = (a.cog + Cfg::kBM - 1) / Cfg::kBM;
   a.tiles_n = (a.HoWo + Cfg::kBN - 1) / Cfg::kBN;
-  const long long total = (long long)a.tiles_m * a.tiles_n * a.nG * B;
-  if (total <= 0 || total > 0x7fffffffLL) return NF_EUNSUPPORTED;
+  const long long groups = (long long)a.tiles_m * a.nG * B, tiles = groups * a.tiles_n;
+  if (tiles <= 0 || tiles > 0x7fffffffLL) return NF_EUNSUPPORTED;
+  a.run = (int)std::min<long long>(a.tiles_n, (tiles + 767) / 768);
+  a.runs = (a.tiles_n + a.run - 1) / a.run;
+  a.run = (a.tiles_n + a.runs - 1) / a.runs;                // in equal parts
   if (a.PW % 8 != 0 || a.PS % 8 != 0 || a.PS % a.PW != 0) return NF_EUNSUPPORTED;
-  const int lds = Cfg::lds_bytes(a.PS);
-  if (lds > 64 * 1024) return NF_EUNSUPPORTED;
-  nf_launch((conv_stem_kernel<Cfg, 3>), dim3((unsigned)total), dim3(256), lds, s, a);
-  return hipGetLastError() == hipSuccess ? NF_OK : NF_ELAUNCH;
+  const int lds = Cfg::lds_bytes(a.PS), chunks = 3 * (a.PS / a.PW) * a.cpr;
+  // offsets inside a group's planes, and positions x Wo (cw_div), in 32 bits
+  if (lds > 160 * 1024 || chunks > 12 * 256 || 3LL * a.H * a.W > 0x7fffffffLL || (long long)a.HoWo * a.Wo >= (1LL << 32)) return NF_EUNSUPPORTED;
+  auto rcp = [](int d, unsigned* r, unsigned* one) {
+    *r = d == 1 ? 0u : (unsigned)(((1ULL << 32) + d - 1) / d);
+    *one = d == 1 ? ~0u : 0u;
+  };
+  rcp(a.Wo, &a.rcp_wo, &a.one_wo);
+  rcp(a.cpr, &a.rcp_cpr, &a.one_cpr);
+  if (chunks <= 4 * 256) return launch_stem<4>(a, groups * a.runs, lds, s);
+  return chunks <= 8 * 256 ? launch_stem<8>(a, groups * a.runs, lds, s) : launch_stem<12>(a, groups * a.runs, lds, s);
 }
 
 }  // namespace nf
