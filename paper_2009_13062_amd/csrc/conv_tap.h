@@ -23,16 +23,24 @@
 // channels are conv_wave.h's (the rule and both sides' times: conv_wave_inst.hip).
 //
 // The patch carries its zero padding: it is zeroed once, and every channel block overwrites only the
-// in-image pixels.  Image column ix lives at patch column ix + kLPad.  One workgroup = one (image, group,
-// 128-position tile, BM output channels); accumulators and the fused epilogue are those of gemm_mfma.h.
+// in-image pixels and clears the rows past the image.  Image column ix lives at patch column ix + kLPad.
+//
+// One workgroup = one (image, group, BM output channels) and a RUN of 128-position tiles.  While a block is multiplied the
+// next one of the tile, or the first of the next tile, is in flight in registers, and the outputs leave from registers
+// (conv_plane.h's epilogue): a tile per workgroup paid for its addresses, its zero fill and an empty memory pipe with
+// every tile, and read the weights of a single block (32 channels, or fused groups) again for each.  Measured per layer, one
+// tile -> a run: 16 models' fused groups of 4 channels at 56 x 56 19.1 -> 15.8 us, of 8 at 28 x 28 12.0 -> 9.2, at stride
+// 2 from 56 x 56 25.9 -> 17.9; 32 models' 64 channels at 56 x 56 23.7 -> 21.8; one tile per run, 3 models x 4 images, 128
+// channels at 25 x 25 10.4 -> 9.9.  The exception is 32 models' 256 channels, 28 -> 14 at stride 2 (30.3 -> 31.7).
+// What bounds it now: LDS reads (a fragment of each operand per MFMA at FM = FN = 1) and their bank conflicts.
 #pragma once
 #include "conv_patch.h"
+#include "conv_plane.h"
 
 namespace nf {
 
 constexpr int kTapCB = 32;          // input channels per block
 constexpr int kTapPixPitch = 40;    // elements per patch pixel (32 channels + 8)
-
 
 template <int BM, int WGM, int WGN, int MINW = 1>
 struct ConvTapCfg {
@@ -45,15 +53,15 @@ struct ConvTapCfg {
   static constexpr int kAPitch = kTaps * kTapCB + 8;     // elements; (pitch / 8) odd -> 16-byte slots rotate
   static_assert((kAPitch / 8) % 2 == 1, "A pitch must rotate bank groups");
   static constexpr int kABytes = BM * kAPitch * 2;
-  static constexpr int kEpiPitch = kBN + 4;
-  static constexpr int kLdsEpi = WGM * 32 * kEpiPitch * (int)sizeof(float);
   static constexpr int kWTasks = BM * (kTapCB / 8);      // weight tasks per block: (row, channel octet)
   static constexpr int kWPer = (kWTasks + 255) / 256;
   static constexpr int kMinWaves = MINW;
-  static constexpr int lds_bytes(int PS) {
-    const int pipe = kABytes + PS * kTapPixPitch * 2;
-    return pipe > kLdsEpi ? pipe : kLdsEpi;
-  }
+  static constexpr int lds_bytes(int PS) { return kABytes + PS * kTapPixPitch * 2; }
+};
+
+struct ConvTapArgs : ConvPatchArgs {
+  int run, runs;                             // position tiles per workgroup, workgroups per (image, group, row tile)
+  unsigned rcp_wo, one_wo;                   // division by Wo (cw_div)
 };
 
 // VW: pixels per patch chunk (= a.VW <= W).  NT: patch tasks per thread (the host checks the bound).
@@ -61,7 +69,7 @@ struct ConvTapCfg {
 // is block diagonal (row r carries its own group's channels at channel offset (r / cog_real) * cig_real,
 // zeros elsewhere), filled once; see conv_patch.h for why no product crosses a group.
 template <class Cfg, int VW, int NT, bool FUSED = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Cfg::kMinWaves))) void conv_tap_kernel(ConvPatchArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Cfg::kMinWaves))) void conv_tap_kernel(ConvTapArgs a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   lds_bf16_t* As = (lds_bf16_t*)smem_raw;
   lds_bf16_t* Ps = As + Cfg::kBM * Cfg::kAPitch;
@@ -73,19 +81,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Cfg::kMinWa
 
   unsigned id = xcd_remap(blockIdx.x, gridDim.x);
   const int tm = id % a.tiles_m;  id /= a.tiles_m;
-  const int tn = id % a.tiles_n;  id /= a.tiles_n;
+  const int rn = id % a.runs;     id /= a.runs;
   const int G = id % a.nG;
   const int b = id / a.nG;
-  const int row0 = tm * Cfg::kBM, p0 = tn * Cfg::kBN;
-  const int rows_left = a.cog - row0, cols_left = a.HoWo - p0;
-
-  // ---- geometry of this tile's patch
-  const int oy_first = p0 / a.Wo;
-  const int p_last = min(p0 + Cfg::kBN, a.HoWo) - 1;
-  const int PH = (p_last / a.Wo - oy_first) * a.stride + 3;          // rows actually needed (<= PS / PW)
-  const int iy0 = oy_first * a.stride - a.pad;
+  const int row0 = tm * Cfg::kBM, rows_left = a.cog - row0;
+  const int t0 = rn * a.run, t1 = min(t0 + a.run, a.tiles_n);
   const bf16_t* xg = a.x + (long)b * a.x_image + (long)G * a.x_group;
   const bf16_t* wg = a.w + ((long)G * a.cog + row0) * a.cig * 9;
+  // ---- geometry of a tile's patch
+  auto out_row = [&](int p) { return (int)cw_div(p, a.rcp_wo, a.one_wo); };
+  auto last_of = [&](int tn) { return min((tn + 1) * Cfg::kBN, a.HoWo) - 1; };
 
   // ---- this thread's share of a channel block.  Weight task = (row, channel octet); patch task = (channel
   // octet, patch row, chunk of VW pixels).  The geometry does not change from block to block.
@@ -119,49 +124,36 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Cfg::kMinWa
   // front of it (measured: 2.8 us from the start of a workgroup to its first load otherwise).
   prefetch_w(0);
 
-
-  // ---- fragment addresses (elements): per-lane base + wave-uniform (tap, channel group) offset
-  int b_off[FN];
-#pragma unroll
-  for (int j = 0; j < FN; ++j) {
-    const int p = min(p0 + wn * Cfg::WN + j * 32 + l32, p_last);     // clamp: columns past the end are discarded
-    const int oy = p / a.Wo, ox = p - oy * a.Wo;
-    b_off[j] = (((oy - oy_first) * a.stride) * a.PW + ox * a.stride + (kLPad - a.pad)) * PP + half * 8;
-  }
   const int a_off = (wm * Cfg::WM + l32) * Cfg::kAPitch + half * 8;
-
-  f32x16_t acc[FM][FN];
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  int g_off[NT], l_off[NT];                                 // g_off < 0: nothing to copy
+  // offsets of this thread's chunks from the patch's first image row, in the image and in LDS; the tallest patch's
+  int g_off[NT], l_off[NT], c_py[NT];
   {
-    const int ntasks = (CB / 8) * PH * a.cpr;
+    const int PHM = a.PS / a.PW, ntasks = (CB / 8) * PHM * a.cpr;
 #pragma unroll
     for (int u = 0; u < NT; ++u) {
       const int task = tid + u * 256;
       const int rest = task / a.cpr;
       // the last chunk of a row is pulled back to end with it: it writes some pixels a second time, with the same values
       const int ix = min((task - rest * a.cpr) * VW, a.W - VW);
-      const int o = rest / PH, py = rest - o * PH;
-      const int iy = iy0 + py;
-      const bool live = task < ntasks && iy >= 0 && iy < a.H;
-      g_off[u] = live ? (8 * o * a.H + iy) * a.W + ix : -1;
+      const int o = rest / PHM, py = rest - o * PHM;
+      c_py[u] = task < ntasks ? py : 1 << 29;                // no chunk: a row that no patch has
+      g_off[u] = (8 * o * a.H + py) * a.W + ix;
       l_off[u] = (py * a.PW + kLPad + ix) * PP + 8 * o;
     }
   }
-  // zero the whole patch once: padding and out-of-image rows are never written again
+  // zero the whole patch once: the columns beside the image are never written again
   for (int c = tid; c < a.PS * PP / 8; c += 256) lds_store16(Ps + c * 8, make_uint4(0, 0, 0, 0));
 
-  auto prefetch_x = [&](int ci0) {
-    const bf16_t* xc = xg + (long)ci0 * plane;
+  int ph_next = 0, iy_next = 0;                              // rows of the patch that is on its way, its first image row
+  auto live_row = [&](int u) { return c_py[u] < ph_next && (unsigned)(iy_next + c_py[u]) < (unsigned)a.H; };
+  auto prefetch_x = [&](int tn, int ci0) {
+    const int oy0 = out_row(tn * Cfg::kBN);
+    iy_next = oy0 * a.stride - a.pad;
+    ph_next = (out_row(last_of(tn)) - oy0) * a.stride + 3;   // <= PS / PW
+    const bf16_t* xc = xg + (long)ci0 * plane + (long)iy_next * a.W;
 #pragma unroll
     for (int u = 0; u < NT; ++u) {
-      if (g_off[u] < 0) continue;
+      if (!live_row(u)) continue;
 #pragma unroll
       for (int c = 0; c < 8; ++c) {
         const bf16_t* p = xc + g_off[u] + c * plane;
@@ -180,18 +172,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Cfg::kMinWa
       }
     }
   };
-  auto prefetch = [&](int ci0) {
-    prefetch_w(ci0);
-    prefetch_x(ci0);
-  };
   // selectors of perm(hi, lo, sel): 16 bits of `lo` (its low or high half) below 16 bits of `hi`
   auto pick = [](int lo_half, int hi_half) -> uint32_t {
     return (lo_half ? 0x0302u : 0x0100u) | ((hi_half ? 0x0706u : 0x0504u) << 16);
   };
-  auto commit = [&]() {
+  auto commit = [&](bool first, bool weights) {
 #pragma unroll
     for (int t = 0; t < Cfg::kWPer; ++t) {
-      if (FUSED || w_dst[t] < 0) continue;
+      if (FUSED || !weights || w_dst[t] < 0) continue;
 #pragma unroll
       for (int tap = 0; tap < 9; ++tap) {
         uint32_t o[4];
@@ -205,7 +193,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Cfg::kMinWa
     }
 #pragma unroll
     for (int u = 0; u < NT; ++u) {
-      if (g_off[u] < 0) continue;
+      if (!live_row(u)) {
+        if (first && c_py[u] < ph_next)                        // rows past the image: zero for all of the tile's blocks
+          for (int i = 0; i < VW; ++i) lds_store16(Ps + l_off[u] + i * PP, make_uint4(0, 0, 0, 0));
+        continue;
+      }
 #pragma unroll
       for (int i = 0; i < VW; ++i) {
         uint32_t o[4];
@@ -217,7 +209,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Cfg::kMinWa
     }
   };
 
-  prefetch_x(0);
+  prefetch_x(t0, 0);
   if constexpr (FUSED) {
     for (int c = tid; c < Cfg::kBM * Cfg::kAPitch / 8; c += 256) lds_store16(As + c * 8, make_uint4(0, 0, 0, 0));
     __syncthreads();
@@ -265,35 +257,70 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Cfg::kMinWa
       }
     }
   }
-  __syncthreads();                                         // the zero fills are complete
-  for (int ci0 = 0; ci0 < a.cig; ci0 += CB) {
-    commit();
-    __syncthreads();
-    if (ci0 + CB < a.cig) prefetch(ci0 + CB);
-#pragma unroll
-    for (int tap = 0; tap < 9; ++tap) {
-      const int tap_off = ((tap / 3) * a.PW + tap % 3) * PP;           // wave-uniform
-#pragma unroll
-      for (int g = 0; g < CB / 16; ++g) {
-        bf16x8_t af[FM], bfr[FN];
-#pragma unroll
-        for (int i = 0; i < FM; ++i) af[i] = *(const lds_bf16x8_t*)(As + a_off + i * 32 * Cfg::kAPitch + tap * CB + g * 16);
-#pragma unroll
-        for (int j = 0; j < FN; ++j) bfr[j] = *(const lds_bf16x8_t*)(Ps + b_off[j] + tap_off + g * 16);
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-          for (int j = 0; j < FN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
-      }
-    }
-    __syncthreads();
-  }
-
-  const long coff = (long)b * a.y_image + (long)G * a.y_group + (long)row0 * a.HoWo + p0;
+  const long out0 = (long)b * a.y_image + (long)G * a.y_group + (long)row0 * a.HoWo;
   const long rvo = (long)G * a.cog + row0;
-  gemm_epilogue<Cfg>(acc, (lds_f32_t*)smem_raw, a.y + coff, a.R ? a.R + coff : nullptr, a.HoWo, rows_left, cols_left,
-                     a.ep, rvo, 0);
+  const bool one_block = a.cig == CB;                      // its weights stay in LDS for the whole run
+  // Several blocks: all loads have landed, on every path, before the next are issued.  The compiler cannot tell by itself
+  // (rows past the image skip their part of a commit) and would wait for a block's weights in the middle of issuing its
+  // pixel loads, whose addresses it builds in registers that it takes to be still waiting (4 models, 8 images, 128 channels
+  // at 28 x 28: 19.3 -> 18.1 us).  One block has no weights on the way, and is as fast without.
+  auto landed = [&] { if (!one_block) __builtin_amdgcn_s_waitcnt(0x0f70); };         // vmcnt(0)
+  landed();
+  __syncthreads();                                         // the zero fills are complete
+  for (int tn = t0; tn < t1; ++tn) {
+    const int p0 = tn * Cfg::kBN, p_last = last_of(tn), oy_first = out_row(p0);
+    // ---- fragment addresses (elements): per-lane base + wave-uniform (tap, channel group) offset
+    int b_off[FN];
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+      const int p = min(p0 + wn * Cfg::WN + j * 32 + l32, p_last);     // clamp: columns past the end are discarded
+      const int oy = out_row(p), ox = p - oy * a.Wo;
+      b_off[j] = (((oy - oy_first) * a.stride) * a.PW + ox * a.stride + (kLPad - a.pad)) * PP + half * 8;
+    }
+    f32x16_t acc[FM][FN];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    for (int ci0 = 0; ci0 < a.cig; ci0 += CB) {
+      commit(ci0 == 0, !one_block || tn == t0);
+      __syncthreads();
+      // the next block, or the next tile's first one, is on its way while this one is multiplied
+      const bool last = ci0 + CB == a.cig;
+      const int ci_next = last ? 0 : ci0 + CB;
+      if (!last || tn + 1 < t1) {
+        if (!one_block) prefetch_w(ci_next);
+        prefetch_x(last ? tn + 1 : tn, ci_next);
+      }
+#pragma unroll
+      for (int tap = 0; tap < 9; ++tap) {
+        const int tap_off = ((tap / 3) * a.PW + tap % 3) * PP;           // wave-uniform
+#pragma unroll
+        for (int g = 0; g < CB / 16; ++g) {
+          bf16x8_t af[FM], bfr[FN];
+#pragma unroll
+          for (int i = 0; i < FM; ++i) af[i] = *(const lds_bf16x8_t*)(As + a_off + i * 32 * Cfg::kAPitch + tap * CB + g * 16);
+#pragma unroll
+          for (int j = 0; j < FN; ++j) bfr[j] = *(const lds_bf16x8_t*)(Ps + b_off[j] + tap_off + g * 16);
+#pragma unroll
+          for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
+        }
+      }
+      landed();
+      __syncthreads();
+    }
+    bf16_t* const C = a.y + out0 + p0;
+    const bf16_t* const R = a.R ? a.R + out0 + p0 : nullptr;
+    const int rw = wm * Cfg::WM, cw = wn * Cfg::WN, ncol = a.HoWo - p0;
+    if (a.ep.act == NF_ACT_RELU) plane_epilogue<FM, FN, NF_ACT_RELU>(acc, C, R, a.HoWo, a.ep, rvo, rw, cw, rows_left, ncol);
+    else if (a.ep.act == NF_ACT_GELU) plane_epilogue<FM, FN, NF_ACT_GELU>(acc, C, R, a.HoWo, a.ep, rvo, rw, cw, rows_left, ncol);
+    else plane_epilogue<FM, FN, NF_ACT_NONE>(acc, C, R, a.HoWo, a.ep, rvo, rw, cw, rows_left, ncol);
+  }
 }
 
 }  // namespace nf

@@ -1,4 +1,5 @@
 // Instantiation and launch of the tap-major 3x3 convolution kernels (conv_tap.h, bf16).
+#include <algorithm>
 #include <atomic>
 #include <cstdlib>
 
@@ -8,7 +9,7 @@
 namespace nf {
 
 template <class Cfg, int VW, int NT, bool FUSED>
-static nf_status launch_tap_kernel(long long total, int lds, const ConvPatchArgs& a, hipStream_t s) {
+static nf_status launch_tap_kernel(long long total, int lds, const ConvTapArgs& a, hipStream_t s) {
   auto kern = conv_tap_kernel<Cfg, VW, NT, FUSED>;
   if (lds > 64 * 1024) {
     static std::atomic<bool> opted_in{false};        // per kernel: idempotent, a benign race
@@ -24,11 +25,15 @@ static nf_status launch_tap_kernel(long long total, int lds, const ConvPatchArgs
 }
 
 template <class Cfg, bool FUSED = false>
-static nf_status launch_tap(ConvPatchArgs& a, int B, hipStream_t s) {
+static nf_status launch_tap(const ConvPatchArgs& args, int B, hipStream_t s) {
+  ConvTapArgs a;
+  (ConvPatchArgs&)a = args;
   a.tiles_m = (a.cog + Cfg::kBM - 1) / Cfg::kBM;
   a.tiles_n = (a.HoWo + Cfg::kBN - 1) / Cfg::kBN;
-  const long long total = (long long)a.tiles_m * a.tiles_n * a.nG * B;
-  if (total <= 0 || total > 0x7fffffffLL) return NF_EUNSUPPORTED;
+  const long long groups = (long long)a.tiles_m * a.nG * B, tiles = groups * a.tiles_n;
+  if (tiles <= 0 || tiles > 0x7fffffffLL || (long long)a.HoWo * a.Wo >= (1LL << 32)) return NF_EUNSUPPORTED;
+  a.rcp_wo = a.Wo == 1 ? 0u : (unsigned)(((1ULL << 32) + a.Wo - 1) / a.Wo);
+  a.one_wo = a.Wo == 1 ? ~0u : 0u;
   a.PS = (a.PS + 7) / 8 * 8;
   // Pixels per chunk: the width with the fewest chunks per thread (a chunk is 8 loads and up to 32 staging registers),
   // the narrowest of those, which spreads the chunks over most threads.  Chunks start at any 2-byte address, so widths
@@ -44,6 +49,21 @@ static nf_status launch_tap(ConvPatchArgs& a, int B, hipStream_t s) {
   }
   const int lds = Cfg::lds_bytes(a.PS);
   if (lds > 160 * 1024) return NF_EUNSUPPORTED;
+  // Tiles per workgroup: the split with the fewest tile times one after another, half a tile's for the start of a workgroup
+  // (its addresses, the zero fill, the first loads), over two workgroups per CU, one where two patches do not fit in LDS.
+  // 32 models, 64 channels at 56 x 56, run 1 (800 workgroups) 22.4 us, 2 (416) 20.2, 4 (224) 28; four images of them 1:
+  // 64.0, 7 (512) 63.2, 5 (640, a second round for a quarter of the chip) 73.6.  16 models of fused groups at
+  // stride 2, 256 channels, 56 -> 28, one workgroup per CU: 1 (896) 24.2, 2 (512) 19.9, 4 (256) 18.9.
+  {
+    const int slots = lds * 2 <= 160 * 1024 ? 512 : 256;
+    double best = 0;
+    for (int runs = 1, run; runs <= a.tiles_n; runs = run > 1 ? (a.tiles_n + run - 2) / (run - 1) : runs + 1) {
+      run = (a.tiles_n + runs - 1) / runs;
+      const double t = (double)((groups * runs + slots - 1) / slots) * (run + 0.5);
+      if (runs == 1 || t < best) { best = t; a.run = run; a.runs = runs; }
+    }
+  }
+  const long long total = groups * a.runs;
 #define NF_TAP(VW_, NT_) return launch_tap_kernel<Cfg, VW_, NT_, FUSED>(total, lds, a, s)
   if (nt > 0) switch (a.VW) {
     case 8: if (nt == 1) NF_TAP(8, 1); if (nt == 2) NF_TAP(8, 2); break;     // 32 staging registers per task
