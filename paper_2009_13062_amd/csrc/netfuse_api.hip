@@ -494,12 +494,12 @@ static int pick_frag(int N, int Nout, int K, int M) {
   return pick;
 }
 
-// The 256 x 256 streaming kernel on packed weights (several column tiles per workgroup through one pipeline;
-// gemm_stream.h).  It takes the shapes the 128-row fragment kernel has no tile for (output widths that are
-// multiples of 256 but not of 96, 288 or 384), and it is preferred where it measured faster: with a GELU
-// epilogue and at least three tiles per compute unit (768 -> 3072 at 512 rows and 32 models: 102 against 107 us;
-// without the GELU the fragment kernel is ahead: 75 against 88, 82 against 98, 32 against 39 us on the other
-// three encoder shapes).  Returns the number of column tiles per workgroup, 0 = not applicable.
+// The 256 x 256 streaming kernel on packed weights (several column tiles per workgroup through one pipeline; gemm_stream.h).  It takes the
+// shapes the 128-row fragment kernel has no tile for (output widths that are multiples of 256 but not of 96, 288 or 384, k that is no
+// multiple of 128).  `preferred`: 256 x 256 tiles measured faster than the fragment kernel's, with a GELU epilogue and at least three of
+// them per compute unit (without the GELU the fragment kernel is ahead: 75 against 88, 82 against 98, 32 against 39 us on the other
+// three encoder shapes); from 256 k up it is then gemm_ring.h's tile that runs (see netfuse_linear_packed).  Returns the number of
+// column tiles per workgroup, 0 = not applicable.
 static int pick_packed_stream(int N, int Nout, int K, int M, int act, bool* preferred) {
   *preferred = false;
   if (N % 256 || Nout % 256 || K % 32) return 0;
@@ -573,6 +573,14 @@ nf_status netfuse_linear_packed(const void* X, const void* Wp, const float* bias
   a.ep.col_bias = bias; a.ep.col_vec_stride0 = Nout;
   a.ep.act = act; a.ep.act_before_residual = 1;
   if (ps > 0 && (ps_preferred || f < 0)) {
+    // The 256 x 256 tile of gemm_ring.h (64 k per barrier) against the streaming one (32), GELU, us: 32 models of 512 rows 768 -> 3072 106.3 -> 101.6, 1536 -> 3072 184 -> 168, 3072
+    // -> 3072 327 -> 297; 64 of 256 rows 125 -> 111; 20 of 512 rows 4096 -> 5120 482 -> 445; 1 of 16384 rows 1024 -> 4096 173 -> 168;
+    // 32 of 512 rows 256 -> 3072 57.8 -> 57.6, 320 -> 3072 63.3 -> 63.7.  Below 256 k the streaming one: 400 models of 256 rows
+    // 128 -> 512 62.3 against 63.8, 64 -> 512 51.7 against 55.7.
+    if (ps_preferred && ring_fits(Nout, K)) {
+      const nf_status st = launch_gemm_ring(RP256x256, true, L, (hipStream_t)stream);
+      if (st != NF_EUNSUPPORTED) return st;
+    }
     a.ep.vec_store = 2;
     const nf_status st = launch_gemm_stream_packed(ps, L, (hipStream_t)stream);
     if (st != NF_EUNSUPPORTED || f < 0) return st;
