@@ -30,7 +30,7 @@
 // (conv_plane.h's epilogue): a tile per workgroup paid for its addresses, its zero fill and an empty memory pipe with
 // every tile, and read the weights of a single block (32 channels, or fused groups) again for each.  Measured per layer, one
 // tile -> a run: 16 models' fused groups of 4 channels at 56 x 56 19.1 -> 15.8 us, of 8 at 28 x 28 12.0 -> 9.2, at stride
-// 2 from 56 x 56 25.9 -> 17.9; 32 models' 64 channels at 56 x 56 23.7 -> 21.8; one tile per run, 3 models x 4 images, 128
+// 2 from 56 x 56 25.9 -> 17.9; 32 models' 64 channels at 56 x 56 23.7 -> 21.8 (before the order of the pixel writes below); one tile per run, 3 models x 4 images, 128
 // channels at 25 x 25 10.4 -> 9.9.  The exception is 32 models' 256 channels, 28 -> 14 at stride 2 (30.3 -> 31.7).
 // What bounds it now: LDS reads (a fragment of each operand per MFMA at FM = FN = 1) and their bank conflicts.
 #pragma once
@@ -176,6 +176,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Cfg::kMinWa
   auto pick = [](int lo_half, int hi_half) -> uint32_t {
     return (lo_half ? 0x0302u : 0x0100u) | ((hi_half ? 0x0706u : 0x0504u) << 16);
   };
+  // Neighbouring lanes write VW pixels apart, 5 VW bank groups of 16 bytes: of the 16 groups, 16 lanes meet 2 (VW = 8), 4 or 8.  Every
+  // other run of 16 / VW lanes therefore writes the two pixels of a pair in the other order, 5 groups off,
+  // and twice as many are met, for no instruction more.  us: 64 channels at 56 x 56, 32 models 22.1 -> 20.9, 8 models 8.7 -> 7.9;
+  // 16 models' fused groups of 4 channels 16.0 -> 14.7, of 8 at stride 2 17.9 -> 16.0.  (Swapping the pairs of VW = 8 as well, for a select
+  // per dword, gave nothing more.)
+  const bool flip = VW >= 2 && (tid * VW / 16) % 2;
+  const uint32_t sel_even = flip ? pick(1, 1) : pick(0, 0), sel_odd = flip ? pick(0, 0) : pick(1, 1);
+  const int swap = flip ? PP : 0;
   auto commit = [&](bool first, bool weights) {
 #pragma unroll
     for (int t = 0; t < Cfg::kWPer; ++t) {
@@ -203,8 +211,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Cfg::kMinWa
         uint32_t o[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-          o[q] = __builtin_amdgcn_perm(pv[u][2 * q + 1][i / 2], pv[u][2 * q][i / 2], pick(i % 2, i % 2));
-        lds_store16(Ps + l_off[u] + i * PP, make_uint4(o[0], o[1], o[2], o[3]));
+          o[q] = __builtin_amdgcn_perm(pv[u][2 * q + 1][i / 2], pv[u][2 * q][i / 2], i % 2 ? sel_odd : sel_even);
+        lds_store16(Ps + (i % 2 ? l_off[u] - swap : l_off[u] + swap) + i * PP, make_uint4(o[0], o[1], o[2], o[3]));
       }
     }
   };
