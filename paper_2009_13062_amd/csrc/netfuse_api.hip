@@ -1122,9 +1122,13 @@ nf_status netfuse_maxpool2d(const void* x, void* y, int B, int Ctot, int H, int 
   if (!aligned(x, esz) || !aligned(y, esz)) return NF_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   if (dt == NF_BF16 && k == 3 && stride == 2 && pad == 1 && W % 8 == 0 && aligned(x, 16) && aligned(y, 8)) {
-    // Wo = W / 2 is a multiple of 4: four outputs per thread from 16-byte loads
-    nf_launch(maxpool3x3s2_bf16_kernel, dim3(grid_for(n_out / 4, 256)), dim3(256), 0, s, (const bf16_t*)x,
-                       (bf16_t*)y, H, W, Ho, Wo, (size_t)(n_out / 4));
+    // Wo = W / 2 is a multiple of 4: four outputs of two rows per thread from 16-byte loads
+    const long long total = n_out / Wo / Ho * ((Ho + 1) / 2) * (Wo / 4);
+    const unsigned grid = grid_for(total, 256);
+    if (total + 256LL * grid < (1LL << 32))                  // the loop's index does not wrap either
+      nf_launch((maxpool3x3s2_bf16_kernel<uint32_t>), dim3(grid), dim3(256), 0, s, (const bf16_t*)x, (bf16_t*)y, H, W, Ho, Wo, (uint32_t)total);
+    else
+      nf_launch((maxpool3x3s2_bf16_kernel<size_t>), dim3(grid), dim3(256), 0, s, (const bf16_t*)x, (bf16_t*)y, H, W, Ho, Wo, (size_t)total);
     return launched();
   }
   const unsigned grid = grid_for(n_out, 256);
