@@ -78,12 +78,32 @@ PyObject* done(const char* fn, nf_status st, PyObject* given, at::Tensor& made) 
   }
   return THPVariable_Wrap(std::move(made));
 }
-// The output: the tensor given, of x's type, or a new one.
-bool output(PyObject* given, const at::Tensor& x, at::IntArrayRef shape, at::Tensor* made, void** p) {
-  if (given != Py_None) return operand(given, x.scalar_type(), p);
-  *made = at::empty(shape, x.options());
-  *p = made->data_ptr();
-  return true;
+
+// The interpreter's lock is not held while this lives.
+struct Unlocked {
+  PyThreadState* const state = PyEval_SaveThread();
+  Unlocked() = default;
+  Unlocked(const Unlocked&) = delete;
+  ~Unlocked() noexcept(false) { PyEval_RestoreThread(state); }   // a daemon thread may end here when the interpreter does
+};
+// The output and the call: call(y) on the tensor given, or on a new one.  The allocation may wait for memory and the launch for room
+// in its queue, for as long as the work in front of it takes, so other Python threads run meanwhile, a host callback that the queue
+// waits for among them (0.05 us).  `call` takes no Python object: every operand is a pointer by then.
+template <class F>
+PyObject* produce(const char* fn, PyObject* given, at::IntArrayRef shape, const at::TensorOptions& like, F&& call) {
+  void* y = nullptr;
+  if (!operand(given, at::typeMetaToScalarType(like.dtype()), &y)) return not_taken();
+  at::Tensor made;
+  nf_status st;
+  {
+    Unlocked unlocked;
+    if (given == Py_None) {
+      made = at::empty(shape, like);
+      y = made.data_ptr();
+    }
+    st = call(y);
+  }
+  return done(fn, st, given, made);
 }
 
 // A C++ error (an allocation that fails) is met again, and raised as torch raises it, by the Python path.
@@ -103,13 +123,13 @@ PyObject* matmul(decltype(f_linear) f, const char* name, PyObject* const* a, Py_
     const at::Tensor *X = plain(a[0]), *W = plain(a[1]);
     if (!X || !W || X->dim() != 3 || W->dim() != 3 || W->scalar_type() != X->scalar_type()) return not_taken();
     int M, N, K, No, act;
-    void *b, *r, *y, *s;
+    void *b, *r, *s;
     if (!size(X->size(0), &M) || !size(X->size(1), &N) || !size(X->size(2), &K) || !size(W->size(2), &No) || W->size(0) != M ||
         W->size(1) != K || !operand(a[2], at::kFloat, &b) || !operand(a[3], X->scalar_type(), &r) || !whole(a[4], &act) || !stream_of(a[6], &s))
       return not_taken();
-    at::Tensor made;
-    if (!output(a[5], *X, {M, N, No}, &made, &y)) return not_taken();
-    return done(name, f(X->data_ptr(), W->data_ptr(), (const float*)b, r, y, M, N, K, No, type_of(*X), (nf_act)act, s), a[5], made);
+    const void *x = X->data_ptr(), *w = W->data_ptr();
+    const nf_dtype dt = type_of(*X);
+    return produce(name, a[5], {M, N, No}, X->options(), [=](void* y) { return f(x, w, (const float*)b, r, y, M, N, K, No, dt, (nf_act)act, s); });
   });
 }
 PyObject* linear(PyObject*, PyObject* const* a, Py_ssize_t n) { return matmul(f_linear, "netfuse_linear", a, n); }
@@ -121,7 +141,7 @@ PyObject* layernorm(PyObject*, PyObject* const* a, Py_ssize_t n) {
     if (n != 9) return not_taken();
     const at::Tensor* x = plain(a[0]);
     int M, layout, rows, H;
-    void *g, *b, *r, *y, *s;
+    void *g, *b, *r, *s;
     if (!x || !whole(a[3], &M) || M <= 0 || !whole(a[6], &layout) || !PyFloat_CheckExact(a[5]) || !operand(a[1], at::kFloat, &g) ||
         !operand(a[2], at::kFloat, &b) || !operand(a[4], x->scalar_type(), &r) || !stream_of(a[8], &s))
       return not_taken();
@@ -130,10 +150,13 @@ PyObject* layernorm(PyObject*, PyObject* const* a, Py_ssize_t n) {
     } else if (x->dim() != 2 || !size(x->size(0), &rows) || !size(x->size(1) / M, &H)) {
       return not_taken();
     }
-    at::Tensor made;
-    if (!output(a[7], *x, x->sizes(), &made, &y)) return not_taken();
-    return done("netfuse_layernorm", f_layernorm(x->data_ptr(), r, (const float*)g, (const float*)b, y, M, rows, H, (float)PyFloat_AS_DOUBLE(a[5]),
-                                                 (nf_merge_dim)layout, type_of(*x), s), a[7], made);
+    const void* in = x->data_ptr();
+    const float eps = (float)PyFloat_AS_DOUBLE(a[5]);
+    const nf_dtype dt = type_of(*x);
+    const at::DimVector shape(x->sizes());
+    return produce("netfuse_layernorm", a[7], shape, x->options(), [=](void* y) {
+      return f_layernorm(in, r, (const float*)g, (const float*)b, y, M, rows, H, eps, (nf_merge_dim)layout, dt, s);
+    });
   });
 }
 
@@ -158,16 +181,16 @@ PyObject* attention_packed(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const at::Tensor* Q = plain(a[0]);
     int M, B, S, heads, d;
     float scale;
-    void *mask, *y, *s;
+    void *mask, *s;
     if (!Q || !packed_qkv(*Q, a[1], a[2], a[3], a[4], &M, &B, &S, &heads, &d, &scale) || !operand(a[5], at::kFloat, &mask) || !stream_of(a[7], &s))
       return not_taken();
     const long Hd = (long)heads * d, N = (long)B * S;
-    at::Tensor made;
-    if (!output(a[6], *Q, {M, N, Hd}, &made, &y)) return not_taken();
     const char* base = (const char*)Q->data_ptr();
     const long step = Hd * (long)Q->element_size();
-    return done("netfuse_attention", f_attention(base, base + step, base + 2 * step, (const float*)mask, y, M, B, S, heads, d, N * 3 * Hd, 3 * Hd, scale,
-                                                 type_of(*Q), s), a[6], made);
+    const nf_dtype dt = type_of(*Q);
+    return produce("netfuse_attention", a[6], {M, N, Hd}, Q->options(), [=](void* y) {
+      return f_attention(base, base + step, base + 2 * step, (const float*)mask, y, M, B, S, heads, d, N * 3 * Hd, 3 * Hd, scale, dt, s);
+    });
   });
 }
 // QKV, Kr, B, S, heads, bias_w, bias_r, scale, mask, out, stream
@@ -177,18 +200,20 @@ PyObject* attention_relpos_packed(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const at::Tensor *Q = plain(a[0]), *Kr = plain(a[1]);
     int M, B, S, heads, d;
     float scale;
-    void *bw, *br, *mask, *y, *s;
+    void *bw, *br, *mask, *s;
     if (!Q || !Kr || Kr->scalar_type() != Q->scalar_type() || !packed_qkv(*Q, a[2], a[3], a[4], a[7], &M, &B, &S, &heads, &d, &scale) ||
         !operand(a[5], at::kFloat, &bw) || !operand(a[6], at::kFloat, &br) || !operand(a[8], at::kFloat, &mask) || !stream_of(a[10], &s))
       return not_taken();
     const long Hd = (long)heads * d, N = (long)B * S;
     if (Kr->dim() != 3 || Kr->size(0) != M || Kr->size(1) != 2LL * S || Kr->size(2) != Hd) return not_taken();
-    at::Tensor made;
-    if (!output(a[9], *Q, {M, N, Hd}, &made, &y)) return not_taken();
     const char* base = (const char*)Q->data_ptr();
+    const void* kr = Kr->data_ptr();
     const long step = Hd * (long)Q->element_size();
-    return done("netfuse_attention_relpos", f_relpos(base, base + step, base + 2 * step, Kr->data_ptr(), (const float*)bw, (const float*)br,
-                                                     (const float*)mask, y, M, B, S, heads, d, N * 3 * Hd, 3 * Hd, scale, type_of(*Q), s), a[9], made);
+    const nf_dtype dt = type_of(*Q);
+    return produce("netfuse_attention_relpos", a[9], {M, N, Hd}, Q->options(), [=](void* y) {
+      return f_relpos(base, base + step, base + 2 * step, kr, (const float*)bw, (const float*)br, (const float*)mask, y, M, B, S, heads, d,
+                      N * 3 * Hd, 3 * Hd, scale, dt, s);
+    });
   });
 }
 
@@ -198,7 +223,7 @@ PyObject* conv2d(PyObject*, PyObject* const* a, Py_ssize_t n) {
     if (n != 14) return not_taken();
     const at::Tensor *x = plain(a[0]), *w = plain(a[1]);
     int M, g, stride, pad, dil, act, B, Ct, H, W, Co, cig, KH, KW;
-    void *bias, *scale, *shift, *r, *y, *s;
+    void *bias, *scale, *shift, *r, *s;
     if (!x || !w || x->dim() != 4 || w->dim() != 4 || w->scalar_type() != x->scalar_type() || !whole(a[2], &M) || M <= 0 || !whole(a[3], &g) || g <= 0 ||
         !operand(a[4], at::kFloat, &bias) || !operand(a[5], at::kFloat, &scale) || !operand(a[6], at::kFloat, &shift) ||
         !operand(a[7], x->scalar_type(), &r) || !whole(a[8], &stride) || stride <= 0 || !whole(a[9], &pad) || pad < 0 || !whole(a[10], &dil) || dil <= 0 ||
@@ -209,10 +234,12 @@ PyObject* conv2d(PyObject*, PyObject* const* a, Py_ssize_t n) {
       return not_taken();
     const int64_t eh = (int64_t)H + 2LL * pad - (int64_t)dil * (KH - 1) - 1, ew = (int64_t)W + 2LL * pad - (int64_t)dil * (KW - 1) - 1;
     if (eh < 0 || ew < 0) return not_taken();
-    at::Tensor made;
-    if (!output(a[12], *x, {B, Co, eh / stride + 1, ew / stride + 1}, &made, &y)) return not_taken();
-    return done("netfuse_conv2d", f_conv2d(x->data_ptr(), w->data_ptr(), (const float*)bias, (const float*)scale, (const float*)shift, r, y, M, B, Ct / M,
-                                           Co / M, g, H, W, KH, KW, stride, pad, dil, type_of(*x), (nf_act)act, s), a[12], made);
+    const void *in = x->data_ptr(), *wt = w->data_ptr();
+    const nf_dtype dt = type_of(*x);
+    return produce("netfuse_conv2d", a[12], {B, Co, eh / stride + 1, ew / stride + 1}, x->options(), [=](void* y) {
+      return f_conv2d(in, wt, (const float*)bias, (const float*)scale, (const float*)shift, r, y, M, B, Ct / M, Co / M, g, H, W, KH, KW, stride, pad,
+                      dil, dt, (nf_act)act, s);
+    });
   });
 }
 

@@ -1,5 +1,7 @@
 """The natively marshalled calls against the Python functions: the same outputs, and for every call that either refuses the same
 exception (the native path hands what it does not take to the Python one)."""
+import ctypes
+
 import pytest
 import torch
 
@@ -85,3 +87,23 @@ def test_runs_on_the_current_stream_and_returns_the_output_given(nf):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, want)
+
+
+def test_other_python_threads_run_during_a_call(nf):
+    """With the interpreter's own "does this thread hold the lock" (1 or 0, read as a status) in the place of every entry point."""
+    address = lambda f: ctypes.cast(f, ctypes.c_void_p).value
+    native, stream, x, g = nf._native, 0, _t(2, 16, 64), _t(2 * 64)
+    w, qkv, kr, image, taps = _t(2, 64, 32), _t(2, 16, 3 * 64), _t(2, 16, 64), _t(1, 4, 5, 5), _t(4, 2, 3, 3)
+    calls = [(native.linear, (x, w, None, None, 0)), (native.linear_packed, (x, w, None, None, 0)), (native.layernorm, (x, g, g, 2, None, 1e-5, 0)),
+             (native.attention_packed, (qkv, 2, 8, 2, None, None)), (native.attention_relpos_packed, (qkv, kr, 2, 8, 2, None, None, None, None)),
+             (native.conv2d, (image, taps, 2, 1, None, None, None, None, 1, 0, 1, 0))]
+    native.bind(nf._check, *[address(ctypes.pythonapi.PyGILState_Check)] * 6)
+    try:
+        for fn, args in calls:
+            made = fn(*args, None, stream)                    # raises if the lock was held
+            assert isinstance(made, torch.Tensor), fn.__name__
+            assert fn(*args, made, stream) is made
+    finally:
+        lib = nf.lib
+        native.bind(nf._check, *(address(f) for f in (lib.netfuse_linear, lib.netfuse_linear_packed, lib.netfuse_layernorm, lib.netfuse_attention,
+                                                      lib.netfuse_attention_relpos, lib.netfuse_conv2d)))
