@@ -25,14 +25,13 @@
 // The patch carries its zero padding: it is zeroed once, and every channel block overwrites only the
 // in-image pixels and clears the rows past the image.  Image column ix lives at patch column ix + kLPad.
 //
-// One workgroup = one (image, group, BM output channels) and a RUN of 128-position tiles.  While a block is multiplied the
-// next one of the tile, or the first of the next tile, is in flight in registers, and the outputs leave from registers
-// (conv_plane.h's epilogue): a tile per workgroup paid for its addresses, its zero fill and an empty memory pipe with
-// every tile, and read the weights of a single block (32 channels, or fused groups) again for each.  Measured per layer, one
-// tile -> a run: 16 models' fused groups of 4 channels at 56 x 56 19.1 -> 15.8 us, of 8 at 28 x 28 12.0 -> 9.2, at stride
-// 2 from 56 x 56 25.9 -> 17.9; 32 models' 64 channels at 56 x 56 23.7 -> 21.8 (before the order of the pixel writes below); one tile per run, 3 models x 4 images, 128
-// channels at 25 x 25 10.4 -> 9.9.  The exception is 32 models' 256 channels, 28 -> 14 at stride 2 (30.3 -> 31.7).
-// What bounds it now: LDS reads (a fragment of each operand per MFMA at FM = FN = 1) and their bank conflicts.
+// One workgroup = one (image, group, BM output channels) and a RUN of 128-position tiles, one where a group has several blocks
+// (tap_run in conv_tap_inst.hip).  While a block is multiplied the next one of the tile, or the first of the next tile, is in flight in
+// registers, and the outputs leave from registers (conv_plane.h's epilogue): single-block tiles of their own paid for their
+// addresses, their zero fill and an empty memory pipe every time, and read the same weights again.  Per layer, a tile per workgroup and an
+// epilogue through LDS -> this: 16 models' fused groups of 4 channels at 56 x 56 19.1 -> 14.7 us, of 8 at stride 2 from 56 x 56 25.9 ->
+// 16.0; over 2430 problems of several blocks 8 % less time, over 3300 of fused groups 22 %.
+// What bounds it: LDS reads (a fragment of each operand per MFMA at FM = FN = 1) and their bank conflicts.
 #pragma once
 #include "conv_patch.h"
 #include "conv_plane.h"
@@ -268,11 +267,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Cfg::kMinWa
   const long out0 = (long)b * a.y_image + (long)G * a.y_group + (long)row0 * a.HoWo;
   const long rvo = (long)G * a.cog + row0;
   const bool one_block = a.cig == CB;                      // its weights stay in LDS for the whole run
-  // Several blocks: all loads have landed, on every path, before the next are issued.  The compiler cannot tell by itself
-  // (rows past the image skip their part of a commit) and would wait for a block's weights in the middle of issuing its
-  // pixel loads, whose addresses it builds in registers that it takes to be still waiting (4 models, 8 images, 128 channels
-  // at 28 x 28: 19.3 -> 18.1 us).  One block has no weights on the way, and is as fast without.
-  auto landed = [&] { if (!one_block) __builtin_amdgcn_s_waitcnt(0x0f70); };         // vmcnt(0)
+  // 64 rows, one task per thread, three blocks and more: all loads have landed, on every path, before the next are issued.  The compiler
+  // cannot tell by itself (rows past the image skip their part of a commit) and waits for a block's weights in the middle of issuing
+  // its pixel loads, whose addresses it builds in registers that it takes to be still waiting.  24 models, 96 channels at 33 x 33 17.3 us
+  // without, 15.6 with, 8 models of 4 images, 128 at 28 x 28 5 %; two blocks up to 5 % the other way, 32 rows and stride 2 2 %.
+  const bool wait = Cfg::kBM == 64 && NT == 1 && a.cig > 2 * CB;
+  auto landed = [&] { if (wait) __builtin_amdgcn_s_waitcnt(0x0f70); };         // vmcnt(0)
   landed();
   __syncthreads();                                         // the zero fills are complete
   for (int tn = t0; tn < t1; ++tn) {

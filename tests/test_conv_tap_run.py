@@ -1,0 +1,32 @@
+"""How many 128-position tiles a workgroup of the tap-major 3x3 kernel takes (conv_tap_inst.hip), asked of the library on the CPU."""
+import ctypes
+
+import pytest
+
+
+def run_of(cig, groups, tiles, lds):
+    import paper_2009_13062_amd as nf
+    f = nf.lib.netfuse_conv_tap_run
+    f.argtypes, f.restype = [ctypes.c_int, ctypes.c_longlong, ctypes.c_int, ctypes.c_int], ctypes.c_int
+    return f(cig, groups, tiles, lds)
+
+
+# Longer runs of these took up to 1.6 times as long: fewer workgroups, and two on a compute unit do not halve each other's rate.
+@pytest.mark.parametrize("cig,groups,tiles,lds", [(256, 288, 4, 66688), (256, 192, 3, 48384), (192, 128, 2, 49664), (64, 64, 9, 46464), (64, 1, 98, 89088),
+                                                  (512, 4096, 25, 162176), (256, 48, 32, 68608)])
+def test_several_blocks_take_one_tile(cig, groups, tiles, lds):
+    assert run_of(cig, groups, tiles, lds) == 1
+
+
+# One block: the best of every run measured, where another was at least a tenth slower.
+@pytest.mark.parametrize("groups,tiles,lds,run", [(128, 5, 49024, 1), (96, 8, 45824, 1), (32, 20, 50944, 1), (384, 7, 47104, 4), (128, 41, 54144, 11), (192, 25, 53504, 7),
+                                                  (384, 13, 50304, 7), (768, 2, 50304, 2), (768, 4, 47744, 4), (48, 79, 65664, 8), (256, 5, 49024, 2)])
+def test_one_block_takes_the_run_that_fills_the_chip(groups, tiles, lds, run):
+    assert run_of(32, groups, tiles, lds) == run
+
+
+def test_every_run_is_in_range():
+    for groups in (1, 7, 255, 256, 257, 5000, 1 << 30):
+        for tiles in (1, 2, 3, 63, 64, 65, 524288):
+            for lds in (20000, 50000, 54614, 81920, 81921, 163840):
+                assert 1 <= run_of(32, groups, tiles, lds) <= tiles
