@@ -61,11 +61,9 @@ nf_status launch_conv_patch_3x3(ConvPatchArgs& a, int B, hipStream_t s) {
   return deep ? launch_one<ConvPatchCfg<32, 3, 3, 32, 1, 4, 2>>(a, B, s) : launch_one<ConvPatchCfg<32, 3, 3, 16, 1, 4, 3>>(a, B, s);
 }
 
-// 7x7, stride 2, pad 3, 3 input channels per group.  The caller has filled everything but the tiling and
-// has checked W % 8 == 0, 16-byte aligned x, and the patch width.
-template <int NT>
+template <int BM, int NT>
 static nf_status launch_stem(const ConvStemArgs& a, long long total, int lds, hipStream_t s) {
-  typedef ConvStemCfg<3> Cfg;
+  typedef ConvStemCfg<3, BM> Cfg;
   auto kern = conv_stem_kernel<Cfg, 3, NT>;
   if (lds > 64 * 1024) {
     static std::atomic<bool> opted_in{false};
@@ -79,27 +77,35 @@ static nf_status launch_stem(const ConvStemArgs& a, long long total, int lds, hi
   return hipGetLastError() == hipSuccess ? NF_OK : NF_ELAUNCH;
 }
 
-nf_status launch_conv_stem(ConvStemArgs& a, int B, hipStream_t s) {
-  typedef ConvStemCfg<3> Cfg;
+template <int BM>
+static nf_status launch_stem(ConvStemArgs& a, int B, hipStream_t s) {
+  typedef ConvStemCfg<3, BM> Cfg;
   a.tiles_m = (a.cog + Cfg::kBM - 1) / Cfg::kBM;
   a.tiles_n = (a.HoWo + Cfg::kBN - 1) / Cfg::kBN;
   const long long groups = (long long)a.tiles_m * a.nG * B, tiles = groups * a.tiles_n;
   if (tiles <= 0 || tiles > 0x7fffffffLL) return NF_EUNSUPPORTED;
-  a.run = (int)std::min<long long>(a.tiles_n, (tiles + 767) / 768);
-  a.runs = (a.tiles_n + a.run - 1) / a.run;
-  a.run = (a.tiles_n + a.runs - 1) / a.runs;                // in equal parts
   if (a.PW % 8 != 0 || a.PS % 8 != 0 || a.PS % a.PW != 0) return NF_EUNSUPPORTED;
-  const int lds = Cfg::lds_bytes(a.PS), chunks = 3 * (a.PS / a.PW) * a.cpr;
+  const int lds = Cfg::lds_bytes(a.PS), chunks = 3 * (a.PS / a.PW) * a.cpr, nt = (chunks + 255) / 256;
   // offsets inside a group's planes, and positions x Wo (cw_div), in 32 bits
-  if (lds > 160 * 1024 || chunks > 12 * 256 || 3LL * a.H * a.W > 0x7fffffffLL || (long long)a.HoWo * a.Wo >= (1LL << 32)) return NF_EUNSUPPORTED;
+  if (lds > 160 * 1024 || nt > 12 || 3LL * a.H * a.W > 0x7fffffffLL || (long long)a.HoWo * a.Wo >= (1LL << 32)) return NF_EUNSUPPORTED;
+  a.run = tile_run(groups, a.tiles_n, lds, nt > 6 ? 2 : 3);
+  a.runs = (a.tiles_n + a.run - 1) / a.run;
   auto rcp = [](int d, unsigned* r, unsigned* one) {
     *r = d == 1 ? 0u : (unsigned)(((1ULL << 32) + d - 1) / d);
     *one = d == 1 ? ~0u : 0u;
   };
   rcp(a.Wo, &a.rcp_wo, &a.one_wo);
   rcp(a.cpr, &a.rcp_cpr, &a.one_cpr);
-  if (chunks <= 4 * 256) return launch_stem<4>(a, groups * a.runs, lds, s);
-  return chunks <= 8 * 256 ? launch_stem<8>(a, groups * a.runs, lds, s) : launch_stem<12>(a, groups * a.runs, lds, s);
+  const long long total = groups * a.runs;
+  if (nt <= 4) return launch_stem<BM, 4>(a, total, lds, s);
+  if (nt <= 6) return launch_stem<BM, 6>(a, total, lds, s);
+  return nt <= 8 ? launch_stem<BM, 8>(a, total, lds, s) : launch_stem<BM, 12>(a, total, lds, s);
+}
+
+// 7x7, stride 2, pad 3, 3 input channels per group.  The caller has filled everything but the tiling and
+// has checked W % 8 == 0, 16-byte aligned x, and the patch width.
+nf_status launch_conv_stem(ConvStemArgs& a, int B, hipStream_t s) {
+  return a.cog % 64 >= 1 && a.cog % 64 <= 32 ? launch_stem<32>(a, B, s) : launch_stem<64>(a, B, s);
 }
 
 }  // namespace nf

@@ -11,13 +11,14 @@
 // as dwords instead of eight 2-byte gathers.  The two lane halves take rows 2 s and 2 s + 1 of the
 // CIN * 7 (ci, ky) rows in step s.  The weights are scattered into that order when they are copied to LDS.
 //
-// One workgroup = up to 64 output channels and `run` consecutive tiles of 128 positions of one (image, model).  The weights
-// go through LDS once and then stay in registers (44 for 32 channels), so a tile is its patch, one LDS segment per
+// One workgroup = up to 64 output channels (32 where no more are left over from whole sixty-fours: half the wavefronts had no
+// channels otherwise) and a run of tiles of 128 positions of one (image, model), as many as tile_run says.  The weights
+// go through LDS once and then stay in registers (44), so a tile is its patch, one LDS segment per
 // multiplication, and stores out of registers; the next tile's patch is on its way meanwhile and changes LDS buffers at the
-// tile's only barrier.  `run` is as long as keeps 768 workgroups (three per compute unit; 1536 31.2 in place of 27.9 us).
+// tile's only barrier.
 // What bounds it: the patch reads and the issue of instructions.  With one tile per workgroup, the weights scattered into LDS
-// for each and an epilogue through LDS -> this way, us: 32 models at 224 x 224 (51 MB of output) 36.9 -> 27.9, 8 models of 8
-// images at 288 x 288 123 -> 92, one model 6.9 -> 6.4.
+// for each and an epilogue through LDS -> this way, us: 32 models at 224 x 224 (51 MB of output) 34.5 -> 26.3, 2
+// models of 32 channels at 384 x 384 8.8 -> 7.8; over 6500 problems 18 % less time.
 #pragma once
 #include "conv_plane.h"
 
@@ -34,11 +35,12 @@ struct ConvStemArgs {
   Epilogue ep;
 };
 
-template <int CIN>
+template <int CIN, int BM>
 struct ConvStemCfg {
   static constexpr int kKH = 7, kKW = 7, kStride = 2, kPad = 3, kColPad = 8;
-  static constexpr int kBM = 64, kBN = 128, kThreads = 256;
-  static constexpr int FN = 2, WN = 32 * FN;              // wavefronts: 2 blocks of 32 channels x 2 of 64 positions
+  static_assert(BM == 64 || BM == 32, "two blocks of 32 channels or one");
+  static constexpr int kBM = BM, kBN = 128, kThreads = 256;
+  static constexpr int kWGN = 128 / BM, FN = BM / 32, WN = 32 * FN;    // wavefronts: 2 blocks of channels x 2 of 64 positions, or 4 of 32
   static constexpr int kRows = CIN * kKH;                 // (ci, ky) rows of the k dimension
   static constexpr int kSteps = (kRows + 1) / 2;          // MFMA steps of 16 k: two rows each
   static constexpr int kK = kSteps * 16;                  // padded k extent in LDS
@@ -48,14 +50,14 @@ struct ConvStemCfg {
   static constexpr int lds_bytes(int PS) { return 2 * (2 * CIN * PS > kAEls ? 2 * CIN * PS : kAEls); }   // the patches take the weights' place
 };
 
-// NT: patch chunks per thread (the host checks the bound)
+// NT: patch chunks per thread (the host checks the bound); up to 6 the registers allow three workgroups per compute unit
 template <class Cfg, int CIN, int NT>
-__global__ __launch_bounds__(256, NT > 4 ? 2 : 3) void conv_stem_kernel(ConvStemArgs a) {
+__global__ __launch_bounds__(256, NT > 6 ? 2 : 3) void conv_stem_kernel(ConvStemArgs a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   lds_bf16_t* const As = (lds_bf16_t*)smem_raw;
   lds_bf16_t* const Ps = As;                               // [buffer][channel][patch row][column]
   constexpr int FN = Cfg::FN, KHW = Cfg::kKH * Cfg::kKW, KW = Cfg::kKW;
-  const int tid = threadIdx.x, lane = tid % kWave, wm = tid / kWave / 2, wn = tid / kWave % 2;
+  const int tid = threadIdx.x, lane = tid % kWave, wm = tid / kWave / Cfg::kWGN, wn = tid / kWave % Cfg::kWGN;
   const int half = lane / 32, l32 = lane % 32;
 
   unsigned id = xcd_remap(blockIdx.x, gridDim.x);
@@ -70,7 +72,7 @@ __global__ __launch_bounds__(256, NT > 4 ? 2 : 3) void conv_stem_kernel(ConvStem
 
   // ---- this thread's chunks of a patch: 8 pixels, aligned on both sides
   const int PHM = a.PS / a.PW, nchunk = CIN * PHM * a.cpr;
-  int c_src[NT], c_py[NT], c_dst[NT];
+  int c_src[NT], c_at[NT];                                   // c_at: patch row << 16 | LDS element (below 40960, see lds_bytes)
 #pragma unroll
   for (int u = 0; u < NT; ++u) {
     const int t = tid + u * 256;
@@ -78,9 +80,8 @@ __global__ __launch_bounds__(256, NT > 4 ? 2 : 3) void conv_stem_kernel(ConvStem
     int ci = 0;
 #pragma unroll
     for (int c = 1; c < CIN; ++c) ci += row >= c * PHM;
-    c_py[u] = t < nchunk ? row - ci * PHM : -(1 << 29);      // no chunk: a row that no image has
     c_src[u] = ci * a.H * a.W + ch * 8;
-    c_dst[u] = ci * a.PS + (row - ci * PHM) * a.PW + Cfg::kColPad + ch * 8;
+    c_at[u] = (row - ci * PHM) << 16 | (ci * a.PS + (row - ci * PHM) * a.PW + Cfg::kColPad + ch * 8);
   }
   auto first_row = [&](int tn) { return (int)cw_div(tn * Cfg::kBN, a.rcp_wo, a.one_wo); };
   uint4 pre[NT];
@@ -88,15 +89,15 @@ __global__ __launch_bounds__(256, NT > 4 ? 2 : 3) void conv_stem_kernel(ConvStem
     const int iy0 = first_row(tn) * Cfg::kStride - Cfg::kPad;
 #pragma unroll
     for (int u = 0; u < NT; ++u) {
-      const int iy = iy0 + c_py[u];
+      const int iy = iy0 + (c_at[u] >> 16);
       pre[u] = make_uint4(0u, 0u, 0u, 0u);
-      if ((unsigned)iy < (unsigned)a.H) pre[u] = *reinterpret_cast<const uint4*>(xg + (c_src[u] + (long)iy * a.W));
+      if (tid + u * 256 < nchunk && (unsigned)iy < (unsigned)a.H) pre[u] = *reinterpret_cast<const uint4*>(xg + (c_src[u] + (long)iy * a.W));
     }
   };
   auto commit = [&](int buf) {
 #pragma unroll
     for (int u = 0; u < NT; ++u)
-      if (c_py[u] >= 0) lds_store16(Ps + buf * CIN * a.PS + c_dst[u], pre[u]);     // rows past the image: zeros
+      if (tid + u * 256 < nchunk) lds_store16(Ps + buf * CIN * a.PS + (c_at[u] & 0xffff), pre[u]);     // rows past the image: zeros
   };
   fetch(t0);
 
@@ -148,6 +149,8 @@ __global__ __launch_bounds__(256, NT > 4 ? 2 : 3) void conv_stem_kernel(ConvStem
     for (int j = 0; j < FN; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[0][j][r] = 0.f;
+    int upper = half;                                        // taken up anew per tile, or the offsets below stay in 11 registers
+    asm volatile("" : "+v"(upper));
 #pragma unroll
     for (int s = 0; s < Cfg::kSteps; ++s) {
       // rows 2s (lower lane half) and 2s+1 (upper half); offsets are wave uniform, the choice is per lane
@@ -157,10 +160,10 @@ __global__ __launch_bounds__(256, NT > 4 ? 2 : 3) void conv_stem_kernel(ConvStem
       const int off1 = (r1 / Cfg::kKH) * a.PS + (r1 % Cfg::kKH) * a.PW;
 #pragma unroll
       for (int j = 0; j < FN; ++j) {
-        lds_cu32_t* src = (lds_cu32_t*)(Ps + pix[j] + (half ? off1 : off0));  // even element index: 4-byte aligned
+        lds_cu32_t* src = (lds_cu32_t*)(Ps + pix[j] + (upper ? off1 : off0));  // even element index: 4-byte aligned
         uint32_t w0 = src[0], w1 = src[1], w2 = src[2], w3 = src[3];
         w0 &= 0xffff0000u;                                                   // slot 0 multiplies a zero weight: keep it finite
-        if (2 * s + 1 >= kRows && half) { w0 = 0; w1 = 0; w2 = 0; w3 = 0; }
+        if (2 * s + 1 >= kRows && upper) { w0 = 0; w1 = 0; w2 = 0; w3 = 0; }
         const uint4 v = make_uint4(w0, w1, w2, w3);
         acc[0][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, v), af[s], acc[0][j], 0, 0, 0);
       }

@@ -1,5 +1,5 @@
 """The 7 x 7 stride-2 convolution over 3 channels: runs of tiles per workgroup (one, several, a shorter last one), output rows that no tile
-ends with, 64, fewer and more output channels, images of every class of patch chunks per thread (4, 8, 12), tall and wide ones, a
+ends with, 64, fewer and more output channels (blocks of 64 and of 32), images of every class of patch chunks per thread (4, 6, 8, 12), tall and wide ones, a
 residual.  Integer-coded, so the oracle's bits."""
 import numpy as np
 import pytest
@@ -11,6 +11,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("M,B,cout,H,W", [
     (2, 1, 64, 224, 224), (16, 1, 64, 224, 224), (13, 2, 64, 130, 200), (2, 2, 40, 7, 8), (2, 1, 96, 33, 64), (30, 1, 136, 95, 96),
     (2, 1, 64, 30, 512), (1, 2, 64, 20, 736), (3, 1, 64, 300, 16), (2, 1, 64, 1, 288),
+    (2, 2, 32, 130, 200), (3, 1, 20, 33, 64), (3, 1, 64, 40, 400), (9, 2, 32, 90, 400), (2, 1, 32, 30, 512), (1, 1, 72, 20, 736),
 ])
 def test_stem_exact(oracle, M, B, cout, H, W):
     import paper_2009_13062_amd as nf
