@@ -119,10 +119,12 @@ static void plane_try(int tile, float margin, const GemmLaunch& L, int* best, fl
 // Stride 1: where it is predicted 7 % faster, for the three tiles of many positions from 512 of k on 18 % (their slope is underestimated
 // for some shapes).  Over the 1400 problems 7 % less time on average, seven slower by 4 to 9 %; 19 % less over 7 x 7 planes (32 models 512 ->
 // 2048 24.8 -> 17.8 us), 14 x 14 256 -> 1024 16.6 -> 14.4, 50 x 50 64 -> 256 of 12 images 12.7 -> 10.1.
-// Odd planes of more than 56 positions gain in the 32 x 64 tile only: the other gathering ones were a tenth slower.
+// (Over 7900 other problems of these ranges, even widths at stride 2 among them, 16 % less time, one in a hundred slower by more than 6 %: the
+// models' error.)  Odd planes of more than 56 positions gain in the 32 x 64 tile only: the other gathering ones were a tenth slower.
 // Strided, eight 2-byte loads per 16 bytes in the register-staged tile: always (3 models of 4 images 512 -> 1024 at 25 x 25 24.7 -> 13.0, 1024
 // -> 2048 at 13 x 13 39.3 -> 18.7 us; 1.6 to 2.1 times as fast over every size).  Stride 2 over an even width, which has loaders of
-// aligned pixel pairs: up to 24 wide where predicted 12 % faster (32 models 1024 -> 2048 at 14 x 14 46 -> 36 us; wider inputs are loaded
+// aligned pixel pairs: up to 24 wide where predicted 16 % faster, as those predictions are off by 16 % themselves (24 models 1024 -> 256 at
+// 25 x 16 with a residual, predicted 13 % faster: 13.9 us in pairs, 19.8 here; 32 models 1024 -> 2048 at 14 x 14 46 -> 36 us; wider inputs are loaded
 // whole for every second pixel: 32 models 256 -> 512 at 56 x 56 34 against 31, 6 models 256 -> 512 at 28 x 28 a tenth slower).
 int pick_conv_plane(const GemmLaunch& L, int now, bool pairs) {
   const GemmArgs& a = L.a;
@@ -132,7 +134,7 @@ int pick_conv_plane(const GemmLaunch& L, int now, bool pairs) {
   int best = -1;
   float limit = one ? plane_us(kPlaneRegCost[big][a.K % (big ? 128 : 256) == 0][a.cols % 4 == 0], tiles, a)
                 : pairs ? plane_us(kPairCost[big], tiles, a) : 3e38f;
-  const float m = one ? 0.93f : 0.88f, wide = a.K >= 512 ? 0.82f : m;
+  const float m = one ? 0.93f : 0.84f, wide = a.K >= 512 ? 0.82f : m;
   plane_try<CfgPW64x64>(PW64x64, m, L, &best, &limit);
   plane_try<CfgPW128x64>(PW128x64, m, L, &best, &limit);
   plane_try<CfgPG32x64>(PG32x64, m, L, &best, &limit);

@@ -292,6 +292,12 @@ nf_status conv_wave(const void* x, const void* w, const void* residual, void* y,
   return launch_conv_wave(c, Ho, B, s);
 }
 
+// The register-staged tile of a convolution.  A gathered B operand (strided or k x k taps): its loads are the expensive part, so a few
+// output positions are better served by tall tiles that gather them once per 128 output channels (measured).
+int conv_reg_tile(int cog, int HoWo, long long problems, bool pointwise) {
+  return !pointwise && forced_tile() < 0 && HoWo <= 64 && cog >= 256 ? (int)T128x128w8 : pick_tile(cog, HoWo, problems);
+}
+
 // Pointwise through the kernels of conv_plane.h where they are ahead of the register-staged tile `now`, or NF_EUNSUPPORTED.
 nf_status conv_plane(const GemmLaunch& L, int H, int W, int Wo, int stride, int now, bool pairs, hipStream_t s) {
   GemmLaunch P = L;
@@ -700,10 +706,7 @@ nf_status netfuse_conv2d(const void* x, const void* w, const float* bias, const 
     while (al > 2 && (Kdim % (al / 2)) != 0) al /= 2;
     const long long problems = (long long)M * g * B;
     const bool pointwise = KH == 1 && KW == 1 && stride == 1 && pad == 0;
-    int tile = pick_tile(cog, HoWo, problems);
-    // gathered B operand (strided or k x k taps): its loads are the expensive part, so a few output
-    // positions are better served by tall tiles that gather them once per 128 output channels (measured)
-    if (!pointwise && forced_tile() < 0 && HoWo <= 64 && cog >= 256) tile = T128x128w8;
+    int tile = conv_reg_tile(cog, HoWo, problems, pointwise);
     if (pointwise) {
       // a 1x1 convolution is a matrix product over the channel dimension with the H*W positions as
       // columns (the converse of Section 3.1's remark that a matmul is a 1x1 convolution)
@@ -892,6 +895,20 @@ nf_status netfuse_conv2d(const void* x, const void* w, const float* bias, const 
                        (const bf16_t*)w, bias, scale, shift, (const bf16_t*)residual, (bf16_t*)y, geo, (int)act,
                        (size_t)n_out);
   return launched();
+}
+
+// For the tests, which name the tile of conv_plane.h that a case is meant to run; not part of the interface.  16-byte aligned operands; -1 =
+// another kernel.  Host only.
+int netfuse_conv_plane_tile(int M, int B, int cig, int cog, int g, int H, int W, int stride, int residual) {
+  GemmLaunch L;
+  memset(&L, 0, sizeof(L));
+  const int Ho = (H - 1) / stride + 1, Wo = (W - 1) / stride + 1;
+  L.a.rows = cog; L.a.cols = Ho * Wo; L.a.K = cig; L.a.nz0 = M * g; L.nz1 = B;
+  L.a.R = residual ? (const bf16_t*)&L : nullptr;
+  L.a.ldb = (long)H * W;
+  L.a.geom.W = W; L.a.geom.Wo = Wo; L.a.geom.stride = stride;
+  if (stride == 1 && L.a.cols % 8 == 0) return -1;
+  return pick_conv_plane(L, conv_reg_tile(cog, L.a.cols, (long long)M * g * B, stride == 1), stride == 2 && W == 2 * Wo);
 }
 
 nf_status netfuse_layernorm(const void* x, const void* residual, const float* gamma, const float* beta, void* y,
