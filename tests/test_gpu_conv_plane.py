@@ -17,7 +17,8 @@ CASES = [   # M, B, cin, cout, H, W, stride
     (16, 1, 320, 520, 18, 18, 1), (40, 1, 128, 40, 4, 51, 1), (8, 2, 320, 264, 14, 14, 1),                           # 64 x 128 of a plane
     (40, 2, 64, 72, 18, 18, 1), (16, 2, 256, 520, 18, 18, 1), (32, 2, 64, 200, 4, 51, 1),                            # 128 x 128 of a plane
     (16, 1, 192, 264, 25, 25, 1), (3, 2, 320, 136, 10, 19, 1), (3, 1, 192, 72, 28, 7, 2), (8, 1, 512, 72, 25, 25, 3),   # 32 x 64
-    (3, 2, 256, 520, 10, 19, 2), (40, 1, 128, 520, 4, 47, 3), (2, 1, 192, 264, 33, 35, 3), (2, 1, 256, 72, 5, 26, 5),   # 128 x 64, strided
+    (2, 1, 256, 72, 5, 26, 5),                                                                                       # the same
+    (3, 2, 256, 520, 10, 19, 2), (40, 1, 128, 520, 4, 47, 3), (2, 1, 192, 264, 33, 35, 3),                           # 128 x 64, strided
     (32, 1, 256, 520, 13, 13, 2), (16, 2, 128, 200, 25, 25, 3), (32, 1, 128, 136, 16, 16, 2),                        # the same, k-steps of 32
     (32, 2, 192, 264, 18, 18, 2), (16, 2, 128, 136, 33, 35, 2),                                                      # 128 x 128, strided
     (2, 1, 256, 72, 3, 601, 2), (2, 1, 128, 136, 5, 301, 3),                                                         # rows too wide

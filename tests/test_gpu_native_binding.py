@@ -57,6 +57,34 @@ def _outcome(call):
         return type(e), str(e)
 
 
+# What the native path does with each of the calls above: T takes it, E raises the entry point's error, - hands it on, . is not asked.
+OUTCOMES = "TTT-" "--.-" "-E--" "E." "TT---" "--" "TT" "-----" "T-" "TT" "E---" "--"
+
+
+class Recorder:
+    def __init__(self, native):
+        self.native, self.seen = native, "."
+
+    def __getattr__(self, name):
+        def call(*args):
+            self.seen = "E"
+            out = getattr(self.native, name)(*args)
+            self.seen = "-" if out is None else "T"
+            return out
+        return call
+
+
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
+def test_takes_the_ordinary_calls(nf, dt, monkeypatch):
+    rec, seen = Recorder(nf._native), []
+    monkeypatch.setattr(nf, "_native", rec)
+    for c in _calls(nf, dt):
+        rec.seen = "."
+        _outcome(c)
+        seen.append(rec.seen)
+    assert "".join(seen) == OUTCOMES + ("TE-" if dt == torch.bfloat16 else "")
+
+
 @pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
 def test_same_as_the_python_path(nf, dt, monkeypatch):
     calls = _calls(nf, dt)
