@@ -30,7 +30,9 @@
 // registers, and the outputs leave from registers (conv_plane.h's epilogue): single-block tiles of their own paid for their
 // addresses, their zero fill and an empty memory pipe every time, and read the same weights again.  Per layer, a tile per workgroup and an
 // epilogue through LDS -> this: 16 models' fused groups of 4 channels at 56 x 56 19.1 -> 14.7 us, of 8 at stride 2 from 56 x 56 25.9 ->
-// 16.0; over 2430 problems of several blocks 8 % less time, over 3300 of fused groups 22 %.
+// 16.0; over 7000 problems of several blocks 8 % less time, over 9000 of fused groups 21 %.
+// Behind: one in a hundred of the former by 6 to 19 %, mostly odd planes with a residual, whose 16-byte pieces straddle lines (64
+// channels at 33 x 33 10.5 -> 12.4 us; through LDS 13 x 13 and 25 x 25 lose a tenth instead).
 // What bounds it: LDS reads (a fragment of each operand per MFMA at FM = FN = 1) and their bank conflicts.
 #pragma once
 #include "conv_patch.h"
