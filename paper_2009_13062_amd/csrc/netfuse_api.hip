@@ -504,7 +504,7 @@ static int pick_frag(int N, int Nout, int K, int M) {
 // shapes the 128-row fragment kernel has no tile for (output widths that are multiples of 256 but not of 96, 288 or 384, k that is no
 // multiple of 128).  `preferred`: 256 x 256 tiles measured faster than the fragment kernel's, with a GELU epilogue and at least three of
 // them per compute unit (without the GELU the fragment kernel is ahead: 75 against 88, 82 against 98, 32 against 39 us on the other
-// three encoder shapes); from 256 k up it is then gemm_ring.h's tile that runs (see netfuse_linear_packed).  Returns the number of
+// three encoder shapes); for long k it is then gemm_ring.h's tile that runs (gelu_ring).  Returns the number of
 // column tiles per workgroup, 0 = not applicable.
 static int pick_packed_stream(int N, int Nout, int K, int M, int act, bool* preferred) {
   *preferred = false;
@@ -523,6 +523,17 @@ static int pick_packed_stream(int N, int Nout, int K, int M, int act, bool* pref
   *preferred = act == NF_ACT_GELU && tiles >= 3 * 256;
   return best;
 }
+
+// The 256 x 256 tile of gemm_ring.h (64 k per barrier) in the place of the streaming one (32), packed weights, GELU, three tiles per compute
+// unit and more: from 512 of k up.  us: 32 models of 512 rows 768 -> 3072 106.3 -> 101.6, 1536 -> 3072 184 -> 168, 3072 -> 3072 327 -> 297;
+// 64 of 256 rows 125 -> 111; 20 of 512 rows 4096 -> 5120 482 -> 445; 1 of 16384 rows 1024 -> 4096 173 -> 168.  Over 400 problems from 512
+// up 10 % less time, 2 % more at most; over 340 from 256 to 448 3 % less and 8 % more at most, so these stay.
+// Where a model has 2048 rows or more whose outputs lie a multiple of 4 KB apart, the ring tile's stores fall behind (8 models of 4096 rows
+// 320 -> 2048 90 us streaming, 118; 768 -> 2048 135 and 169; 1024 of k 2 % less on average, 4 % more at most): from 1536 of k.
+static bool gelu_ring(int N, int K, int Nout) { return K >= (N >= 2048 && Nout % 2048 == 0 ? 1536 : 512) && ring_fits(Nout, K); }
+
+// For the tests; not part of the interface.  Host only.
+int netfuse_packed_gelu_ring(int N, int K, int Nout) { return gelu_ring(N, K, Nout); }
 
 int netfuse_linear_packed_supported(int M, int N, int K, int Nout, nf_dtype dt) {
   if (dt != NF_BF16 || M <= 0 || N <= 0 || K <= 0 || Nout <= 0) return 0;
@@ -579,11 +590,7 @@ nf_status netfuse_linear_packed(const void* X, const void* Wp, const float* bias
   a.ep.col_bias = bias; a.ep.col_vec_stride0 = Nout;
   a.ep.act = act; a.ep.act_before_residual = 1;
   if (ps > 0 && (ps_preferred || f < 0)) {
-    // The 256 x 256 tile of gemm_ring.h (64 k per barrier) against the streaming one (32), GELU, us: 32 models of 512 rows 768 -> 3072 106.3 -> 101.6, 1536 -> 3072 184 -> 168, 3072
-    // -> 3072 327 -> 297; 64 of 256 rows 125 -> 111; 20 of 512 rows 4096 -> 5120 482 -> 445; 1 of 16384 rows 1024 -> 4096 173 -> 168;
-    // 32 of 512 rows 256 -> 3072 57.8 -> 57.6, 320 -> 3072 63.3 -> 63.7.  Below 256 k the streaming one: 400 models of 256 rows
-    // 128 -> 512 62.3 against 63.8, 64 -> 512 51.7 against 55.7.
-    if (ps_preferred && ring_fits(Nout, K)) {
+    if (ps_preferred && gelu_ring(N, K, Nout)) {
       const nf_status st = launch_gemm_ring(RP256x256, true, L, (hipStream_t)stream);
       if (st != NF_EUNSUPPORTED) return st;
     }

@@ -1,6 +1,6 @@
-"""Packed weights, GELU, three 256 x 256 tiles per compute unit and more (kernels chosen by k): the shortest k of the ring tile, a k that the
-128-row tiles do not take, an odd number of 64-k steps, a last round that is not full, one row tile per model and many, k too
-short for the ring tile."""
+"""Packed weights, GELU, three 256 x 256 tiles per compute unit and more (kernels chosen by k): the shortest k of the ring tile and the shorter
+ones of the streaming one, a k that the 128-row tiles do not take, an odd number of 64-k steps, a last round that is not full, one row
+tile per model and many, outputs a multiple of 4 KB apart."""
 import numpy as np
 import pytest
 import torch
@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("M,N,K,Nout,res", [
     (768, 256, 256, 256, False), (97, 512, 320, 1024, True), (20, 1024, 576, 2560, False), (32, 512, 768, 3072, True),
-    (1, 16384, 1024, 3072, False), (400, 256, 128, 512, False),
+    (1, 16384, 1024, 3072, False), (400, 256, 128, 512, False), (256, 256, 512, 768, False), (12, 2048, 1536, 2048, True), (12, 2048, 768, 2048, False),
 ])
 def test_gelu_tiles(nf, oracle, M, N, K, Nout, res):
     sample = sorted({0, M - 1})
