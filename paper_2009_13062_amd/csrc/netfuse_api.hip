@@ -1146,13 +1146,17 @@ nf_status netfuse_maxpool2d(const void* x, void* y, int B, int Ctot, int H, int 
   if (!aligned(x, esz) || !aligned(y, esz)) return NF_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   if (dt == NF_BF16 && k == 3 && stride == 2 && pad == 1 && W % 8 == 0 && aligned(x, 16) && aligned(y, 8)) {
-    // Wo = W / 2 is a multiple of 4: four outputs of two rows per thread from 16-byte loads
-    const long long total = n_out / Wo / Ho * ((Ho + 1) / 2) * (Wo / 4);
+    // Wo = W / 2 is a multiple of 4: four outputs of one or two rows per thread from 16-byte loads
+    const int rows = W <= 32 || Ho == 1 ? 1 : 2;
+    const long long total = n_out / Wo / Ho * ((Ho + rows - 1) / rows) * (Wo / 4);
     const unsigned grid = grid_for(total, 256);
-    if (total + 256LL * grid < (1LL << 32))                  // the loop's index does not wrap either
-      nf_launch((maxpool3x3s2_bf16_kernel<uint32_t>), dim3(grid), dim3(256), 0, s, (const bf16_t*)x, (bf16_t*)y, H, W, Ho, Wo, (uint32_t)total);
-    else
-      nf_launch((maxpool3x3s2_bf16_kernel<size_t>), dim3(grid), dim3(256), 0, s, (const bf16_t*)x, (bf16_t*)y, H, W, Ho, Wo, (size_t)total);
+#define NF_POOL(kernel, I) nf_launch((kernel<I>), dim3(grid), dim3(256), 0, s, (const bf16_t*)x, (bf16_t*)y, H, W, Ho, Wo, (I)total)
+    if (total + 256LL * grid < (1LL << 32)) {                // the loop's index does not wrap either
+      if (rows == 1) NF_POOL(maxpool3x3s2_bf16_row_kernel, uint32_t); else NF_POOL(maxpool3x3s2_bf16_kernel, uint32_t);
+    } else {
+      if (rows == 1) NF_POOL(maxpool3x3s2_bf16_row_kernel, size_t); else NF_POOL(maxpool3x3s2_bf16_kernel, size_t);
+    }
+#undef NF_POOL
     return launched();
   }
   const unsigned grid = grid_for(n_out, 256);

@@ -336,6 +336,8 @@ __global__ __launch_bounds__(256) void maxpool2d_kernel(const T* __restrict__ x,
 // indices where they fit (a 64-bit division is a hundred instructions).  What bounds it: HBM.  One output row per thread,
 // 64-bit indices and loads behind branches -> this, us: 2048 planes of 112 x 112 15.2 -> 12.6 (5.1 TB/s), 1024 9.0 -> 7.9, 8 x 2048 112 -> 108,
 // 64 2.9 -> 2.8, 1024 of 113 x 96 8.3 -> 7.3.
+// Up to 32 columns, and for a single row, lanes that are two output rows apart meet in fewer lines, and the row kernel below is ahead
+// (8192 planes of 112 x 8 5.4 us against 6.6, 512 columns in one row 4.6 and 5.3).
 template <typename I>
 __global__ __launch_bounds__(256) void maxpool3x3s2_bf16_kernel(const bf16_t* __restrict__ x, bf16_t* y, int H, int W,
                                                                 int Ho, int Wo, I total) {
@@ -381,6 +383,45 @@ __global__ __launch_bounds__(256) void maxpool3x3s2_bf16_kernel(const bf16_t* __
       }
       *reinterpret_cast<uint2*>(y + ((size_t)bc * Ho + oy + e) * Wo + ox0) = make_uint2(out[0], out[1]);
     }
+  }
+}
+
+// The same with one output row per thread, whose window is loaded only where it lies in the image.
+template <typename I>
+__global__ __launch_bounds__(256) void maxpool3x3s2_bf16_row_kernel(const bf16_t* __restrict__ x, bf16_t* y, int H, int W,
+                                                                int Ho, int Wo, I total4) {
+  const unsigned q = Wo / 4;
+  for (I o = (I)blockIdx.x * 256 + threadIdx.x; o < total4; o += (I)gridDim.x * 256) {
+    const I t = o / q, bc = t / (unsigned)Ho;
+    const int ox0 = (int)(o - t * q) * 4, oy = (int)(t - bc * (unsigned)Ho);
+    const bf16_t* xc = x + (size_t)bc * H * W;
+    float m[9];                                   // column maxima over the 3 input rows: cols 2 ox0 - 1 .. 2 ox0 + 7
+#pragma unroll
+    for (int c = 0; c < 9; ++c) m[c] = -INFINITY;
+#pragma unroll
+    for (int ky = 0; ky < 3; ++ky) {
+      const int iy = oy * 2 + ky - 1;
+      if (iy < 0 || iy >= H) continue;
+      const bf16_t* row = xc + (size_t)iy * W + ox0 * 2;
+      const uint4 v = *reinterpret_cast<const uint4*>(row);
+      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+      if (ox0 > 0) { const float l = bf16_to_f32(row[-1]); m[0] = l > m[0] ? l : m[0]; }
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        const float f = __uint_as_float(c % 2 ? (w[c / 2] & 0xffff0000u) : (w[c / 2] << 16));
+        m[c + 1] = f > m[c + 1] ? f : m[c + 1];
+      }
+    }
+    uint32_t out[2];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      float best = m[2 * j];
+      best = m[2 * j + 1] > best ? m[2 * j + 1] : best;
+      best = m[2 * j + 2] > best ? m[2 * j + 2] : best;
+      const uint32_t h = (uint32_t)f32_to_bf16(best);
+      if (j % 2) out[j / 2] |= h << 16; else out[j / 2] = h;
+    }
+    *reinterpret_cast<uint2*>(y + ((size_t)bc * Ho + oy) * Wo + ox0) = make_uint2(out[0], out[1]);
   }
 }
 
