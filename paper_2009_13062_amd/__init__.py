@@ -116,10 +116,13 @@ def _check(fn: str, st: int):
 
 
 # The calls of a forward pass marshalled in native code (csrc/binding.cpp); None where it was not built, or was built for another
-# torch: the functions below then do all of it themselves.
+# torch or Python, which may load all the same: the functions below then do all of it themselves.
 _Tensor = torch.Tensor
 try:
     from . import _binding as _native
+    from .build import binding_target
+    if getattr(_native, "built_for", "") != binding_target():
+        raise ImportError("built for another")
     _address = lambda f: ctypes.cast(f, ctypes.c_void_p).value
     _native.bind(_check, _address(lib.netfuse_linear), _address(lib.netfuse_linear_packed), _address(lib.netfuse_layernorm),
                  _address(lib.netfuse_attention), _address(lib.netfuse_attention_relpos), _address(lib.netfuse_conv2d))

@@ -54,19 +54,32 @@ def _compile(src: str, extra, verbose: bool, force: bool) -> str:
     return obj
 
 
+def binding_target() -> str:
+    """The Python and torch that a binding built now is for: their inlined accessors and struct layouts are compiled in."""
+    import torch
+    return "python %d.%d, torch %s %s" % (sys.version_info[0], sys.version_info[1], torch.__version__, torch.version.git_version)
+
+
+def _built_for(target: str) -> bool:
+    with open(BINDING, "rb") as f:
+        return target.encode() + b"\0" in f.read()
+
+
 def _build_binding(verbose: bool, force: bool) -> None:
     """The call marshalling of the Python package (csrc/binding.cpp): a host-only extension against the installed torch."""
     import sysconfig
 
     import torch
     src = os.path.join(CSRC, "binding.cpp")
-    if not force and os.path.exists(BINDING) and os.path.getmtime(BINDING) > max(os.path.getmtime(src), _newest_header()):
+    target = binding_target()
+    if not force and os.path.exists(BINDING) and os.path.getmtime(BINDING) > max(os.path.getmtime(src), _newest_header()) and _built_for(target):
         return
     root = os.path.dirname(torch.__file__)                   # its libraries are found by name: the package imports torch first
     # NDEBUG: without it a header keeps a thread-local counter.  A library with thread-local storage that is loaded late and whose storage is
     # never touched leaves glibc 2.35 on the slow path of every other library's (17 % on torch's small operators).
     cmd = ["g++", "-O2", "-DNDEBUG", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-isystem", os.path.join(root, "include"),
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, '-DNETFUSE_BUILT_FOR="%s"' % target,
+           "-isystem", os.path.join(root, "include"),
            "-isystem", sysconfig.get_paths()["include"], src, "-o", BINDING + ".tmp",
            "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
     if verbose:

@@ -272,4 +272,9 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, methods, n
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__binding() { return PyModule_Create(&module); }
+// built_for: the Python and torch whose headers are compiled in; the package uses the module with no other.
+PyMODINIT_FUNC PyInit__binding() {
+  PyObject* m = PyModule_Create(&module);
+  if (m && PyModule_AddStringConstant(m, "built_for", NETFUSE_BUILT_FOR) < 0) Py_CLEAR(m);
+  return m;
+}
