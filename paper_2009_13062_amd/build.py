@@ -66,8 +66,11 @@ def _built_for(target: str) -> bool:
 
 
 def _build_binding(verbose: bool, force: bool) -> None:
-    """The call marshalling of the Python package (csrc/binding.cpp): a host-only extension against the installed torch."""
+    """The call marshalling of the Python package (csrc/binding.cpp): a host-only extension against the installed torch.  The package runs
+    without it, so a box without a host compiler or these headers gets a warning; code that does not compile is an error."""
+    import shutil
     import sysconfig
+    import warnings
 
     import torch
     src = os.path.join(CSRC, "binding.cpp")
@@ -75,6 +78,13 @@ def _build_binding(verbose: bool, force: bool) -> None:
     if not force and os.path.exists(BINDING) and os.path.getmtime(BINDING) > max(os.path.getmtime(src), _newest_header()) and _built_for(target):
         return
     root = os.path.dirname(torch.__file__)                   # its libraries are found by name: the package imports torch first
+    headers = [os.path.join(sysconfig.get_paths()["include"], "Python.h"), os.path.join(root, "include", "ATen", "ATen.h")]
+    missing = ["g++"] * (shutil.which("g++") is None) + [h for h in headers if not os.path.exists(h)]
+    if missing:
+        warnings.warn("calls are marshalled in Python: csrc/binding.cpp is not built without " + ", ".join(missing))
+        if os.path.exists(BINDING):
+            os.remove(BINDING)                               # of other sources, or of another torch
+        return
     # NDEBUG: without it a header keeps a thread-local counter.  A library with thread-local storage that is loaded late and whose storage is
     # never touched leaves glibc 2.35 on the slow path of every other library's (17 % on torch's small operators).
     cmd = ["g++", "-O2", "-DNDEBUG", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
@@ -94,12 +104,12 @@ def build(verbose: bool = False, extra=(), force: bool = True, jobs: int = 8) ->
     with ThreadPoolExecutor(max_workers=jobs) as ex:
         binding = ex.submit(_build_binding, verbose, force)
         objs = list(ex.map(lambda s: _compile(s, extra, verbose, force), SOURCES))
-        binding.result()
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", LIB + ".tmp"]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)
     os.replace(LIB + ".tmp", LIB)
+    binding.result()                                         # the library is there whatever became of it
     return LIB
 
 
