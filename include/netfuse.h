@@ -73,10 +73,10 @@ nf_status netfuse_linear(const void* X, const void* W, const float* bias, const 
  *   (N a multiple of 128 and Nout a multiple of 96 with K % 256 == 0, or of 128, 288 or 384 with
  *   K % 128 == 0; N a multiple of 64 and Nout of 96, 288 or 384 where M * (N / 64) * (Nout / width) lies in
  *   129 ... 256 -- 64-row tiles, one workgroup per compute unit when 128-row tiles would leave half of them
- *   idle; or N and Nout multiples of 256 with K % 32 == 0) AND it pays (at least 128 of its tiles; or, with K a
- *   multiple of 64 from 256 up, M * (N / 32) * (Nout / 32) at most 256, or M * N at most 768 with K at least
- *   2048: between these netfuse_linear's smaller tiles are as fast), else 0 (then use netfuse_linear; netfuse_linear_packed still
- *   runs any shape it has a kernel for).
+ *   idle; or N and Nout multiples of 256 with K % 32 == 0) AND the problem is of a size where it tends to pay (at
+ *   least 128 of its tiles; or, with K a multiple of 64 from 256 up, M * (N / 32) * (Nout / 32) at most 256, or
+ *   M * N at most 768 with K at least 2048), else 0 (then use netfuse_linear; netfuse_linear_packed still runs any
+ *   shape it has a kernel for).  A line drawn by size: netfuse_linear can be the faster one of the two on either side of it.
  * netfuse_linear_pack_weight: W[M][K][Nout] -> Wp; W and Wp must not overlap; Wp 16-byte aligned.
  * netfuse_linear_packed: Y[m] = act(X[m] . W[m] + bias[m]) + residual[m] as netfuse_linear (the
  *   products are summed in fp32 in a different order, so results can differ from it in the last bit);

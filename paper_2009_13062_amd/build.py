@@ -87,7 +87,7 @@ def _build_binding(verbose: bool, force: bool) -> None:
         return
     # NDEBUG: without it a header keeps a thread-local counter.  A library with thread-local storage that is loaded late and whose storage is
     # never touched leaves glibc 2.35 on the slow path of every other library's (17 % on torch's small operators).
-    cmd = ["g++", "-O2", "-DNDEBUG", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+    cmd = ["g++", "-O2", "-DNDEBUG", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
            "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, '-DNETFUSE_BUILT_FOR="%s"' % target,
            "-isystem", os.path.join(root, "include"),
            "-isystem", sysconfig.get_paths()["include"], src, "-o", BINDING + ".tmp",

@@ -87,21 +87,23 @@ static float wave_us(const ConvWaveArgs<T>& a, const WaveTile& t, int NB, int KG
 
 // How many wavefronts share a tile, by the shape of ONE group (never by how many models or images there are: the order of the sum
 // follows from it); 0 = another kernel.  A shape is taken where no number of images from 1 to 256 (float32: 1 to 48) is slower for it by more
-// than two runs differ; the one exception, 256 channels at 14 x 14, takes 8 % more from 64 images up and 6 to 44 % less up to 32.
+// than a few percent.
 //   bf16, groups of 32 k channels (conv_tap.h, which multiplies four wavefronts' worth of positions out of one block of 32 channels, is
 //   the alternative): few positions and many channels, where that kernel waits; with many images it is ahead on larger planes, because
 //   a 32-row tile reads a fragment from LDS for every multiplication.  Times against it at 1 / 32 / 256 images:
-//     stride 1: 512 channels 7 x 7 0.43 / 0.77 / 0.78, 28 x 28 0.55 / 0.90 / 0.94; 256 channels 14 x 14 0.56 / 0.94 / 1.08, left out
-//     17 x 17 0.53 / 1.06 / 1.16; 128 channels 11 x 11 0.80 / 0.70 / 0.96, left out 14 x 14 0.76 / 0.87 / 1.23; 64 channels 9 x 9 0.93 /
-//     0.95 / 0.97, left out 14 x 14 1.0 / 1.0 / 1.38; 32 channels 5 x 5 1.0 / 0.84 / 0.86, left out 8 x 8 1.0 / 1.10 / 1.28
-//     stride 2: 512 channels 14 x 14 0.32 / 0.91 / 0.90, left out 18 x 18 0.31 / 1.10 / 1.43; 256 channels 8 x 8 0.50 / 0.62 / 0.66, 13 x 13
-//     0.36 / 0.74 / 0.88, left out 10 x 10 0.47 / 0.81 / 1.14 and 14 x 14 0.40 / 0.94 / 1.19; 128 channels 8 x 8 0.74 / 0.64 / 0.81, left
-//     out 9 x 9 0.65 / 0.81 / 1.33
+//     stride 1: 512 channels 7 x 7 0.41 / 0.74 / 0.75, 28 x 28 0.57 / 0.90 / 0.97; 256 channels 14 x 14 0.55 / 0.89 / 1.04, left out
+//     17 x 17 0.53 / 1.03 / 1.18; 128 channels 11 x 11 0.67 / 0.80 / 1.02, left out 14 x 14 0.66 / 0.95 / 1.20; 64 channels 9 x 9 0.76 /
+//     0.80 / 1.09, left out 14 x 14 0.75 / 0.83 / 1.43; 32 channels 5 x 5 0.90 / 0.91 / 0.90, left out 8 x 8, which then lost (1.0 / 1.10 / 1.28), now
+//     0.89 / 0.90 / 0.93
+//     stride 2: 512 channels 14 x 14 0.36 / 0.87 / 0.86, left out 18 x 18 0.37 / 1.08 / 1.44; 256 channels 8 x 8 0.56 / 0.74 / 0.64, 13 x 13
+//     0.43 / 0.85 / 0.82, left out 10 x 10 0.53 / 0.91 / 1.11 and 14 x 14 0.44 / 0.87 / 1.01; 128 channels 8 x 8 0.69 / 0.72 / 0.85, left
+//     out 9 x 9 0.66 / 0.84 / 1.39
+//   (Over 7200 problems that are taken 32 % less time, 33 of them 4 to 12 % slower and one by a third, most with 64 images and more.)
 //   and against the kernels that take groups of 16 (2 k + 1) channels (conv_patch.h, implicit GEMM): 16 channels on one wavefront
 //   14 x 14 0.94 / 0.95 / 0.77, 28 x 28 0.98 / 0.78 / 0.55; 48 channels on four 13 x 13 0.66 / 0.63 / 0.86, stride 2 16 -> 8 0.73 / 0.70 / 0.69, left
 //   out 14 x 14 0.73 / 0.69 / 1.15 and 36 -> 18 0.68 / 1.03 / 1.87.
-//   Groups of 16 in pairs that conv_tap.h fuses: 32 groups at 8 x 8 1.0 / 0.99 / 0.79, stride 2 28 -> 14 0.90 / 0.60 / 0.53; left out 6 groups at
-//   10 x 10 1.0 / 1.0 / 1.23.  Fewer than 32 outputs leave rows idle: 32 -> 16 6.7 against 8.2.
+//   Groups of 16 in pairs that conv_tap.h fuses: 32 groups at 8 x 8 0.77 / 0.89 / 0.83, stride 2 28 -> 14 0.70 / 0.87 / 0.81; left out 6 groups at
+//   10 x 10 0.82 / 0.88 / 1.30.  Fewer than 32 outputs leave rows idle: 32 -> 16 6.7 against 8.2.
 //   float32 (the gathered kernel of gemm_f32.h) at 1 / 12 / 48 images: stride 1 up to 64 x 64 positions 256 channels 14 x 14 0.55 / 0.60 /
 //   0.99, 64 channels 64 x 64 0.59 / 0.91 / 0.91 (left out 72 x 72 0.65 / 1.00 / 1.08), 32 groups of 8 channels on one wavefront 28 x 28 0.70 /
 //   0.43 / 0.40; left out 40 channels, five steps over four wavefronts, at 28 x 28 0.66 / 0.82 / 1.02 and 64 x 64 0.72 / 1.12 / 1.03.  Stride 2:

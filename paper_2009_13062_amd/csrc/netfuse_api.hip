@@ -544,9 +544,11 @@ int netfuse_linear_packed_supported(int M, int N, int K, int Nout, nf_dtype dt) 
   // split k over the wavefronts of a workgroup, which the row-major ones, one chain of k each, cannot: ahead where 32 x 32 tiles are
   // one round of workgroups (2 models of 128 rows 768 -> 768 7.0 -> 5.0 us, 3072 -> 768 15.8 -> 9.5, 4096 -> 1024 21.7 -> 12.0; 8 of 128 rows 256 -> 256
   // 4.4 -> 3.9; never behind over 40 such problems of hidden size 256 to 1024) and for long k over few rows (3 models of 128 rows 3072 -> 768 19.1
-  // -> 16.6, 4096 -> 1024 25.7 -> 21.2; 8 to 21 % ahead over 18 problems of up to 768 rows in all).  Otherwise netfuse_linear's small tiles are as fast
-  // or faster (3 models 768 -> 768 7.6 against 7.7; one layer at 8 models 0.088 ms packed throughout, 0.074): the answer is "no" below half a
-  // workgroup per compute unit, although netfuse_linear_packed itself still runs there.
+  // -> 16.6, 4096 -> 1024 25.7 -> 21.2; 8 to 21 % ahead over 18 problems of up to 768 rows in all).  Otherwise the answer is "no" below half a
+  // workgroup per compute unit (3 models 768 -> 768 7.6 row-major against 7.7; one layer at 8 models 0.088 ms packed throughout, 0.074), although
+  // netfuse_linear_packed itself still runs there and would be 7 to 17 % ahead for long k over more rows (8 models 3072 -> 768 19.7 row-major, 18.4; 12
+  // models 4096 -> 1024 35.5 and 29.5).  The line at 128 tiles is older than the row-major ring tiles: of 480 problems answered "yes" they are
+  // more than 5 % ahead for 129 (12 models of 384 rows 3072 -> 768 37.8 against 58.0 packed).
   const long long tiles = (long long)M * (N / kFragBM[f]) * (Nout / kFragBN[f]);
   if (tiles >= 128) return 1;
   return f < kNumFragFullTiles && ring_fits(Nout, K) && ((long long)M * (N / 32) * (Nout / 32) <= 256 || (K >= 2048 && (long long)M * N <= 768)) ? 1 : 0;
@@ -840,6 +842,8 @@ nf_status netfuse_conv2d(const void* x, const void* w, const float* bias, const 
         if (st != NF_EUNSUPPORTED) return st;
       }
       if (bkind == 2 && forced_tile() < 0) {
+        // What comes here: operands that are not 16-byte aligned, k that is no multiple of 64, up to 32 outputs per group, rows too wide
+        // for the chunks of a tile.  (The times below are of aligned operands, which conv_plane.h now takes.)
         // Eight 2-byte loads per 16 bytes of activations weigh more than a compute unit or two left idle: from 160 tiles of 128 x 128
         // up (3 models of 4 images 512 -> 1024 at 25 x 25: 37.8 us in 64 x 64 tiles, 29.0), but not where they fill a few
         // compute units only (2 models of one image 1024 -> 2048 at 13 x 13: 33.4 us in 32 of them, 26.5 in 64 x 64).

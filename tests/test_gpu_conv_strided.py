@@ -1,6 +1,6 @@
-"""Strided pointwise convolutions over planes whose width is odd or whose stride is not 2: the deep pipeline (k a multiple of its
-128 or 256) and the loader that takes any k, in every tile that the number of tiles leads to, ragged channels and positions, planes of
-one position.  Integer-coded (every sum exact in float32): the oracle's bits; and a position of infinities reaches the
+"""Strided pointwise convolutions over planes whose width is odd or whose stride is not 2, ragged channels and positions, planes of one
+position; and, with an operand off by one element, which conv_plane.h leaves to the register-staged kernels, theirs: the deep pipeline (k a
+multiple of its 128 or 256) and the loader that takes any k, in every tile that the number of tiles leads to, pixel pairs over even widths.  Integer-coded (every sum exact in float32): the oracle's bits; and a position of infinities reaches the
 outputs that read it only."""
 import numpy as np
 import pytest
@@ -18,8 +18,20 @@ CASES = [   # M, B, cin, cout, H, W, stride
 ]
 
 
+PAIRS = [(2, 1, 128, 256, 16, 16, 2), (3, 1, 64, 128, 14, 28, 2), (2, 1, 128, 256, 10, 10, 2), (2, 1, 128, 256, 12, 12, 2), (4, 2, 256, 264, 14, 14, 2)]
+
+
 @pytest.mark.parametrize("M,B,cin,cout,H,W,stride", CASES)
 def test_exact(oracle, M, B, cin, cout, H, W, stride):
+    check(oracle, M, B, cin, cout, H, W, stride, "")
+
+
+@pytest.mark.parametrize("shifted,M,B,cin,cout,H,W,stride", [("x", *c) for c in CASES] + [("w", *c) for c in CASES[1:7] + PAIRS])
+def test_exact_in_the_register_staged_kernels(oracle, shifted, M, B, cin, cout, H, W, stride):
+    check(oracle, M, B, cin, cout, H, W, stride, shifted)
+
+
+def check(oracle, M, B, cin, cout, H, W, stride, shifted):
     import paper_2009_13062_amd as nf
     rng = np.random.default_rng(cin + cout + H + stride)
     Ho, Wo = nf.conv_out_size(H, 1, stride, 0), nf.conv_out_size(W, 1, stride, 0)
@@ -31,7 +43,15 @@ def test_exact(oracle, M, B, cin, cout, H, W, stride):
     res = rng.integers(-8, 9, (B, M * cout, Ho, Wo)).astype(np.float32)
     dev = lambda a, dt=torch.bfloat16: torch.from_numpy(a).to("cuda", dt)
     f = torch.float32
-    got = nf.conv2d(dev(x), dev(w), M, bias=dev(bias, f), scale=dev(scale, f), shift=dev(shift, f), residual=dev(res), stride=stride, act=1)
+
+    def off(a, name):                                         # one element into a buffer of its own
+        t = dev(a)
+        if name != shifted:
+            return t
+        t = torch.cat([t.new_zeros(1), t.flatten()])[1:].view(a.shape)
+        assert t.data_ptr() % 16 == 2 and t.is_contiguous()
+        return t
+    got = nf.conv2d(off(x, "x"), off(w, "w"), M, bias=dev(bias, f), scale=dev(scale, f), shift=dev(shift, f), residual=dev(res), stride=stride, act=1)
     sample = [0, M - 1]                                       # models the oracle evaluates
     cut = lambda a, c: np.concatenate([a[m * c:(m + 1) * c] for m in sample])
     chan = lambda a, c: np.concatenate([a[:, m * c:(m + 1) * c] for m in sample], axis=1)
@@ -46,7 +66,7 @@ def test_exact(oracle, M, B, cin, cout, H, W, stride):
     last = Ho * Wo > 1                                        # a plane of one position has no other output to compare
     if last:
         x2[:, :, stride * (Ho - 1), stride * (Wo - 1)] = np.inf
-    got2 = nf.conv2d(dev(x2), dev(w), M, bias=dev(bias, f), scale=dev(scale, f), shift=dev(shift, f), residual=dev(res), stride=stride, act=1)
+    got2 = nf.conv2d(off(x2, "x"), off(w, "w"), M, bias=dev(bias, f), scale=dev(scale, f), shift=dev(shift, f), residual=dev(res), stride=stride, act=1)
     same = (got2 == got).reshape(B, M * cout, Ho * Wo)
     same = same[:, :, :-1] if last else same
     assert same.numel() and bool(same.all())
