@@ -25,7 +25,7 @@
 // The patch carries its zero padding: it is zeroed once, and every channel block overwrites only the
 // in-image pixels and clears the rows past the image.  Image column ix lives at patch column ix + kLPad.
 //
-// One workgroup = one (image, group, BM output channels) and a RUN of 128-position tiles, one where a group has several blocks
+// One workgroup = one (image, group, BM output channels) and a RUN of 128-position tiles, one where a group has many blocks
 // (tap_run in conv_tap_inst.hip).  While a block is multiplied the next one of the tile, or the first of the next tile, is in flight in
 // registers, and the outputs leave from registers (conv_plane.h's epilogue): single-block tiles of their own paid for their
 // addresses, their zero fill and an empty memory pipe every time, and read the same weights again.  Per layer, a tile per workgroup and an

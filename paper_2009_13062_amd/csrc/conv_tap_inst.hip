@@ -24,9 +24,9 @@ static nf_status launch_tap_kernel(long long total, int lds, const ConvTapArgs& 
   return hipGetLastError() == hipSuccess ? NF_OK : NF_ELAUNCH;
 }
 
-int tile_run(long long groups, int tiles_n, int lds, int most) {
+int tile_run(long long groups, int tiles_n, int lds, int most, double alone, double start) {
   const int at_once = std::max(1, std::min(160 * 1024 / 1280 / ((lds + 1279) / 1280), most));
-  auto per_tile = [](int run, long long j) { return 3 + run * std::max(2.6, (double)j); };
+  auto per_tile = [&](int run, long long j) { return start + run * std::max(alone, (double)j); };
   double best = 0;
   int pick = 1;
   for (int runs = 1, run; runs <= tiles_n; runs = run > 1 ? (tiles_n + run - 2) / (run - 1) : runs + 1) {
@@ -38,14 +38,18 @@ int tile_run(long long groups, int tiles_n, int lds, int most) {
   return pick;
 }
 
-// Position tiles per workgroup of `groups` x tiles_n.
-//   Several blocks of 32 channels: one.  The next block's loads already run under a multiplication and every tile needs its weights
-//   anew, so a longer run only takes workgroups away, and two that share a compute unit do not halve each other's rate: 24 models, 256
-//   channels at 20 x 20, 3 images 66 us in tiles of their own, 108 in runs of two; 12 models of 256 at 64 x 64 80 and 99.  (Over 2430
-//   problems of up to 98 tiles the best run is 1.1 % ahead of one tile, and no rule on their number finds it without losing elsewhere.)
-//   One block, whose weights stay in LDS: tile_run.  Over 4000 problems of 32 channels and of fused groups 0.1 % behind the best run and
-//   21 % less time than a tile per workgroup and an epilogue through LDS.
-static int tap_run(int cig, long long groups, int tiles_n, int lds) { return cig == kTapCB ? tile_run(groups, tiles_n, lds, 3) : 1; }
+// Position tiles per workgroup (bm rows) of `groups` x tiles_n.
+//   One block of 32 channels, whose weights stay in LDS: tile_run.  Over 4000 problems of 32 channels and of fused groups 0.1 % behind the
+//   best run and 21 % less time than a tile per workgroup and an epilogue through LDS.
+//   Two and three blocks: a long run saves the start of a tile only, next to nothing, and two workgroups that share a compute unit do not
+//   halve each other's rate.  Over 900 problems 1.3 % ahead of one tile each, 0.1 % behind the best run (32 models, 64 channels at 56 x 56 22.4 us in
+//   tiles of their own, 20.2 in runs of two).
+//   More: one tile.  The best run is 0.7 to 1.2 % ahead of it, and a wrong one far behind: 24 models, 256 channels at 20 x 20, 3 images 66 us in
+//   tiles of their own, 108 in runs of two; 12 models of 256 at 64 x 64 80 and 99.
+static int tap_run(int cig, int bm, long long groups, int tiles_n, int lds) {
+  if (cig == kTapCB) return tile_run(groups, tiles_n, lds, 3);
+  return cig <= 3 * kTapCB ? tile_run(groups, tiles_n, lds, bm > 32 ? 2 : 3, 1.5, 0.1) : 1;
+}
 
 template <class Cfg, bool FUSED = false>
 static nf_status launch_tap(const ConvPatchArgs& args, int B, hipStream_t s) {
@@ -72,7 +76,7 @@ static nf_status launch_tap(const ConvPatchArgs& args, int B, hipStream_t s) {
   }
   const int lds = Cfg::lds_bytes(a.PS);
   if (lds > 160 * 1024) return NF_EUNSUPPORTED;
-  a.run = tap_run(a.cig, groups, a.tiles_n, lds);
+  a.run = tap_run(a.cig, Cfg::kBM, groups, a.tiles_n, lds);
   a.runs = (a.tiles_n + a.run - 1) / a.run;
   const long long total = groups * a.runs;
 #define NF_TAP(VW_, NT_) return launch_tap_kernel<Cfg, VW_, NT_, FUSED>(total, lds, a, s)
@@ -136,4 +140,4 @@ nf_status launch_conv_tap_3x3(ConvPatchArgs& a, int B, hipStream_t s) {
 }  // namespace nf
 
 // For the tests; not part of the interface.  Host only.
-extern "C" int netfuse_conv_tap_run(int cig, long long groups, int tiles_n, int lds) { return nf::tap_run(cig, groups, tiles_n, lds); }
+extern "C" int netfuse_conv_tap_run(int cig, int bm, long long groups, int tiles_n, int lds) { return nf::tap_run(cig, bm, groups, tiles_n, lds); }

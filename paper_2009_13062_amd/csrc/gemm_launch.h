@@ -76,11 +76,12 @@ nf_status launch_gemm_ring(int tile, bool packed, GemmLaunch& L, hipStream_t s);
 // The same for a pointwise convolution (A = weights, B = planes of cols % 8 == 0 positions, K % 64 == 0 channels).
 enum RingConvTileId { RC64x64 = 0, RC64x128, RC64x256, RC128x128, RC128x256, kNumRingConvTiles };
 nf_status launch_conv_ring(int tile, GemmLaunch& L, hipStream_t s);
-// Tiles per workgroup for `groups` x tiles_n of them, where a workgroup walks a run of tiles (7x7 stem, single-block 3x3): the split with
-// the fewest tile times one after another.  A compute unit holds as many workgroups as its LDS, in pieces of 1280 bytes, and `most`
-// for their registers; of j together each takes max(j, 2.6) per tile and 3 tiles to start (addresses, zero fill, first loads).
-// Fitted to 4000 3x3 and 2400 stem problems timed with every run: 0.1 % behind the best one on average, 13 % at most.
-int tile_run(long long groups, int tiles_n, int lds, int most);
+// Tiles per workgroup for `groups` x tiles_n of them, where a workgroup walks a run of tiles (7x7 stem, 3x3): the split with the fewest
+// tile times one after another.  A compute unit holds as many workgroups as its LDS, in pieces of 1280 bytes, and `most` for their
+// registers; of j together each takes max(j, alone) per tile and `start` tiles to start (addresses, zero fill, first loads).
+// alone 2.6 and start 3, fitted to 4000 3x3 problems of one channel block and 2400 stem problems timed with every run: 0.1 % behind the
+// best one on average, 13 % at most.
+int tile_run(long long groups, int tiles_n, int lds, int most, double alone = 2.6, double start = 3);
 // Pointwise convolutions over planes of any size and any stride (conv_plane.h; 16-byte aligned operands, K % 64 == 0; geom holds W,
 // Wo and the stride, ldb the positions of an input plane).  PW: tiles that span planes of up to 56 positions, or of 4 k up to 200; PQ:
 // 128 positions of a plane of 4 k; PG: any, strided.  NF_EUNSUPPORTED if the shape does not fit the tile.
