@@ -30,10 +30,12 @@
 // registers, and the outputs leave from registers (conv_plane.h's epilogue): single-block tiles of their own paid for their
 // addresses, their zero fill and an empty memory pipe every time, and read the same weights again.  Per layer, a tile per workgroup and an
 // epilogue through LDS -> this: 16 models' fused groups of 4 channels at 56 x 56 19.1 -> 14.7 us, of 8 at stride 2 from 56 x 56 25.9 ->
-// 16.0; over 7000 problems of several blocks 8 % less time, over 9000 of fused groups 21 %.
-// Behind: one in a hundred of the former by 6 to 19 %, mostly odd planes with a residual, whose 16-byte pieces straddle lines (64
+// 16.0; over 6000 problems of 32 to 512 channels 9 % less time, over 9000 of fused groups 21 %.
+// Behind: one in a hundred of the former by 6 to 20 %, odd planes with a residual, whose 16-byte pieces straddle lines (64
 // channels at 33 x 33 10.5 -> 12.4 us; through LDS 13 x 13 and 25 x 25 lose a tenth instead).
-// What bounds it: LDS reads (a fragment of each operand per MFMA at FM = FN = 1) and their bank conflicts.
+// What bounds it: no one pipe.  LDS is active for 15 to 35 % of the clocks (a fragment of each operand per MFMA at FM = FN = 1; a tenth to a
+// half of that bank conflicts), a quarter to a half of the issue slots are filled; the rest is a block's commit, loads and multiplications behind
+// two barriers with one or two wavefronts per SIMD.
 #pragma once
 #include "conv_patch.h"
 #include "conv_plane.h"
@@ -65,15 +67,18 @@ struct ConvTapArgs : ConvPatchArgs {
 };
 
 // VW: pixels per patch chunk (= a.VW <= W).  NT: patch tasks per thread (the host checks the bound).
-// FUSED: S > 1 narrow groups (4, 8 or 16 channels each) share the single 32-channel block: the weight tile
+// kTapFused: S > 1 narrow groups (4, 8 or 16 channels each) share the single 32-channel block: the weight tile
 // is block diagonal (row r carries its own group's channels at channel offset (r / cog_real) * cig_real,
 // zeros elsewhere), filled once; see conv_patch.h for why no product crosses a group.
-template <class Cfg, int VW, int NT, bool FUSED = false>
+// kTapTile: several blocks, one tile per workgroup; kTapRun: any blocks, any run.
+enum ConvTapKind { kTapRun, kTapTile, kTapFused };
+template <class Cfg, int VW, int NT, int KIND>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Cfg::kMinWaves))) void conv_tap_kernel(ConvTapArgs a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   lds_bf16_t* As = (lds_bf16_t*)smem_raw;
   lds_bf16_t* Ps = As + Cfg::kBM * Cfg::kAPitch;
   constexpr int FM = Cfg::FM, FN = Cfg::FN, CB = kTapCB, PP = kTapPixPitch;
+  constexpr bool FUSED = KIND == kTapFused, TILE = KIND == kTapTile;
   constexpr int kDw = VW >= 2 ? VW / 2 : 1;            // dwords per loaded chunk
   const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
   const int wm = wave / Cfg::kWGN, wn = wave % Cfg::kWGN;
@@ -85,7 +90,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Cfg::kMinWa
   const int G = id % a.nG;
   const int b = id / a.nG;
   const int row0 = tm * Cfg::kBM, rows_left = a.cog - row0;
-  const int t0 = rn * a.run, t1 = min(t0 + a.run, a.tiles_n);
+  const int t0 = TILE ? rn : rn * a.run, t1 = TILE ? t0 + 1 : min(t0 + a.run, a.tiles_n);
   const bf16_t* xg = a.x + (long)b * a.x_image + (long)G * a.x_group;
   const bf16_t* wg = a.w + ((long)G * a.cog + row0) * a.cig * 9;
   // ---- geometry of a tile's patch
@@ -267,13 +272,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Cfg::kMinWa
   }
   const long out0 = (long)b * a.y_image + (long)G * a.y_group + (long)row0 * a.HoWo;
   const long rvo = (long)G * a.cog + row0;
-  const bool one_block = a.cig == CB;                      // its weights stay in LDS for the whole run
-  // 64 rows, one task per thread, three blocks and more: all loads have landed, on every path, before the next are issued.  The compiler
-  // cannot tell by itself (rows past the image skip their part of a commit) and waits for a block's weights in the middle of issuing
-  // its pixel loads, whose addresses it builds in registers that it takes to be still waiting.  24 models, 96 channels at 33 x 33 17.3 us
-  // without, 15.6 with, 8 models of 4 images, 128 at 28 x 28 5 %; two blocks up to 5 % the other way, 32 rows and stride 2 2 %.
-  const bool wait = Cfg::kBM == 64 && NT == 1 && a.cig > 2 * CB;
-  auto landed = [&] { if (wait) __builtin_amdgcn_s_waitcnt(0x0f70); };         // vmcnt(0)
+  const bool one_block = !TILE && a.cig == CB;             // its weights stay in LDS for the whole run
+  // Several blocks.  The compiler cannot tell that no load is on its way any more once a block has been written to LDS (rows past the image
+  // skip their part of a commit) and waits for a block's weights in the middle of issuing its pixel loads, whose addresses it builds in
+  // registers that it takes to be still waiting.  Two ways to tell it so:
+  //   kTapTile: a wait after the commit, where there is nothing to wait for.  us: 32 models, 256 channels, 28 -> 14 at stride 2 31.4 -> 29.4, 128
+  //   channels, 56 -> 28 26.8 -> 25.8; over 260 problems of two and three tasks per thread 3 to 5 % less time (6 % more once).  With one task per
+  //   thread that form is behind by as much (96 channels at 24 x 24 and 32 x 32 a tenth).
+  //   One task per thread, 64 rows, three blocks and more: a wait in front of the barrier.  24 models, 96 channels at 33 x 33 17.3 -> 15.6 us, 8 models of
+  //   4 images, 128 at 28 x 28 5 %; two blocks up to 5 % the other way, 32 rows and stride 2 2 %.
+  auto none_on_the_way = [] { __builtin_amdgcn_s_waitcnt(0x0f70); };     // vmcnt(0)
+  const bool wait = !TILE && Cfg::kBM == 64 && NT == 1 && a.cig > 2 * CB;
+  auto landed = [&] { if (wait) none_on_the_way(); };
   landed();
   __syncthreads();                                         // the zero fills are complete
   for (int tn = t0; tn < t1; ++tn) {
@@ -294,12 +304,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Cfg::kMinWa
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
     for (int ci0 = 0; ci0 < a.cig; ci0 += CB) {
-      commit(ci0 == 0, !one_block || tn == t0);
+      commit(ci0 == 0, TILE || !one_block || tn == t0);
       __syncthreads();
       // the next block, or the next tile's first one, is on its way while this one is multiplied
       const bool last = ci0 + CB == a.cig;
       const int ci_next = last ? 0 : ci0 + CB;
-      if (!last || tn + 1 < t1) {
+      if constexpr (TILE) {
+        if (!last) {
+          none_on_the_way();
+          prefetch_w(ci_next);
+          prefetch_x(tn, ci_next);
+        }
+      } else if (!last || tn + 1 < t1) {
         if (!one_block) prefetch_w(ci_next);
         prefetch_x(last ? tn + 1 : tn, ci_next);
       }

@@ -8,9 +8,11 @@
 
 namespace nf {
 
-template <class Cfg, int VW, int NT, bool FUSED>
+template <class Cfg, int VW, int NT, int KIND>
 static nf_status launch_tap_kernel(long long total, int lds, const ConvTapArgs& a, hipStream_t s) {
-  auto kern = conv_tap_kernel<Cfg, VW, NT, FUSED>;
+  if constexpr (KIND == kTapRun && NT > 1)
+    if (a.cig > kTapCB && a.run == 1) return launch_tap_kernel<Cfg, VW, NT, kTapTile>(total, lds, a, s);
+  auto kern = conv_tap_kernel<Cfg, VW, NT, KIND>;
   if (lds > 64 * 1024) {
     static std::atomic<bool> opted_in{false};        // per kernel: idempotent, a benign race
     if (!opted_in.load(std::memory_order_acquire)) {
@@ -24,8 +26,10 @@ static nf_status launch_tap_kernel(long long total, int lds, const ConvTapArgs& 
   return hipGetLastError() == hipSuccess ? NF_OK : NF_ELAUNCH;
 }
 
+static int fit_at_once(int lds, int most) { return std::max(1, std::min(160 * 1024 / 1280 / ((lds + 1279) / 1280), most)); }
+
 int tile_run(long long groups, int tiles_n, int lds, int most, double alone, double start) {
-  const int at_once = std::max(1, std::min(160 * 1024 / 1280 / ((lds + 1279) / 1280), most));
+  const int at_once = fit_at_once(lds, most);
   auto per_tile = [&](int run, long long j) { return start + run * std::max(alone, (double)j); };
   double best = 0;
   int pick = 1;
@@ -41,14 +45,17 @@ int tile_run(long long groups, int tiles_n, int lds, int most, double alone, dou
 // Position tiles per workgroup (bm rows) of `groups` x tiles_n.
 //   One block of 32 channels, whose weights stay in LDS: tile_run.  Over 4000 problems of 32 channels and of fused groups 0.1 % behind the
 //   best run and 21 % less time than a tile per workgroup and an epilogue through LDS.
-//   Two and three blocks: a long run saves the start of a tile only, next to nothing, and two workgroups that share a compute unit do not
-//   halve each other's rate.  Over 900 problems 1.3 % ahead of one tile each, 0.1 % behind the best run (32 models, 64 channels at 56 x 56 22.4 us in
-//   tiles of their own, 20.2 in runs of two).
+//   Two and three blocks: a run saves next to nothing of the start of a tile, and two workgroups that share a compute unit do not halve each
+//   other's rate, so it pays only where it evens out the last round of one or two workgroups per compute unit.  Over 2000 problems 1.3 % ahead of
+//   one tile each, 0.2 % behind the best run, 4 % slower at most (32 models, 64 channels at 56 x 56 22.4 us in tiles of their own, 20.2 in runs
+//   of two; whole rounds as they are: 32 models, 8 images, 64 -> 128 at 28 x 28 58 us, 67 in runs of seven).
 //   More: one tile.  The best run is 0.7 to 1.2 % ahead of it, and a wrong one far behind: 24 models, 256 channels at 20 x 20, 3 images 66 us in
 //   tiles of their own, 108 in runs of two; 12 models of 256 at 64 x 64 80 and 99.
 static int tap_run(int cig, int bm, long long groups, int tiles_n, int lds) {
   if (cig == kTapCB) return tile_run(groups, tiles_n, lds, 3);
-  return cig <= 3 * kTapCB ? tile_run(groups, tiles_n, lds, bm > 32 ? 2 : 3, 1.5, 0.1) : 1;
+  const int most = bm > 32 ? 2 : 3, at_once = fit_at_once(lds, most);
+  if (cig > 3 * kTapCB || at_once > 2 || groups * tiles_n % (256 * at_once) == 0) return 1;
+  return tile_run(groups, tiles_n, lds, most, 1.5, 0.1);
 }
 
 template <class Cfg, bool FUSED = false>
@@ -79,7 +86,7 @@ static nf_status launch_tap(const ConvPatchArgs& args, int B, hipStream_t s) {
   a.run = tap_run(a.cig, Cfg::kBM, groups, a.tiles_n, lds);
   a.runs = (a.tiles_n + a.run - 1) / a.run;
   const long long total = groups * a.runs;
-#define NF_TAP(VW_, NT_) return launch_tap_kernel<Cfg, VW_, NT_, FUSED>(total, lds, a, s)
+#define NF_TAP(VW_, NT_) return launch_tap_kernel<Cfg, VW_, NT_, FUSED ? kTapFused : kTapRun>(total, lds, a, s)
   if (nt > 0) switch (a.VW) {
     case 8: if (nt == 1) NF_TAP(8, 1); if (nt == 2) NF_TAP(8, 2); break;     // 32 staging registers per task
     case 4: if (nt == 1) NF_TAP(4, 1); if (nt == 2) NF_TAP(4, 2); if (nt == 3) NF_TAP(4, 3); break;

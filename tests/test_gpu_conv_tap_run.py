@@ -1,5 +1,5 @@
 """3 x 3 convolutions with several 128-position tiles per workgroup: a run that divides the tiles and one that does not, a tile whose rows end
-inside the image and one that reaches past it, one channel block (its weights stay) and several, fused narrow groups, stride 2, pad 0, planes
+inside the image and one that reaches past it, one channel block (its weights stay) and several, one task per thread and two, fused narrow groups, stride 2, pad 0, planes
 whose rows hold no whole chunks, a residual.  Integer-coded, so the oracle's bits."""
 import numpy as np
 import pytest
@@ -12,6 +12,7 @@ pytestmark = pytest.mark.gpu
     (8, 8, 32, 32, 1, 40, 40, 1, 1), (8, 8, 64, 40, 1, 41, 39, 1, 1), (32, 1, 64, 64, 1, 56, 56, 1, 1), (32, 4, 64, 64, 1, 57, 55, 1, 1),
     (16, 1, 128, 128, 32, 56, 56, 1, 1), (16, 1, 256, 256, 32, 56, 56, 2, 1), (16, 1, 256, 256, 32, 57, 55, 2, 1),
     (16, 2, 64, 64, 4, 33, 47, 1, 0), (8, 8, 32, 64, 1, 75, 81, 2, 1), (7, 9, 32, 32, 1, 130, 17, 1, 1),
+    (2, 3, 128, 136, 1, 56, 56, 2, 1), (3, 1, 160, 72, 1, 61, 47, 2, 1), (2, 1, 128, 40, 1, 100, 100, 1, 1), (26, 2, 256, 128, 1, 40, 43, 2, 1),
 ])
 def test_runs_exact(oracle, M, B, cin, cout, g, H, W, stride, pad):
     import paper_2009_13062_amd as nf
