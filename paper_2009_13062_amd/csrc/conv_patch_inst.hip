@@ -86,16 +86,12 @@ static nf_status launch_stem(ConvStemArgs& a, int B, hipStream_t s) {
   if (tiles <= 0 || tiles > 0x7fffffffLL) return NF_EUNSUPPORTED;
   if (a.PW % 8 != 0 || a.PS % 8 != 0 || a.PS % a.PW != 0) return NF_EUNSUPPORTED;
   const int lds = Cfg::lds_bytes(a.PS), chunks = 3 * (a.PS / a.PW) * a.cpr, nt = (chunks + 255) / 256;
-  // offsets inside a group's planes, and positions x Wo (cw_div), in 32 bits
-  if (lds > 160 * 1024 || nt > 12 || 3LL * a.H * a.W > 0x7fffffffLL || (long long)a.HoWo * a.Wo >= (1LL << 32)) return NF_EUNSUPPORTED;
+  // offsets of a group's third plane in 32 bits
+  if (lds > 160 * 1024 || nt > 12 || 2LL * a.H * a.W + a.W >= (1LL << 32) || !cw_div_exact(a.HoWo, a.Wo)) return NF_EUNSUPPORTED;
   a.run = tile_run(groups, a.tiles_n, lds, nt > 6 ? 2 : 3);
   a.runs = (a.tiles_n + a.run - 1) / a.run;
-  auto rcp = [](int d, unsigned* r, unsigned* one) {
-    *r = d == 1 ? 0u : (unsigned)(((1ULL << 32) + d - 1) / d);
-    *one = d == 1 ? ~0u : 0u;
-  };
-  rcp(a.Wo, &a.rcp_wo, &a.one_wo);
-  rcp(a.cpr, &a.rcp_cpr, &a.one_cpr);
+  cw_divisor(a.Wo, &a.rcp_wo, &a.one_wo);
+  cw_divisor(a.cpr, &a.rcp_cpr, &a.one_cpr);
   const long long total = groups * a.runs;
   if (nt <= 4) return launch_stem<BM, 4>(a, total, lds, s);
   if (nt <= 6) return launch_stem<BM, 6>(a, total, lds, s);

@@ -41,12 +41,8 @@ static nf_status launch_plane(const GemmLaunch& L, hipStream_t s) {
   (GemmArgs&)a = L.a;
   a.step = plane_step<Cfg>(L.a, &a.cps);
   if (a.step <= 0 || a.K % Cfg::kBK || (Cfg::kQuad && (a.geom.stride != 1 || a.cols % 4))) return NF_EUNSUPPORTED;
-  auto rcp = [](int d, unsigned* r, unsigned* one) {
-    *r = d == 1 ? 0u : (unsigned)(((1ULL << 32) + d - 1) / d);
-    *one = d == 1 ? ~0u : 0u;
-  };
-  rcp(a.cps, &a.rcp_cps, &a.one_cps);
-  rcp(a.geom.Wo, &a.rcp_wo, &a.one_wo);
+  cw_divisor(a.cps, &a.rcp_cps, &a.one_cps);
+  cw_divisor(a.geom.Wo, &a.rcp_wo, &a.one_wo);
   a.tiles_m = (a.rows + Cfg::kBM - 1) / Cfg::kBM;
   a.tiles_n = (a.cols + a.step - 1) / a.step;
   const long long total = (long long)a.tiles_m * a.tiles_n * a.nz0 * L.nz1;

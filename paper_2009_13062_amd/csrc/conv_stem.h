@@ -72,7 +72,7 @@ __global__ __launch_bounds__(256, NT > 6 ? 2 : 3) void conv_stem_kernel(ConvStem
 
   // ---- this thread's chunks of a patch: 8 pixels, aligned on both sides
   const int PHM = a.PS / a.PW, nchunk = CIN * PHM * a.cpr;
-  int c_src[NT], c_at[NT];                                   // c_at: patch row << 16 | LDS element (below 40960, see lds_bytes)
+  unsigned c_src[NT], c_at[NT];                                 // c_at: patch row << 16 | LDS element (below 40960, see lds_bytes)
 #pragma unroll
   for (int u = 0; u < NT; ++u) {
     const int t = tid + u * 256;
@@ -80,7 +80,7 @@ __global__ __launch_bounds__(256, NT > 6 ? 2 : 3) void conv_stem_kernel(ConvStem
     int ci = 0;
 #pragma unroll
     for (int c = 1; c < CIN; ++c) ci += row >= c * PHM;
-    c_src[u] = ci * a.H * a.W + ch * 8;
+    c_src[u] = (unsigned)ci * (unsigned)(a.H * a.W) + ch * 8;
     c_at[u] = (row - ci * PHM) << 16 | (ci * a.PS + (row - ci * PHM) * a.PW + Cfg::kColPad + ch * 8);
   }
   auto first_row = [&](int tn) { return (int)cw_div(tn * Cfg::kBN, a.rcp_wo, a.one_wo); };
@@ -89,7 +89,7 @@ __global__ __launch_bounds__(256, NT > 6 ? 2 : 3) void conv_stem_kernel(ConvStem
     const int iy0 = first_row(tn) * Cfg::kStride - Cfg::kPad;
 #pragma unroll
     for (int u = 0; u < NT; ++u) {
-      const int iy = iy0 + (c_at[u] >> 16);
+      const int iy = iy0 + (int)(c_at[u] >> 16);
       pre[u] = make_uint4(0u, 0u, 0u, 0u);
       if (tid + u * 256 < nchunk && (unsigned)iy < (unsigned)a.H) pre[u] = *reinterpret_cast<const uint4*>(xg + (c_src[u] + (long)iy * a.W));
     }

@@ -65,9 +65,8 @@ static nf_status launch_tap(const ConvPatchArgs& args, int B, hipStream_t s) {
   a.tiles_m = (a.cog + Cfg::kBM - 1) / Cfg::kBM;
   a.tiles_n = (a.HoWo + Cfg::kBN - 1) / Cfg::kBN;
   const long long groups = (long long)a.tiles_m * a.nG * B, tiles = groups * a.tiles_n;
-  if (tiles <= 0 || tiles > 0x7fffffffLL || (long long)a.HoWo * a.Wo >= (1LL << 32)) return NF_EUNSUPPORTED;
-  a.rcp_wo = a.Wo == 1 ? 0u : (unsigned)(((1ULL << 32) + a.Wo - 1) / a.Wo);
-  a.one_wo = a.Wo == 1 ? ~0u : 0u;
+  if (tiles <= 0 || tiles > 0x7fffffffLL || !cw_div_exact(a.HoWo, a.Wo)) return NF_EUNSUPPORTED;
+  cw_divisor(a.Wo, &a.rcp_wo, &a.one_wo);
   a.PS = (a.PS + 7) / 8 * 8;
   // Pixels per chunk: the width with the fewest chunks per thread (a chunk is 8 loads and up to 32 staging registers),
   // the narrowest of those, which spreads the chunks over most threads.  Chunks start at any 2-byte address, so widths
@@ -147,4 +146,5 @@ nf_status launch_conv_tap_3x3(ConvPatchArgs& a, int B, hipStream_t s) {
 }  // namespace nf
 
 // For the tests; not part of the interface.  Host only.
+extern "C" int netfuse_div_exact(long long n, int d) { return nf::cw_div_exact(n, d); }
 extern "C" int netfuse_conv_tap_run(int cig, int bm, long long groups, int tiles_n, int lds) { return nf::tap_run(cig, bm, groups, tiles_n, lds); }

@@ -77,7 +77,7 @@ __device__ __forceinline__ void wave_lds_order() {
   __builtin_amdgcn_wave_barrier();
 }
 
-// n / d, branch free; exact while n < 2^32 / d
+// n / d, branch free (cw_divisor, cw_div_exact in gemm_launch.h); exact at least while n < 2^32 / d
 __device__ __forceinline__ unsigned cw_div(unsigned n, unsigned rcp, unsigned one) { return __umulhi(n, rcp) + (n & one); }
 
 // The fragments of tap + ahead are read in front of the instructions of a tap: enough of them to cover an LDS read.

@@ -155,12 +155,8 @@ template <typename T>
 nf_status launch_conv_wave(ConvWaveArgs<T>& a, int Ho, int B, hipStream_t s) {
   const WaveChoice c = choose_wave(a, Ho, B);
   if (c.kg == 0 || ((uintptr_t)a.w & 15) != 0) return NF_EUNSUPPORTED;
-  auto rcp = [](int d, unsigned* r, unsigned* one) {
-    *r = d == 1 ? 0u : (unsigned)(((1ULL << 32) + d - 1) / d);
-    *one = d == 1 ? ~0u : 0u;
-  };
-  rcp(a.W, &a.rcp_w, &a.one_w);
-  rcp(a.Wo, &a.rcp_wo, &a.one_wo);
+  cw_divisor(a.W, &a.rcp_w, &a.one_w);
+  cw_divisor(a.Wo, &a.rcp_wo, &a.one_wo);
 #define NF_CWT(NB_, KG_) if (c.kg == KG_ && c.nb == NB_) return launch_tile<T, NB_, KG_>(c.tile, a, B, s)
   NF_CWT(1, 4); NF_CWT(2, 4); NF_CWT(3, 4); NF_CWT(4, 4); NF_CWT(5, 4); NF_CWT(7, 4);
   NF_CWT(1, 1); NF_CWT(2, 1); NF_CWT(4, 1);

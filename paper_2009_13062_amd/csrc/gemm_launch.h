@@ -76,6 +76,16 @@ nf_status launch_gemm_ring(int tile, bool packed, GemmLaunch& L, hipStream_t s);
 // The same for a pointwise convolution (A = weights, B = planes of cols % 8 == 0 positions, K % 64 == 0 channels).
 enum RingConvTileId { RC64x64 = 0, RC64x128, RC64x256, RC128x128, RC128x256, kNumRingConvTiles };
 nf_status launch_conv_ring(int tile, GemmLaunch& L, hipStream_t s);
+// Operands of cw_div (conv_wave.h), n / d as the high half of n * rcp: rcp = (2^32 + e) / d with 0 <= e < d, exact while n * e < 2^32.
+inline void cw_divisor(int d, unsigned* rcp, unsigned* one) {
+  *rcp = d == 1 ? 0u : (unsigned)(((1ULL << 32) + d - 1) / d);
+  *one = d == 1 ? ~0u : 0u;
+}
+inline bool cw_div_exact(long long n, int d) {
+  const unsigned long long rcp = ((1ULL << 32) + d - 1) / d;
+  return n < (1LL << 32) && (unsigned long long)n * (rcp * d - (1ULL << 32)) < (1ULL << 32);
+}
+
 // Tiles per workgroup for `groups` x tiles_n of them, where a workgroup walks a run of tiles (7x7 stem, 3x3): the split with the fewest
 // tile times one after another.  A compute unit holds as many workgroups as its LDS, in pieces of 1280 bytes, and `most` for their
 // registers; of j together each takes max(j, alone) per tile and `start` tiles to start (addresses, zero fill, first loads).

@@ -39,3 +39,21 @@ def test_every_run_is_in_range():
         for tiles in (1, 2, 3, 63, 64, 65, 524288):
             for lds in (20000, 50000, 54614, 81920, 81921, 163840):
                 assert 1 <= run_of(32, groups, tiles, lds) <= tiles
+
+
+def test_division_is_called_exact_where_it_is():
+    """Positions / width as the high half of a product: refused shapes run other kernels, so the bound is the exact one."""
+    import paper_2009_13062_amd as nf
+    f = nf.lib.netfuse_div_exact
+    f.argtypes, f.restype = [ctypes.c_longlong, ctypes.c_int], ctypes.c_int
+    for d in list(range(1, 700)) + [1000, 4095, 4097, 65535, 65537]:
+        rcp = -(-2 ** 32 // d)
+        most = 2 ** 32 - 1 if rcp * d == 2 ** 32 else (2 ** 32 - 1) // (rcp * d - 2 ** 32)       # the largest n that is called exact
+        assert f(most, d) and not f(most + 1, d), d
+        assert most >= 2 ** 32 // d - 1                        # never less than the bound that holds for every divisor
+        for k in (1, 2, most // d // 2, most // d):           # the last value before a step and the step itself
+            for n in (k * d - 1, k * d, most):
+                if d > 1 and 0 <= n <= most:
+                    assert n * rcp >> 32 == n // d, (n, d)
+    # tall planes: 128 and 512 columns are powers of two, 650 divides 2^32 + 4
+    assert f(524287 * 128, 128) and f(2 ** 26 - 1, 512) and f(2 ** 26 - 1, 650)

@@ -69,3 +69,22 @@ def test_3x3(H, cin, cout, g, pad):
         ref = torch.cat([w[i * cout // g:(i + 1) * cout // g].float().flatten(1) @ taps[i * cin // g:(i + 1) * cin // g].flatten(0, 2)
                          for i in range(g)])
         assert torch.equal(y[0, :, oy], ref.bfloat16()), oy
+
+
+# The 7 x 7 stem over 3 channels, whose third plane starts beyond 2^30 elements and, in the larger one, whose three end beyond 2^31.
+@pytest.mark.parametrize("H", [1050001, 1400003])
+def test_stem(H):
+    import paper_2009_13062_amd as nf
+    W, cout = 512, 8
+    x, w = integers((1, 3, H, W), -2, 3, H), integers((cout, 3, 7, 7), -1, 2, 5)
+    y = nf.conv2d(x, w, 1, stride=2, pad=3)
+    Ho, Wo = y.shape[2:]
+    assert 2 * H * W > 2 ** 30 and (3 * H * W > 2 ** 31) == (H > 1.3e6)
+    for oy in (0, 1, Ho // 2 + 1, Ho - 1):
+        rows = torch.zeros(3, 7, W + 6, device="cuda")
+        for ky in range(7):
+            iy = 2 * oy - 3 + ky
+            if 0 <= iy < H:
+                rows[:, ky, 3:3 + W] = x[0, :, iy].float()
+        taps = torch.stack([rows[:, :, kx:kx + 2 * Wo:2] for kx in range(7)], 2)
+        assert torch.equal(y[0, :, oy], (w.float().flatten(1) @ taps.flatten(0, 2)).bfloat16()), oy
