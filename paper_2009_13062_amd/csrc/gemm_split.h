@@ -1,0 +1,316 @@
+// float32 contraction on the bf16 matrix instructions: merged matmul, float32 storage.
+//
+//   C[z][i][j] = sum_k A[z][i][k] * B[z][k][j]     one fused epilogue
+//
+// A float32 is EXACTLY the sum of three bf16 numbers (24 bits of significand, 8 in each): x = x1 + x2 + x3 with x1 = bf16(x),
+// x2 = bf16(x - x1), x3 = x - x1 - x2, every difference exact.  Of the nine products of two such sums the six down to
+// 2^-16 of the first are multiplied and summed in float32 on v_mfma_f32_16x16x32_bf16; the three left out come to 2^-25 of a product on
+// average (at most 2^-23), less than a float32 product's own rounding.  Six bf16 instructions take 96 clocks for 16 x 16 x 32 products, the
+// float32 ones (v_mfma_f32_16x16x4_f32) 256.
+//
+// A result that is not finite (an operand that is not, or one within 2^-8 of the largest number, whose x1 is infinite, or a sum that
+// overflows) is computed again from the operands themselves, in float32.
+//
+// A workgroup is four wavefronts, one per chain of k, that share nothing until their sums meet in LDS: no barrier couples them in the loop.
+// B: a lane loads 8 rows of FN neighbouring columns straight into registers, where v_cvt_pk_bf16_f32 makes pairs along k of them, so nothing
+// is transposed (column FN c + j of the tile is column c of block j).  A: 8 rows x 128 bytes per load, through LDS of the wavefront's own into
+// the operand's layout: straight from memory a load touched 16 half lines, and that alone bounded the kernel (8 models of 128 rows
+// 3072 -> 768: 41 us with loads and nothing else; per byte A cost 2.3 times what B did).  The splitting of a row block (5.5 instructions per
+// element) is dealt out between the multiplications of the block before it: a lone wavefront issues a vector instruction every 6 clocks and
+// both in one stretch each took 50 us there where this takes 38.  Loads are buffer loads of any 4-byte alignment whose resource covers
+// one problem's operand: what lies past its end comes back as 0 (rows of k past the end, columns behind the last row).
+//
+// What bounds it: operands of 4 bytes from L2, 35 to 45 bytes per ns and compute unit, then issue slots.  Measured (8 models of 128 rows, us,
+// gemm_f32.h -> this): 768 -> 2304 44.5 -> 34.5, 768 -> 768 18.3 -> 14.8, 768 -> 3072 49 -> 38, 3072 -> 768 55.5 -> 38; 12 models of 512 rows 768 ->
+// 3072 285 -> 206, 3072 -> 768 300 -> 191; 1 model of 128 rows 3072 -> 768 23.9 -> 15.3.
+// Error against 64 bits (2-norm, K = 64, 768, 3072): 1.0e-7, 3.5e-7, 4.9e-7 -> 0.5e-7, 2.0e-7, 4.2e-7.
+//
+// Measured and dropped: stages of a 128 x 128 tile split once per workgroup and shared through LDS (1.3 us per 32 k: LDS traffic and the barrier,
+// 203 us at 12 models of 512 rows 768 -> 3072, 259 with 3072 -> 768); eight chains of k in as many wavefronts (no change).
+//
+// One order of the sum for every tile: 32-k step n belongs to chain n mod 4, one chain per wavefront, and the chains are added
+// in ascending order.
+#pragma once
+#include "gemm_dma.h"
+#include "gemm_f32.h"
+
+namespace nf {
+
+template <int FM_, int FN_, int D_>
+struct SplitCfg {
+  static constexpr int FM = FM_, FN = FN_, D = D_;             // 16-row blocks, 16-column blocks, steps of loads in flight
+  static constexpr int kBM = 16 * FM, kBN = 16 * FN, kKG = 4, kThreads = kKG * kWave, kBK = 32;
+  static constexpr int kALoads = 2 * FM, kAStage = FM * 2048;   // 1 KB loads of a step's rows (8 rows x 128 bytes), bytes of a stage
+  static constexpr int kLdsA = kKG * 2 * kAStage, kLdsSums = kKG * FM * FN * kWave * 16;
+  static constexpr int kLdsBytes = kLdsA > kLdsSums ? kLdsA : kLdsSums;
+  static_assert(D == 1 || D == 2, "one remainder step");
+};
+
+// x, y (consecutive k) -> their three bf16 parts, packed in pairs
+__device__ __forceinline__ void split3(float x, float y, uint32_t& p1, uint32_t& p2, uint32_t& p3) {
+  p1 = pack_bf16x2(x, y);
+  x -= __uint_as_float(p1 << 16);
+  y -= __uint_as_float(p1 & 0xffff0000u);
+  p2 = pack_bf16x2(x, y);
+  x -= __uint_as_float(p2 << 16);
+  y -= __uint_as_float(p2 & 0xffff0000u);
+  p3 = pack_bf16x2(x, y);
+}
+
+struct SplitFrag { u32x4_t p[3]; };
+
+template <int FN>
+__device__ __forceinline__ void buf_load_cols(float (&v)[FN], __amdgpu_buffer_rsrc_t r, unsigned off) {
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
+  if constexpr (FN == 4) {
+    const u32x4_t t = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0);
+#pragma unroll
+    for (int j = 0; j < FN; ++j) v[j] = __uint_as_float(t[j]);
+  } else if constexpr (FN == 3) {
+    const u32x3 t = __builtin_amdgcn_raw_buffer_load_b96(r, (int)off, 0, 0);
+#pragma unroll
+    for (int j = 0; j < FN; ++j) v[j] = __uint_as_float(t[j]);
+  } else if constexpr (FN == 2) {
+    const u32x2 t = __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0);
+#pragma unroll
+    for (int j = 0; j < FN; ++j) v[j] = __uint_as_float(t[j]);
+  } else {
+    v[0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
+  }
+}
+
+// A sum that came out infinite or NaN, from the operands themselves.
+__device__ __attribute__((noinline)) float split_again(const float* a, const float* b, long ldb, int K) {
+  float t = 0.f;
+  for (int k = 0; k < K && t == t; ++k) t = fmaf(a[k], b[(long)k * ldb], t);       // NaN stays NaN
+  return t;
+}
+
+// FN neighbouring columns of one output row: what the epilogue reads, and the epilogue.
+template <int FN>
+struct SplitRow {
+  typedef float vec_t __attribute__((ext_vector_type(FN)));
+  vec_t res;
+  float rbias, rscale, rshift;
+  long at;
+
+  __device__ __forceinline__ void read(const GemmF32Args& a, int z0, int z1, int row, int col) {
+    const Epilogue& ep = a.ep;
+    const long rv = z0 * ep.row_vec_stride0 + row;
+    at = z0 * a.sC0 + z1 * a.sC1 + (long)row * a.ldc + col;
+    rbias = ep.row_bias ? ep.row_bias[rv] : 0.f;
+    rscale = ep.row_scale ? ep.row_scale[rv] : 1.f;
+    rshift = ep.row_scale ? ep.row_shift[rv] : 0.f;
+#pragma unroll
+    for (int j = 0; j < FN; ++j) res[j] = 0.f;
+    if (a.R) {
+      if (col + FN <= a.cols) __builtin_memcpy(&res, a.R + at, sizeof(float) * FN);
+      else
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+          if (col + j < a.cols) res[j] = a.R[at + j];
+    }
+  }
+  __device__ __forceinline__ void finish(const GemmF32Args& a, int col, const float (&v)[FN], const float (&bias)[FN]) const {
+    vec_t out;
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+      float x = v[j] + rbias + bias[j];
+      if (a.ep.row_scale) x = fmaf(x, rscale, rshift);
+      out[j] = a.ep.act_before_residual ? apply_act(x, a.ep.act) + res[j] : apply_act(x + res[j], a.ep.act);
+    }
+    if (col + FN <= a.cols) __builtin_memcpy(a.C + at, &out, sizeof(float) * FN);
+    else
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+        if (col + j < a.cols) a.C[at + j] = out[j];
+  }
+};
+
+// What lanes of a wavefront exchange through LDS: the hardware keeps a wavefront's LDS accesses in order, the compiler has to.
+__device__ __forceinline__ void wave_lds_fence() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// TAIL: K is no multiple of 32 (but of 4).
+template <class Cfg, bool TAIL>
+__global__ __launch_bounds__(Cfg::kThreads, 2) void gemm_split_kernel(GemmF32Args a) {
+  constexpr int FM = Cfg::FM, FN = Cfg::FN, D = Cfg::D, KG = Cfg::kKG;
+  extern __shared__ __align__(16) float smem[];
+  const int lane = threadIdx.x % kWave, g = lane / 16, l16 = lane % 16;
+  const int q = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+
+  unsigned id = xcd_remap(blockIdx.x, gridDim.x);
+  const int tm = id % a.tiles_m;  id /= a.tiles_m;
+  const int tn = id % a.tiles_n;  id /= a.tiles_n;
+  const int z0 = id % a.nz0, z1 = id / a.nz0;
+  const int row0 = tm * Cfg::kBM, col0 = tn * Cfg::kBN;
+  const float* const A = a.A + z0 * a.sA0;
+  const float* const B = a.B + z0 * a.sB0 + z1 * a.sB1;
+  const __amdgpu_buffer_rsrc_t ra = f32_rsrc(A, a.a_bytes), rb = f32_rsrc(B, a.b_bytes);
+
+  // A: load t is rows 8 t .. 8 t + 7, 128 bytes of each; through LDS of the wavefront's own, 16-byte chunks of a row exchanged by its
+  // number, so that reads and writes meet every bank equally.  Rows past the end are the last one again.
+  unsigned a_off[Cfg::kALoads];
+#pragma unroll
+  for (int t = 0; t < Cfg::kALoads; ++t) a_off[t] = (unsigned)(((long)min(row0 + 8 * t + lane / 8, a.rows - 1) * a.lda + lane % 8 * 4) * 4);
+  lds_u8_t* const own_lds = (lds_u8_t*)smem + q * 2 * Cfg::kAStage;
+  lds_u8_t* const a_to = own_lds + lane / 8 * 128;             // rows 8 t + lane / 8: exchanged by (row / 2) % 8 = 4 (t % 2) + lane / 16
+  const int a_chunk = lane % 8;
+  const lds_u8_t* const a_from = own_lds + l16 * 128;
+  // columns past the end read what lies there (they are not stored)
+  const unsigned pitch = (unsigned)a.ldb * 4u;
+  const unsigned b_off = (unsigned)(8 * g) * pitch + (unsigned)(col0 + FN * l16) * 4u;
+
+  u32x4_t ar[Cfg::kALoads];
+  float bv[D][8][FN];
+  auto load_a = [&](int k0) {
+#pragma unroll
+    for (int t = 0; t < Cfg::kALoads; ++t) {
+      unsigned off = a_off[t] + (unsigned)k0 * 4u;
+      if constexpr (TAIL) off = k0 + a_chunk * 4 < a.K ? off : kF32Oob;
+      ar[t] = buf_load16(ra, off);
+    }
+  };
+  auto write_a = [&](int stage) {
+#pragma unroll
+    for (int t = 0; t < Cfg::kALoads; ++t)
+      *(lds_u32x4_t*)(a_to + stage * Cfg::kAStage + t * 1024 + ((a_chunk ^ (t % 2 * 4 + lane / 16)) * 16)) = ar[t];
+  };
+  auto load_b = [&](int slot, int k0) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) buf_load_cols<FN>(bv[slot][i], rb, b_off + (unsigned)(k0 + i) * pitch);
+  };
+
+  f32x4_t acc[FM][FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+  const int nk = (a.K + 31) / 32, n = (nk - q + KG - 1) / KG;  // steps in all, of this wavefront
+  auto k_of = [&](int s) { return (s * KG + q) * 32; };        // past the end: B comes back as 0 and is not used
+  // Step s, u = s modulo 2: the rows of step s + 1 go to LDS and those of s + 2 are asked for, the columns of step s are split and
+  // those of s + D asked for, and a row block at a time is read, split and multiplied.
+  auto step = [&](int u, int s) {
+    write_a(u ^ 1);
+    load_a(k_of(s + 2));
+    SplitFrag fb[FN];
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        uint32_t p1, p2, p3;
+        split3(bv[u % D][2 * p][j], bv[u % D][2 * p + 1][j], p1, p2, p3);
+        fb[j].p[0][p] = p1; fb[j].p[1][p] = p2; fb[j].p[2][p] = p3;
+      }
+    load_b(u % D, k_of(s + D));
+    SplitFrag fa[2];
+    f32x4v_t ax[2][2];
+    auto read_a = [&](int i) {
+#pragma unroll
+      for (int c = 0; c < 2; ++c) ax[i % 2][c] = *(const lds_f32x4_t*)(a_from + u * Cfg::kAStage + i * 2048 + (((2 * g + c) ^ (l16 / 2)) * 16));
+    };
+    auto split_a = [&](int i) {
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          uint32_t p1, p2, p3;
+          split3(ax[i % 2][c][2 * h], ax[i % 2][c][2 * h + 1], p1, p2, p3);
+          fa[i % 2].p[0][2 * c + h] = p1; fa[i % 2].p[1][2 * c + h] = p2; fa[i % 2].p[2][2 * c + h] = p3;
+        }
+    };
+    read_a(0);
+    split_a(0);
+    if (FM > 1) read_a(1);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+      constexpr int kPa[6] = {2, 0, 1, 1, 0, 0}, kPb[6] = {0, 2, 1, 0, 1, 0};      // smallest products first
+      if (i + 2 < FM) read_a(i + 2);
+#pragma unroll
+      for (int t = 0; t < 6; ++t)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, fa[i % 2].p[kPa[t]]),
+                                                              __builtin_bit_cast(bf16x8_t, fb[j].p[kPb[t]]), acc[i][j], 0, 0, 0);
+      if (i + 1 < FM) split_a(i + 1);
+#pragma unroll
+      for (int t = 0; t < 6 * FN; ++t) {
+        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+        if (i + 1 < FM) __builtin_amdgcn_sched_group_barrier(0x2, (44 + 6 * FN - 1) / (6 * FN), 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    wave_lds_fence();                                          // the next step's writes are behind this step's reads
+  };
+  load_a(k_of(0));
+#pragma unroll
+  for (int d = 0; d < D; ++d) load_b(d, k_of(d));
+  write_a(0);
+  load_a(k_of(1));
+  wave_lds_fence();
+  int s = 0;
+  for (; s + 2 <= n; s += 2) {
+    step(0, s);
+    step(1, s + 1);
+  }
+  if (s < n) step(0, s);
+  __syncthreads();                                             // the sums go where the stages were
+
+  // Every wavefront leaves its sums in LDS ([chain][block][lane]) and finishes a quarter of the rows, whose residuals and constants are
+  // on their way meanwhile.
+  const int col = col0 + FN * l16;
+  auto block_of = [&](int u) { return FM == 4 ? q : (q * FM + u) / 4; };        // of this wavefront's FM rows per lane
+  auto row_of = [&](int u) { return 4 * g + (FM == 4 ? u : (q * FM + u) % 4); };
+  SplitRow<FN> rows[FM];
+  float bias[FN];
+  const float* const cb = a.ep.col_bias ? a.ep.col_bias + z0 * a.ep.col_vec_stride0 : nullptr;
+#pragma unroll
+  for (int j = 0; j < FN; ++j) bias[j] = cb && col + j < a.cols ? cb[col + j] : 0.f;
+#pragma unroll
+  for (int u = 0; u < FM; ++u) {
+    const int row = row0 + 16 * block_of(u) + row_of(u);
+    if (row < a.rows && col < a.cols) rows[u].read(a, z0, z1, row, col);
+  }
+  lds_f32_t* const part = (lds_f32_t*)smem + lane * 4;
+  constexpr int kChain = FM * FN * kWave * 4;
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+      *(lds_f32x4_t*)(part + q * kChain + (i * FN + j) * kWave * 4) = __builtin_bit_cast(f32x4v_t, acc[i][j]);
+  __syncthreads();
+
+  f32x4v_t own[FM == 4 ? FN : 1];
+  if constexpr (FM == 4)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+      f32x4v_t c[KG];
+#pragma unroll
+      for (int p = 0; p < KG; ++p) c[p] = *(const lds_f32x4_t*)(part + p * kChain + (q * FN + j) * kWave * 4);
+      own[j] = ((c[0] + c[1]) + c[2]) + c[3];
+    }
+#pragma unroll
+  for (int u = 0; u < FM; ++u) {
+    const int row = row0 + 16 * block_of(u) + row_of(u);
+    if (row >= a.rows || col >= a.cols) continue;
+    float v[FN];
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+      if constexpr (FM == 4) {
+        v[j] = own[j][u];
+      } else {
+        const lds_f32_t* src = part + (block_of(u) * FN + j) * kWave * 4 + row_of(u) - 4 * g;
+        v[j] = ((src[0] + src[kChain]) + src[2 * kChain]) + src[3 * kChain];
+      }
+      if (!(fabsf(v[j]) <= 3.402823466e38f) && col + j < a.cols) v[j] = split_again(A + (long)row * a.lda, B + col + j, a.ldb, a.K);
+    }
+    rows[u].finish(a, col, v, bias);
+  }
+}
+
+}  // namespace nf

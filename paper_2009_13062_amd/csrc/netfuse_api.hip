@@ -447,7 +447,9 @@ nf_status netfuse_linear(const void* X, const void* W, const float* bias, const 
     const bool gather = Nout % 4 != 0;                      // then a weight row is a one-row image of Nout positions
     a.H = 1; a.W = Nout; a.KW = 1; a.khw = 1; a.Wo = Nout; a.stride = 1; a.dil = 1;
     f32_divisors(a);
-    const nf_status st = launch_gemm_f32(a, 1, gather, s);
+    nf_status st = launch_gemm_split(a, s);
+    if (st != NF_EUNSUPPORTED) return st;
+    st = launch_gemm_f32(a, 1, gather, s);
     if (st != NF_EUNSUPPORTED) return st;
   }
   const int tiles_m = (N + 63) / 64, tiles_n = (Nout + 63) / 64;
@@ -861,7 +863,7 @@ nf_status netfuse_conv2d(const void* x, const void* w, const float* bias, const 
     return launch_gemm_any(bkind, al, tile, L, s);
   }
 
-  // float32: the matrix-pipe kernel, except for narrow groups.  Its lowest tile is 16 rows x 64 positions with k padded to
+  // float32: the matrix-pipe kernels, except for narrow groups.  Its lowest tile is 16 rows x 64 positions with k padded to
   // 64 or 128, so a group of a few products per position costs it as much as one of 16 x 64; the direct kernel (one
   // thread per output) pays for what there is, but walks k alone: 0.15 to 0.3 us per k where the chip is not full.
   // Hence a limit on the products per position, by the taps that the other kernel has to look up per tile, and one on k

@@ -1,0 +1,102 @@
+"""float32 matmul on bf16 matrix instructions: the edges of every tile (64, 48, 32 and 16 wide or high), k remainders
+of the 32-element steps and of the four chains, both sides of the rule that chooses the kernel, operands that the split into bf16
+parts does not represent, and the same bits whatever tile the number of models or images leads to.
+
+Bounds: a product is off by at most 2^-23 (the three of nine products of parts that are left out) and a sum of K of them in any order by
+K 2^-24 of sum |x||w|; each 32-k step adds six products of parts.  The measured error, in the 2-norm, is half of a plain float32 sum's."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+rng = np.random.default_rng(77)
+
+
+@pytest.fixture(scope="module")
+def nf():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2009_13062_amd as nf_
+    return nf_
+
+
+def rnd(*shape):
+    return rng.standard_normal(shape).astype(np.float32)
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a, np.float32)).cuda()
+
+
+def check(got, ref, absref, K):
+    got = got.detach().cpu().numpy().astype(np.float64)
+    bound = (K + 10) * 2.0 ** -24 * absref + 1e-30
+    assert got.shape == ref.shape and np.isfinite(got).all()
+    assert (np.abs(got - ref) <= bound).all(), float((np.abs(got - ref) / bound).max())
+
+
+@pytest.mark.parametrize("M,N,K,Nout", [
+    (1, 1, 64, 1), (2, 15, 68, 31), (2, 17, 92, 33), (1, 16, 256, 64),            # 16-row tiles, k of 32 n + 4 .. 28
+    (8, 33, 260, 65), (16, 48, 124, 96), (24, 65, 288, 49), (32, 63, 416, 47),    # 32- and 64-row tiles
+    (12, 130, 768, 193), (32, 129, 96, 769), (6, 257, 1028, 95),                  # several tiles per compute unit
+    (2, 1030, 64, 255), (2, 1025, 64, 256), (2, 1024, 64, 257),                   # either side of the rule below 128 of k
+    (1, 1449, 128, 1447), (1, 1449, 128, 1449), (1, 40, 60, 40), (3, 21, 66, 20),  # below 256 of k; too few k, k not in fours
+], ids=lambda v: str(v))
+def test_linear(nf, M, N, K, Nout):
+    X, W, b, R = rnd(M, N, K), rnd(M, K, Nout), rnd(M, Nout), rnd(M, N, Nout)
+    x, w = X.astype(np.float64), W.astype(np.float64)
+    prod = np.matmul(x, w) + b[:, None]
+    size = np.matmul(np.abs(x), np.abs(w)) + np.abs(b)[:, None] + np.abs(R)
+    check(nf.linear(dev(X), dev(W), bias=dev(b), residual=dev(R), act=nf.ACT_RELU), np.maximum(prod, 0) + R, size, K)
+    if M > 1:                                    # nothing of another problem is read, not even times zero
+        X[1:], W[1:] = np.nan, np.nan
+        check(nf.linear(dev(X), dev(W))[:1], np.matmul(x, w)[:1], size[:1], K)
+
+
+@pytest.mark.parametrize("N,K,Nout", [(128, 768, 768), (93, 1024, 257), (40, 3072, 130)], ids=lambda v: str(v))
+def test_no_further_from_64_bits_than_a_float32_sum(nf, N, K, Nout):
+    """The 2-norm of the error against that of the products summed in float32, one rounding each, in four chains of k."""
+    X, W = rnd(1, N, K), rnd(1, K, Nout)
+    ref = np.matmul(X.astype(np.float64), W.astype(np.float64))
+    chains = np.zeros((4, N, Nout), np.float32)
+    for k in range(K):
+        chains[k // 32 % 4] += X[0, :, k, None] * W[0, k]
+    plain = chains[0] + chains[1] + chains[2] + chains[3]
+    got = nf.linear(dev(X), dev(W)).cpu().numpy()
+    assert np.linalg.norm(got - ref) <= np.linalg.norm(plain - ref)
+
+
+def test_operands_without_three_parts(nf):
+    """Infinities times numbers of one part (whose other parts are 0), NaN, numbers that round up to infinity in 8 bits, products that overflow:
+    what float32 gives; rows and columns beside them as they were."""
+    N, K, Nout = 40, 96, 70
+    X, W = rnd(1, N, K), rnd(1, K, Nout)
+    plain = nf.linear(dev(X), dev(W)).cpu().numpy()
+    W[0, 5] = np.where(W[0, 5] > 0, 1.0, -1.0)
+    clean = nf.linear(dev(X), dev(W)).cpu().numpy()
+    bad = X.copy()
+    bad[0, 3, 5], bad[0, 7, 5], bad[0, 20, 40], bad[0, 33, 5] = np.inf, -np.inf, np.nan, 3.4e38
+    got = nf.linear(dev(bad), dev(W)).cpu().numpy()
+    assert np.array_equal(got[0, 3], np.inf * W[0, 5]) and np.array_equal(got[0, 7], -np.inf * W[0, 5])
+    assert np.isnan(got[0, 20]).all()
+    assert np.allclose(got[0, 33], 3.4e38 * W[0, 5], rtol=1e-6)
+    keep = [i for i in range(N) if i not in (3, 7, 20, 33)]
+    assert np.array_equal(got[0, keep], clean[0, keep])
+    big = nf.linear(dev(X * np.float32(1e30)), dev(W * np.float32(1e30))).cpu().numpy()
+    assert not np.isfinite(big).any()
+    tiny = nf.linear(dev(X * np.float32(2.0 ** -40)), dev(W * np.float32(2.0 ** 20))).cpu().numpy()
+    assert np.array_equal(tiny, clean * np.float32(2.0 ** -20)) and plain.shape == clean.shape
+
+
+@pytest.mark.parametrize("rows,cols,K,taken", [(1, 1, 64, 1), (1, 1, 60, 0), (512, 512, 64, 1), (512, 513, 64, 0), (2048, 1024, 128, 1),
+                                                (2048, 1025, 128, 0), (2048, 1025, 256, 1), (64, 64, 130, 0)])
+def test_rule(nf, rows, cols, K, taken):
+    assert bool(nf.lib.netfuse_f32_split_takes(rows, cols, K)) == bool(taken)
+
+
+@pytest.mark.parametrize("N,K,Nout", [(16, 768, 2304), (65, 96, 100), (128, 4096, 1024), (300, 260, 47)], ids=lambda v: str(v))
+def test_merged_equals_single(nf, N, K, Nout):
+    X, W = torch.randn(32, N, K, device="cuda"), torch.randn(32, K, Nout, device="cuda")
+    one = nf.linear(X[31:], W[31:])
+    for M in (2, 3, 7, 16, 32):
+        assert torch.equal(nf.linear(X[32 - M:], W[32 - M:])[M - 1], one[0]), M
