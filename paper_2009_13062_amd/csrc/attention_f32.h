@@ -97,8 +97,7 @@ __global__ __launch_bounds__(256) void attention_f32_kernel(AttnArgs a, int qblo
         sc[kb][r] = key < a.S ? sc[kb][r] * a.scale + (mk ? mk[key] : 0.f) : kLowest;
         mloc = fmaxf(mloc, sc[kb][r]);
       }
-    mloc = fmaxf(mloc, __shfl_xor(mloc, 16, kWave));
-    mloc = fmaxf(mloc, __shfl_xor(mloc, 32, kWave));
+    mloc = across_halves(across_rows(mloc, MaxOp{}), MaxOp{});
     const float mnew = fmaxf(mrun, mloc), corr = expf(mrun - mnew);
     mrun = mnew;
     lrun *= corr;
@@ -124,8 +123,7 @@ __global__ __launch_bounds__(256) void attention_f32_kernel(AttnArgs a, int qblo
       }
     __syncthreads();                            // the stage is free
   }
-  lrun += __shfl_xor(lrun, 16, kWave);
-  lrun += __shfl_xor(lrun, 32, kWave);
+  lrun = across_halves(across_rows(lrun, AddOp{}), AddOp{});
   if (q >= a.S) return;
   float* Op = (float*)a.O + (((long)m * a.B + b) * a.S + q) * ((long)a.heads * a.d) + (long)h * a.d;
 #pragma unroll

@@ -320,7 +320,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void a
     for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
       for (int r = 0; r < 16; ++r) mloc = fmaxf(mloc, s_acc[sb][r]);
-    mloc = fmaxf(mloc, __shfl_xor(mloc, 32, kWave));
+    mloc = across_halves(mloc, MaxOp{});
     if (raw) mloc = fmaxf(mloc * sc, kLowest);
     const float mnew = fmaxf(mrun, mloc);
     const float corr = __builtin_amdgcn_exp2f(mrun - mnew);
@@ -372,7 +372,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void a
     __syncthreads();
   }
 
-  const float ltot = lrun + __shfl_xor(lrun, 32, kWave);
+  const float ltot = across_halves(lrun, AddOp{});
   if (q < a.S) {
     const float inv = 1.0f / ltot;
     bf16_t* Op = (bf16_t*)a.O + (((long)m * a.B + b) * a.S + q) * ((long)a.heads * kAttnD) + (long)h * kAttnD;
@@ -618,7 +618,7 @@ __global__ __launch_bounds__(256, 2) void attention_relpos_mfma_d64_kernel(AttnR
     for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
       for (int r = 0; r < 16; ++r) mloc = fmaxf(mloc, s_acc[sb][r]);
-    mloc = fmaxf(mloc, __shfl_xor(mloc, 32, kWave));
+    mloc = across_halves(mloc, MaxOp{});
     if (raw) mloc = fmaxf(mloc * sc, kLowest);
     const float mnew = fmaxf(mrun, mloc);
     const float corr = __builtin_amdgcn_exp2f(mrun - mnew);
@@ -663,7 +663,7 @@ __global__ __launch_bounds__(256, 2) void attention_relpos_mfma_d64_kernel(AttnR
     __syncthreads();                                        // the stage is free for the next block's commit
   }
 
-  const float ltot = lrun + __shfl_xor(lrun, 32, kWave);
+  const float ltot = across_halves(lrun, AddOp{});
   if (q < a.S) {
     const float inv = 1.0f / ltot;
     bf16_t* Op = (bf16_t*)a.O + (((long)m * a.B + b) * a.S + q) * hd + (long)h * kAttnD;

@@ -76,16 +76,35 @@ __device__ __forceinline__ float apply_act(float v, int act) {
   return v;
 }
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
-  return v;
+// Reductions over a wavefront without a trip through LDS (__shfl_xor is one, some hundred clocks each): the halves and the 16-lane rows
+// are exchanged by the lane-permute instructions, the rest within a row by DPP operands.  The partners are those of the butterfly with
+// offsets 32, 16, 8, 4, 2, 1 (a rotation by 4 meets the same value as lane ^ 4, rows being equal 8 apart by then), so its bits are too.  Layer
+// norm with a residual, bf16 rows of 768 (two of these sums, one behind the other, in every launch): 256 rows 2.86 -> 2.52 us, 4096 4.94 -> 4.68, 16384
+// 14.4 -> 13.9.
+template <int CTRL> __device__ __forceinline__ float dpp(float v) {
+  return __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), CTRL, 0xf, 0xf, true));
 }
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, kWave));
-  return v;
+constexpr int kRowRor8 = 0x128, kRowRor4 = 0x124, kQuadXor2 = 0x4e, kQuadXor1 = 0xb1;
+// v with lanes 32 apart, lanes 16 apart combined
+template <class Op> __device__ __forceinline__ float across_halves(float v, Op&& op) {
+  const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return op(__uint_as_float(s[0]), __uint_as_float(s[1]));
 }
+template <class Op> __device__ __forceinline__ float across_rows(float v, Op&& op) {
+  const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return op(__uint_as_float(s[0]), __uint_as_float(s[1]));
+}
+template <class Op> __device__ __forceinline__ float wave_reduce(float v, Op&& op) {
+  v = across_rows(across_halves(v, op), op);
+  v = op(v, dpp<kRowRor8>(v));
+  v = op(v, dpp<kRowRor4>(v));
+  v = op(v, dpp<kQuadXor2>(v));
+  return op(v, dpp<kQuadXor1>(v));
+}
+struct AddOp { __device__ __forceinline__ float operator()(float a, float b) const { return a + b; } };
+struct MaxOp { __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); } };
+__device__ __forceinline__ float wave_sum(float v) { return wave_reduce(v, AddOp{}); }
+__device__ __forceinline__ float wave_max(float v) { return wave_reduce(v, MaxOp{}); }
 
 // Workgroups are handed to the 8 XCDs round-robin (id % 8), and each XCD has its own L2.  This
 // maps the hardware id to a logical id such that consecutive logical ids run on the same XCD, so
