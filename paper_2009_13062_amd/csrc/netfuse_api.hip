@@ -1165,6 +1165,20 @@ nf_status netfuse_maxpool2d(const void* x, void* y, int B, int Ctot, int H, int 
 #undef NF_POOL
     return launched();
   }
+  // Any other width from 8 columns, and float32.  Below 2^14 outputs, and in planes of one row, the launch is the time and the kernel for any
+  // window is level or ahead (us, it and this one: 64 planes of 12 x 12 in float32 2.85 and 2.90, of 31 x 31 2.95 and 2.95, 4 of 1 x 4000 2.18 and
+  // 2.41; 4096 of 9 x 9 in bf16 3.14 and 2.92, of 14 x 14 3.56 and 2.81).  The limits on H and W: a row or column past the edge is a 32-bit number too.
+  if (k == 3 && stride == 2 && pad == 1 && W >= 8 && Ho > 1 && n_out > (1 << 14) && H < (1 << 30) && W < (1 << 30)) {
+    const int nbx = (Wo + 3) / 4, nby = (Ho + 1) / 2;
+    const long long total = n_out / Wo / Ho * nby * nbx;
+    const unsigned grid = grid_for(total, 256);
+    const bool small = total + 256LL * grid < (1LL << 32);
+#define NF_POOL(T, I) nf_launch((maxpool3x3s2_any_kernel<T, I>), dim3(grid), dim3(256), 0, s, (const T*)x, (T*)y, H, W, Ho, Wo, nbx, nby, (I)total)
+    if (dt == NF_F32) { if (small) NF_POOL(float, uint32_t); else NF_POOL(float, size_t); }
+    else { if (small) NF_POOL(bf16_t, uint32_t); else NF_POOL(bf16_t, size_t); }
+#undef NF_POOL
+    return launched();
+  }
   const unsigned grid = grid_for(n_out, 256);
   if (dt == NF_F32)
     nf_launch(maxpool2d_kernel<float>, dim3(grid), dim3(256), 0, s, (const float*)x, (float*)y, H, W, Ho,

@@ -425,6 +425,67 @@ __global__ __launch_bounds__(256) void maxpool3x3s2_bf16_row_kernel(const bf16_t
   }
 }
 
+// The same windows over rows of 8 columns or more, of any width and alignment, bf16 or float32: four outputs of two rows per thread out of
+// five input rows, 8 columns of each in loads of 16 bytes at any element and the one to their left.  The last thread of a row begins where four
+// outputs still fit and writes some of its neighbour's again: threads that went through their columns one by one held up their wavefronts (64
+// planes of 31 x 31 in bf16 3.2 us so, 2.8 this way).  Bound by memory where the kernel for any window, one output per thread with its 64-bit
+// divisions and nine loads behind branches, is bound by instructions.  That one -> this, us: 512 planes of 112 x 112 in float32 15.7 -> 8.6, 2048
+// 49.9 -> 22.0 (5.8 TB/s); 768 of 100 x 100 in bf16 16.3 -> 5.1, 2048 of 110 x 110 46.2 -> 12.9.
+template <typename T, typename I>
+__global__ __launch_bounds__(256) void maxpool3x3s2_any_kernel(const T* __restrict__ x, T* y, int H, int W, int Ho, int Wo, int nbx, int nby, I total) {
+  typedef T row_t __attribute__((ext_vector_type(8)));
+  typedef T out_t __attribute__((ext_vector_type(4)));
+  auto larger = [](float v, float best) { return v > best ? v : best; };        // a NaN is never larger
+  for (I o = (I)blockIdx.x * 256 + threadIdx.x; o < total; o += (I)gridDim.x * 256) {
+    const I t = o / (I)nbx;
+    const int ox = min((int)(o - t * (I)nbx) * 4, Wo - 4), ix = 2 * ox;
+    const bool odd_end = ix + 8 > W;                           // only by one column: the load starts one to the left and the last is met twice
+    const I pl = t / (I)nby;
+    const int oy = (int)(t - pl * (I)nby) * 2;
+    const size_t plane = (size_t)pl;
+    const T* const xc = x + plane * H * W;
+    row_t v[5];
+    T left[5];
+#pragma unroll
+    for (int r = 0; r < 5; ++r) {
+      const T* const row = xc + (size_t)min(max(2 * oy - 1 + r, 0), H - 1) * W + ix;
+      v[r] = load_at<row_t>(row - odd_end);
+      left[r] = row[ix > 0 ? -1 : 0];
+    }
+    T c[5][9];
+#pragma unroll
+    for (int r = 0; r < 5; ++r) {
+      c[r][0] = left[r];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) c[r][1 + e] = odd_end ? v[r][min(e + 1, 7)] : v[r][e];
+    }
+    float best[2][4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) best[0][j] = best[1][j] = -INFINITY;
+#pragma unroll
+    for (int r = 0; r < 5; ++r)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float h = larger(load_f32(&c[r][2 * j + 2]), larger(load_f32(&c[r][2 * j + 1]), larger(load_f32(&c[r][2 * j]), -INFINITY)));
+        if (r < 3) best[0][j] = larger(h, best[0][j]);
+        if (r > 1) best[1][j] = larger(h, best[1][j]);
+      }
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      if (oy + q >= Ho) break;
+      T* const to = y + (plane * Ho + oy + q) * Wo + ox;
+      out_t w;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        T one;
+        store_f32(&one, best[q][j]);
+        w[j] = one;
+      }
+      store_at(to, w);
+    }
+  }
+}
+
 // Global average pooling: one wavefront per (b, channel).
 template <typename T>
 __global__ __launch_bounds__(256) void avgpool_global_kernel(const T* __restrict__ x, T* y, size_t nchan,
