@@ -1057,17 +1057,28 @@ nf_status netfuse_attention(const void* Q, const void* K, const void* V, const f
     return launched();
   }
   const long long head_elems = (long long)(S - 1) * stride_row + d;         // one head's rows, first to last element
-  // Up to 8 tokens a 64-query workgroup is nearly empty and the wavefront-per-query kernel below is ahead.  float32, 32 models x 8
-  // sequences x 12 heads of 64 (us, that kernel / this one): 1 token 4.8 / 38.8, 4 11.6 / 39.5, 8 27.6 / 39.1, 10 38.8 / 39.1, 16
-  // 72 / 40; one model, 1 sequence: 3.8 / 6.4, 4.9 / 6.5 at 8, 6.4 / 6.6 at 20.
+  // Up to 8 tokens the wavefront-per-query kernel below: of 64 features the two are level at 5 (us, that kernel / this one, 32 models x 8 sequences x 12
+  // heads: 1 token 4.4 / 16.4, 4 11.7 / 16.3, 5 15.5 / 16.3, 8 27.6 / 16.5; one model, 1 sequence: 3.4 / 4.1, 3.9 / 3.8, 4.0 / 3.7, 4.5 / 3.8), other head sizes
+  // have no form of 16 queries and pay for 32.
   if (dt == NF_F32 && S > 8 && d % 4 == 0 && d <= 128 && head_elems < (1LL << 29)) {
-    const int qblocks = (S + kAttnF32Queries - 1) / kAttnF32Queries;
+    // Query groups and key shares, by the sequence length alone: the shares decide the order of the sums, and a model's bits do not depend on
+    // what is merged with it.  Where 16 or 32 rows are all there are, wavefronts without queries take keys instead (us, 4 groups x 1 share / 2 x 2 /
+    // 1 x 4: 12 models x 8 sequences of 10 tokens 16.1 / 11.3 / 8.5, 32 x 8 of 16 35.5 / 24.8 / 18.4, one of 16 5.5 / 4.6 / 4.1).  Above that shares gain in
+    // small grids and lose in full ones (128 tokens, 2 models 8.4 / 6.4 / 5.4, 12 x 8 51 / 59 / 69; 40 tokens, 12 x 8 18.8 / 20.9 / 19.7).
+    const int groups = S > 32 ? 4 : S > 16 || d <= 32 || d > 64 ? 2 : 1;
+    const int qblocks = (S + 16 * groups - 1) / (16 * groups);
     const long long total = prod({M, B, heads, qblocks});
     if (total > kMaxGrid) return NF_EUNSUPPORTED;
     const unsigned bytes = (unsigned)(head_elems * 4);
-    if (d <= 32) nf_launch((attention_f32_kernel<2, 64>), dim3((unsigned)total), dim3(256), 0, s, a, qblocks, bytes);
-    else if (d <= 64) nf_launch((attention_f32_kernel<4, 64>), dim3((unsigned)total), dim3(256), 0, s, a, qblocks, bytes);
-    else nf_launch((attention_f32_kernel<8, 32>), dim3((unsigned)total), dim3(256), 0, s, a, qblocks, bytes);
+#define NF_ATT(NB, KB, QG, KS) nf_launch((attention_f32_kernel<NB, KB, QG, KS>), dim3((unsigned)total), dim3(256), 0, s, a, qblocks, bytes)
+    if (d <= 32) {
+      if (groups == 4) NF_ATT(2, 64, 4, 1); else NF_ATT(2, 64, 2, 2);
+    } else if (d <= 64) {
+      if (groups == 4) NF_ATT(4, 64, 4, 1); else if (groups == 2) NF_ATT(4, 64, 2, 2); else NF_ATT(4, 64, 1, 4);
+    } else {
+      if (groups == 4) NF_ATT(8, 32, 4, 1); else NF_ATT(8, 32, 2, 2);
+    }
+#undef NF_ATT
     return launched();
   }
   if (d > 256) return NF_EUNSUPPORTED;
