@@ -26,9 +26,13 @@
 //
 // Measured (8 models, us; the plain FMA kernels before -> this): 128 x 768 x 3072 matmul 187 -> 45 (31.6 at the fp32
 // matrix peak), 128 x 3072 x 768 750 -> 52, pointwise 64 -> 256 at 56 x 56 460 -> 17; a 12-layer encoder 16.3 -> 3.2 ms.
-// Matmuls of enough k are gemm_split.h's since.  Of the convolutions it runs the pointwise ones, k x k but 3 x 3, and 3 x 3 over wide planes at stride 2 or groups that are no
-// multiple of 8 channels; the other 3 x 3 ones are conv_wave.h's.  Narrow groups and few k over many rows stay with the FMA
-// kernels (netfuse_api.hip).
+// Matmuls of enough k are gemm_split.h's since.  Of the convolutions it runs the pointwise ones, k x k but 3 x 3, and 3 x 3 over wide planes at
+// stride 2 or groups that are no multiple of 8 channels; the other 3 x 3 ones are conv_wave.h's.  Narrow groups and few k over many rows stay with
+// the FMA kernels (netfuse_api.hip).
+//
+// Rows of B of any length move 16 bytes at a time; those that are no multiple of 4 were gathered 4 bytes at a time (8 models, us: 2048 -> 512 over 7 x 7 27.6 ->
+// 17.8, 512 -> 2048 with residual 20.7 -> 17.1, 256 -> 64 over 49 x 49 18.4 -> 13.0; 32 models of 384 rows 64 -> 1001 35 -> 30; 536 drawn problems: 27 % less
+// time, none slower).
 #pragma once
 #include "gemm_launch.h"
 
@@ -70,7 +74,8 @@ __device__ __forceinline__ uint32_t buf_load4(__amdgpu_buffer_rsrc_t r, unsigned
 // n / d, branch free; exact while n < 2^32 / d
 __device__ __forceinline__ unsigned div_by(unsigned n, unsigned rcp, unsigned one) { return __umulhi(n, rcp) + (n & one); }
 
-// KIND kF32Dense: B rows of whole 4-column chunks; kF32Gather / kF32GatherWide: B through the convolution geometry,
+// KIND kF32Dense: B moves 4 columns at a time, at any 4-byte alignment; the columns past a row's end are the next row's first, or 0, and are
+// not stored.  kF32Gather / kF32GatherWide: B through the convolution geometry,
 // 4 bytes at a time, any shape, with at most 31 / 63 taps.  AVEC: K % 4 == 0, so A moves in whole 4-k chunks.
 template <class Cfg, int KIND, bool AVEC>
 __global__ __launch_bounds__(Cfg::kThreads, 2) void gemm_f32_kernel(GemmF32Args a) {   // 2: keeps the chains out of the

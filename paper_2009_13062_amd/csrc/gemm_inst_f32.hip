@@ -22,6 +22,7 @@ using F16x64q = F32Cfg<16, 64, 1, 4, 32, 2, 4, 4>;
 enum { kF64x64, kF64x64s, kF64x48s, kF32x64s, kF32x64q, kF16x64s, kF16x64q, kNumF32Tiles };
 constexpr int kBMs[kNumF32Tiles] = {64, 64, 64, 32, 32, 16, 16};
 constexpr int kBNs[kNumF32Tiles] = {64, 64, 48, 64, 64, 64, 64};
+constexpr int kGroups[kNumF32Tiles] = {1, 2, 2, 2, 4, 2, 4};
 // Measured time per unit of tile area and k of the busiest compute unit, dense / gathered B, where a compute unit
 // has one tile / several (then its workgroups fill each other's waits).  With one tile per unit the forms with k
 // split over 2 or 4 groups of wavefronts are ahead of the plain ones (128 x 3072 x 768 at 8 models: 51 us against 64;
@@ -85,7 +86,11 @@ nf_status launch_gemm_f32(GemmF32Args& a, int nz1, bool gather, hipStream_t s) {
     if (gather && t == kF64x48s) continue;
     if ((t == kF32x64q || t == kF16x64q) && !chains4) continue;
     const long long rounds = (tiles(t) + 255) / 256;
-    const long long cost = rounds * kBMs[t] * kBNs[t] * kUnitCost[gather][rounds > 1][t];
+    // Up to 64 k a tile on one group walks 64 of them, one on two groups 128, half of them zeros; with several tiles per compute unit that is
+    // time (us, without this factor / with it: 12 models of 1500 rows 50 -> 99 14.6 / 10.7, 18 of 1243 48 -> 258 31.9 / 19.7).  With one the two groups
+    // are ahead all the same (5 x 3 images of 14 x 14, 31 -> 88 5.5 against 6.4), and with a few of 16 rows (7 x 2 of 30 x 30, 41 -> 34 7.1 against 7.7).
+    const int walked = a.K <= 64 && kGroups[t] == 2 && rounds > (kBMs[t] == 16 ? 3 : 1) ? 2 : 1;
+    const long long cost = rounds * kBMs[t] * kBNs[t] * kUnitCost[gather][rounds > 1][t] * walked;
     if (best < 0 || cost < best_cost) { best = t; best_cost = cost; }
   }
   return chains4 ? launch_tile<4>(best, a, problems, gather, s) : launch_tile<2>(best, a, problems, gather, s);

@@ -444,12 +444,9 @@ nf_status netfuse_linear(const void* X, const void* W, const float* bias, const 
     a.rows = N; a.cols = Nout; a.K = K; a.nz0 = M;
     a.ep.col_bias = bias; a.ep.col_vec_stride0 = Nout;
     a.ep.act = act; a.ep.act_before_residual = 1;
-    const bool gather = Nout % 4 != 0;                      // then a weight row is a one-row image of Nout positions
-    a.H = 1; a.W = Nout; a.KW = 1; a.khw = 1; a.Wo = Nout; a.stride = 1; a.dil = 1;
-    f32_divisors(a);
     nf_status st = launch_gemm_split(a, s);
     if (st != NF_EUNSUPPORTED) return st;
-    st = launch_gemm_f32(a, 1, gather, s);
+    st = launch_gemm_f32(a, 1, false, s);
     if (st != NF_EUNSUPPORTED) return st;
   }
   const int tiles_m = (N + 63) / 64, tiles_n = (Nout + 63) / 64;
@@ -870,7 +867,7 @@ nf_status netfuse_conv2d(const void* x, const void* w, const float* bias, const 
   // where a model has few groups.  Direct / matrix (us): depthwise 3x3 of 1024 channels at 14 x 14 5 / 50, 16 -> 1
   // channels per group 29 / 64, 4 -> 8 38 / 47, 8 -> 8 81 / 47; 7x7 depthwise 10 / 63, 2 -> 8 79 / 83; pointwise 8 -> 8
   // 23 / 25, 16 -> 8 38 / 25; one model with one group at 56 x 56: 8 -> 1 13 / 7, 16 -> 1 24 / 8.
-  const bool f32_dense = KH == 1 && KW == 1 && stride == 1 && pad == 0 && HoWo % 4 == 0;
+  const bool f32_pointwise = KH == 1 && KW == 1 && stride == 1 && pad == 0, f32_dense = f32_pointwise && HoWo % 4 == 0;
   const bool f32_narrow = (long long)cog * Kdim <= (f32_dense ? 64 : 220 + 10LL * KH * KW) && (g >= 64 || Kdim <= (f32_dense ? 16 : 72));
   if (dt == NF_F32 && KH * KW < 64 && !f32_narrow && f32_fits((long long)cog * Kdim, prod({cig, H, W}), Kdim)) {
     GemmF32Args a;
@@ -890,7 +887,7 @@ nf_status netfuse_conv2d(const void* x, const void* w, const float* bias, const 
       const nf_status st = conv_wave<float>(x, w, residual, y, a.ep, M, B, Cin, Cout, g, H, W, (int)Ho, (int)Wo, stride, pad, s);
       if (st != NF_EUNSUPPORTED) return st;
     }
-    const nf_status st = launch_gemm_f32(a, B, !f32_dense, s);
+    const nf_status st = launch_gemm_f32(a, B, !f32_pointwise, s);
     if (st != NF_EUNSUPPORTED) return st;               // more tiles than a grid holds: the direct kernel strides over any number
   }
 
