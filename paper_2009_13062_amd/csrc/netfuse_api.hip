@@ -867,6 +867,7 @@ nf_status netfuse_conv2d(const void* x, const void* w, const float* bias, const 
   // where a model has few groups.  Direct / matrix (us): depthwise 3x3 of 1024 channels at 14 x 14 5 / 50, 16 -> 1
   // channels per group 29 / 64, 4 -> 8 38 / 47, 8 -> 8 81 / 47; 7x7 depthwise 10 / 63, 2 -> 8 79 / 83; pointwise 8 -> 8
   // 23 / 25, 16 -> 8 38 / 25; one model with one group at 56 x 56: 8 -> 1 13 / 7, 16 -> 1 24 / 8.
+  // Pointwise layers over planes that are no multiple of 4 positions keep the line measured when their rows were gathered.
   const bool f32_pointwise = KH == 1 && KW == 1 && stride == 1 && pad == 0, f32_dense = f32_pointwise && HoWo % 4 == 0;
   const bool f32_narrow = (long long)cog * Kdim <= (f32_dense ? 64 : 220 + 10LL * KH * KW) && (g >= 64 || Kdim <= (f32_dense ? 16 : 72));
   if (dt == NF_F32 && KH * KW < 64 && !f32_narrow && f32_fits((long long)cog * Kdim, prod({cig, H, W}), Kdim)) {
