@@ -22,8 +22,10 @@
  *     deterministic and the calls can be captured into a HIP graph.
  *   - Tensors are dense row-major (last index fastest) unless a stride is given.
  *   - `dt` is the STORAGE type of activations and weight tensors (float or bfloat16 bit
- *     patterns).  Arithmetic is always fp32 (fp32 accumulation); a bf16 output is rounded once,
- *     to nearest even, when it is stored.  Per-feature / per-channel vectors (bias, scale,
+ *     patterns).  Arithmetic is always fp32 (fp32 accumulation; products of float32 matrices may be
+ *     formed from bf16 parts of the operands that hold all of their bits, no further from the exact
+ *     result than fp32 products at any scale); a bf16 output is rounded once, to nearest even, when
+ *     it is stored.  Per-feature / per-channel vectors (bias, scale,
  *     shift, gamma, beta, mean, var) and attention masks are ALWAYS float, for either `dt`.
  *   - Inputs are never written.  Outputs are fully overwritten.  An output may alias the
  *     `residual` operand or (norms, pools excepted where stated) not alias anything else.

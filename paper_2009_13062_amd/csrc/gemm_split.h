@@ -2,27 +2,30 @@
 //
 //   C[z][i][j] = sum_k A[z][i][k] * B[z][k][j]     one fused epilogue
 //
-// A float32 is EXACTLY the sum of three bf16 numbers (24 bits of significand, 8 in each): x = x1 + x2 + x3 with x1 = bf16(x),
-// x2 = bf16(x - x1), x3 = x - x1 - x2, every difference exact.  Of the nine products of two such sums the six down to
-// 2^-16 of the first are multiplied and summed in float32 on v_mfma_f32_16x16x32_bf16; the three left out come to 2^-25 of a product on
-// average (at most 2^-23), less than a float32 product's own rounding.  Six bf16 instructions take 96 clocks for 16 x 16 x 32 products, the
-// float32 ones (v_mfma_f32_16x16x4_f32) 256.
+// A float32 is the sum of three bf16 numbers (24 bits of significand, 8 in each): x = x1 + x2 + x3 with x1 = bf16(x),
+// x2 = bf16(x - x1), x3 = x - x1 - x2, every difference exact as long as the last bit of x3 is a bf16 number: bf16 has float32's exponents
+// but ends at 2^-133 where float32 ends at 2^-149.  So both operands are multiplied by 2^24 first, which puts the last bit of ANY float32 at a normal
+// bf16 number, and the sums by 2^-48 at the end.  Of the nine products of two such sums the six down to 2^-16 of the first are multiplied and
+// summed in float32 on v_mfma_f32_16x16x32_bf16; the three left out come to 2^-28.2 of a product on average, at most 2^-24.2 (4 million drawn
+// products).  Six bf16 instructions take 96 clocks for 16 x 16 x 32 products, the float32 ones (v_mfma_f32_16x16x4_f32) 256.  (bf16 splitting with
+// six products: Henry, Tang, Heinecke, "Leveraging the bfloat16 Artificial Intelligence Datatype For Higher-Precision Computations", 2019.)
 //
-// A result that is not finite (an operand that is not, or one within 2^-8 of the largest number, whose x1 is infinite, or a sum that
-// overflows) is computed again from the operands themselves, in float32.
+// A sum that is not finite (an operand that is not, or one of 2^104 and more, whose first part is infinite, or a sum of 2^80 and more on its way)
+// is computed again from the operands themselves, in float32.
 //
 // A workgroup is four wavefronts, one per chain of k, that share nothing until their sums meet in LDS: no barrier couples them in the loop.
 // B: a lane loads 8 rows of FN neighbouring columns straight into registers, where v_cvt_pk_bf16_f32 makes pairs along k of them, so nothing
 // is transposed (column FN c + j of the tile is column c of block j).  A: 8 rows x 128 bytes per load, through LDS of the wavefront's own into
 // the operand's layout: straight from memory a load touched 16 half lines, and that alone bounded the kernel (8 models of 128 rows
-// 3072 -> 768: 41 us with loads and nothing else; per byte A cost 2.3 times what B did).  The splitting of a row block (5.5 instructions per
+// 3072 -> 768: 41 us with loads and nothing else; per byte A cost 2.3 times what B did).  The splitting of a row block (6.5 instructions per
 // element) is dealt out between the multiplications of the block before it: a lone wavefront issues a vector instruction every 6 clocks and
 // both in one stretch each took 50 us there where this takes 38.  Loads are buffer loads of any 4-byte alignment whose resource covers
 // one problem's operand: what lies past its end comes back as 0 (rows of k past the end, columns behind the last row).
 //
 // What bounds it: operands of 4 bytes from L2, 35 to 45 bytes per ns and compute unit, then issue slots.  Measured (8 models of 128 rows, us,
-// gemm_f32.h -> this): 768 -> 2304 44.5 -> 34.5, 768 -> 768 18.3 -> 14.8, 768 -> 3072 49 -> 38, 3072 -> 768 55.5 -> 38; 12 models of 512 rows 768 ->
-// 3072 285 -> 206, 3072 -> 768 300 -> 191; 1 model of 128 rows 3072 -> 768 23.9 -> 15.3.
+// gemm_f32.h -> this): 768 -> 2304 39.8 -> 33.0, 768 -> 768 15.9 -> 13.9, 768 -> 3072 43.0 -> 36.2, 3072 -> 768 48.2 -> 37.9; 12 models of 512 rows 768 ->
+// 3072 235 -> 190, 3072 -> 768 236 -> 181; 1 model of 128 rows 3072 -> 768 21.4 -> 16.0.  The multiplication by 2^24 is 4 to 8 % of it (31.4, 13.2, 34.8,
+// 35.6, 179, 171 and 14.4 without it, and an error of 3.5e-5 where an operand is 2^-120).
 // Error against 64 bits (2-norm, K = 64, 768, 3072): 1.0e-7, 3.5e-7, 4.9e-7 -> 0.5e-7, 2.0e-7, 4.2e-7.
 //
 // Measured and dropped: stages of a 128 x 128 tile split once per workgroup and shared through LDS (1.3 us per 32 k: LDS traffic and the barrier,
@@ -46,8 +49,12 @@ struct SplitCfg {
   static_assert(D == 1 || D == 2, "one remainder step");
 };
 
-// x, y (consecutive k) -> their three bf16 parts, packed in pairs
+constexpr float kSplitScale = 0x1p24f, kSplitUnscale = 0x1p-48f;
+
+// x, y (consecutive k) -> the three bf16 parts of 2^24 x, 2^24 y, packed in pairs
 __device__ __forceinline__ void split3(float x, float y, uint32_t& p1, uint32_t& p2, uint32_t& p3) {
+  x *= kSplitScale;
+  y *= kSplitScale;
   p1 = pack_bf16x2(x, y);
   x -= __uint_as_float(p1 << 16);
   y -= __uint_as_float(p1 & 0xffff0000u);
@@ -241,7 +248,7 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void gemm_split_kernel(GemmF32Arg
 #pragma unroll
       for (int t = 0; t < 6 * FN; ++t) {
         __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
-        if (i + 1 < FM) __builtin_amdgcn_sched_group_barrier(0x2, (44 + 6 * FN - 1) / (6 * FN), 0);
+        if (i + 1 < FM) __builtin_amdgcn_sched_group_barrier(0x2, (52 + 6 * FN - 1) / (6 * FN), 0);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -307,7 +314,8 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void gemm_split_kernel(GemmF32Arg
         const lds_f32_t* src = part + (block_of(u) * FN + j) * kWave * 4 + row_of(u) - 4 * g;
         v[j] = ((src[0] + src[kChain]) + src[2 * kChain]) + src[3 * kChain];
       }
-      if (!(fabsf(v[j]) <= 3.402823466e38f) && col + j < a.cols) v[j] = split_again(A + (long)row * a.lda, B + col + j, a.ldb, a.K);
+      if (fabsf(v[j]) <= 3.402823466e38f) v[j] *= kSplitUnscale;
+      else if (col + j < a.cols) v[j] = split_again(A + (long)row * a.lda, B + col + j, a.ldb, a.K);
     }
     rows[u].finish(a, col, v, bias);
   }

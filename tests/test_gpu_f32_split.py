@@ -1,6 +1,6 @@
 """float32 matmul on bf16 matrix instructions: the edges of every tile (64, 48, 32 and 16 wide or high), k remainders
-of the 32-element steps and of the four chains, both sides of the rule that chooses the kernel, operands that the split into bf16
-parts does not represent, and the same bits whatever tile the number of models or images leads to.
+of the 32-element steps and of the four chains, both sides of the rule that chooses the kernel, operands of every size, some that the split
+into bf16 parts does not represent, and the same bits whatever tile the number of models or images leads to.
 
 Bounds: a product is off by at most 2^-23 (the three of nine products of parts that are left out) and a sum of K of them in any order by
 K 2^-24 of sum |x||w|; each 32-k step adds six products of parts.  The measured error, in the 2-norm, is half of a plain float32 sum's."""
@@ -86,6 +86,20 @@ def test_operands_without_three_parts(nf):
     assert not np.isfinite(big).any()
     tiny = nf.linear(dev(X * np.float32(2.0 ** -40)), dev(W * np.float32(2.0 ** 20))).cpu().numpy()
     assert np.array_equal(tiny, clean * np.float32(2.0 ** -20)) and plain.shape == clean.shape
+
+
+@pytest.mark.parametrize("ex,ew", [(-100, 90), (-112, 100), (-120, 100), (-126, 100), (-140, 100), (100, -120), (-70, -70), (100, 20)])
+@pytest.mark.parametrize("N,K,Nout", [(3, 64, 35), (65, 776, 97)], ids=lambda v: str(v))
+def test_every_finite_operand(nf, N, K, Nout, ex, ew):
+    """Operands down to the smallest float32 numbers beside large ones, so that results are ordinary numbers: the parts hold every bit of them.  The
+    bound of a sum at scale 1 holds at every scale, and half a unit of the smallest number for results down there."""
+    X = np.ldexp(rng.standard_normal((2, N, K)), ex).astype(np.float32)
+    W = np.ldexp(rng.standard_normal((2, K, Nout)), ew).astype(np.float32)
+    x, w = X.astype(np.float64), W.astype(np.float64)
+    got, ref, size = nf.linear(dev(X), dev(W)).cpu().numpy().astype(np.float64), np.matmul(x, w), np.matmul(np.abs(x), np.abs(w))
+    assert (np.abs(got - ref) <= (K + 10) * 2.0 ** -24 * size + 2.0 ** -149).all(), float((np.abs(got - ref) / size).max())
+    if -126 < min(ex, ew) and abs(ex + ew) < 60:              # the 2-norm too is what it is at scale 1: 0.5e-7 and 2.0e-7 for these K
+        assert np.linalg.norm(got - ref) <= (1e-7 if K == 64 else 3e-7) * np.linalg.norm(ref)
 
 
 @pytest.mark.parametrize("rows,cols,K,taken", [(1, 1, 64, 1), (1, 1, 60, 0), (512, 512, 64, 1), (512, 513, 64, 0), (2048, 1024, 128, 1),
