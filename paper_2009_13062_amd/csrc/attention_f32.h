@@ -7,10 +7,15 @@
 // 4 g + t in instruction t.  Block i of V^T is features i, NB + i, 2 NB + i ..., so a lane reads NB neighbouring ones at once and ends up
 // with 4 NB neighbouring outputs.  Loads are buffer loads over one head's rows; keys past the sequence and features past d come back as 0.
 //
-// Bound by latency where the chip is not full, by the matrix pipe where it is (12 models x 512 tokens: 65 % of its 157 TFLOP/s).
-// Measured (12 heads of 64, us; with expf, bounds and mask looked up per key and V read 4 bytes at a time -> this): 2 models of 128 tokens
-// 10.6 -> 8.4, 8 11.1 -> 9.2, 12 x 8 sequences 59 -> 51, 12 of 300 with a mask 50 -> 41, 12 of 512 116 -> 96.  Error against 64 bits (2-norm): 64
-// tokens 2.84e-7 -> 2.80e-7, 128 3.34e-7 -> 3.33e-7, 512 4.98e-7 -> 4.93e-7.
+// Scores, mask and maximum stay in natural units, weights come from expf: in log2 units (one fma and v_exp_f32 per key, 10 to 15 % faster: 12 models of 512 tokens
+// 96 against 111) scale and mask were rounded once more, which with a mask of ordinary numbers raised the error against 64 bits by up to 15 % (12 tokens
+// 1.12e-7 -> 1.32e-7, 128 2.75e-7 -> 3.03e-7), weights below 2^-126 became 0, and scores past 2^31 gave NaN: the rounded maximum lay 2^7 and more beside
+// the largest score.
+//
+// Bound by latency where the chip is not full, by the matrix pipe where it is (12 models x 512 tokens: 55 % of its 157 TFLOP/s).
+// Measured (12 heads of 64, us; with bounds and mask looked up per key and V read 4 bytes at a time -> this): 2 models of 128 tokens
+// 10.6 -> 9.4, 8 11.2 -> 10.3, 12 x 8 sequences 59 -> 58, 12 of 300 with a mask 50 -> 46, 12 of 512 117 -> 111, with a mask 124 -> 111.  Error against 64
+// bits (2-norm): 64 tokens 2.87e-7 -> 2.85e-7, 128 3.35e-7 -> 3.32e-7, 512 5.04e-7 -> 4.99e-7; with a mask 2.08e-7 -> 2.04e-7, 2.80e-7 -> 2.75e-7, 4.90e-7 -> 4.72e-7.
 #pragma once
 #include "attention_kernels.h"
 #include "gemm_f32.h"
@@ -30,7 +35,7 @@ __global__ __launch_bounds__(QG * KS * kWave) void attention_f32_kernel(AttnArgs
   __shared__ __align__(16) float mask_smem[KB];
   lds_f32_t* const Ks = (lds_f32_t*)smem;
   lds_f32_t* const Vs = Ks + KB * kPitch;
-  lds_f32_t* const Ms = (lds_f32_t*)mask_smem;  // the key mask of a stage, in log2 units
+  lds_f32_t* const Ms = (lds_f32_t*)mask_smem;  // the key mask of a stage
   const int tid = threadIdx.x, lane = tid % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int g = lane / 16, l16 = lane % 16;
@@ -45,11 +50,6 @@ __global__ __launch_bounds__(QG * KS * kWave) void attention_f32_kernel(AttnArgs
   const __amdgpu_buffer_rsrc_t rk = f32_rsrc((const float*)a.K + head_off, head_bytes);
   const __amdgpu_buffer_rsrc_t rv = f32_rsrc((const float*)a.V + head_off, head_bytes);
   const float* mk = a.mask ? a.mask + ((long)m * a.B + b) * a.S : nullptr;
-  const float scale = a.scale * 1.4426950408889634f;           // scores are kept in log2 units
-  // Without a mask and with a positive scale (uniform over the launch) the scores stay unscaled: scale and maximum enter the exponent in
-  // one fma, so the only rounding there is that of the difference.
-  const bool raw = mk == nullptr && scale > 0.f;
-  const float esc = raw ? scale : 1.0f;
 
   const int q = (qb * QG + wave % QG) * 16 + l16;
   f32x4_t qf[NB];
@@ -72,7 +72,7 @@ __global__ __launch_bounds__(QG * KS * kWave) void attention_f32_kernel(AttnArgs
     }
   };
   auto commit = [&]() {
-    if (mk && tid < KB) Ms[tid] = mask_log2(mreg);
+    if (mk && tid < KB) Ms[tid] = mreg;
 #pragma unroll
     for (int t = 0; t < kPer; ++t) {
       const int c = tid + t * kThreads, o = c / (D / 4) * kPitch + c % (D / 4) * 4;
@@ -104,14 +104,12 @@ __global__ __launch_bounds__(QG * KS * kWave) void attention_f32_kernel(AttnArgs
         for (int kb = 0; kb < kOwn; ++kb) sc[kb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[kb][t], qf[s][t], sc[kb], 0, 0, 0);
     }
     // element r of block kb: key j0 + key0 + 16 kb + 4 g + r of query l16
-    if (!raw) {
 #pragma unroll
-      for (int kb = 0; kb < kOwn; ++kb) {
-        f32x4v_t mv = {0.f, 0.f, 0.f, 0.f};
-        if (mk) mv = *(const lds_f32x4_t*)(Ms + key0 + kb * 16 + 4 * g);
+    for (int kb = 0; kb < kOwn; ++kb) {
+      f32x4v_t mv = {0.f, 0.f, 0.f, 0.f};
+      if (mk) mv = *(const lds_f32x4_t*)(Ms + key0 + kb * 16 + 4 * g);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) sc[kb][r] = fmaf(sc[kb][r], scale, mv[r]);
-      }
+      for (int r = 0; r < 4; ++r) sc[kb][r] = fmaf(sc[kb][r], a.scale, mv[r]);
     }
     if (j0 + KB > a.S) {                        // uniform: only the last stage has keys past the end
 #pragma unroll
@@ -125,14 +123,13 @@ __global__ __launch_bounds__(QG * KS * kWave) void attention_f32_kernel(AttnArgs
 #pragma unroll
       for (int r = 0; r < 4; ++r) mloc = fmaxf(mloc, sc[kb][r]);
     mloc = across_halves(across_rows(mloc, MaxOp{}), MaxOp{});
-    if (raw) mloc = fmaxf(mloc * scale, kLowest);
-    const float mnew = fmaxf(mrun, mloc), corr = __builtin_amdgcn_exp2f(mrun - mnew);
+    const float mnew = fmaxf(mrun, mloc), corr = expf(mrun - mnew);
     mrun = mnew;
     lrun *= corr;
 #pragma unroll
     for (int kb = 0; kb < kOwn; ++kb) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) sc[kb][r] = __builtin_amdgcn_exp2f(fmaf(sc[kb][r], esc, -mnew));
+      for (int r = 0; r < 4; ++r) sc[kb][r] = expf(sc[kb][r] - mnew);
       lrun += (sc[kb][0] + sc[kb][1]) + (sc[kb][2] + sc[kb][3]);
     }
 #pragma unroll
@@ -189,7 +186,7 @@ __global__ __launch_bounds__(QG * KS * kWave) void attention_f32_kernel(AttnArgs
     lrun = 0.f;
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
-      c[s] = __builtin_amdgcn_exp2f(max_of[first + s * QG * kWave] - top);
+      c[s] = expf(max_of[first + s * QG * kWave] - top);
       lrun = fmaf(sum_of[first + s * QG * kWave], c[s], lrun);
     }
 #pragma unroll

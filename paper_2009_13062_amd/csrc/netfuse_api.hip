@@ -1055,14 +1055,14 @@ nf_status netfuse_attention(const void* Q, const void* K, const void* V, const f
     return launched();
   }
   const long long head_elems = (long long)(S - 1) * stride_row + d;         // one head's rows, first to last element
-  // Up to 8 tokens the wavefront-per-query kernel below: of 64 features the two are level at 5 (us, that kernel / this one, 32 models x 8 sequences x 12
-  // heads: 1 token 4.4 / 16.4, 4 11.7 / 16.3, 5 15.5 / 16.3, 8 27.6 / 16.5; one model, 1 sequence: 3.4 / 4.1, 3.9 / 3.8, 4.0 / 3.7, 4.5 / 3.8), other head sizes
-  // have no form of 16 queries and pay for 32.
+  // Up to 8 tokens the wavefront-per-query kernel below: of 64 features the two are level between 5 and 6 (us, that kernel / this one, 32 models x 8
+  // sequences x 12 heads: 1 token 4.4 / 18.0, 4 11.3 / 17.2, 5 15.0 / 17.4, 6 20.0 / 17.4, 8 26.7 / 17.5; one model, 1 sequence: 3.3 / 4.5, 3.8 / 4.1, 3.9 / 3.8,
+  // 4.1 / 3.8, 4.4 / 3.9), other head sizes have no form of 16 queries and pay for 32 (32 features: 8 tokens 14.8 / 15.6, 9 15.6 / 15.6).
   if (dt == NF_F32 && S > 8 && d % 4 == 0 && d <= 128 && head_elems < (1LL << 29)) {
     // Query groups and key shares, by the sequence length alone: the shares decide the order of the sums, and a model's bits do not depend on
     // what is merged with it.  Where 16 or 32 rows are all there are, wavefronts without queries take keys instead (us, 4 groups x 1 share / 2 x 2 /
-    // 1 x 4: 12 models x 8 sequences of 10 tokens 16.1 / 11.3 / 8.5, 32 x 8 of 16 35.5 / 24.8 / 18.4, one of 16 5.5 / 4.6 / 4.1).  Above that shares gain in
-    // small grids and lose in full ones (128 tokens, 2 models 8.4 / 6.4 / 5.4, 12 x 8 51 / 59 / 69; 40 tokens, 12 x 8 18.8 / 20.9 / 19.7).
+    // 1 x 4: 12 models x 8 sequences of 10 tokens 18.3 / 12.5 / 9.3, 32 x 8 of 16 39.3 / 26.7 / 19.6, of 32 41 / 28.7 / 33.8, one of 16 5.9 / 4.6 / 4.0).  Above that
+    // shares gain in small grids and lose in full ones (128 tokens, 2 models 9.4 / 6.8 / 5.5, 12 x 8 58 / 64 / 76; 40 tokens, 12 x 8 20.2 / 21.9 / 20.9).
     const int groups = S > 32 ? 4 : S > 16 || d <= 32 || d > 64 ? 2 : 1;
     const int qblocks = (S + 16 * groups - 1) / (16 * groups);
     const long long total = prod({M, B, heads, qblocks});
