@@ -11,7 +11,9 @@
 // six products: Henry, Tang, Heinecke, "Leveraging the bfloat16 Artificial Intelligence Datatype For Higher-Precision Computations", 2019.)
 //
 // A sum that is not finite (an operand that is not, or one of 2^104 and more, whose first part is infinite, or a sum of 2^80 and more on its way)
-// is computed again from the operands themselves, in float32.
+// is computed again from the operands themselves, on the float32 instructions: the wavefront that finishes it walks all of k once more for its 16
+// rows.  8 models of 128 rows 3072 -> 768 with one row that holds an infinity 42 -> 82 us, with one in every row 86 (a walk of one lane per sum took 2260
+// and 9370), 768 -> 2304 38 -> 64 and 73.
 //
 // A workgroup is four wavefronts, one per chain of k, that share nothing until their sums meet in LDS: no barrier couples them in the loop.
 // B: a lane loads 8 rows of FN neighbouring columns straight into registers, where v_cvt_pk_bf16_f32 makes pairs along k of them, so nothing
@@ -49,7 +51,7 @@ struct SplitCfg {
   static_assert(D == 1 || D == 2, "one remainder step");
 };
 
-constexpr float kSplitScale = 0x1p24f, kSplitUnscale = 0x1p-48f;
+constexpr float kSplitScale = 0x1p24f, kSplitUnscale = 0x1p-48f, kSplitLargest = 3.402823466e38f;
 
 // x, y (consecutive k) -> the three bf16 parts of 2^24 x, 2^24 y, packed in pairs
 __device__ __forceinline__ void split3(float x, float y, uint32_t& p1, uint32_t& p2, uint32_t& p3) {
@@ -85,13 +87,6 @@ __device__ __forceinline__ void buf_load_cols(float (&v)[FN], __amdgpu_buffer_rs
   } else {
     v[0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
   }
-}
-
-// A sum that came out infinite or NaN, from the operands themselves.
-__device__ __attribute__((noinline)) float split_again(const float* a, const float* b, long ldb, int K) {
-  float t = 0.f;
-  for (int k = 0; k < K && t == t; ++k) t = fmaf(a[k], b[(long)k * ldb], t);       // NaN stays NaN
-  return t;
 }
 
 // FN neighbouring columns of one output row: what the epilogue reads, and the epilogue.
@@ -154,9 +149,7 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void gemm_split_kernel(GemmF32Arg
   const int tn = id % a.tiles_n;  id /= a.tiles_n;
   const int z0 = id % a.nz0, z1 = id / a.nz0;
   const int row0 = tm * Cfg::kBM, col0 = tn * Cfg::kBN;
-  const float* const A = a.A + z0 * a.sA0;
-  const float* const B = a.B + z0 * a.sB0 + z1 * a.sB1;
-  const __amdgpu_buffer_rsrc_t ra = f32_rsrc(A, a.a_bytes), rb = f32_rsrc(B, a.b_bytes);
+  const __amdgpu_buffer_rsrc_t ra = f32_rsrc(a.A + z0 * a.sA0, a.a_bytes), rb = f32_rsrc(a.B + z0 * a.sB0 + z1 * a.sB1, a.b_bytes);
 
   // A: load t is rows 8 t .. 8 t + 7, 128 bytes of each; through LDS of the wavefront's own, 16-byte chunks of a row exchanged by its
   // number, so that reads and writes meet every bank equally.  Rows past the end are the last one again.
@@ -292,6 +285,8 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void gemm_split_kernel(GemmF32Arg
       *(lds_f32x4_t*)(part + q * kChain + (i * FN + j) * kWave * 4) = __builtin_bit_cast(f32x4v_t, acc[i][j]);
   __syncthreads();
 
+  float sum[FM][FN];
+  bool again = false;                                          // a sum that is infinite or NaN
   f32x4v_t own[FM == 4 ? FN : 1];
   if constexpr (FM == 4)
 #pragma unroll
@@ -302,23 +297,72 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void gemm_split_kernel(GemmF32Arg
       own[j] = ((c[0] + c[1]) + c[2]) + c[3];
     }
 #pragma unroll
-  for (int u = 0; u < FM; ++u) {
-    const int row = row0 + 16 * block_of(u) + row_of(u);
-    if (row >= a.rows || col >= a.cols) continue;
-    float v[FN];
+  for (int u = 0; u < FM; ++u)
 #pragma unroll
     for (int j = 0; j < FN; ++j) {
       if constexpr (FM == 4) {
-        v[j] = own[j][u];
+        sum[u][j] = own[j][u];
       } else {
         const lds_f32_t* src = part + (block_of(u) * FN + j) * kWave * 4 + row_of(u) - 4 * g;
-        v[j] = ((src[0] + src[kChain]) + src[2 * kChain]) + src[3 * kChain];
+        sum[u][j] = ((src[0] + src[kChain]) + src[2 * kChain]) + src[3 * kChain];
       }
-      if (fabsf(v[j]) <= 3.402823466e38f) v[j] *= kSplitUnscale;
-      else if (col + j < a.cols) v[j] = split_again(A + (long)row * a.lda, B + col + j, a.ldb, a.K);
+      again |= !(fabsf(sum[u][j]) <= kSplitLargest) && row0 + 16 * block_of(u) + row_of(u) < a.rows && col + j < a.cols;
     }
-    rows[u].finish(a, col, v, bias);
+  if (__any(again)) {
+    // The 16 rows of which this wavefront finishes some once more, from the operands themselves, 16 k in ascending order at a time; in the block, too, the
+    // sums of column c of block j are lane c's, so the values replaced are those that are not finite and no others.
+    f32x4_t whole[FN];
+#pragma unroll
+    for (int j = 0; j < FN; ++j) whole[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    const unsigned again_a = (unsigned)(((long)min(row0 + 16 * block_of(0) + l16, a.rows - 1) * a.lda + 4 * g) * 4);
+    const unsigned again_b = (unsigned)(4 * g) * pitch + (unsigned)col * 4u;
+    constexpr int kDeep = FN == 2 ? 3 : 2;                     // registers: no more than the loop above
+    u32x4_t x[2][kDeep];
+    float w[2][kDeep][4][FN];
+    auto fetch = [&](int slot, int k0) {                       // past the end of k both operands are 0
+#pragma unroll
+      for (int i = 0; i < kDeep; ++i) {
+        x[slot][i] = buf_load16(ra, k0 + 16 * i + 4 * g < a.K ? again_a + (unsigned)(k0 + 16 * i) * 4u : kF32Oob);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) buf_load_cols<FN>(w[slot][i][t], rb, again_b + (unsigned)(k0 + 16 * i + t) * pitch);
+      }
+    };
+    auto multiply = [&](int slot) {
+#pragma unroll
+      for (int i = 0; i < kDeep; ++i)
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+          for (int j = 0; j < FN; ++j)
+            whole[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(x[slot][i][t]), w[slot][i][t][j], whole[j], 0, 0, 0);
+    };
+    fetch(0, 0);
+    for (int k0 = 0; k0 < a.K; k0 += 32 * kDeep) {
+      fetch(1, k0 + 16 * kDeep);
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(0);
+      fetch(0, k0 + 32 * kDeep);
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(1);
+    }
+#pragma unroll
+    for (int u = 0; u < FM; ++u)
+#pragma unroll
+      for (int j = 0; j < FN; ++j) {
+        float v = whole[j][0];
+#pragma unroll
+        for (int r = 1; r < 4; ++r) v = row_of(u) - 4 * g == r ? whole[j][r] : v;
+        sum[u][j] = fabsf(sum[u][j]) <= kSplitLargest ? sum[u][j] * kSplitUnscale : v;
+      }
+  } else {
+#pragma unroll
+    for (int u = 0; u < FM; ++u)
+#pragma unroll
+      for (int j = 0; j < FN; ++j) sum[u][j] *= kSplitUnscale;
   }
+#pragma unroll
+  for (int u = 0; u < FM; ++u)
+    if (row0 + 16 * block_of(u) + row_of(u) < a.rows && col < a.cols) rows[u].finish(a, col, sum[u], bias);
 }
 
 }  // namespace nf

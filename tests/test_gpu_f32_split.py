@@ -102,6 +102,46 @@ def test_every_finite_operand(nf, N, K, Nout, ex, ew):
         assert np.linalg.norm(got - ref) <= (1e-7 if K == 64 else 3e-7) * np.linalg.norm(ref)
 
 
+@pytest.mark.parametrize("M,N,K,Nout", [(1, 9, 68, 31), (2, 17, 92, 33), (24, 65, 288, 49), (32, 63, 416, 47), (12, 130, 776, 193), (32, 129, 96, 769),
+                                        (1, 40, 3084, 70)], ids=lambda v: str(v))
+def test_sums_past_the_range_of_the_parts(nf, M, N, K, Nout):
+    """Every second row so large that its sums of parts overflow while float32's do not, beside rows with infinities at either end of k and ordinary ones: in
+    every tile float32's results, the ordinary rows with the bits that they have alone."""
+    X, W = rnd(M, N, K), rnd(M, K, Nout)
+    W[:, 0] = np.where(W[:, 0] > 0, 1.0, -1.0)
+    W[:, -1] = np.where(W[:, -1] > 0, 1.0, -1.0)
+    clean = nf.linear(dev(X), dev(W)).cpu().numpy()
+    bad = X.copy()
+    bad[:, ::2] *= np.float32(2.0 ** 110)
+    bad[:, 1::4, 0], bad[:, 3::8, -1] = np.inf, -np.inf
+    got = nf.linear(dev(bad), dev(W)).cpu().numpy()
+    check(torch.from_numpy(got[:, ::2]), np.matmul(bad[:, ::2].astype(np.float64), W.astype(np.float64)),
+          np.matmul(np.abs(bad[:, ::2]).astype(np.float64), np.abs(W).astype(np.float64)), K)
+    assert np.array_equal(got[:, 1::4], np.broadcast_to(np.inf * W[:, :1], got[:, 1::4].shape))
+    assert np.array_equal(got[:, 3::8], np.broadcast_to(-np.inf * W[:, -1:], got[:, 3::8].shape))
+    assert np.array_equal(got[:, 7::8], clean[:, 7::8])
+
+
+def test_infinities_cost_one_more_pass(nf):
+    """An infinity in every row, so that no sum is finite: another walk over k (2 to 3 times as long), not one per output (200 times)."""
+    X, W, Y = torch.randn(8, 128, 3072, device="cuda"), torch.rand(8, 3072, 768, device="cuda"), torch.empty(8, 128, 768, device="cuda")
+
+    def us():
+        best = 1e9
+        for _ in range(6):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(8):
+                nf.linear(X, W, out=Y)
+            end.record()
+            end.synchronize()
+            best = min(best, start.elapsed_time(end) * 1000 / 8)
+        return best
+    finite = us()
+    X[:, :, 1000] = float("inf")
+    assert us() < 10 * finite and bool((Y == float("inf")).all())
+
+
 @pytest.mark.parametrize("rows,cols,K,taken", [(1, 1, 64, 1), (1, 1, 60, 0), (512, 512, 64, 1), (512, 513, 64, 0), (2048, 1024, 128, 1),
                                                 (2048, 1025, 128, 0), (2048, 1025, 256, 1), (64, 64, 130, 0)])
 def test_rule(nf, rows, cols, K, taken):
