@@ -118,8 +118,8 @@ struct GemmF32Args {
   unsigned rcp_khw, rcp_kw;                // ceil(2^32 / d), or 0 for d = 1, where
   unsigned one_khw, one_kw;                // all bits are set here instead
 };
-// the same on bf16 matrix instructions, operands split three ways (gemm_split.h): matmuls of enough k.  NF_EUNSUPPORTED = not its
-// shape
+// the same on bf16 matrix instructions, operands split three ways (gemm_split.h): matmuls of enough k, z = one of nz0, column bias, activation before the
+// residual.  NF_EUNSUPPORTED = not its shape
 nf_status launch_gemm_split(GemmF32Args& a, hipStream_t s);
 // gather: B through the convolution geometry (any shape); else dense rows, cols % 4 == 0
 nf_status launch_gemm_f32(GemmF32Args& a, int nz1, bool gather, hipStream_t s);

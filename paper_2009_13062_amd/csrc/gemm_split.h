@@ -1,6 +1,6 @@
 // float32 contraction on the bf16 matrix instructions: merged matmul, float32 storage.
 //
-//   C[z][i][j] = sum_k A[z][i][k] * B[z][k][j]     one fused epilogue
+//   C[z][i][j] = act(sum_k A[z][i][k] * B[z][k][j] + bias[z][j]) + R[z][i][j]
 //
 // A float32 is the sum of three bf16 numbers (24 bits of significand, 8 in each): x = x1 + x2 + x3 with x1 = bf16(x),
 // x2 = bf16(x - x1), x3 = x - x1 - x2, every difference exact as long as the last bit of x3 is a bf16 number: bf16 has float32's exponents
@@ -72,6 +72,7 @@ template <int FN>
 __device__ __forceinline__ void buf_load_cols(float (&v)[FN], __amdgpu_buffer_rsrc_t r, unsigned off) {
   typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
   typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
+  static_assert(FN >= 2 && FN <= 4, "8, 12 or 16 bytes");
   if constexpr (FN == 4) {
     const u32x4_t t = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0);
 #pragma unroll
@@ -80,30 +81,22 @@ __device__ __forceinline__ void buf_load_cols(float (&v)[FN], __amdgpu_buffer_rs
     const u32x3 t = __builtin_amdgcn_raw_buffer_load_b96(r, (int)off, 0, 0);
 #pragma unroll
     for (int j = 0; j < FN; ++j) v[j] = __uint_as_float(t[j]);
-  } else if constexpr (FN == 2) {
+  } else {
     const u32x2 t = __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0);
 #pragma unroll
     for (int j = 0; j < FN; ++j) v[j] = __uint_as_float(t[j]);
-  } else {
-    v[0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
   }
 }
 
-// FN neighbouring columns of one output row: what the epilogue reads, and the epilogue.
+// FN neighbouring columns of one output row: the residual that the epilogue reads, and the epilogue.
 template <int FN>
 struct SplitRow {
   typedef float vec_t __attribute__((ext_vector_type(FN)));
   vec_t res;
-  float rbias, rscale, rshift;
   long at;
 
-  __device__ __forceinline__ void read(const GemmF32Args& a, int z0, int z1, int row, int col) {
-    const Epilogue& ep = a.ep;
-    const long rv = z0 * ep.row_vec_stride0 + row;
-    at = z0 * a.sC0 + z1 * a.sC1 + (long)row * a.ldc + col;
-    rbias = ep.row_bias ? ep.row_bias[rv] : 0.f;
-    rscale = ep.row_scale ? ep.row_scale[rv] : 1.f;
-    rshift = ep.row_scale ? ep.row_shift[rv] : 0.f;
+  __device__ __forceinline__ void read(const GemmF32Args& a, int z, int row, int col) {
+    at = z * a.sC0 + (long)row * a.ldc + col;
 #pragma unroll
     for (int j = 0; j < FN; ++j) res[j] = 0.f;
     if (a.R) {
@@ -117,11 +110,7 @@ struct SplitRow {
   __device__ __forceinline__ void finish(const GemmF32Args& a, int col, const float (&v)[FN], const float (&bias)[FN]) const {
     vec_t out;
 #pragma unroll
-    for (int j = 0; j < FN; ++j) {
-      float x = v[j] + rbias + bias[j];
-      if (a.ep.row_scale) x = fmaf(x, rscale, rshift);
-      out[j] = a.ep.act_before_residual ? apply_act(x, a.ep.act) + res[j] : apply_act(x + res[j], a.ep.act);
-    }
+    for (int j = 0; j < FN; ++j) out[j] = apply_act(v[j] + bias[j], a.ep.act) + res[j];
     if (col + FN <= a.cols) __builtin_memcpy(a.C + at, &out, sizeof(float) * FN);
     else
 #pragma unroll
@@ -147,9 +136,9 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void gemm_split_kernel(GemmF32Arg
   unsigned id = xcd_remap(blockIdx.x, gridDim.x);
   const int tm = id % a.tiles_m;  id /= a.tiles_m;
   const int tn = id % a.tiles_n;  id /= a.tiles_n;
-  const int z0 = id % a.nz0, z1 = id / a.nz0;
+  const int z = id;
   const int row0 = tm * Cfg::kBM, col0 = tn * Cfg::kBN;
-  const __amdgpu_buffer_rsrc_t ra = f32_rsrc(a.A + z0 * a.sA0, a.a_bytes), rb = f32_rsrc(a.B + z0 * a.sB0 + z1 * a.sB1, a.b_bytes);
+  const __amdgpu_buffer_rsrc_t ra = f32_rsrc(a.A + z * a.sA0, a.a_bytes), rb = f32_rsrc(a.B + z * a.sB0, a.b_bytes);
 
   // A: load t is rows 8 t .. 8 t + 7, 128 bytes of each; through LDS of the wavefront's own, 16-byte chunks of a row exchanged by its
   // number, so that reads and writes meet every bank equally.  Rows past the end are the last one again.
@@ -268,13 +257,13 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void gemm_split_kernel(GemmF32Arg
   auto row_of = [&](int u) { return 4 * g + (FM == 4 ? u : (q * FM + u) % 4); };
   SplitRow<FN> rows[FM];
   float bias[FN];
-  const float* const cb = a.ep.col_bias ? a.ep.col_bias + z0 * a.ep.col_vec_stride0 : nullptr;
+  const float* const cb = a.ep.col_bias ? a.ep.col_bias + z * a.ep.col_vec_stride0 : nullptr;
 #pragma unroll
   for (int j = 0; j < FN; ++j) bias[j] = cb && col + j < a.cols ? cb[col + j] : 0.f;
 #pragma unroll
   for (int u = 0; u < FM; ++u) {
     const int row = row0 + 16 * block_of(u) + row_of(u);
-    if (row < a.rows && col < a.cols) rows[u].read(a, z0, z1, row, col);
+    if (row < a.rows && col < a.cols) rows[u].read(a, z, row, col);
   }
   lds_f32_t* const part = (lds_f32_t*)smem + lane * 4;
   constexpr int kChain = FM * FN * kWave * 4;
