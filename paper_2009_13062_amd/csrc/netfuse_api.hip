@@ -867,9 +867,11 @@ nf_status netfuse_conv2d(const void* x, const void* w, const float* bias, const 
   // where a model has few groups.  Direct / matrix (us): depthwise 3x3 of 1024 channels at 14 x 14 5 / 50, 16 -> 1
   // channels per group 29 / 64, 4 -> 8 38 / 47, 8 -> 8 81 / 47; 7x7 depthwise 10 / 63, 2 -> 8 79 / 83; pointwise 8 -> 8
   // 23 / 25, 16 -> 8 38 / 25; one model with one group at 56 x 56: 8 -> 1 13 / 7, 16 -> 1 24 / 8.
-  // Pointwise layers over planes that are no multiple of 4 positions keep the line measured when their rows were gathered.
-  const bool f32_pointwise = KH == 1 && KW == 1 && stride == 1 && pad == 0, f32_dense = f32_pointwise && HoWo % 4 == 0;
-  const bool f32_narrow = (long long)cog * Kdim <= (f32_dense ? 64 : 220 + 10LL * KH * KW) && (g >= 64 || Kdim <= (f32_dense ? 16 : 72));
+  // Pointwise layers have one line for planes of any size.  Over 919 problems of 1 to 64 groups and 1 to 32 models, odd planes of 7 x 7 to 49 x 49 (and even
+  // ones of 8 x 8 to 50 x 50), the form picked takes 5 % (5 %) longer than the better one on average, at the line of the k x k layers 55 % (55 %); of
+  // the problems between the two lines 3 are more than 3 % behind here, by up to 13 % (32 models, 32 -> 2 channels in 32 groups).
+  const bool f32_pointwise = KH == 1 && KW == 1 && stride == 1 && pad == 0;
+  const bool f32_narrow = (long long)cog * Kdim <= (f32_pointwise ? 64 : 220 + 10LL * KH * KW) && (g >= 64 || Kdim <= (f32_pointwise ? 16 : 72));
   if (dt == NF_F32 && KH * KW < 64 && !f32_narrow && f32_fits((long long)cog * Kdim, prod({cig, H, W}), Kdim)) {
     GemmF32Args a;
     memset(&a, 0, sizeof(a));

@@ -44,3 +44,33 @@ def test_a_column_keeps_its_nan(nf):
     got = nf.linear(x.cuda(), w.cuda()).cpu()
     assert got[0, :, 0].isnan().all() and got[0, :, 1:].isfinite().all()
     assert not got[1, :, 0].isfinite().any() and got[1, :, 1:].isfinite().all()
+
+
+@pytest.mark.parametrize("hw", [1, 5, 7, 15])
+@pytest.mark.parametrize("cig,cog,g", [(4, 16, 1), (16, 4, 3), (17, 3, 2), (17, 3, 64), (8, 9, 5), (9, 8, 64), (16, 13, 4), (72, 3, 1), (73, 3, 1), (8, 28, 64)])
+def test_pointwise_of_narrow_groups(nf, hw, cig, cog, g):
+    """Either side of the line between the kernel of one thread per output and the matrix kernel."""
+    M, B = 2, 2
+    gen = torch.Generator().manual_seed(100 * hw + cig)
+    x, w = torch.randn(B, M * g * cig, hw, hw, generator=gen), torch.randn(M * g * cog, cig, 1, 1, generator=gen)
+    got = nf.conv2d(x.cuda(), w.cuda(), M, g)
+    xd, wd = x.double().view(B, M * g, cig, hw * hw), w.double().view(1, M * g, cog, cig)
+    close(got, (wd @ xd).view(got.shape), (wd.abs() @ xd.abs()).view(got.shape), cig)
+
+
+def test_an_odd_plane_is_no_slower_than_a_larger_even_one(nf):
+    """8 -> 28 and 16 -> 13 channels per group over 15 x 15 against 16 x 16 positions: the same kernel for both."""
+    def us(cig, cog, g, hw):
+        x, w = torch.randn(1, 32 * g * cig, hw, hw, device="cuda"), torch.randn(32 * g * cog, cig, 1, 1, device="cuda")
+        out, best = nf.conv2d(x, w, 32, g), 1e9
+        for _ in range(6):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(10):
+                nf.conv2d(x, w, 32, g, out=out)
+            end.record()
+            end.synchronize()
+            best = min(best, start.elapsed_time(end) * 100)
+        return best
+    for cig, cog in ((8, 28), (16, 13)):
+        assert us(cig, cog, 64, 15) < 1.5 * us(cig, cog, 64, 16)
