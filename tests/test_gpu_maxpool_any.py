@@ -7,9 +7,12 @@ import torch
 pytestmark = pytest.mark.gpu
 
 
-# (3, 5, 7, 7), (2, 9, 40, 40), (1, 4, 1, 9000) and (1, 2048, 3, 8): the kernel for any window, below 8 columns, 2^14 outputs, two rows, and at the line
-@pytest.mark.parametrize("B,C,H,W", [(3, 5, 7, 7), (2, 9, 40, 40), (1, 4, 1, 9000), (1, 2048, 3, 8), (1, 2049, 4, 8), (2, 1700, 3, 9), (1, 2050, 5, 10),
-                                     (2, 700, 6, 15), (1, 911, 3, 17), (3, 20, 9, 100), (1, 7, 113, 113), (1, 12, 6, 1030)])
+# the kernel for any window: below 8 columns, 2^14 outputs, two rows, and at the line
+GENERIC = [(3, 5, 7, 7), (2, 9, 40, 40), (1, 4, 1, 9000), (1, 2048, 3, 8)]
+ROWS = [(1, 2049, 4, 8), (2, 1700, 3, 9), (1, 2050, 5, 10), (2, 700, 6, 15), (1, 911, 3, 17), (3, 23, 9, 100), (1, 7, 113, 113), (1, 12, 6, 1030)]
+
+
+@pytest.mark.parametrize("B,C,H,W", GENERIC + ROWS)
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("shift", [0, 1])
 def test_values(oracle, B, C, H, W, dtype, shift):
@@ -19,6 +22,7 @@ def test_values(oracle, B, C, H, W, dtype, shift):
     f[::5], f[1::7], f[2::11] = np.nan, -np.inf, np.inf
     x[:, 0] = torch.finfo(dtype).min
     Ho, Wo = (H - 1) // 2 + 1, (W - 1) // 2 + 1
+    assert (W >= 8 and Ho > 1 and B * C * Ho * Wo > 2 ** 14) == ((B, C, H, W) in ROWS)
     xs = torch.empty(x.size + 9, dtype=dtype, device="cuda")
     ys = torch.full((B * C * Ho * Wo + 9,), 77.0, dtype=dtype, device="cuda")
     xin = xs[shift:shift + x.size].view(B, C, H, W)
