@@ -8,7 +8,8 @@ constexpr int kSplitBM[kNumSplitTiles] = {64, 64, 64, 32, 32, 16, 16};
 constexpr int kSplitBN[kNumSplitTiles] = {64, 48, 32, 64, 32, 64, 32};
 // Time model of a tile (us): latency a + l per 768 of k; per 256 tiles p + q per 768 of k; per round of tiles over the 256 compute units
 // begun s per 768 of k + r.  Fitted to every tile over 260 problems (an encoder's matmuls at hidden sizes 256 to 1024, 4 ... 1500 rows, and
-// 64 to 2048 rows times 16 to 4500 columns, 1 ... 32 models): mean error of a prediction 4 to 7 %, the tile it picks 0.9 % behind the best.
+// 64 to 2048 rows times 16 to 4500 columns, 1 ... 32 models); over 316 others, 1 ... 2048 rows, the mean error of a prediction is 5 to 8 % and the tile it picks
+// 0.5 % behind the best.
 constexpr float kSplitCost[kNumSplitTiles][6] = {   // a, l, p, q, s, r
     {3.91f, 1.69f, 0.508f, 2.22f, 6.08f, 1.67f},
     {3.5f, 1.73f, 0.229f, 2.22f, 4.78f, 1.76f},
@@ -35,17 +36,19 @@ static nf_status launch_split(GemmF32Args& a, long long problems, hipStream_t s)
 }
 
 // Whether a problem of this shape is this kernel's.  By the shape of one problem alone: its sums round differently from gemm_f32.h's, and a
-// model's bits must not depend on how many are merged with it.  Few k over a large output is mostly the meeting of the chains in LDS (us,
-// gemm_f32.h / here: 7 models of 512 rows 64 -> 1496 16.4 / 22.4, 4 of 2048 rows 128 -> 1296 36.6 / 41.3, but 6 of 64 rows 64 -> 2750 12.1 / 9.0, 11 of
-// 1024 rows 128 -> 1610 75.6 / 67.2).  Over 260 problems, of which 8 stay with gemm_f32.h, 25 % less time (k from 1024 up 31 %); behind by more than
-// 5 % in one (13 models of 4 rows 3072 -> 768, 29.2 / 35.8).
-// Matmuls only.  Pointwise convolutions gain as much one by one (8 models 2048 -> 512 over 7 x 7 26 / 17, 512 -> 256 over 28 x 28 22.5 / 18.9; few channels
-// nothing), but these multiplications draw more power than float32 ones, the clock of the whole chip follows, and the 3 x 3 layers
-// and the stem around them pay for it: an image network of 8 models with its pointwise layers here took 54 us less in them at full clock and
-// 26 us more in all in the steady state (1187 / 1213), its untouched kernels 7 % slower.
+// model's bits must not depend on how many are merged with it.  Few k over a large output is mostly the meeting of the chains in LDS, and at 64 of k
+// gemm_f32.h walks no padding (us, gemm_f32.h / here: 13 models of 1913 rows 64 -> 69 10.4 / 12.9, 7 of 512 rows 64 -> 1496 18.2 / 22.2, 2 of 421 rows
+// 64 -> 92 4.2 / 3.5; from 68 to 124 of k this is 6 to 18 % ahead up to 2^18 outputs, 3 to 13 % above; 4 of 2048 rows 128 -> 1296 41.0 / 41.0).  Of 511 drawn problems of 64 to 128 of k none is more than 5 % behind (13 with the line of 68 for 64 too), and 1.7 % more time than
+// the better kernel on average.  Over 316 others (an encoder's matmuls at hidden sizes 256 to 1024; 64 to 4096 of k, 1 ... 2048 rows times 16 to 4500
+// columns; 1 ... 32 models) 15 % less time, k from 1024 up 19 %; 9 are 5 to 11 % behind, of 3 to 36 rows over many models (13 of 4 rows 3072 -> 768
+// 23.4 / 26.8, but one of 7 rows 4096 -> 1024 26.9 / 18.2).
+// Matmuls only.  Pointwise convolutions gained one by one before the multiplication by 2^24 (8 models 2048 -> 512 over 7 x 7 26 / 17, 512 -> 256 over 28 x 28
+// 22.5 / 18.9), but these multiplications draw more power than float32 ones and the clock of the whole chip follows: an image network of 8 models with
+// its pointwise layers here takes 1191 us a pass in the steady state, 1152 without, at 2304 and 2403 MHz, its 3 x 3 layers and stem 4 % longer
+// and most of the pointwise layers too.
 bool split_takes(int rows, int cols, int K) {
   const long long out = (long long)rows * cols;
-  return K % 4 == 0 && K >= 64 && (K >= 256 || out <= (K >= 128 ? 1 << 21 : 1 << 18));
+  return K % 4 == 0 && K >= 64 && (K >= 256 || out <= (K >= 128 ? 1 << 21 : K > 64 ? 1 << 18 : 1 << 16));
 }
 
 nf_status launch_gemm_split(GemmF32Args& a, hipStream_t s) {

@@ -2,7 +2,7 @@
 of the 32-element steps and of the four chains, both sides of the rule that chooses the kernel, operands of every size, some that the split
 into bf16 parts does not represent, and the same bits whatever tile the number of models or images leads to.
 
-Bounds: a product is off by at most 2^-23 (the three of nine products of parts that are left out) and a sum of K of them in any order by
+Bounds: a product is off by at most 2^-24.2 (the three of nine products of parts that are left out) and a sum of K of them in any order by
 K 2^-24 of sum |x||w|; each 32-k step adds six products of parts.  The measured error, in the 2-norm, is half of a plain float32 sum's."""
 import numpy as np
 import pytest
@@ -39,7 +39,8 @@ def check(got, ref, absref, K):
     (1, 1, 64, 1), (2, 15, 68, 31), (2, 17, 92, 33), (1, 16, 256, 64),            # 16-row tiles, k of 32 n + 4 .. 28
     (8, 33, 260, 65), (16, 48, 124, 96), (24, 65, 288, 49), (32, 63, 416, 47),    # 32- and 64-row tiles
     (12, 130, 768, 193), (32, 129, 96, 769), (6, 257, 1028, 95),                  # several tiles per compute unit
-    (2, 1030, 64, 255), (2, 1025, 64, 256), (2, 1024, 64, 257),                   # either side of the rule below 128 of k
+    (2, 256, 64, 256), (2, 257, 64, 256), (2, 1030, 64, 255), (2, 1025, 64, 256), (2, 1024, 64, 257),      # either side of the rule at 64 of k
+    (2, 1024, 68, 256), (2, 1025, 68, 256),                                       # from 68 of k
     (1, 1449, 128, 1447), (1, 1449, 128, 1449), (1, 40, 60, 40), (3, 21, 66, 20),  # below 256 of k; too few k, k not in fours
 ], ids=lambda v: str(v))
 def test_linear(nf, M, N, K, Nout):
@@ -142,7 +143,8 @@ def test_infinities_cost_one_more_pass(nf):
     assert us() < 10 * finite and bool((Y == float("inf")).all())
 
 
-@pytest.mark.parametrize("rows,cols,K,taken", [(1, 1, 64, 1), (1, 1, 60, 0), (512, 512, 64, 1), (512, 513, 64, 0), (2048, 1024, 128, 1),
+@pytest.mark.parametrize("rows,cols,K,taken", [(1, 1, 64, 1), (1, 1, 60, 0), (256, 256, 64, 1), (256, 257, 64, 0), (512, 512, 64, 0), (512, 512, 68, 1),
+                                                (512, 513, 68, 0), (2048, 1024, 128, 1),
                                                 (2048, 1025, 128, 0), (2048, 1025, 256, 1), (64, 64, 130, 0)])
 def test_rule(nf, rows, cols, K, taken):
     assert bool(nf.lib.netfuse_f32_split_takes(rows, cols, K)) == bool(taken)
