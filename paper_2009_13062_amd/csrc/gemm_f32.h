@@ -24,9 +24,8 @@
 // those 2 apart, then the two sums.  Which tile runs depends on how many models (and images) are merged, and a model's
 // bits must not, so CH follows from K alone; the tiles differ in how many groups of wavefronts the chains are dealt to.
 //
-// Measured (8 models, us; the plain FMA kernels before -> this): 128 x 768 x 3072 matmul 187 -> 45 (31.6 at the fp32
-// matrix peak), 128 x 3072 x 768 750 -> 52, pointwise 64 -> 256 at 56 x 56 460 -> 17; a 12-layer encoder 16.3 -> 3.2 ms.
-// Matmuls of enough k are gemm_split.h's since.  Of the convolutions it runs the pointwise ones, k x k but 3 x 3, and 3 x 3 over wide planes at
+// Measured (8 models, us; the plain FMA kernels -> this): pointwise 64 -> 256 at 56 x 56 460 -> 17.
+// Matmuls of enough k are gemm_split.h's.  Of the convolutions it runs the pointwise ones, k x k but 3 x 3, and 3 x 3 over wide planes at
 // stride 2 or groups that are no multiple of 8 channels; the other 3 x 3 ones are conv_wave.h's.  Narrow groups and few k over many rows stay with
 // the FMA kernels (netfuse_api.hip).
 //

@@ -121,7 +121,7 @@ struct GemmF32Args {
 // the same on bf16 matrix instructions, operands split three ways (gemm_split.h): matmuls of enough k, z = one of nz0, column bias, activation before the
 // residual.  NF_EUNSUPPORTED = not its shape
 nf_status launch_gemm_split(GemmF32Args& a, hipStream_t s);
-// gather: B through the convolution geometry (any shape); else dense rows, cols % 4 == 0
+// gather: B through the convolution geometry (any shape); else dense rows of any length, at any 4-byte alignment
 nf_status launch_gemm_f32(GemmF32Args& a, int nz1, bool gather, hipStream_t s);
 
 struct ConvPatchArgs;

@@ -25,9 +25,9 @@
 // one problem's operand: what lies past its end comes back as 0 (rows of k past the end, columns behind the last row).
 //
 // What bounds it: operands of 4 bytes from L2, 35 to 45 bytes per ns and compute unit, then issue slots.  Measured (8 models of 128 rows, us,
-// gemm_f32.h -> this): 768 -> 2304 39.8 -> 33.0, 768 -> 768 15.9 -> 13.9, 768 -> 3072 43.0 -> 36.2, 3072 -> 768 48.2 -> 37.9; 12 models of 512 rows 768 ->
-// 3072 235 -> 190, 3072 -> 768 236 -> 181; 1 model of 128 rows 3072 -> 768 21.4 -> 16.0.  The multiplication by 2^24 is 4 to 8 % of it (31.4, 13.2, 34.8,
-// 35.6, 179, 171 and 14.4 without it, and an error of 3.5e-5 where an operand is 2^-120).
+// gemm_f32.h -> this): 768 -> 2304 39.0 -> 32.5, 768 -> 768 15.8 -> 13.1, 768 -> 3072 43.7 -> 35.9, 3072 -> 768 49.4 -> 37.7; 12 models of 512 rows 768 ->
+// 3072 230 -> 186, 3072 -> 768 239 -> 181; 1 model of 128 rows 3072 -> 768 21.5 -> 14.2.  The multiplication by 2^24 is 4 to 8 % of it (768 -> 2304 31.4 -> 33.0,
+// 12 models of 512 rows 3072 -> 768 171 -> 181; without it the error is 3.5e-5 where an operand is 2^-120).
 // Error against 64 bits (2-norm, K = 64, 768, 3072): 1.0e-7, 3.5e-7, 4.9e-7 -> 0.5e-7, 2.0e-7, 4.2e-7.
 //
 // Measured and dropped: stages of a 128 x 128 tile split once per workgroup and shared through LDS (1.3 us per 32 k: LDS traffic and the barrier,
