@@ -867,11 +867,15 @@ nf_status netfuse_conv2d(const void* x, const void* w, const float* bias, const 
   // where a model has few groups.  Direct / matrix (us): depthwise 3x3 of 1024 channels at 14 x 14 5 / 50, 16 -> 1
   // channels per group 29 / 64, 4 -> 8 38 / 47, 8 -> 8 81 / 47; 7x7 depthwise 10 / 63, 2 -> 8 79 / 83; pointwise 8 -> 8
   // 23 / 25, 16 -> 8 38 / 25; one model with one group at 56 x 56: 8 -> 1 13 / 7, 16 -> 1 24 / 8.
-  // Pointwise layers have one line for planes of any size.  Over 919 problems of 1 to 64 groups and 1 to 32 models, odd planes of 7 x 7 to 49 x 49 (and even
-  // ones of 8 x 8 to 50 x 50), the form picked takes 5 % (5 %) longer than the better one on average, at the line of the k x k layers 55 % (55 %); of
-  // the problems between the two lines 3 are more than 3 % behind here, by up to 13 % (32 models, 32 -> 2 channels in 32 groups).
+  // Pointwise layers over planes that are no multiple of 4 positions: from 8 channels of k up the matrix kernel is ahead beyond 64 products (direct / matrix,
+  // 32 models: 16 -> 13 in 64 groups over 15 x 15 132 / 59), below it depends on the number of models (one: 1 -> 64 channels in one group 0.6 to 0.7 of its
+  // time, 64 groups in 32: 1.5 to 1.9), as up to 64 products.  Over 1619 odd problems of 1 to 64 groups and 1 to 32 models the form picked takes 13 % longer
+  // than the better one on average (45 % at the line of the k x k layers, 4 % at that of the even planes, which is up to 1.8 times behind with few models).
   const bool f32_pointwise = KH == 1 && KW == 1 && stride == 1 && pad == 0;
-  const bool f32_narrow = (long long)cog * Kdim <= (f32_pointwise ? 64 : 220 + 10LL * KH * KW) && (g >= 64 || Kdim <= (f32_pointwise ? 16 : 72));
+  const long long f32_products = (long long)cog * Kdim;     // per position
+  const bool f32_narrow = f32_pointwise && HoWo % 4 != 0 ? f32_products <= (Kdim < 8 ? 230 : 64)
+                          : f32_pointwise                ? f32_products <= 64 && (g >= 64 || Kdim <= 16)
+                                                         : f32_products <= 220 + 10LL * KH * KW && (g >= 64 || Kdim <= 72);
   if (dt == NF_F32 && KH * KW < 64 && !f32_narrow && f32_fits((long long)cog * Kdim, prod({cig, H, W}), Kdim)) {
     GemmF32Args a;
     memset(&a, 0, sizeof(a));

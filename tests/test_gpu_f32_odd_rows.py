@@ -47,7 +47,8 @@ def test_a_column_keeps_its_nan(nf):
 
 
 @pytest.mark.parametrize("hw", [1, 5, 7, 15])
-@pytest.mark.parametrize("cig,cog,g", [(4, 16, 1), (16, 4, 3), (17, 3, 2), (17, 3, 64), (8, 9, 5), (9, 8, 64), (16, 13, 4), (72, 3, 1), (73, 3, 1), (8, 28, 64)])
+@pytest.mark.parametrize("cig,cog,g", [(4, 16, 1), (16, 4, 3), (17, 3, 2), (17, 4, 64), (7, 32, 5), (7, 33, 3), (8, 8, 5), (8, 9, 5), (16, 13, 4), (64, 1, 2),
+                                          (65, 1, 64), (8, 28, 64), (1, 230, 1), (1, 231, 1)])
 def test_pointwise_of_narrow_groups(nf, hw, cig, cog, g):
     """Either side of the line between the kernel of one thread per output and the matrix kernel."""
     M, B = 2, 2
